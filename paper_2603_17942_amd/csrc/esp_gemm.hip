@@ -25,7 +25,7 @@
 //    also depends on the number of row tiles (gemm_plan), so a row's low-order bits can differ
 //    between a block of 320 rows and a block of 68.
 //
-// fp32 path (tiny configuration): plain LDS-tiled FMA kernel with bounds checks, row-major weights.
+// fp32 path (tiny configuration, k_gemm_f32): 32 x 32 tiles on the fp32 matrix instruction, row-major weights.
 #include <algorithm>
 
 #include <hip/hip_ext.h>
@@ -547,50 +547,78 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                                                       out2, draw_pos, seed);
 }
 
-// ---- fp32: 64x64 tile, 16-deep k steps, 256 threads, 4x4 outputs per thread -----------------------
-__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, const int32_t* __restrict__ a_rows,
-                                                  const float* __restrict__ W, float* __restrict__ out, int M,
-                                                  int N, int K) {
-  __shared__ float As[16][65];
-  __shared__ float Ws[16][65];
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int i = threadIdx.x; i < 64 * 16; i += 256) {
-      int r = i >> 4, kk = i & 15;
-      int m = m0 + r, n = n0 + r, k = k0 + kk;
-      float av = 0.f, wv = 0.f;
-      if (m < M && k < K) {
-        int pm = a_rows ? max(a_rows[m], 0) : m;
-        av = A[(size_t)pm * K + k];
-      }
-      if (n < N && k < K) wv = W[(size_t)n * K + k];
-      As[kk][r] = av;
-      Ws[kk][r] = wv;
+// ---- fp32: one 32 x 32 tile per workgroup, its eight waves split K (v_mfma_f32_32x32x2_f32) --------
+// The fp32 models are small (256 x 256 to 4096 x 256 weights): latency is the bound, so a tile is as
+// small as a matrix instruction, every wave has an eighth of K to itself and issues its loads up front
+// (F32_U chunks of 8 k in flight, no barrier in the loop), and the eight partial tiles meet once in LDS,
+// added in wave order.  Within a chunk the k index is permuted alike for both operands (lane half g
+// holds k = 8 c + 4 g + 0..3), so a lane's operands of four matrix instructions are one 16-byte load.
+// K not a multiple of 4, or rows that are not 16-byte aligned (VEC false): the same with scalar loads.
+// MI355X, a step of the 2-layer d = 256 model at 60 rows (nine of these launches): 678 -> 176 us against a
+// 64 x 64 tile walked in 16-deep steps through LDS, each step exposing a memory latency (39 to 123 us
+// a launch).
+constexpr int F32_WAVES = 8, F32_U = 4;
+
+template <bool VEC>
+__device__ __forceinline__ f32x4_t f32_piece(const float* __restrict__ row, int k, int K) {
+  f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+  if (VEC) {
+    if (k < K) v = *reinterpret_cast<const f32x4_t*>(row + k);   // K % 4 == 0: all or nothing
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (k + e < K) v[e] = row[k + e];
+  }
+  return v;
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(64 * F32_WAVES) void k_gemm_f32(const float* __restrict__ A, const int32_t* __restrict__ a_rows,
+                                                             const float* __restrict__ W, float* __restrict__ out, int M,
+                                                             int N, int K) {
+  __shared__ float part[F32_WAVES][16][64];
+  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lr = lane & 31, lg = lane >> 5;
+  int m = min(m0 + lr, M - 1);                      // clamped rows and columns are computed, never stored
+  if (a_rows) m = max(a_rows[m], 0);
+  const float* ar = A + (size_t)m * K;
+  const float* wr = W + (size_t)min(n0 + lr, N - 1) * K;
+  const int chunks = (K + 7) >> 3;
+  const int mine = (chunks - wave + F32_WAVES - 1) / F32_WAVES;   // chunks wave, wave + 8, ...
+  f32x16_t acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  f32x4_t a[2][F32_U], w[2][F32_U];
+  auto load = [&](int buf, int i0) {
+#pragma unroll
+    for (int u = 0; u < F32_U; ++u) {
+      const int k = (i0 + u < mine ? (wave + F32_WAVES * (i0 + u)) * 8 : K) + 4 * lg;   // past the share: zeros
+      a[buf][u] = f32_piece<VEC>(ar, k, K);
+      w[buf][u] = f32_piece<VEC>(wr, k, K);
     }
-    __syncthreads();
+  };
+  load(0, 0);
+  for (int i0 = 0; i0 < mine; i0 += 2 * F32_U) {
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], w[4];
+    for (int b = 0; b < 2; ++b) {
+      load(b ^ 1, i0 + (b + 1) * F32_U);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
+      for (int u = 0; u < F32_U; ++u)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) w[j] = Ws[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[b][u][e], w[b][u][e], acc, 0, 0, 0);
     }
-    __syncthreads();
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int v = 0; v < 16; ++v) part[wave][v][lane] = acc[v];
+  __syncthreads();
+  for (int e = tid; e < 1024; e += 64 * F32_WAVES) {
+    const int v = e >> 6, l = e & 63;
+    float sum = part[0][v][l];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < M && n < N) out[(size_t)m * N + n] = acc[i][j];
-    }
+    for (int q = 1; q < F32_WAVES; ++q) sum += part[q][v][l];
+    const int mo = m0 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3), no = n0 + (l & 31);
+    if (mo < M && no < N) out[(size_t)mo * N + no] = sum;
+  }
 }
 
 // row-major [N][K] -> tiles of 32 rows x 64 k stored as [chunk][row block][step][lane][8]
@@ -672,7 +700,7 @@ GemmPlan gemm_plan(int dtype, int M, int N, int K) {
   GemmPlan p;
   p.wm = 1;
   if (dtype == ESP_F32) {
-    p.splits = 1; p.mt = 2; p.nb = 2; p.m_tiles = (M + 63) / 64; p.n_tiles = (N + 63) / 64;
+    p.splits = 1; p.mt = 1; p.nb = 1; p.m_tiles = (M + 31) / 32; p.n_tiles = (N + 31) / 32;
     return p;
   }
   const int tiles32 = (M + 31) / 32;
@@ -812,8 +840,9 @@ hipError_t launch_gemm(hipStream_t st, int dtype, const void* A, const int32_t* 
                        float* out, int M, int N, int K, const GemmPlan& p, bool w_packed, int a_ld) {
   if (M <= 0) return hipSuccess;
   if (dtype == ESP_F32) {
-    hipLaunchKernelGGL(k_gemm_f32, dim3(p.n_tiles, p.m_tiles), dim3(256), 0, st, (const float*)A, a_rows,
-                       (const float*)W, out, M, N, K);
+    const bool vec = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0;
+    hipLaunchKernelGGL(vec ? k_gemm_f32<true> : k_gemm_f32<false>, dim3(p.n_tiles, p.m_tiles), dim3(64 * F32_WAVES), 0, st,
+                       (const float*)A, a_rows, (const float*)W, out, M, N, K);
     return hipGetLastError();
   }
 #define ESP_GEMM_CASE(MT_, NB_)                                                                  \
