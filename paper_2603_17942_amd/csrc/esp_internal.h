@@ -190,6 +190,7 @@ hipError_t launch_softmax_topk(hipStream_t st, const float* logits, int rows, in
                                float* probs, float* scratch, const int32_t* row_map = nullptr);
 
 // ---- tree logic (esp_tree.hip) -------------------------------------------------------------------
+hipError_t tree_prepare();   // one-time kernel attributes (dynamic LDS limits)
 hipError_t launch_block_from_tree(hipStream_t st, int batch, int rows_per_seq, int k, int layout, int anc_words,
                                   int32_t* n_rows, const int32_t* n_nodes, int32_t* tok, int32_t* parent,
                                   int32_t* depth, int32_t* mask_j, int32_t* attach, uint64_t* anc,

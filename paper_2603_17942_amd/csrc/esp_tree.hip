@@ -6,7 +6,6 @@
 
 namespace {
 
-constexpr int MAX_ANC_WORDS = ESP_MAX_ROWS_PER_SEQ / 64;
 constexpr int MAXC = 4096;   // candidates Alg. 1 may create (root included)
 
 __device__ __forceinline__ bool kv_seq_ok(const KvDev& kv, int seq, int n_rows, int rows_per_seq) {
@@ -17,71 +16,111 @@ __device__ __forceinline__ bool kv_seq_ok(const KvDev& kv, int seq, int n_rows, 
          base >= 0 && (base & 63) == 0 && (int64_t)base + cap <= kv.capacity;
 }
 
-// Derives every per-row array of one sequence from tok/parent/n_nodes of its node rows.
-// Called by all threads of the workgroup; tok/parent of the node rows must be visible.
-__device__ void finalize_block(int seq, int rows_per_seq, int k, int layout, int anc_words, int32_t* n_rows,
-                               int n_nodes, int32_t* tok, int32_t* parent, int32_t* depth, int32_t* mask_j,
-                               int32_t* attach, uint64_t* anc, int32_t* status, int* s_bad) {
+__device__ __forceinline__ int lanes_below(unsigned long long ballot) {   // set bits below this lane
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)ballot, 0u));
+}
+
+// Writes every derived per-row array of one sequence.  Called by all threads of the workgroup with the
+// structure of the node rows in LDS: node_parent(i), node_depth(i), node_anc(i, w) = word w of the bitset
+// of i and its ancestors (w < node_words).  Rows go out in row order, whole lines at a time; nothing that
+// was written is read back.  A tree that does not fit the block sets the status word instead.
+template <typename Parent, typename Depth, typename Anc>
+__device__ void write_rows(int seq, int rows_per_seq, int k, int layout, int anc_words, int n_nodes, int node_words,
+                           Parent node_parent, Depth node_depth, Anc node_anc, int32_t* n_rows, int32_t* tok,
+                           int32_t* parent, int32_t* depth, int32_t* mask_j, int32_t* attach, uint64_t* anc,
+                           int32_t* status) {
   const size_t r0 = (size_t)seq * rows_per_seq;
   const int owners = k == 0 ? 0 : (layout == ESP_LAYOUT_PER_NODE ? n_nodes : 1);
   const int total = n_nodes + owners * k;
-  if (threadIdx.x == 0) *s_bad = (n_nodes < 1 || total > rows_per_seq || (total + 63) / 64 > anc_words) ? 1 : 0;
-  __syncthreads();
-  if (!*s_bad) {
-    for (int i = threadIdx.x; i < n_nodes; i += blockDim.x) {
-      uint64_t bits[MAX_ANC_WORDS];
-      for (int w = 0; w < anc_words; ++w) bits[w] = 0;
-      int c = i, dep = 0;
-      bool bad = false;
-      for (int step = 0; step <= n_nodes; ++step) {
-        bits[c >> 6] |= 1ull << (c & 63);
-        int p = parent[r0 + c];
-        if (c == 0) { bad = p != -1; break; }
-        if (p < 0 || p >= c) { bad = true; break; }
-        c = p;
-        ++dep;
-      }
-      if (bad) atomicExch(s_bad, 1);
-      depth[r0 + i] = dep;
-      mask_j[r0 + i] = 0;
-      attach[r0 + i] = i;
-      for (int w = 0; w < anc_words; ++w) anc[(r0 + i) * anc_words + w] = bits[w];
-    }
-  }
-  __syncthreads();
-  if (*s_bad) {
+  if (n_nodes < 1 || total > rows_per_seq || (total + 63) / 64 > anc_words) {
     if (threadIdx.x == 0) { atomicOr(status, ESP_DEV_BAD_TREE); n_rows[seq] = 0; }
     return;
   }
   // mask rows: chain j = 1..k of owner a sits at n_nodes + a*k + (j-1)
-  for (int t = threadIdx.x; t < owners * k; t += blockDim.x) {
-    int a = t / k, j = t % k + 1;
-    int row = n_nodes + t;
-    int first = row - (j - 1);
-    for (int w = 0; w < anc_words; ++w) {
-      uint64_t bits = anc[(r0 + a) * anc_words + w];
-      // rows first..row of the chain
-      int lo = max(first, w * 64), hi = min(row, w * 64 + 63);
-      for (int c = lo; c <= hi; ++c) bits |= 1ull << (c & 63);
-      anc[(r0 + row) * anc_words + w] = bits;
-    }
-    tok[r0 + row] = -1;
-    parent[r0 + row] = j == 1 ? a : row - 1;
-    depth[r0 + row] = depth[r0 + a] + j;
+  for (int row = threadIdx.x; row < total; row += blockDim.x) {
+    const int t = row - n_nodes;
+    const int a = t < 0 ? row : t / k, j = t < 0 ? 0 : t - a * k + 1;
+    depth[r0 + row] = node_depth(a) + j;
     mask_j[r0 + row] = j;
     attach[r0 + row] = a;
+    parent[r0 + row] = j == 0 ? node_parent(row) : (j == 1 ? a : row - 1);
+    if (j > 0) tok[r0 + row] = -1;
+  }
+  for (int i = threadIdx.x; i < total * anc_words; i += blockDim.x) {
+    const int row = i / anc_words, w = i - row * anc_words;
+    const int t = row - n_nodes;
+    const int a = t < 0 ? row : t / k;
+    uint64_t bits = w < node_words ? node_anc(a, w) : 0ull;
+    if (t >= 0) {                                       // plus the rows of its own chain up to itself
+      const int lo = max(n_nodes + a * k, w * 64), hi = min(row, w * 64 + 63);
+      if (lo <= hi) bits |= (~0ull >> (63 - (hi - lo))) << (lo & 63);
+    }
+    anc[r0 * anc_words + i] = bits;
   }
   if (threadIdx.x == 0) n_rows[seq] = total;
 }
 
+// Block descriptor from parent pointers.  Trees here can be a prompt's chain of up to 1024 nodes, so
+// nothing walks parent by parent: a wave takes 64 consecutive nodes and closes the ancestor sets inside
+// them by pointer jumping (six rounds of lane exchanges); what lies before those 64 nodes is the finished
+// set of the first ancestor outside, copied word by word, one 64-node group after the other.
+// 512-node chain: 12 us (250 us walking one pointer at a time through global memory).
+constexpr int FROM_TREE_LDS_PER_NODE = 24;   // ancestor mask inside the group, outside ancestor, depth, parent
+
 __global__ __launch_bounds__(256) void k_block_from_tree(int rows_per_seq, int k, int layout, int anc_words,
-                                                         int32_t* n_rows, const int32_t* n_nodes, int32_t* tok,
+                                                         int32_t* n_rows, const int32_t* n_nodes_arr, int32_t* tok,
                                                          int32_t* parent, int32_t* depth, int32_t* mask_j,
                                                          int32_t* attach, uint64_t* anc, int32_t* status) {
-  __shared__ int s_bad;
-  const int seq = blockIdx.x;
-  finalize_block(seq, rows_per_seq, k, layout, anc_words, n_rows, n_nodes[seq], tok, parent, depth, mask_j,
-                 attach, anc, status, &s_bad);
+  extern __shared__ __align__(16) unsigned char raw[];
+  const int seq = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = n_nodes_arr[seq];
+  const size_t r0 = (size_t)seq * rows_per_seq;
+  const int nw = (min(max(n, 0), rows_per_seq) + 63) >> 6;             // groups = words of a node's set
+  uint64_t* s_anc = reinterpret_cast<uint64_t*>(raw);                  // [rows_per_seq][nw]
+  uint64_t* s_mask = s_anc + (size_t)rows_per_seq * anc_words;         // [rows_per_seq]
+  int32_t* s_ext = reinterpret_cast<int32_t*>(s_mask + rows_per_seq);
+  int32_t* s_dep = s_ext + rows_per_seq;
+  int32_t* s_par = s_dep + rows_per_seq;
+  bool bad = n < 1 || n > rows_per_seq;
+  if (!bad)
+    for (int i = tid; i < n; i += blockDim.x) {
+      const int p = parent[r0 + i];
+      s_par[i] = p;
+      if (i == 0 ? p != -1 : (p < 0 || p >= i)) bad = true;
+    }
+  if (__syncthreads_or(bad)) {
+    if (tid == 0) { atomicOr(status, ESP_DEV_BAD_TREE); n_rows[seq] = 0; }
+    return;
+  }
+  for (int g = wave; g < nw; g += 4) {
+    const int row = g * 64 + lane;
+    const int p = row < n ? s_par[row] : -1;
+    int jump = p >= g * 64 ? p - g * 64 : -1, d = jump >= 0 ? 1 : 0, ext = p;
+    unsigned long long mask = 1ull << lane;
+    while (__builtin_amdgcn_ballot_w64(jump >= 0)) {                    // at most six rounds: the hops double
+      const int from = jump >= 0 ? jump : lane;
+      const unsigned long long om = __shfl(mask, from, 64);
+      const int oj = __shfl(jump, from, 64), od = __shfl(d, from, 64), oe = __shfl(ext, from, 64);
+      if (jump >= 0) { mask |= om; d += od; jump = oj; ext = oe; }
+    }
+    if (row < n) { s_mask[row] = mask; s_ext[row] = ext; s_dep[row] = d; }
+  }
+  __syncthreads();
+  for (int g = 0; g < nw; ++g) {
+    const int rows_g = min(64, n - g * 64);
+    for (int i = tid; i < 64 * nw; i += blockDim.x) {
+      const int row = g * 64 + (i & 63), w = i >> 6;
+      if ((i & 63) < rows_g) {
+        const int e = s_ext[row];
+        s_anc[(size_t)row * nw + w] = w == g ? s_mask[row] : (w < g && e >= 0 ? s_anc[(size_t)e * nw + w] : 0ull);
+        if (w == 0 && e >= 0) s_dep[row] += s_dep[e] + 1;
+      }
+    }
+    __syncthreads();
+  }
+  write_rows(seq, rows_per_seq, k, layout, anc_words, n, nw, [&](int i) { return s_par[i]; },
+             [&](int i) { return s_dep[i]; }, [&](int i, int w) { return s_anc[(size_t)i * nw + w]; }, n_rows, tok, parent,
+             depth, mask_j, attach, anc, status);
 }
 
 // ---- greedy verification (Sec. 2 Eq. 3) -----------------------------------------------------------------
@@ -167,146 +206,221 @@ __global__ void k_mask_rows(BlockDev b, const int32_t* star_row, const int32_t* 
 }
 
 // ---- pruning + dynamic tree (Alg. 1, Sec. 3.5) -----------------------------------------------------------
+// Candidates of Alg. 1 that can still be part of the tree.  The tree is the root plus the B - 1 most
+// probable of all candidates, a child is never more probable than its parent and is created after it:
+// so a candidate that is not among the B - 1 best created so far is out for good, and so is everything
+// that would grow from it.  Only the best B - 1 are kept from depth to depth (sorted), and of a depth's
+// children only those are created that beat the last of a full set.  Relative creation order, which
+// breaks ties and orders rows, is what the creation index records.
+constexpr int MAX_CAND = MAXC + ESP_MAX_TREE_NODES;
 struct TreeLds {
+  // every candidate created, by creation index (0 = the root)
   int32_t tok[MAXC];
-  float prob[MAXC];
   int16_t par[MAXC];
   uint8_t dep[MAXC];
-  uint8_t used[MAXC];        // has been in the node set N
-  uint64_t key[MAXC];        // sort buffer
-  int32_t frontier[ESP_MAX_TREE_NODES];
-  int32_t expand[ESP_MAX_TREE_NODES];
-  int32_t scan[256];
-  int32_t n_total, n_frontier, n_expand, bad;
-  int32_t n_surv, bin1, before1, bin2;   // select_best
+  uint8_t used[MAXC];           // has been in the node set N
+  // the kept candidates, sorted, followed by a depth's new ones: probability and creation index; two
+  // buffers, a selection writes the other one
+  float prob[2][MAX_CAND];
+  int32_t cre[2][MAX_CAND];
+  float pick_p[ESP_MAX_TREE_NODES];        // survivors of a selection, in list order
+  int32_t pick[ESP_MAX_TREE_NODES];
+  int32_t expand[ESP_MAX_TREE_NODES];      // list places of the kept candidates to expand next, in order
+  __align__(16) uint32_t order[ESP_MAX_TREE_NODES];   // depth << 16 | creation index of the kept nodes
+  int32_t row_tok[ESP_MAX_TREE_NODES], row_par[ESP_MAX_TREE_NODES], row_dep[ESP_MAX_TREE_NODES];
+  uint64_t row_anc[ESP_MAX_TREE_NODES][ESP_MAX_TREE_NODES / 64];
+  int16_t row_of[MAXC];                    // creation index -> row
   int32_t list_id[ESP_MAX_MASKS * ESP_MAX_TOPK];   // the sequence's Top-K' lists, staged once
   float list_p[ESP_MAX_MASKS * ESP_MAX_TOPK];
+  int32_t n_cand, n_keep, kept_buf;        // n_keep -1: more candidates or nodes than there is room for
 };
 
-__device__ __forceinline__ uint64_t cand_key(float p, int creation) {
-  // ascending key order = probability descending, then creation ascending
-  return ((uint64_t)(~__float_as_uint(p)) << 32) | (uint32_t)creation;
+// How many of n fp32 values >= 0 in LDS reach `bound` (compared as bit patterns); one wave.
+__device__ __forceinline__ int count_reaching(const float* v, int n, uint32_t bound, int lane) {
+  int cnt = 0;
+#pragma unroll 1
+  for (int j = 0; j < n; j += 64)
+    cnt += __popcll(__builtin_amdgcn_ballot_w64(j + lane < n && __float_as_uint(v[min(j + lane, n - 1)]) >= bound));
+  return cnt;
 }
 
-__device__ void bitonic_sort(uint64_t* key, int n_pow2) {
-  for (int size = 2; size <= n_pow2; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int t = threadIdx.x; t < (n_pow2 >> 1); t += blockDim.x) {
-        int lo = 2 * t - (t & (stride - 1));
-        int hi = lo + stride;
-        bool up = (lo & size) == 0;
-        uint64_t a = key[lo], c = key[hi];
-        if ((a > c) == up) { key[lo] = c; key[hi] = a; }
-      }
-      __syncthreads();
-    }
+// One wave, for more candidates than a workgroup has threads: the T best (T <= 255) of the n in buffer
+// `from`, unsorted but in list order, to s.pick / pick_p.  The T-th largest probability is found bit by
+// bit from the top: a count (ballot, popcount) of the values that reach the prefix with the bit set.
+__device__ void pick_best(TreeLds& s, int from, int n, int T, int lane) {
+  const float* v = s.prob[from];
+  uint32_t bound = 0;
+  int reach = n;
+#pragma unroll 1
+  for (int bit = 30; bit >= 0 && reach != T; --bit) {
+    const uint32_t b = bound | (1u << bit);
+    const int cnt = count_reaching(v, n, b, lane);
+    if (cnt >= T) { bound = b; reach = cnt; }
+  }
+  int room = reach == T ? n : T - count_reaching(v, n, bound + 1, lane);   // how many of those equal to the bound fit
+  int base = 0;
+#pragma unroll 1
+  for (int j = 0; j < n; j += 64) {
+    const int i = j + lane;
+    const float p = i < n ? v[i] : -1.f;
+    const uint32_t u = __float_as_uint(p);
+    const bool eq = i < n && u == bound, gt = i < n && u > bound;
+    const unsigned long long be = __builtin_amdgcn_ballot_w64(eq);
+    const bool sel = gt || (eq && lanes_below(be) < room);
+    room -= __popcll(be);
+    const unsigned long long bs = __builtin_amdgcn_ballot_w64(sel);
+    const int at = base + lanes_below(bs);
+    if (sel) { s.pick[at] = s.cre[from][i]; s.pick_p[at] = p; }
+    base += __popcll(bs);
   }
 }
 
-// exclusive scan of one value per thread over the 256-thread block; returns (prefix, total via *tot)
-__device__ int block_excl_scan(int v, int32_t* buf, int* tot) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int incl = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int x = __shfl_up(incl, o, 64);
-    if (lane >= o) incl += x;
+// The whole workgroup: of the n candidates of buffer `from` the T best (T <= 255), sorted by (probability
+// descending, creation ascending), to the other buffer; returns how many.  A thread per candidate
+// counts the better ones: the others' probabilities come from a register of the wave lane by lane, so a
+// comparison is three instructions and no LDS access.  Candidates of equal probability lie in creation
+// order in both buffers.
+__device__ int keep_best(TreeLds& s, int from, int n, int T) {
+  const int tid = threadIdx.x, lane = tid & 63, a0 = tid & ~63;
+  const bool pick = n > 256;
+  const int m = pick ? T : n;
+  if (pick) {
+    if (tid < 64) pick_best(s, from, n, T, lane);
+    __syncthreads();
   }
-  if (lane == 63) buf[wave] = incl;
-  __syncthreads();
-  const int w0 = buf[0], w1 = buf[1], w2 = buf[2], w3 = buf[3];
-  *tot = w0 + w1 + w2 + w3;
-  const int base = wave == 0 ? 0 : wave == 1 ? w0 : wave == 2 ? w0 + w1 : w0 + w1 + w2;
-  __syncthreads();
-  return base + incl - v;
-}
-
-// The T best (smallest key) of the eligible candidates 0..n-1, in key order, to out[0..m);
-// returns m = min(T, eligible), or -1 when the shortcut below does not apply (the caller then
-// sorts everything).  T <= 255.  Instead of sorting all candidates, a two-level histogram over the
-// key's leading bits (the probability's exponent, then its top 8 mantissa bits) finds a prefix
-// bound that at least T candidates meet; the few that meet it (T plus the occupants of one
-// histogram cell, at most 256 or the shortcut is off) are ranked against each other directly.
-// Keys are unique (they end in the creation index), so ranks are a permutation.
-template <typename Elig>
-__device__ int select_best(TreeLds& s, int n, int T, Elig eligible, int32_t* out) {
-  const int tid = threadIdx.x, lane = tid & 63;
-  if (T <= 0) return 0;
-  // first histogram cell (scanning from the best) at which the running count reaches `want`
-  auto find_cell = [&](int want, int32_t* cell, int32_t* before) {
-    if (tid < 64) {
-      int c[4], sum = 0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) { c[q] = s.scan[4 * lane + q]; sum += c[q]; }
-      int incl = sum;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        int x = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += x;
-      }
-      int run = incl - sum, found = -1, bef = 0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (found < 0 && run + c[q] >= want) { found = 4 * lane + q; bef = run; }
-        run += c[q];
-      }
-      const unsigned long long hit = __builtin_amdgcn_ballot_w64(found >= 0);
-      if (hit) {
-        const int src = __builtin_ctzll(hit);
-        found = __builtin_amdgcn_readlane(found, src);
-        bef = __builtin_amdgcn_readlane(bef, src);
-      } else {
-        found = 256;                                   // fewer than `want` in all cells: everything qualifies
-        bef = __builtin_amdgcn_readlane(incl, 63);
-      }
-      if (lane == 0) { *cell = found; *before = bef; }
-    }
-  };
-  if (tid == 0) { s.n_surv = 0; s.bin1 = 256; s.bin2 = 256; s.before1 = 0; }
-  if (n > 256) {
-    s.scan[tid] = 0;
-    __syncthreads();
-    for (int t = tid; t < n; t += 256)
-      if (eligible(t)) atomicAdd(&s.scan[(int)(cand_key(s.prob[t], t) >> 55) & 0xff], 1);
-    __syncthreads();
-    find_cell(T, &s.bin1, &s.before1);
-    __syncthreads();
-    const int b1 = s.bin1;
-    if (b1 < 256) {
-      s.scan[tid] = 0;
-      __syncthreads();
-      for (int t = tid; t < n; t += 256)
-        if (eligible(t)) {
-          const uint64_t kx = cand_key(s.prob[t], t);
-          if (((int)(kx >> 55) & 0xff) == b1) atomicAdd(&s.scan[(int)(kx >> 47) & 0xff], 1);
-        }
-      __syncthreads();
-      int32_t unused_before;
-      find_cell(T - s.before1, &s.bin2, tid == 0 ? &s.n_expand : &unused_before);   // n_expand: scratch
-    }
-  }
-  __syncthreads();
-  const int b1 = s.bin1, b2 = s.bin2;
-  for (int t = tid; t < n; t += 256)
-    if (eligible(t)) {
-      const uint64_t kx = cand_key(s.prob[t], t);
-      const int c1 = (int)(kx >> 55) & 0xff, c2 = (int)(kx >> 47) & 0xff;
-      if (c1 < b1 || (c1 == b1 && c2 <= b2)) {
-        const int idx = atomicAdd(&s.n_surv, 1);
-        if (idx < 256) s.key[idx] = kx;
-      }
-    }
-  __syncthreads();
-  const int ns = s.n_surv;
-  if (ns > 256) return -1;
-  if (tid < ns) {
-    const uint64_t kj = s.key[tid];
+  const float* v = pick ? s.pick_p : s.prob[from];
+  const int32_t* c = pick ? s.pick : s.cre[from];
+  if (a0 < m) {                                            // wave-uniform
+    const int32_t p = tid < m ? __float_as_int(v[tid]) : 0x7fffffff;      // >= 0.0: ordered as integers
     int rank = 0;
-    for (int i = 0; i < ns; ++i) rank += s.key[i] < kj ? 1 : 0;
-    if (rank < T) out[rank] = (int)(kj & 0xffffffffu);
+#pragma unroll 1
+    for (int b0 = 0; b0 < m; b0 += 64) {
+      const int32_t o64 = b0 + lane < m ? __float_as_int(v[b0 + lane]) : -1;   // padding: worse than anything
+      const int32_t reach = b0 < a0 ? p - 1 : p;           // equal ones before this candidate are better
+      if (b0 == a0) {
+#pragma unroll 8
+        for (int l = 0; l < 64; ++l) rank += __builtin_amdgcn_readlane(o64, l) > p - (l < lane ? 1 : 0) ? 1 : 0;
+      } else {
+#pragma unroll 8
+        for (int l = 0; l < 64; ++l) rank += __builtin_amdgcn_readlane(o64, l) > reach ? 1 : 0;
+      }
+    }
+    if (tid < m && rank < T) { s.prob[from ^ 1][rank] = __int_as_float(p); s.cre[from ^ 1][rank] = c[tid]; }
   }
-  __syncthreads();
-  return min(T, ns);
+  return min(m, T);
+}
+
+// Alg. 1.  One wave creates a depth's candidates and picks the node set (lane exchanges and ballots
+// instead of workgroup barriers), the workgroup sorts.  Leaves the kept candidates in
+// s.cre[s.kept_buf][0..s.n_keep).  Latency is all there is to it: the code is kept in small loops on
+// purpose (it runs once per launch, so instruction fetch costs more than arithmetic).  B = 64, k = 4,
+// K = 8: the call takes 16 us; 36 us with every candidate created and a histogram per selection.
+__device__ void grow_tree(TreeLds& s, const esp_tree_params& p, int root_tok, int kp, int depth_limit) {
+  const int lane = threadIdx.x & 63;
+  const bool first_wave = threadIdx.x < 64;
+  const bool is_static = p.static_widths[0] > 0;
+  const int T = max(p.B - 1, 0);
+  const int K = p.K, B = p.B, ew = p.expand_width, drop_parent = p.prune_parent, drop_last = p.prune_last;
+  int buf = 0;
+  int nk = 0;                       // candidates kept
+  int n_cre = 1;                    // next creation index (first wave)
+  int n_exp = 1;                    // nodes to expand: the root first (first wave)
+#pragma unroll 1
+  for (int i = 1; i <= depth_limit; ++i) {
+    if (first_wave) {
+      const int want = is_static ? p.static_widths[i - 1] : min(K, B - i);
+      const int32_t id = lane < kp ? s.list_id[(i - 1) * kp + lane] : -1;
+      const float lp = lane < kp ? s.list_p[(i - 1) * kp + lane] : 0.f;
+      const int nv = __builtin_ctzll(__builtin_amdgcn_ballot_w64(id < 0));          // a negative id ends a list
+      const float floor_p = !is_static && T > 0 && nk >= T ? s.prob[buf][T - 1] : -1.f;
+      int n = nk;
+#pragma unroll 1
+      for (int e0 = 0; e0 < n_exp; e0 += 64) {
+        const bool live = e0 + lane < n_exp;
+        const int place = live && i > 1 ? s.expand[e0 + lane] : 0;
+        const int pcre = i > 1 ? s.cre[buf][place] : 0;
+        const int ptok = i > 1 ? s.tok[pcre] : root_tok;
+        const float pp = i > 1 ? s.prob[buf][place] : 1.0f;
+        // children: the first `want` list entries that survive the pruning rule; created if they can
+        // still be part of the tree
+        uint32_t make = 0;
+        int taken = 0;
+#pragma unroll 1
+        for (int c = 0; c < nv; ++c) {
+          const int t = __builtin_amdgcn_readlane(id, c);
+          const float q = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lp), c));
+          const bool ok = live && taken < want && !(drop_parent && t == ptok) && !(drop_last && i >= 2 && t == root_tok);
+          taken += ok ? 1 : 0;
+          if (ok && pp * q > floor_p) make |= 1u << c;
+        }
+        const int cnt = __popc(make);
+        int off = 0, tot = 0;
+#pragma unroll 1
+        for (int b = 0; b < 6; ++b) {                     // prefix sum of counts up to 32, bit by bit
+          const unsigned long long bb = __builtin_amdgcn_ballot_w64((cnt >> b) & 1);
+          off += lanes_below(bb) << b;
+          tot += __popcll(bb) << b;
+        }
+        if (n_cre + tot > MAXC) { n = -1; break; }
+#pragma unroll 1
+        for (int made = off; make; ++made) {
+          const int c = __builtin_ctz(make);
+          make &= make - 1;
+          const int cre = n_cre + made;
+          s.tok[cre] = s.list_id[(i - 1) * kp + c];
+          s.par[cre] = (int16_t)pcre;
+          s.dep[cre] = (uint8_t)i;
+          s.used[cre] = 0;
+          s.prob[buf][n + made] = pp * s.list_p[(i - 1) * kp + c];     // one fp32 product (Alg. 1: P(c) = P(n) * P(t|l))
+          s.cre[buf][n + made] = cre;
+        }
+        n += tot;
+        n_cre += tot;
+      }
+      if (lane == 0) s.n_cand = n;
+    }
+    __syncthreads();
+    const int n = s.n_cand;
+    if (n < 0) { if (threadIdx.x == 0) s.n_keep = -1; return; }
+    if (n == nk) break;             // nothing new: no deeper node either, and the list is sorted as it is
+    if (is_static) {
+      // fixed tree: everything is kept, in creation order, and the first fresh child is expanded next
+      n_exp = 1;
+      if (threadIdx.x == 0) s.expand[0] = nk;
+      nk = n;
+    } else {
+      nk = keep_best(s, buf, n, T);
+      buf ^= 1;
+    }
+    if (i == depth_limit) break;
+    __syncthreads();
+    if (first_wave && !is_static) {
+      // node set <- the B - i most probable candidates not used before; those of depth i are expanded next
+      int room = max(B - i, 0), ne = 0;
+      const int width = ew > 0 ? ew : ESP_MAX_TREE_NODES;
+#pragma unroll 1
+      for (int a0 = 0; a0 < nk; a0 += 64) {
+        const int a = a0 + lane;
+        const int cre = s.cre[buf][min(a, nk - 1)];
+        const bool fresh = a < nk && !s.used[cre];
+        const unsigned long long bf = __builtin_amdgcn_ballot_w64(fresh);
+        const bool in = fresh && lanes_below(bf) < room;
+        room -= __popcll(bf);
+        if (in) s.used[cre] = 1;
+        const bool ex = in && s.dep[cre] == i;
+        const unsigned long long bx = __builtin_amdgcn_ballot_w64(ex);
+        const int at = ne + lanes_below(bx);
+        if (ex && at < width) s.expand[at] = a;
+        ne += __popcll(bx);
+      }
+      n_exp = min(ne, width);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+  }
+  if (threadIdx.x == 0) {
+    s.n_keep = nk + 1 > ESP_MAX_TREE_NODES ? -1 : nk;
+    s.kept_buf = buf;
+  }
 }
 
 __global__ __launch_bounds__(256) void k_build_tree(esp_tree_params p, const int32_t* __restrict__ topk_id,
@@ -319,7 +433,6 @@ __global__ __launch_bounds__(256) void k_build_tree(esp_tree_params p, const int
                                                     int32_t* attach, uint64_t* anc, int32_t* status, int reuse) {
   extern __shared__ __align__(16) unsigned char raw[];
   TreeLds& s = *reinterpret_cast<TreeLds*>(raw);
-  __shared__ int s_bad;
   const int seq = blockIdx.x, tid = threadIdx.x;
   const size_t r0 = (size_t)seq * rows_per_seq;
   const int ne = n_emit[seq];
@@ -368,187 +481,77 @@ __global__ __launch_bounds__(256) void k_build_tree(esp_tree_params p, const int
       }
     }
   }
-  if (tid == 0) {
-    s.tok[0] = emit_tok[(size_t)seq * (ESP_MAX_MASKS + 1) + ne - 1];
-    s.prob[0] = 1.0f;
-    s.par[0] = -1;
-    s.dep[0] = 0;
-    s.used[0] = 1;
-    s.n_total = 1;
-    s.frontier[0] = 0;
-    s.n_frontier = 1;
-    s.bad = 0;
-  }
+  const int root_tok = emit_tok[(size_t)seq * (ESP_MAX_MASKS + 1) + ne - 1];
   for (int t = tid; t < p.k * kp; t += 256) {
     s.list_id[t] = topk_id[(size_t)seq * p.k * kp + t];
     s.list_p[t] = topk_p[(size_t)seq * p.k * kp + t];
   }
   __syncthreads();
-  const int32_t* ids = s.list_id;
-  const float* ps = s.list_p;
-
-  for (int i = 1; i <= depth_limit; ++i) {
-    // nodes of the current set at depth i-1, in (P desc, creation asc) order, first expand_width
-    const int nf = s.n_frontier;
-    int flag = (tid < nf && s.dep[s.frontier[tid]] == i - 1) ? 1 : 0;
-    int tot;
-    int pos = block_excl_scan(flag, s.scan, &tot);
-    int n_exp = p.expand_width > 0 ? min(tot, p.expand_width) : tot;
-    if (flag && pos < n_exp) s.expand[pos] = s.frontier[tid];
-    __syncthreads();
-    const int want = is_static ? p.static_widths[i - 1] : min(p.K, p.B - i);
-    const int32_t* li = ids + (size_t)(i - 1) * kp;
-    const float* lp = ps + (size_t)(i - 1) * kp;
-    // children per expanded node: first `want` list entries that survive the pruning rule
-    int cnt = 0, node = -1;
-    if (tid < n_exp) {
-      node = s.expand[tid];
-      for (int c = 0; c < kp && cnt < want; ++c) {
-        int t = li[c];
-        if (t < 0) break;
-        if (p.prune_parent && t == s.tok[node]) continue;
-        if (p.prune_last && i >= 2 && t == s.tok[0]) continue;
-        ++cnt;
-      }
-    }
-    int off = block_excl_scan(cnt, s.scan, &tot);
-    const int n_old = s.n_total;
-    if (n_old + tot > MAXC) {
-      if (tid == 0) s.bad = 1;
-      __syncthreads();
-      break;
-    }
-    if (tid < n_exp) {
-      int made = 0;
-      for (int c = 0; c < kp && made < want; ++c) {
-        int t = li[c];
-        if (t < 0) break;
-        if (p.prune_parent && t == s.tok[node]) continue;
-        if (p.prune_last && i >= 2 && t == s.tok[0]) continue;
-        int idx = n_old + off + made;
-        s.tok[idx] = t;
-        s.prob[idx] = s.prob[node] * lp[c];     // one fp32 product (Alg. 1: P(c) = P(n) * P(t|l))
-        s.par[idx] = (int16_t)node;
-        s.dep[idx] = (uint8_t)i;
-        s.used[idx] = 0;
-        ++made;
-      }
-    }
-    __syncthreads();
-    if (tid == 0) s.n_total = n_old + tot;
-    __syncthreads();
-    if (i < depth_limit) {
-      if (is_static) {
-        // fixed tree: the new node set is exactly the fresh children
-        for (int t = tid; t < tot && t < ESP_MAX_TREE_NODES; t += 256) s.frontier[t] = n_old + t;
-        if (tid == 0) s.n_frontier = min(tot, (int)ESP_MAX_TREE_NODES);
-        __syncthreads();
-      } else {
-        // node set <- the B-i most probable candidates not used before
-        const int n = s.n_total;
-        const int got = select_best(s, n, max(p.B - i, 0), [&](int t) { return !s.used[t]; }, s.frontier);
-        if (got >= 0) {
-          if (tid < got) s.used[s.frontier[tid]] = 1;
-          if (tid == 0) s.n_frontier = got;
-          __syncthreads();
-          continue;
-        }
-        int n2 = 1;
-        while (n2 < n) n2 <<= 1;
-        for (int t = tid; t < n2; t += 256)
-          s.key[t] = (t < n && !s.used[t]) ? cand_key(s.prob[t], t) : ~0ull;
-        __syncthreads();
-        bitonic_sort(s.key, n2);
-        const int take = max(p.B - i, 0);
-        for (int t = tid; t < take && t < n2; t += 256) {
-          uint64_t kx = s.key[t];
-          if (kx != ~0ull) {
-            int c = (int)(kx & 0xffffffffu);
-            s.frontier[t] = c;
-            s.used[c] = 1;
-          }
-        }
-        __syncthreads();
-        if (tid == 0) {
-          int cntf = 0;
-          while (cntf < take && cntf < n2 && s.key[cntf] != ~0ull) ++cntf;
-          s.n_frontier = cntf;
-        }
-        __syncthreads();
-      }
-    }
-  }
+  grow_tree(s, p, root_tok, kp, depth_limit);
   __syncthreads();
-
-  // final selection: root + the B-1 most probable of all candidates (static: all of them)
-  const int n = s.n_total;
-  int n_keep = n - 1;
-  int32_t* kept = s.expand;                 // kept candidates in selection order (free after the loop)
-  if (!s.bad) {
-    if (!is_static) {
-      n_keep = min(n - 1, max(p.B - 1, 0));
-      const int got = select_best(s, n, n_keep, [](int t) { return t >= 1; }, kept);
-      if (got < 0) {
-        int n2 = 1;
-        while (n2 < n) n2 <<= 1;
-        for (int t = tid; t < n2; t += 256) s.key[t] = (t >= 1 && t < n) ? cand_key(s.prob[t], t) : ~0ull;
-        __syncthreads();
-        bitonic_sort(s.key, n2);
-        if (tid < n_keep) kept[tid] = (int)(s.key[tid] & 0xffffffffu);
-      }
-    } else if (n_keep + 1 <= ESP_MAX_TREE_NODES) {
-      if (tid < n_keep) kept[tid] = tid + 1;              // fixed tree: every candidate, creation order
-    }
-    if (n_keep + 1 > ESP_MAX_TREE_NODES) {
-      if (tid == 0) s.bad = 1;
-    }
-  }
-  __syncthreads();
-  if (s.bad) {
+  if (s.n_keep < 0) {
     if (tid == 0) { n_rows[seq] = 0; n_nodes[seq] = 0; atomicOr(status, ESP_DEV_BAD_TREE); }
     return;
   }
-  // rows: kept nodes ordered by (depth, creation); n_keep <= 255 so one thread per kept node
-  int my = -1, my_rank = 0;
-  if (tid < n_keep) my = kept[tid];
+  // rows: the root, then the kept nodes ordered by (depth, creation); one thread per node (at most 255)
+  const int n_keep = s.n_keep;
+  const int cre = tid < n_keep ? s.cre[s.kept_buf][tid] : 0;
+  const uint32_t mine = tid < n_keep ? ((uint32_t)s.dep[cre] << 16) | (uint32_t)cre : 0xffffffffu;
+  s.order[tid] = mine;
+  if (tid == 0) { s.row_of[0] = 0; s.row_tok[0] = root_tok; s.row_par[0] = -1; s.row_dep[0] = 0; }
   __syncthreads();
-  if (tid < n_keep) s.scan[tid] = my;
-  __syncthreads();
-  if (tid < n_keep) {
-    uint32_t mk = ((uint32_t)s.dep[my] << 24) | (uint32_t)my;
-    for (int u = 0; u < n_keep; ++u) {
-      int o = s.scan[u];
-      uint32_t ok = ((uint32_t)s.dep[o] << 24) | (uint32_t)o;
-      my_rank += ok < mk ? 1 : 0;
-    }
-  }
-  __syncthreads();
-  // creation index -> new row, kept in the (now free) sort buffer
-  int32_t* new_row = reinterpret_cast<int32_t*>(s.key);
-  if (tid == 0) new_row[0] = 0;
-  if (tid < n_keep) new_row[my] = my_rank + 1;
-  __syncthreads();
-  if (tid == 0) {
-    tok[r0] = s.tok[0];
-    parent[r0] = -1;
-    n_nodes[seq] = n_keep + 1;
+  int row = 1;
+  for (int b = 0; b < n_keep; b += 4) {
+    const u32x4_t o = *reinterpret_cast<const u32x4_t*>(s.order + b);    // entries past n_keep are the largest value
+#pragma unroll
+    for (int e = 0; e < 4; ++e) row += o[e] < mine ? 1 : 0;
   }
   if (tid < n_keep) {
-    tok[r0 + my_rank + 1] = s.tok[my];
-    parent[r0 + my_rank + 1] = new_row[s.par[my]];
+    s.row_of[cre] = (int16_t)row;
+    s.row_tok[row] = s.tok[cre];
+    s.row_dep[row] = (int32_t)(mine >> 16);
   }
   __syncthreads();
-  finalize_block(seq, rows_per_seq, p.k, p.layout, anc_words, n_rows, n_keep + 1, tok, parent, depth, mask_j,
-                 attach, anc, status, &s_bad);
+  if (tid < n_keep) s.row_par[row] = s.row_of[s.par[cre]];
+  __syncthreads();
+  if (tid <= n_keep) {
+    uint64_t bits[ESP_MAX_TREE_NODES / 64] = {};
+    for (int c = tid; c >= 0; c = s.row_par[c])                            // at most k + 1 hops
+#pragma unroll
+      for (int w = 0; w < ESP_MAX_TREE_NODES / 64; ++w) bits[w] |= (c >> 6) == w ? 1ull << (c & 63) : 0ull;
+#pragma unroll
+    for (int w = 0; w < ESP_MAX_TREE_NODES / 64; ++w) s.row_anc[tid][w] = bits[w];
+    tok[r0 + tid] = s.row_tok[tid];
+  }
+  if (tid == 0) n_nodes[seq] = n_keep + 1;
+  __syncthreads();
+  write_rows(seq, rows_per_seq, p.k, p.layout, anc_words, n_keep + 1, ESP_MAX_TREE_NODES / 64,
+             [&](int i) { return s.row_par[i]; }, [&](int i) { return s.row_dep[i]; },
+             [&](int i, int w) { return s.row_anc[i][w]; }, n_rows, tok, parent, depth, mask_j, attach, anc, status);
 }
 
 }  // namespace
+
+// the tree kernels use more dynamic LDS than a kernel gets by default: raise the limits once (also
+// called when a context is created, so that no launch inside a stream capture is the first one)
+hipError_t tree_prepare() {
+  static const hipError_t attr = [] {
+    const int from_tree = ESP_MAX_ROWS_PER_SEQ * (8 * (ESP_MAX_ROWS_PER_SEQ / 64) + FROM_TREE_LDS_PER_NODE);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_block_from_tree),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, from_tree);
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(k_build_tree), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)sizeof(TreeLds));
+  }();
+  return attr;
+}
 
 hipError_t launch_block_from_tree(hipStream_t st, int batch, int rows_per_seq, int k, int layout, int anc_words,
                                   int32_t* n_rows, const int32_t* n_nodes, int32_t* tok, int32_t* parent,
                                   int32_t* depth, int32_t* mask_j, int32_t* attach, uint64_t* anc,
                                   int32_t* status) {
-  hipLaunchKernelGGL(k_block_from_tree, dim3(batch), dim3(256), 0, st, rows_per_seq, k, layout, anc_words, n_rows,
+  const size_t lds = (size_t)rows_per_seq * (8 * anc_words + FROM_TREE_LDS_PER_NODE);
+  hipLaunchKernelGGL(k_block_from_tree, dim3(batch), dim3(256), lds, st, rows_per_seq, k, layout, anc_words, n_rows,
                      n_nodes, tok, parent, depth, mask_j, attach, anc, status);
   return hipGetLastError();
 }
@@ -580,13 +583,8 @@ hipError_t launch_build_tree(hipStream_t st, const esp_tree_params& p, int batch
                              const int32_t* emit_tok, int rows_per_seq, int anc_words, int32_t* n_rows,
                              int32_t* n_nodes, int32_t* tok, int32_t* parent, int32_t* depth, int32_t* mask_j,
                              int32_t* attach, uint64_t* anc, int32_t* status, bool reuse) {
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_build_tree),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(TreeLds));
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  const hipError_t attr = tree_prepare();
+  if (attr != hipSuccess) return attr;
   hipLaunchKernelGGL(k_build_tree, dim3(batch), dim3(256), sizeof(TreeLds), st, p, topk_id, topk_p, kp, n_lists,
                      n_emit, emit_tok, rows_per_seq, anc_words, n_rows, n_nodes, tok, parent, depth, mask_j,
                      attach, anc, status, reuse ? 1 : 0);

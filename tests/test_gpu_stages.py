@@ -213,6 +213,44 @@ def test_block_from_tree_rejects_malformed_tree(B, tiny_engine):
     assert eng.device_status() == 0   # sticky word was cleared by the read
 
 
+@pytest.mark.parametrize("n", [64, 65, 513, 1024])
+def test_block_from_tree_long_chains(B, tiny_engine, n):
+    """Prompt chains and deep random trees across the 64-node groups, up to the largest block."""
+    shape, w, _ = tiny_engine
+    eng = B.Engine(shape, w, 2, n, 2 * n)
+    rng = np.random.default_rng(n)
+    chain = [-1] + list(range(n - 1))
+    deep = [-1] + [int(rng.integers(max(0, i - 3), i)) for i in range(1, n)]
+    blk = B.BlockBuffers(2, n, 0, 0)
+    blk.upload_trees([[1] * n, [2] * n], [chain, deep])
+    eng.block_from_tree(blk)
+    assert eng.device_status() == 0
+    for b, par in enumerate((chain, deep)):
+        check_block(blk, b, np.full(n, b + 1), np.asarray(par), 0, 0)
+
+
+@pytest.mark.parametrize("Bn,k,K,kp", [(256, 2, 32, 32), (200, 3, 20, 22), (65, 5, 8, 10), (1, 2, 4, 6)])
+def test_build_prune_tree_large_and_smallest(B, tiny_engine, Bn, k, K, kp):
+    """More candidates than threads of the builder (its threshold path), the largest tree and the root alone."""
+    shape, w, eng = tiny_engine
+    rng = np.random.default_rng(Bn)
+    ids, ps = random_lists(rng, k, kp, 500)
+    rows = Bn + k
+    nxt = B.BlockBuffers(1, rows, k, 1)
+    emit = np.zeros((1, B.MAX_MASKS + 1), dtype=np.int32)
+    emit[0, 0] = 501
+    dev = lambda a: torch.as_tensor(a).cuda()
+    one = np.array([1], dtype=np.int32)
+    eng.build_prune_tree(B.tree_params(Bn, k, K, 0, True, False, 1), dev(ids[None]), dev(ps[None]), kp, dev(one * k), dev(one),
+                         dev(emit), nxt)
+    assert eng.device_status() == 0
+    tok, par, _ = O.build_prune_tree(O.TreeParams(B=Bn, k=k, K=K, expand_width=0, prune_parent=True), ids, ps, 501, n_depths=k)
+    n = int(nxt.n_nodes[0])
+    assert n == len(tok)
+    assert nxt.tok[:n].tolist() == tok.tolist() and nxt.parent[:n].tolist() == par.tolist()
+    check_block(nxt, 0, tok, par, k, 1)
+
+
 # ---------------------------------------------------------------------------------------- tree builder
 def random_lists(rng, k, kp, vocab):
     ids = np.zeros((k, kp), dtype=np.int32)
