@@ -229,7 +229,7 @@ def test_block_from_tree_long_chains(B, tiny_engine, n):
         check_block(blk, b, np.full(n, b + 1), np.asarray(par), 0, 0)
 
 
-@pytest.mark.parametrize("Bn,k,K,kp", [(256, 2, 32, 32), (200, 3, 20, 22), (65, 5, 8, 10), (1, 2, 4, 6)])
+@pytest.mark.parametrize("Bn,k,K,kp", [(256, 2, 32, 32), (200, 3, 10, 12), (65, 5, 8, 10), (1, 2, 4, 6)])
 def test_build_prune_tree_large_and_smallest(B, tiny_engine, Bn, k, K, kp):
     """More candidates than threads of the builder (its threshold path), the largest tree and the root alone."""
     shape, w, eng = tiny_engine
