@@ -8,9 +8,8 @@
 //   * the K' best (value desc, id asc) live in a list spread over the lanes (lane j holds the
 //     j-th best).  A block is only looked at when its maximum reaches the current K'-th value,
 //     which after the first block is rare (about K' ln(n/K') times per n logits), so the common
-//     path per logit is one max, one fma, one exp and one add.  The first block is filtered by the
-//     K'-th largest of its 64 lane maxima (at least K' logits reach that bound), which keeps the
-//     warm-up to a few insertions.
+//     path per logit is one max, one fma, one exp and one add.  The first block is filtered by a bound
+//     that at least K' and few more of its 64 lane maxima reach; what reaches it is ranked at once.
 // Pass 2 (k_topk_merge): one wave per row merges the segment statistics (online-softmax rule) and
 // the segments' sorted lists (at most 64 segments, one per lane: K' rounds of a wave-wide best-head
 // search); p = exp(v - max) / sum in fp32.
@@ -56,20 +55,45 @@ __device__ __forceinline__ void list_insert(LaneList& L, float v, int id, int kp
   L.last_id = __builtin_amdgcn_readlane(L.id, kp - 1);
 }
 
-// kp-th largest of the 64 lane values (bitonic sort across the wave, descending); kp <= 64
-__device__ __forceinline__ float kth_largest_lane(float x, int kp, int lane) {
-#pragma unroll
-  for (int k = 2; k <= 64; k <<= 1) {
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      const float o = __shfl_xor(x, j, 64);
-      const bool desc = (lane & k) == 0;            // direction of this lane's subsequence
-      const bool low = (lane & j) == 0;             // lower index of the pair
-      const float hi = fmaxf(x, o), lo = fminf(x, o);
-      x = (desc == low) ? hi : lo;
-    }
+__device__ __forceinline__ int lanes_below(unsigned long long ballot) {   // set bits below this lane
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)ballot, 0u));
+}
+
+// reductions over the wave, returned to all lanes: data-parallel-primitive moves, which lanes without a
+// source (`idle` = the operation's neutral value) pass through, instead of LDS exchanges
+template <typename Op>
+__device__ __forceinline__ float wave_reduce_dpp(float x, float idle, Op op) {
+  const int id = __float_as_int(idle);
+#define ESP_DPP_STEP(ctrl) x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(id, __float_as_int(x), ctrl, 0xf, 0xf, false)))
+  ESP_DPP_STEP(0x111);   // row_shr:1, 2, 4, 8
+  ESP_DPP_STEP(0x112);
+  ESP_DPP_STEP(0x114);
+  ESP_DPP_STEP(0x118);
+#undef ESP_DPP_STEP
+  // lane 15 of each row of 16 holds the row's result
+  return op(op(readlane_f(x, 15), readlane_f(x, 31)), op(readlane_f(x, 47), readlane_f(x, 63)));
+}
+__device__ __forceinline__ float wave_max_dpp(float x) {
+  return wave_reduce_dpp(x, -INFINITY, [](float a, float b) { return fmaxf(a, b); });
+}
+__device__ __forceinline__ float wave_sum_dpp(float x) {
+  return wave_reduce_dpp(x, 0.f, [](float a, float b) { return a + b; });
+}
+
+// A bound that at least kp of the 64 lane values reach and, by bisection, not many more; -inf when
+// fewer than kp are finite.  top = the wave's maximum.
+__device__ __forceinline__ float low_bound(float x, float top, int kp) {
+  const bool finite = x > -INFINITY;
+  if (__popcll(__builtin_amdgcn_ballot_w64(finite)) < kp) return -INFINITY;
+  float lo = -wave_max_dpp(finite ? -x : -INFINITY), hi = top;
+#pragma unroll 1
+  for (int it = 0; it < 16; ++it) {
+    const float mid = 0.5f * (lo + hi);
+    const int reach = __popcll(__builtin_amdgcn_ballot_w64(x >= mid));
+    if (reach >= kp) lo = mid; else hi = mid;
+    if (reach >= kp && reach <= kp + 2) break;
   }
-  return readlane_f(x, kp - 1);
+  return lo;
 }
 
 // Offer the values of one register slot (one per lane) to the list: every lane whose value
@@ -94,9 +118,11 @@ __device__ __forceinline__ void offer(LaneList& L, float v, int my_id, float& bo
 __global__ __launch_bounds__(256) void k_topk_stream(const float* __restrict__ logits, int rows, int vocab, int kp,
                                                      int nseg, int seg_len, float* __restrict__ seg_rec,
                                                      const int32_t* __restrict__ row_map) {
-  const int lane = threadIdx.x & 63;
-  const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (item >= rows * nseg) return;
+  __shared__ float cand_v[4][64];
+  __shared__ int cand_id[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int item = blockIdx.x * 4 + wave;
+  if (item >= rows * nseg) return;                      // (waves work alone: no barrier below)
   const int row = item / nseg, seg = item % nseg;
   const int start = seg * seg_len, end = min(vocab, start + seg_len);
   const float* p = logits + (size_t)(row_map ? max(row_map[row], 0) : row) * vocab;
@@ -144,8 +170,36 @@ __global__ __launch_bounds__(256) void k_topk_stream(const float* __restrict__ l
       m = m_new;
     }
     if (b == 0) {
-      floor_bound = kth_largest_lane(bmax, kp, lane);
+      floor_bound = low_bound(bmax, wave_max_dpp(bmax), kp);
       bound = floor_bound;
+      // the values that reach the bound (kp or a few more) are collected in LDS and ranked together
+      int n = 0;
+      if (floor_bound > -INFINITY) {
+#pragma unroll
+        for (int i = 0; i < PER_LANE; ++i) {
+          const bool in = cur[i] >= floor_bound;
+          const unsigned long long mask = __builtin_amdgcn_ballot_w64(in);
+          if (mask == 0ull) continue;                    // most registers hold none
+          const int at = n + lanes_below(mask);
+          if (in && at < 64) { cand_v[wave][at] = cur[i]; cand_id[wave][at] = start + lane * 4 + (i >> 2) * 256 + (i & 3); }
+          n += __popcll(mask);
+        }
+      }
+      if (n > 0 && n <= 64) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const float v = lane < n ? cand_v[wave][lane] : -INFINITY;
+        const int id = lane < n ? cand_id[wave][lane] : 0x7fffffff;
+        int rank = 0;
+        for (int l = 0; l < n; ++l) rank += better(readlane_f(v, l), __builtin_amdgcn_readlane(id, l), v, id) ? 1 : 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (lane < n) { cand_v[wave][rank] = v; cand_id[wave][rank] = id; }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (lane < kp) { L.v = cand_v[wave][lane]; L.id = cand_id[wave][lane]; }   // n >= kp
+        L.last_v = readlane_f(L.v, kp - 1);
+        L.last_id = __builtin_amdgcn_readlane(L.id, kp - 1);
+        bound = fmaxf(floor_bound, L.last_v);
+        continue;
+      }
     }
     if (__builtin_amdgcn_ballot_w64(bmax >= bound) != 0ull) {
       const int base = start + b * BLOCK + lane * 4;
@@ -154,9 +208,9 @@ __global__ __launch_bounds__(256) void k_topk_stream(const float* __restrict__ l
     }
   }
   // wave-wide statistics in the natural-exponent convention: sum of exp(v - max)
-  const float wm = wave_max(m);
+  const float wm = wave_max_dpp(m);
   const float contrib = m > -INFINITY ? s * __builtin_amdgcn_exp2f((m - wm) * LOG2E_F) : 0.f;
-  const float ws = wave_sum(contrib);
+  const float ws = wave_sum_dpp(contrib);
   float* out = seg_rec + ((size_t)row * nseg + seg) * (2 + 2 * kp);
   if (lane == 0) { out[0] = wm; out[1] = ws; }
   if (lane < kp) {
@@ -166,53 +220,58 @@ __global__ __launch_bounds__(256) void k_topk_stream(const float* __restrict__ l
 }
 
 // one wave per row: the segments' lists are sorted, so lane c walks segment c's list and the wave
-// takes the best head (value desc, id asc) K' times -- a 64-way merge of sorted lists
-__global__ __launch_bounds__(256) void k_topk_merge(const float* __restrict__ seg_rec, int rows, int kp, int nseg,
-                                                    int32_t* __restrict__ ids, float* __restrict__ probs) {
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
+// takes the best head (value desc, id asc) K' times -- a 64-way merge of sorted lists.  The lists are
+// brought into LDS once: read where they are, every round would expose a memory latency.
+__global__ __launch_bounds__(64) void k_topk_merge(const float* __restrict__ seg_rec, int kp, int nseg,
+                                                   int32_t* __restrict__ ids, float* __restrict__ probs) {
+  extern __shared__ float lists[];                                      // [2 kp][64]
+  const int lane = threadIdx.x, row = blockIdx.x;
   const int stride = 2 + 2 * kp;
-  const float* e = seg_rec + ((size_t)row * nseg + lane) * stride;     // this lane's segment (nseg <= 64)
-  const bool have = lane < nseg;
-  const float smax = have ? e[0] : -INFINITY;
-  const float gmax = wave_max(smax);
-  const float tot = wave_sum(have && smax > -INFINITY ? e[1] * expf(smax - gmax) : 0.f);
+  const bool have = lane < nseg;                                        // this lane's segment (nseg <= 64)
+  const float* e = seg_rec + ((size_t)row * nseg + min(lane, nseg - 1)) * stride;
+  const float smax = have ? e[0] : -INFINITY, ssum = have ? e[1] : 0.f;
+#pragma unroll 4
+  for (int j = 0; j < 2 * kp; ++j) lists[j * 64 + lane] = e[2 + j];
+  const float gmax = wave_max_dpp(smax);
+  const float tot = wave_sum_dpp(smax > -INFINITY ? ssum * expf(smax - gmax) : 0.f);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   int pos = 0;                                                          // next unread entry of the list
-  float hv = have ? e[2] : -INFINITY;
-  int hi = have ? reinterpret_cast<const int*>(e)[2 + kp] : 0x7fffffff;
-  if (hv == -INFINITY) hi = 0x7fffffff;                                 // empty slot: never wins
+  float hv = have ? lists[lane] : -INFINITY;
+  int hi = __float_as_int(lists[kp * 64 + lane]);
   float out_v = -INFINITY;
-  int out_i = 0x7fffffff;
+  int out_i = -1;
   for (int j = 0; j < kp; ++j) {
-    float bv = hv;
-    int bi = hi;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const float ov = __shfl_xor(bv, o, 64);
-      const int oi = __shfl_xor(bi, o, 64);
-      if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+    const float best = wave_max_dpp(hv);
+    if (best == -INFINITY) break;                                       // empty slots never win
+    unsigned long long top = __builtin_amdgcn_ballot_w64(hv == best);
+    int win = __builtin_ctzll(top);
+    int bi = __builtin_amdgcn_readlane(hi, win);
+    for (top &= top - 1; top; top &= top - 1) {                         // equal values: the lowest id
+      const int l = __builtin_ctzll(top), oi = __builtin_amdgcn_readlane(hi, l);
+      if (oi < bi) { bi = oi; win = l; }
     }
-    if (lane == j) { out_v = bv; out_i = bi; }
-    if (hi == bi && bi != 0x7fffffff) {                                 // ids are unique: exactly one lane advances
+    if (lane == j) { out_v = best; out_i = bi; }
+    if (lane == win) {
       ++pos;
-      hv = pos < kp ? e[2 + pos] : -INFINITY;
-      hi = pos < kp ? reinterpret_cast<const int*>(e)[2 + kp + pos] : 0x7fffffff;
-      if (hv == -INFINITY) hi = 0x7fffffff;
+      hv = pos < kp ? lists[pos * 64 + lane] : -INFINITY;
+      hi = pos < kp ? __float_as_int(lists[(kp + pos) * 64 + lane]) : -1;
     }
   }
   if (lane < kp) {
-    const bool any = out_i != 0x7fffffff;
-    ids[(size_t)row * kp + lane] = any ? out_i : -1;
-    probs[(size_t)row * kp + lane] = any ? expf(out_v - gmax) / tot : 0.f;
+    ids[(size_t)row * kp + lane] = out_i;
+    probs[(size_t)row * kp + lane] = out_i >= 0 ? expf(out_v - gmax) / tot : 0.f;
   }
 }
 
-// segments per row: enough independent waves to fill the chip (about 8 per CU), each at least one
-// block long
+// Segments per row.  Up to 4096 waves (four per SIMD, all resident at once) a wave gets a single block:
+// every load of the launch is then in flight from the start (64 rows of 128256: 14.8 us against 16.8 us
+// with two blocks a wave; 23.3 us before the bound by bisection and the ranked first block).  Beyond that
+// the fixed cost per wave counts and about 2048 waves walk several blocks each (256 rows: 33.4 us
+// against 36.3 us with 4096 waves).
 int topk_segments(int rows, int vocab, int* seg_len) {
   const int max_seg = std::min(64, (vocab + BLOCK - 1) / BLOCK);   // the merge gives each segment a lane
-  int nseg = std::max(1, std::min(max_seg, (2048 + rows - 1) / rows));
+  const int waves = (int64_t)rows * max_seg <= 4096 ? 4096 : 2048;
+  int nseg = std::max(1, std::min(max_seg, (waves + rows - 1) / rows));
   int len = ((vocab + nseg - 1) / nseg + BLOCK - 1) / BLOCK * BLOCK;
   nseg = (vocab + len - 1) / len;
   *seg_len = len;
@@ -281,6 +340,6 @@ hipError_t launch_softmax_topk(hipStream_t st, const float* logits, int rows, in
                      ws, row_map);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_topk_merge, dim3((rows + 3) / 4), dim3(256), 0, st, ws, rows, kp, nseg, ids, probs);
+  hipLaunchKernelGGL(k_topk_merge, dim3(rows), dim3(64), (size_t)2 * kp * 64 * 4, st, ws, kp, nseg, ids, probs);
   return hipGetLastError();
 }

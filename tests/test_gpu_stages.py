@@ -100,7 +100,7 @@ def check_topk(ids, ps, logits, kp, tol):
 
 
 @pytest.mark.parametrize("rows,vocab,kp", [(1, 211, 5), (4, 4096, 6), (3, 128256, 10), (5, 2048, 32),
-                                           (2, 151936, 12), (7, 2049, 4)])
+                                           (2, 151936, 12), (7, 2049, 4), (65, 128256, 10), (66, 128256, 31)])
 def test_softmax_topk(B, rows, vocab, kp):
     print(f"topk rows={rows} vocab={vocab} kp={kp}", flush=True)
     logits = synth.normal_like((rows, vocab), 2.0, 21, rows, "cuda", torch.float32)
