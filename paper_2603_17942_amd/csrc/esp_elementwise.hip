@@ -82,8 +82,11 @@ hipError_t launch_embed(hipStream_t st, int dtype, const BlockDev& b, const KvDe
 }
 
 // ---- residual add of split-K partials + RMSNorm ------------------------------------------------
-// One workgroup of 1024 threads per row; a thread owns float4 columns, so all split loads of a
-// column are independent and in flight together.  d must be a multiple of 4.
+// One workgroup per row; a thread owns float4 columns (one each up to d = 4096).  The kernel is bound by the
+// fp32 partials it reads (S * d * 4 bytes per row), so the split count is a template parameter: all S loads of
+// a column are in flight before the first is waited for, and the row stays in registers between the two
+// passes.  d must be a multiple of 4.  d = 4096: 4.4 us at one row, 5.7 us at 68 rows (8 partials, 9 MB), 11 to
+// 13 us at 320 (42 MB); with a running split count and the row read back: 12 to 13 us at 320.
 template <typename T> struct Pack4;
 template <> struct Pack4<float> {
   static __device__ __forceinline__ void store(float* p, f32x4_t v) { *reinterpret_cast<f32x4_t*>(p) = v; }
@@ -101,115 +104,175 @@ template <> struct Pack4<bf16_t> {
   }
 };
 
-template <typename T>
+// v + the S partials at p, p + stride, ..., added in split order
+template <int S>
+__device__ __forceinline__ f32x4_t add_splits(f32x4_t v, const float* __restrict__ p, size_t stride) {
+  f32x4_t x[S > 0 ? S : 1];
+#pragma unroll
+  for (int s = 0; s < S; ++s) x[s] = *reinterpret_cast<const f32x4_t*>(p + (size_t)s * stride);
+#pragma unroll
+  for (int s = 0; s < S; ++s) v += x[s];
+  return v;
+}
+
+template <typename T, int S>
 __global__ __launch_bounds__(1024) void k_residual_norm(float* __restrict__ h, const float* __restrict__ part,
-                                                        int splits, size_t split_stride, int d,
-                                                        const T* __restrict__ gain, float eps,
-                                                        T* __restrict__ xn) {
+                                                        size_t split_stride, int d, const T* __restrict__ gain,
+                                                        float eps, T* __restrict__ xn) {
   __shared__ float red[16];
   const size_t row = blockIdx.x;
   float* hr = h + row * d;
-  const int d4 = d >> 2;
+  const int d4 = d >> 2, tid = threadIdx.x, step = blockDim.x;
+  f32x4_t keep = {0.f, 0.f, 0.f, 0.f}, g0 = keep;    // this thread's first column and its gain
+  if (tid < d4) g0 = Pack4<T>::load(gain + 4 * tid);
   float ss = 0.f;
-  for (int i = threadIdx.x; i < d4; i += 1024) {
-    f32x4_t v = *reinterpret_cast<const f32x4_t*>(hr + 4 * i);
-    for (int s = 0; s < splits; ++s)
-      v += *reinterpret_cast<const f32x4_t*>(part + (size_t)s * split_stride + row * d + 4 * i);
-    *reinterpret_cast<f32x4_t*>(hr + 4 * i) = v;
+  for (int i = tid; i < d4; i += step) {
+    const f32x4_t v = add_splits<S>(*reinterpret_cast<const f32x4_t*>(hr + 4 * i), part + row * d + 4 * i, split_stride);
+    if (S > 0) *reinterpret_cast<f32x4_t*>(hr + 4 * i) = v;
+    if (i == tid) keep = v;
     ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
   }
   ss = wave_sum(ss);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  if ((tid & 63) == 0) red[tid >> 6] = ss;
   __syncthreads();
   float tot = 0.f;
-#pragma unroll
-  for (int w = 0; w < 16; ++w) tot += red[w];
+  for (int w = 0; w < step >> 6; ++w) tot += red[w];
   const float inv = 1.0f / sqrtf(tot / (float)d + eps);
-  for (int i = threadIdx.x; i < d4; i += 1024) {
-    f32x4_t v = *reinterpret_cast<const f32x4_t*>(hr + 4 * i);   // written by this thread above
-    f32x4_t g = Pack4<T>::load(gain + 4 * i);
+  for (int i = tid; i < d4; i += step) {
+    const f32x4_t v = i == tid ? keep : *reinterpret_cast<const f32x4_t*>(hr + 4 * i);   // written by this thread above
+    const f32x4_t g = i == tid ? g0 : Pack4<T>::load(gain + 4 * i);
     Pack4<T>::store(xn + row * d + 4 * i, v * inv * g);
   }
 }
 
+// the split count of a launch as a template argument (gemm_plan gives at most 8)
+#define ESP_SPLITS(splits, ...)                                   \
+  switch (splits) {                                               \
+    case 1: { constexpr int S = 1; __VA_ARGS__; } break;          \
+    case 2: { constexpr int S = 2; __VA_ARGS__; } break;          \
+    case 3: { constexpr int S = 3; __VA_ARGS__; } break;          \
+    case 4: { constexpr int S = 4; __VA_ARGS__; } break;          \
+    case 5: { constexpr int S = 5; __VA_ARGS__; } break;          \
+    case 6: { constexpr int S = 6; __VA_ARGS__; } break;          \
+    case 7: { constexpr int S = 7; __VA_ARGS__; } break;          \
+    case 8: { constexpr int S = 8; __VA_ARGS__; } break;          \
+    default: return hipErrorInvalidValue;                         \
+  }
+
 hipError_t launch_residual_norm(hipStream_t st, int dtype, float* h, const float* part, int splits, int M,
                                 int d, const void* gain, float eps, void* xn_out) {
-  ESP_DISPATCH(dtype, hipLaunchKernelGGL(k_residual_norm<T>, dim3(M), dim3(1024), 0, st, h, part, splits,
-                                         (size_t)M * d, d, (const T*)gain, eps, (T*)xn_out));
+  const dim3 grid(M), block(std::min(1024, ((d >> 2) + 63) & ~63));
+  const size_t stride = (size_t)M * d;
+  if (splits == 0) {
+    ESP_DISPATCH(dtype, hipLaunchKernelGGL((k_residual_norm<T, 0>), grid, block, 0, st, h, part, stride, d,
+                                           (const T*)gain, eps, (T*)xn_out));
+  } else if (dtype == ESP_F32) {   // the fp32 GEMM splits K inside a workgroup
+    if (splits != 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_residual_norm<float, 1>), grid, block, 0, st, h, part, stride, d, (const float*)gain, eps,
+                       (float*)xn_out);
+  } else {
+    ESP_SPLITS(splits, hipLaunchKernelGGL((k_residual_norm<bf16_t, S>), grid, block, 0, st, h, part, stride, d,
+                                          (const bf16_t*)gain, eps, (bf16_t*)xn_out));
+  }
   return hipGetLastError();
 }
 
 // ---- QKV epilogue: split-K reduce, optional per-head RMSNorm, rotary, KV append ----------------
-// one wave per (row, head); lane i < hd/2 owns the rotary pair (i, i + hd/2)
-template <typename T>
+// hd/8 lanes per (row, head): a lane owns the features 4 i .. 4 i + 3 of both halves of the head, i.e. four
+// rotary pairs, as two 16-byte pieces of every partial; all 2 S loads are in flight at once.
+template <typename T, int HD, int S>
 __global__ __launch_bounds__(256) void k_qkv_post(BlockDev b, KvDev kv, int layer, const float* __restrict__ part,
-                                                  int splits, size_t split_stride, int hq, int hkv, int hd,
-                                                  int qk_norm, const T* __restrict__ qg, const T* __restrict__ kg,
-                                                  float eps, const float* __restrict__ rope_tab,
-                                                  T* __restrict__ q_out) {
+                                                  size_t split_stride, int hq, int hkv, int qk_norm,
+                                                  const T* __restrict__ qg, const T* __restrict__ kg, float eps,
+                                                  const float* __restrict__ rope_tab, T* __restrict__ q_out) {
+  constexpr int LPH = HD / 8, HALF = HD / 2;
   const int row = blockIdx.y;
-  const int hidx = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
+  const int hidx = (blockIdx.x * 256 + threadIdx.x) / LPH;
+  const int f0 = (threadIdx.x % LPH) * 4;
   const int n_heads = hq + 2 * hkv;
   if (hidx >= n_heads) return;
+  const size_t c0 = ((size_t)row * n_heads + hidx) * HD + f0;
+  f32x4_t x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
+  x0 = add_splits<S>(x0, part + c0, split_stride);
+  x1 = add_splits<S>(x1, part + c0 + HALF, split_stride);
   const int seq = row / b.rows_per_seq, r = row % b.rows_per_seq;
   const int nr = b.n_rows[seq];
   const bool live = seq_ok(kv, seq, nr) && nr <= b.rows_per_seq && r < nr;
-  const int half = hd >> 1;
-  const int ncol = n_heads * hd;
-  const bool act = lane < half;
-  float x0 = 0.f, x1 = 0.f;
-  if (act && live) {
-    size_t c0 = (size_t)row * ncol + (size_t)hidx * hd + lane;
-    for (int s = 0; s < splits; ++s) {
-      x0 += part[(size_t)s * split_stride + c0];
-      x1 += part[(size_t)s * split_stride + c0 + half];
+  const int64_t slot = (int64_t)kv.base[seq] + kv.len[seq] + r;
+  if (!live) {   // a row that is not there: its query is zero, whatever its partials hold
+    if (hidx < hq) {
+      T* qo = q_out + ((size_t)row * hq + hidx) * HD + f0;
+      const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+      Pack4<T>::store(qo, zero);
+      Pack4<T>::store(qo + HALF, zero);
     }
+    return;
   }
   if (hidx < hq + hkv) {
     if (qk_norm) {
-      float ss = wave_sum(x0 * x0 + x1 * x1);
-      float inv = 1.0f / sqrtf(ss / (float)hd + eps);
-      const T* g = hidx < hq ? qg : kg;
-      if (act) {
-        x0 *= inv * to_f32(g[lane]);
-        x1 *= inv * to_f32(g[lane + half]);
+      float ss = 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ss += x0[e] * x0[e] + x1[e] * x1[e];
+#pragma unroll
+      for (int o = LPH / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+      const float inv = 1.0f / sqrtf(ss / (float)HD + eps);
+      const T* g = (hidx < hq ? qg : kg) + f0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {   // scalar loads: the caller's gains need no more than their type's alignment
+        x0[e] *= inv * to_f32(g[e]);
+        x1[e] *= inv * to_f32(g[HALF + e]);
       }
     }
-    if (!act) return;
-    float c = rope_tab[((size_t)row * half + lane) * 2 + 0];
-    float s = rope_tab[((size_t)row * half + lane) * 2 + 1];
-    float y0 = x0 * c - x1 * s;
-    float y1 = x1 * c + x0 * s;
+    const float* rt = rope_tab + ((size_t)row * HALF + f0) * 2;      // cos, sin of four pairs
+    const f32x4_t t0 = *reinterpret_cast<const f32x4_t*>(rt), t1 = *reinterpret_cast<const f32x4_t*>(rt + 4);
+    const f32x4_t c = {t0[0], t0[2], t1[0], t1[2]}, s = {t0[1], t0[3], t1[1], t1[3]};
+    const f32x4_t y0 = x0 * c - x1 * s, y1 = x1 * c + x0 * s;
     if (hidx < hq) {
-      size_t o = ((size_t)row * hq + hidx) * hd + lane;
-      q_out[o] = from_f32<T>(y0);
-      q_out[o + half] = from_f32<T>(y1);
-    } else if (live) {
-      int kvh = hidx - hq;
-      int64_t slot = (int64_t)kv.base[seq] + kv.len[seq] + r;
-      T* kp = (T*)kv.k + kv_plane(layer, kvh, hkv, kv.capacity, hd);
-      kp[k_off(slot, lane, hd)] = from_f32<T>(y0);
-      kp[k_off(slot, lane + half, hd)] = from_f32<T>(y1);
+      T* qo = q_out + ((size_t)row * hq + hidx) * HD + f0;
+      Pack4<T>::store(qo, y0);
+      Pack4<T>::store(qo + HALF, y1);
+    } else {       // four features are consecutive in a K fragment
+      T* kp = (T*)kv.k + kv_plane(layer, hidx - hq, hkv, kv.capacity, HD);
+      if constexpr (HD == 128 && sizeof(T) == 2) {   // the attention kernel of this form reads 16-byte pieces anyway
+        Pack4<T>::store(kp + k_off(slot, f0, HD), y0);
+        Pack4<T>::store(kp + k_off(slot, f0 + HALF, HD), y1);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          kp[k_off(slot, f0 + e, HD)] = from_f32<T>(y0[e]);
+          kp[k_off(slot, f0 + HALF + e, HD)] = from_f32<T>(y1[e]);
+        }
+      }
     }
-  } else if (act && live) {
-    int kvh = hidx - hq - hkv;
-    int64_t slot = (int64_t)kv.base[seq] + kv.len[seq] + r;
-    T* vp = (T*)kv.v + kv_plane(layer, kvh, hkv, kv.capacity, hd);
-    vp[v_off(slot, lane, hd)] = from_f32<T>(x0);
-    vp[v_off(slot, lane + half, hd)] = from_f32<T>(x1);
+  } else {
+    T* vp = (T*)kv.v + kv_plane(layer, hidx - hq - hkv, hkv, kv.capacity, HD);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      vp[v_off(slot, f0 + e, HD)] = from_f32<T>(x0[e]);
+      vp[v_off(slot, f0 + HALF + e, HD)] = from_f32<T>(x1[e]);
+    }
   }
 }
 
 hipError_t launch_qkv_post(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, int layer,
                            const float* part, int splits, int M, int hq, int hkv, int hd, int qk_norm,
                            const void* qg, const void* kg, float eps, const float* rope_tab, void* q_out) {
-  int n_heads = hq + 2 * hkv;
-  dim3 grid((n_heads + 3) / 4, M);
-  size_t stride = (size_t)M * n_heads * hd;
-  ESP_DISPATCH(dtype, hipLaunchKernelGGL(k_qkv_post<T>, grid, dim3(256), 0, st, b, kv, layer, part, splits,
-                                         stride, hq, hkv, hd, qk_norm, (const T*)qg, (const T*)kg, eps, rope_tab,
-                                         (T*)q_out));
+  const int n_heads = hq + 2 * hkv;
+  const dim3 grid((n_heads * (hd / 8) + 255) / 256, M);
+  const size_t stride = (size_t)M * n_heads * hd;
+#define ESP_QKV_POST(T_, HD_, S_)                                                                                     \
+  hipLaunchKernelGGL((k_qkv_post<T_, HD_, S_>), grid, dim3(256), 0, st, b, kv, layer, part, stride, hq, hkv, qk_norm, \
+                     (const T_*)qg, (const T_*)kg, eps, rope_tab, (T_*)q_out)
+  if (dtype == ESP_F32) {
+    if (splits != 1) return hipErrorInvalidValue;
+    if (hd == 64) ESP_QKV_POST(float, 64, 1);
+    else ESP_QKV_POST(float, 128, 1);
+  } else if (hd == 64) {
+    ESP_SPLITS(splits, ESP_QKV_POST(bf16_t, 64, S));
+  } else {
+    ESP_SPLITS(splits, ESP_QKV_POST(bf16_t, 128, S));
+  }
+#undef ESP_QKV_POST
   return hipGetLastError();
 }
 
