@@ -27,6 +27,7 @@
 //
 // fp32 path (tiny configuration, k_gemm_f32): 32 x 32 tiles on the fp32 matrix instruction, row-major weights.
 #include <algorithm>
+#include <type_traits>
 
 #include <hip/hip_ext.h>
 
@@ -247,9 +248,15 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
   u32x4_t wreg[D][NB][4];
   u32x4_t areg[D][MT];
 
-  // Every iteration issues the same loads (chunk indices past the split are clamped to its last
-  // chunk, an L2 hit, and their activations are zeroed so they add nothing): with a fixed number
-  // of loads in flight the compiler can wait for exactly the chunk it needs.
+  // Every group of D chunks but the last refills the ring with the same loads (chunk indices past the
+  // split are clamped to its last chunk, an L2 hit, and their activations are zeroed so they add
+  // nothing): with a fixed number of loads in flight the compiler can wait for exactly the chunk it
+  // needs.  The last group is code of its own that loads nothing: its refills would be D chunks of
+  // repeated reads a workgroup (the O projection has 8 of its own), waited for by nobody but queued
+  // before the next kernel's.  Without them, relative to one common earlier build timed in the same run:
+  // one-row step 1.022 -> 1.031 times as fast, 30 rows 1.022 -> 1.041, 68 rows 1.009 -> 1.016, 101 rows of the
+  // Qwen3 shape 1.006 -> 1.018.  (Deeper rings on top, 8 chunks at <= 64 rows and 6 above, are slower:
+  // 1.000, 1.019, 0.969 and 0.971.)
   const int c_last = max(c_end - 1, c_begin);
   const u32x4_t zero4 = {0u, 0u, 0u, 0u};
   // prologue: chunks c_begin .. c_begin+D-1
@@ -270,7 +277,8 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
   __syncthreads();
 
   const int n_iter = (c_end - c_begin + D - 1) / D;   // groups of D chunks, the last one zero-padded
-  for (int it = 0; it < n_iter; ++it) {
+  auto group = [&](int it, auto refill) {
+    constexpr bool REFILL = decltype(refill)::value;
 #pragma unroll
     for (int u = 0; u < D; ++u) {
       const int c = c_begin + it * D + u;
@@ -287,7 +295,7 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
         for (int i = 0; i < MT; ++i) {
           if (s < 3)
             af[(s + 1) & 1][i] = *reinterpret_cast<const bf16x8_t*>(abase + i * 32 * A_ROW_BYTES + 16 * (s + 1));
-          {
+          if constexpr (REFILL) {
             // refill of ring slot u with chunk c+D, one load per MFMA group (a burst after the
             // MFMAs would hold the wave at the memory pipeline's address queue while the matrix
             // cores idle): the activation registers are free (stored to LDS a chunk ago), the
@@ -305,20 +313,24 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
           __builtin_amdgcn_sched_barrier(0);
         }
       }
+      if (!REFILL && u == D - 1) return;                // nothing follows
       // activations of chunk c+1 (ring slot u+1) -> the other LDS buffer
 #pragma unroll
       for (int i = 0; i < MT; ++i)
         *reinterpret_cast<u32x4_t*>(lds + (buf ^ 1) * A_BUF + a_lds[i]) =
             c + 1 < c_end ? areg[(u + 1) % D][i] : zero4;   // zeroed at use, not at load
       // the last step's weight registers of ring slot u
-      {
+      if constexpr (REFILL) {
         const int cc = min(c + D, c_last);
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) wreg[u][nb][3] = wp[nb][(size_t)cc * W_CHUNK + 3 * W_STEP];
       }
       __syncthreads();
     }
-  }
+  };
+  for (int it = 0; it + 1 < n_iter; ++it) group(it, std::true_type{});
+  if (n_iter > 0) group(n_iter - 1, std::false_type{});
+  __syncthreads();                                      // the epilogues reuse the LDS
   }   // register-ring path
 
   // epilogue: lane holds column n, rows 8*(v/4) + 4*lg + v%4 of each 32x32 tile

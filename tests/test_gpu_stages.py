@@ -48,6 +48,21 @@ def test_gemm_bf16(B, M, N, K):
         assert np.array_equal(got1[0], got[0])
 
 
+@pytest.mark.parametrize("chunks", [1, 5, 6, 7, 8, 9, 12, 13, 17, 26])
+@pytest.mark.parametrize("M", [1, 64, 65, 128])
+def test_gemm_bf16_ring_depth(B, M, chunks):
+    """Reduction lengths below, at and above the depth of the operand ring of the small-row kernel: one
+    group of 64-wide chunks, an exact number of groups, and a last group that is partly padding; N = 160 leaves the
+    second column tile one live wave."""
+    N, K = 160, 64 * chunks
+    print(f"gemm bf16 ring M={M} N={N} K={K}", flush=True)
+    a = synth.normal_like((M, K), 1.0, 12, 0, "cuda", torch.bfloat16)
+    w = synth.normal_like((N, K), 0.05, 12, 1, "cuda", torch.bfloat16)
+    got = B.gemm(a, B.pack_weight(w), packed=True).cpu().numpy()
+    assert np.array_equal(got, B.gemm(a, w).cpu().numpy())      # same chunks in the same order
+    assert rel_err_rows(got, to_np(a) @ to_np(w).T) < 1e-5      # fp32 sums of at most 1664 exact products
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 512, 128), (68, 4096, 256), (128, 1056, 192), (129, 768, 256), (320, 4096, 512),
                                    (200, 2048, 128), (1344, 1280, 256), (700, 33 * 32, 192), (180, 512, 64)])
 def test_gemm_argmax_epilogue(B, M, N, K):
