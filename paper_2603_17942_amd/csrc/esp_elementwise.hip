@@ -210,11 +210,17 @@ __global__ __launch_bounds__(256) void k_qkv_post(BlockDev b, KvDev kv, int laye
   }
   if (hidx < hq + hkv) {
     if (qk_norm) {
-      float ss = 0.f;
+      // The squares are added as a balanced tree over the rotary pairs, the farthest pairs first (distance
+      // HD/4, HD/8, ..., 1): across the lanes for each of the four pairs, then the pairs of the lane.  Order and
+      // fused form fix the last bit of the norm, which a bf16 model carries through its layers.
+      float sq[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) ss += x0[e] * x0[e] + x1[e] * x1[e];
+      for (int e = 0; e < 4; ++e) sq[e] = fmaf(x1[e], x1[e], x0[e] * x0[e]);
 #pragma unroll
-      for (int o = LPH / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+      for (int o = LPH / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sq[e] += __shfl_xor(sq[e], o, 64);
+      const float ss = (sq[0] + sq[2]) + (sq[1] + sq[3]);
       const float inv = 1.0f / sqrtf(ss / (float)HD + eps);
       const T* g = (hidx < hq ? qg : kg) + f0;
 #pragma unroll

@@ -445,6 +445,39 @@ def test_verify_accept_and_kv_commit(B, tiny_engine):
     assert total_acc >= 3
 
 
+# ---------------------------------------------------------------------------------------- QKV epilogue
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_qk_norm_sum_order(B, head_dim):
+    """The per-head RMSNorm adds its squares as a balanced tree over the rotary pairs, farthest pairs first:
+    bit for bit.  K and V share one weight matrix and every row sits at position 0 (no rotation), so the V
+    rows in the cache are the norm's inputs and the K rows its outputs."""
+    shape = small_shape(d_model=128, n_q_heads=3, n_kv_heads=3, head_dim=head_dim, d_ff=176, vocab=517, n_layers=1,
+                        qk_norm=True)
+    w = synth.make_weights(shape, seed=6, unit_gains=False)
+    w["layers"][0]["wv"] = w["layers"][0]["wk"]
+    batch = 16
+    eng = B.Engine(shape, w, batch, 1, 64)
+    kv = B.KvCache(shape, [64] * batch)
+    kv.set_len([0] * batch)
+    blk = B.BlockBuffers(batch, 1, 0, 0)
+    blk.upload_trees([[31 * b + 1] for b in range(batch)], [[-1]] * batch)
+    eng.block_from_tree(blk)
+    hidden = torch.zeros((batch, shape.d_model), dtype=torch.float32, device="cuda")
+    eng.tree_forward(blk, None, kv, hidden, None)
+    assert eng.device_status() == 0
+    k, v = (np.stack(t) for t in zip(*[[x.cpu().numpy()[0] for x in eng.kv_load(kv, 0, b, 0, 1)] for b in range(batch)]))
+    eng.close()
+    half = head_dim // 2
+    x0, x1 = v[..., :half], v[..., half:]                      # [batch, heads, pairs]
+    s = (x1.astype(np.longdouble) ** 2 + x0 * x0).astype(np.float32)     # fma(x1, x1, x0 * x0)
+    while s.shape[-1] > 1:
+        n = s.shape[-1] // 2
+        s = s[..., :n] + s[..., n:]
+    inv = np.float32(1) / np.sqrt(s / np.float32(head_dim) + np.float32(shape.rms_eps))
+    gain = w["layers"][0]["k_norm"].cpu().numpy().astype(np.float32)
+    assert np.array_equal(k, v * (inv * gain))
+
+
 # ---------------------------------------------------------------------------------------- attention
 def run_attention_case(B, shape, eng, n_nodes, k, layout, cache_lens, seed):
     batch = len(cache_lens)
