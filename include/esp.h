@@ -71,7 +71,8 @@ enum {
 /* bits of the device status word */
 enum {
   ESP_DEV_LEN_OVER_BOUND = 1,  /* kv.len[b] + n_rows[b] exceeds kv.len_bound or seq capacity */
-  ESP_DEV_BAD_TREE = 2,        /* parent not before child, n_nodes/n_rows out of range      */
+  ESP_DEV_BAD_TREE = 2,        /* parent not before child, n_nodes/n_rows out of range, list */
+                               /* entries above 1 that keep a node without its parent        */
   ESP_DEV_BAD_TOKEN = 4        /* token id outside the vocabulary                            */
 };
 
@@ -246,6 +247,9 @@ esp_status esp_mask_topk(esp_ctx *ctx, const esp_block *blk, const int32_t *star
  * that the block holds a tree of that size and that no list runs out, and builds in full if not).
  * A caller that writes the structure arrays of such a block itself must pass the block through
  * esp_block_from_tree before the next esp_build_prune_tree.
+ * topk_p: probabilities, 0 <= p <= 1, which is what esp_mask_topk and esp_softmax_topk hand out; a child is
+ * then never more probable than its parent, so the chosen nodes form a tree.  With an entry above 1 they
+ * may not (a child kept, its parent cut): such a sequence gets n_rows = n_nodes = 0 and ESP_DEV_BAD_TREE.
  * Errors: EINVAL (B, k, K, Kp out of range; k != next->k_masks), ECAPACITY (rows of the tree
  * exceed next->rows_per_seq). */
 esp_status esp_build_prune_tree(esp_ctx *ctx, const esp_tree_params *p, const int32_t *topk_id,

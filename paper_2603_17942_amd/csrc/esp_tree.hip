@@ -229,10 +229,11 @@ struct TreeLds {
   __align__(16) uint32_t order[ESP_MAX_TREE_NODES];   // depth << 16 | creation index of the kept nodes
   int32_t row_tok[ESP_MAX_TREE_NODES], row_par[ESP_MAX_TREE_NODES], row_dep[ESP_MAX_TREE_NODES];
   uint64_t row_anc[ESP_MAX_TREE_NODES][ESP_MAX_TREE_NODES / 64];
-  int16_t row_of[MAXC];                    // creation index -> row
+  int16_t row_of[MAXC];                    // creation index -> row, -1: not in the tree
   int32_t list_id[ESP_MAX_MASKS * ESP_MAX_TOPK];   // the sequence's Top-K' lists, staged once
   float list_p[ESP_MAX_MASKS * ESP_MAX_TOPK];
   int32_t n_cand, n_keep, kept_buf;        // n_keep -1: more candidates or nodes than there is room for
+  int32_t orphan;                          // a kept node whose parent is not
 };
 
 // How many of n fp32 values >= 0 in LDS reach `bound` (compared as bit patterns); one wave.
@@ -371,6 +372,7 @@ __device__ void grow_tree(TreeLds& s, const esp_tree_params& p, int root_tok, in
           s.par[cre] = (int16_t)pcre;
           s.dep[cre] = (uint8_t)i;
           s.used[cre] = 0;
+          s.row_of[cre] = -1;
           s.prob[buf][n + made] = pp * s.list_p[(i - 1) * kp + c];     // one fp32 product (Alg. 1: P(c) = P(n) * P(t|l))
           s.cre[buf][n + made] = cre;
         }
@@ -498,7 +500,7 @@ __global__ __launch_bounds__(256) void k_build_tree(esp_tree_params p, const int
   const int cre = tid < n_keep ? s.cre[s.kept_buf][tid] : 0;
   const uint32_t mine = tid < n_keep ? ((uint32_t)s.dep[cre] << 16) | (uint32_t)cre : 0xffffffffu;
   s.order[tid] = mine;
-  if (tid == 0) { s.row_of[0] = 0; s.row_tok[0] = root_tok; s.row_par[0] = -1; s.row_dep[0] = 0; }
+  if (tid == 0) { s.row_of[0] = 0; s.row_tok[0] = root_tok; s.row_par[0] = -1; s.row_dep[0] = 0; s.orphan = 0; }
   __syncthreads();
   int row = 1;
   for (int b = 0; b < n_keep; b += 4) {
@@ -512,11 +514,22 @@ __global__ __launch_bounds__(256) void k_build_tree(esp_tree_params p, const int
     s.row_dep[row] = (int32_t)(mine >> 16);
   }
   __syncthreads();
-  if (tid < n_keep) s.row_par[row] = s.row_of[s.par[cre]];
+  // A list entry above 1 lets a child outrank its parent, and the cut at B - 1 can then fall between the two: the
+  // nodes left are no tree.  All threads agree on that before anything is written; below, every parent row
+  // precedes its child's.
+  if (tid < n_keep) {
+    const int up = s.row_of[s.par[cre]];
+    s.row_par[row] = up;
+    if (up < 0 || up >= row) s.orphan = 1;
+  }
   __syncthreads();
+  if (s.orphan) {
+    if (tid == 0) { n_rows[seq] = 0; n_nodes[seq] = 0; atomicOr(status, ESP_DEV_BAD_TREE); }
+    return;
+  }
   if (tid <= n_keep) {
     uint64_t bits[ESP_MAX_TREE_NODES / 64] = {};
-    for (int c = tid; c >= 0; c = s.row_par[c])                            // at most k + 1 hops
+    for (int c = tid, hop = 0; c >= 0 && hop <= p.k; c = s.row_par[c], ++hop)   // a node at depth <= k
 #pragma unroll
       for (int w = 0; w < ESP_MAX_TREE_NODES / 64; ++w) bits[w] |= (c >> 6) == w ? 1ull << (c & 63) : 0ull;
 #pragma unroll

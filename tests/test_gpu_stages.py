@@ -385,6 +385,48 @@ def test_build_prune_tree_with_every_probability_tied(B, tiny_engine):
         assert nxt.parent[r0:r0 + n].tolist() == par.tolist()
 
 
+@pytest.mark.parametrize("Bn,k,K,kp,layout", [(64, 4, 8, 10, 1), (96, 5, 10, 12, 0), (5, 3, 4, 4, 1)])
+def test_build_prune_tree_refuses_a_node_without_its_parent(B, tiny_engine, Bn, k, K, kp, layout):
+    """List entries above 1 (here the first of each list, by a few units in the last place, over a tail of tiny
+    ones) let a child outrank its parent, and the cut at B - 1 can fall between them: what Alg. 1 selects is then
+    no tree (the oracle cannot name a parent row).  The sequence is refused with the status bit, nothing is
+    written for it, and its neighbours in the batch are built as usual."""
+    shape, w, eng = tiny_engine
+    batch = 3
+    rng = np.random.default_rng(5 * Bn)
+    op = O.TreeParams(B=Bn, k=k, K=K, expand_width=0, prune_parent=True)
+    ids = np.zeros((batch, k, kp), dtype=np.int32)
+    ps = np.zeros((batch, k, kp), dtype=np.float32)
+    for b in (0, 2):
+        ids[b], ps[b] = random_lists(rng, k, kp, 500)
+    for _ in range(200):                            # the first draw whose selection is not ancestor-closed
+        ids[1], _p = random_lists(rng, k, kp, 500)
+        ps[1] = np.sort(rng.uniform(1e-11, 2.5e-8, (k, kp)))[:, ::-1].astype(np.float32)
+        ps[1, :, 0] = 1.0000005
+        try:
+            O.build_prune_tree(op, ids[1], ps[1], 501, n_depths=k)
+        except KeyError:
+            break
+    else:
+        raise AssertionError("no draw without an orphan")
+    rows = Bn * (k + 1) if layout == 0 else Bn + k
+    nxt = B.BlockBuffers(batch, rows, k, layout)
+    nxt.n_rows.fill_(-7), nxt.n_nodes.fill_(-7), nxt.tok.fill_(-7), nxt.parent.fill_(-7)
+    emit = np.full((batch, B.MAX_MASKS + 1), 501, dtype=np.int32)
+    dev = lambda a: torch.as_tensor(a).cuda()
+    one = np.ones(batch, dtype=np.int32)
+    print(f"refused tree B={Bn} k={k} K={K}", flush=True)
+    eng.build_prune_tree(B.tree_params(Bn, k, K, 0, True, False, layout), dev(ids), dev(ps), kp, dev(one * k), dev(one), dev(emit),
+                         nxt)
+    assert eng.device_status() == B.DEV_BAD_TREE
+    assert int(nxt.n_rows[1]) == 0 and int(nxt.n_nodes[1]) == 0
+    assert bool((nxt.tok[rows:2 * rows] == -7).all()) and bool((nxt.parent[rows:2 * rows] == -7).all())
+    for b in (0, 2):
+        tok, par, _ = O.build_prune_tree(op, ids[b], ps[b], 501, n_depths=k)
+        assert nxt.parent[b * rows:b * rows + len(tok)].tolist() == par.tolist()
+        check_block(nxt, b, tok, par, k, layout)
+
+
 # ---------------------------------------------------------------------------------------- verify + KV commit
 def test_verify_accept_and_kv_commit(B, tiny_engine):
     shape, w, eng = tiny_engine
