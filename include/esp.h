@@ -248,8 +248,10 @@ esp_status esp_mask_topk(esp_ctx *ctx, const esp_block *blk, const int32_t *star
  * A caller that writes the structure arrays of such a block itself must pass the block through
  * esp_block_from_tree before the next esp_build_prune_tree.
  * topk_p: probabilities, 0 <= p <= 1, which is what esp_mask_topk and esp_softmax_topk hand out; a child is
- * then never more probable than its parent, so the chosen nodes form a tree.  With an entry above 1 they
- * may not (a child kept, its parent cut): such a sequence gets n_rows = n_nodes = 0 and ESP_DEV_BAD_TREE.
+ * then never more probable than its parent, so the chosen nodes form a tree.  Entries above 1 are taken as
+ * they are (the build is then slower: nothing can be dropped early), NaN ranks above all, negative entries count
+ * as 0.  Where the nodes chosen are no tree (a child kept, its parent cut) the sequence gets n_rows = n_nodes = 0
+ * and ESP_DEV_BAD_TREE.
  * Errors: EINVAL (B, k, K, Kp out of range; k != next->k_masks), ECAPACITY (rows of the tree
  * exceed next->rows_per_seq). */
 esp_status esp_build_prune_tree(esp_ctx *ctx, const esp_tree_params *p, const int32_t *topk_id,

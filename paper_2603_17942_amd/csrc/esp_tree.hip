@@ -2,6 +2,8 @@
 // commit, row lists for the proposal pass, pruning + dynamic tree construction
 // (paper Sec. 2 Eq. 3, Sec. 3.3-3.5, Alg. 1, App. C, App. E).  One workgroup per sequence;
 // everything is integer work except the fp32 products of Alg. 1.
+#include <climits>
+
 #include "esp_internal.h"
 
 namespace {
@@ -212,6 +214,8 @@ __global__ void k_mask_rows(BlockDev b, const int32_t* star_row, const int32_t* 
 // that would grow from it.  Only the best B - 1 are kept from depth to depth (sorted), and of a depth's
 // children only those are created that beat the last of a full set.  Relative creation order, which
 // breaks ties and orders rows, is what the creation index records.
+// A list entry above 1 (or NaN) voids the second premise: then every candidate is created and stays in the pool
+// that the selections choose from, as Alg. 1 is written ("wide" below).
 constexpr int MAX_CAND = MAXC + ESP_MAX_TREE_NODES;
 struct TreeLds {
   // every candidate created, by creation index (0 = the root)
@@ -234,6 +238,9 @@ struct TreeLds {
   float list_p[ESP_MAX_MASKS * ESP_MAX_TOPK];
   int32_t n_cand, n_keep, kept_buf;        // n_keep -1: more candidates or nodes than there is room for
   int32_t orphan;                          // a kept node whose parent is not
+  __align__(16) int32_t odd[4];            // per wave: an entry outside [0, 1] among those it staged
+  float all_p[MAXC];                       // wide: probability by creation index
+  int32_t n_cre, n_pool;                   // wide: candidates created + 1, candidates not used yet
 };
 
 // How many of n fp32 values >= 0 in LDS reach `bound` (compared as bit patterns); one wave.
@@ -316,14 +323,18 @@ __device__ int keep_best(TreeLds& s, int from, int n, int T) {
 // s.cre[s.kept_buf][0..s.n_keep).  Latency is all there is to it: the code is kept in small loops on
 // purpose (it runs once per launch, so instruction fetch costs more than arithmetic).  B = 64, k = 4,
 // K = 8: the call takes 16 us; 36 us with every candidate created and a histogram per selection.
+template <bool wide>
 __device__ void grow_tree(TreeLds& s, const esp_tree_params& p, int root_tok, int kp, int depth_limit) {
   const int lane = threadIdx.x & 63;
   const bool first_wave = threadIdx.x < 64;
-  const bool is_static = p.static_widths[0] > 0;
+  const bool is_static = !wide && p.static_widths[0] > 0;
   const int T = max(p.B - 1, 0);
   const int K = p.K, B = p.B, ew = p.expand_width, drop_parent = p.prune_parent, drop_last = p.prune_last;
-  int buf = 0;
-  int nk = 0;                       // candidates kept
+  // P(child) = P(parent) * P(t|l), one fp32 product (Alg. 1).  Both are >= +0 or a positive NaN, and so is the product
+  // (the sign of 0 * infinity is cleared): ordered as integers everywhere
+  auto child_prob = [](float parent, float entry) { return wide ? fabsf(parent * entry) : parent * entry; };
+  int buf = 0;                      // where the kept candidates are (wide: the node set last chosen)
+  int nk = 0;                       // candidates kept (wide: in the pool, which is buffer 0)
   int n_cre = 1;                    // next creation index (first wave)
   int n_exp = 1;                    // nodes to expand: the root first (first wave)
 #pragma unroll 1
@@ -333,7 +344,8 @@ __device__ void grow_tree(TreeLds& s, const esp_tree_params& p, int root_tok, in
       const int32_t id = lane < kp ? s.list_id[(i - 1) * kp + lane] : -1;
       const float lp = lane < kp ? s.list_p[(i - 1) * kp + lane] : 0.f;
       const int nv = __builtin_ctzll(__builtin_amdgcn_ballot_w64(id < 0));          // a negative id ends a list
-      const float floor_p = !is_static && T > 0 && nk >= T ? s.prob[buf][T - 1] : -1.f;
+      const int dst = wide ? 0 : buf;
+      const int floor_p = !wide && !is_static && T > 0 && nk >= T ? __float_as_int(s.prob[buf][T - 1]) : INT_MIN;
       int n = nk;
 #pragma unroll 1
       for (int e0 = 0; e0 < n_exp; e0 += 64) {
@@ -352,7 +364,7 @@ __device__ void grow_tree(TreeLds& s, const esp_tree_params& p, int root_tok, in
           const float q = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lp), c));
           const bool ok = live && taken < want && !(drop_parent && t == ptok) && !(drop_last && i >= 2 && t == root_tok);
           taken += ok ? 1 : 0;
-          if (ok && pp * q > floor_p) make |= 1u << c;
+          if (ok && __float_as_int(child_prob(pp, q)) > floor_p) make |= 1u << c;
         }
         const int cnt = __popc(make);
         int off = 0, tot = 0;
@@ -373,28 +385,41 @@ __device__ void grow_tree(TreeLds& s, const esp_tree_params& p, int root_tok, in
           s.dep[cre] = (uint8_t)i;
           s.used[cre] = 0;
           s.row_of[cre] = -1;
-          s.prob[buf][n + made] = pp * s.list_p[(i - 1) * kp + c];     // one fp32 product (Alg. 1: P(c) = P(n) * P(t|l))
-          s.cre[buf][n + made] = cre;
+          const float pc = child_prob(pp, s.list_p[(i - 1) * kp + c]);
+          s.prob[dst][n + made] = pc;
+          s.cre[dst][n + made] = cre;
+          if (wide) s.all_p[cre] = pc;
         }
         n += tot;
         n_cre += tot;
       }
-      if (lane == 0) s.n_cand = n;
+      if (lane == 0) { s.n_cand = n; if (wide) s.n_cre = n_cre; }
     }
     __syncthreads();
-    const int n = s.n_cand;
+    int n = s.n_cand;
     if (n < 0) { if (threadIdx.x == 0) s.n_keep = -1; return; }
-    if (n == nk) break;             // nothing new: no deeper node either, and the list is sorted as it is
+    if (!wide && n == nk) break;    // nothing new: no deeper node either, and the list is sorted as it is
+    const bool last = i == depth_limit || (wide && n == nk);
     if (is_static) {
       // fixed tree: everything is kept, in creation order, and the first fresh child is expanded next
       n_exp = 1;
       if (threadIdx.x == 0) s.expand[0] = nk;
       nk = n;
     } else {
-      nk = keep_best(s, buf, n, T);
-      buf ^= 1;
+      int src = buf, take = T;
+      if (wide) {
+        src = 0;
+        take = last ? T : max(B - i, 0);
+        if (last) {                   // the tree is chosen from all candidates, used ones included
+          n = s.n_cre - 1;
+          for (int c = threadIdx.x; c < n; c += 256) { s.prob[0][c] = s.all_p[c + 1]; s.cre[0][c] = c + 1; }
+          __syncthreads();
+        }
+      }
+      nk = keep_best(s, src, n, take);
+      buf = src ^ 1;
     }
-    if (i == depth_limit) break;
+    if (last) break;
     __syncthreads();
     if (first_wave && !is_static) {
       // node set <- the B - i most probable candidates not used before; those of depth i are expanded next
@@ -417,6 +442,24 @@ __device__ void grow_tree(TreeLds& s, const esp_tree_params& p, int root_tok, in
       }
       n_exp = min(ne, width);
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (wide) {                     // the used ones leave the pool, the others close up
+        int left = 0;
+#pragma unroll 1
+        for (int j = 0; j < n; j += 64) {
+          const int at = min(j + lane, n - 1), c = s.cre[0][at];
+          const float pc = s.prob[0][at];
+          const bool stay = j + lane < n && !s.used[c];
+          const unsigned long long bs = __builtin_amdgcn_ballot_w64(stay);
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          if (stay) { s.cre[0][left + lanes_below(bs)] = c; s.prob[0][left + lanes_below(bs)] = pc; }
+          left += __popcll(bs);
+        }
+        if (lane == 0) s.n_pool = left;
+      }
+    }
+    if (wide) {
+      __syncthreads();
+      nk = s.n_pool;
     }
   }
   if (threadIdx.x == 0) {
@@ -484,12 +527,28 @@ __global__ __launch_bounds__(256) void k_build_tree(esp_tree_params p, const int
     }
   }
   const int root_tok = emit_tok[(size_t)seq * (ESP_MAX_MASKS + 1) + ne - 1];
+  bool odd = false;                     // an entry outside [0, 1], by its bits: above 1, negative or NaN
   for (int t = tid; t < p.k * kp; t += 256) {
     s.list_id[t] = topk_id[(size_t)seq * p.k * kp + t];
-    s.list_p[t] = topk_p[(size_t)seq * p.k * kp + t];
+    const float q = topk_p[(size_t)seq * p.k * kp + t];
+    s.list_p[t] = q;
+    odd |= __float_as_uint(q) > __float_as_uint(1.f);
   }
+  const bool wave_odd = __builtin_amdgcn_ballot_w64(odd) != 0ull;
+  if ((tid & 63) == 0) s.odd[tid >> 6] = wave_odd ? 1 : 0;
   __syncthreads();
-  grow_tree(s, p, root_tok, kp, depth_limit);
+  bool wide = false;
+  if (__builtin_expect((s.odd[0] | s.odd[1] | s.odd[2] | s.odd[3]) != 0, 0)) {
+    bool above = false;                 // among the entries that count
+    for (int t = tid; t < p.k * kp; t += 256) {
+      const float q = s.list_p[t];
+      s.list_p[t] = q > 0.f ? q : (q == q ? 0.f : fabsf(q));   // negative entries count as 0
+      above |= t < depth_limit * kp && s.list_id[t] >= 0 && !(q <= 1.f);
+    }
+    wide = __syncthreads_or(above && !is_static) != 0;
+  }
+  if (__builtin_expect(wide, 0)) grow_tree<true>(s, p, root_tok, kp, depth_limit);
+  else grow_tree<false>(s, p, root_tok, kp, depth_limit);
   __syncthreads();
   if (s.n_keep < 0) {
     if (tid == 0) { n_rows[seq] = 0; n_nodes[seq] = 0; atomicOr(status, ESP_DEV_BAD_TREE); }
@@ -514,7 +573,7 @@ __global__ __launch_bounds__(256) void k_build_tree(esp_tree_params p, const int
     s.row_dep[row] = (int32_t)(mine >> 16);
   }
   __syncthreads();
-  // A list entry above 1 lets a child outrank its parent, and the cut at B - 1 can then fall between the two: the
+  // An entry above 1 lets a child outrank its parent, and the cut at B - 1 can then fall between the two: the
   // nodes left are no tree.  All threads agree on that before anything is written; below, every parent row
   // precedes its child's.
   if (tid < n_keep) {

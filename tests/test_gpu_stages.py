@@ -427,6 +427,72 @@ def test_build_prune_tree_refuses_a_node_without_its_parent(B, tiny_engine, Bn, 
         check_block(nxt, b, tok, par, k, layout)
 
 
+@pytest.mark.parametrize("Bn,k,K,kp,width", [(12, 4, 5, 8, 0), (24, 3, 6, 6, 2), (15, 4, 4, 6, 1), (90, 3, 10, 12, 0),
+                                             (200, 2, 32, 32, 0)])
+def test_build_prune_tree_lists_above_one(B, tiny_engine, Bn, k, K, kp, width):
+    """Lists that are no probabilities (scores above 1, NaN, negative entries): Alg. 1 as it is written, bit-exact
+    against the oracle, and refused exactly where the nodes it selects are no tree.  Includes pools of more than
+    256 candidates."""
+    shape, w, eng = tiny_engine
+    rng = np.random.default_rng(Bn)
+    op = O.TreeParams(B=Bn, k=k, K=K, expand_width=width, prune_parent=True)
+    params = B.tree_params(Bn, k, K, width, True, False, 1)
+    dev = lambda a: torch.as_tensor(a).cuda()
+    batch, rows = 3, Bn + k
+    one = np.ones(batch, dtype=np.int32)
+    emit = np.full((batch, B.MAX_MASKS + 1), 501, dtype=np.int32)
+    built = refused = 0
+    for rnd in range(8):
+        ids = np.zeros((batch, k, kp), dtype=np.int32)
+        ps = np.zeros((batch, k, kp), dtype=np.float32)
+        for b in range(batch):
+            ids[b], ps[b] = random_lists(rng, k, kp, 60)
+            ps[b] *= np.float32(1.0000005 / ps[b].max()) if rnd % 4 == 0 else rng.choice([1, 2, 4, 20], (k, 1)).astype(np.float32)
+        same = ps.copy()                              # what the oracle is handed
+        if rnd == 3:
+            ps[0], same[0] = np.nan, 1.0              # all equal: creation order decides
+            ps[1, :, -1], same[1, :, -1] = -0.5, 0.0
+        nxt = B.BlockBuffers(batch, rows, k, 1)
+        print(f"lists above one B={Bn} k={k} K={K} width={width} draw {rnd}", flush=True)
+        eng.build_prune_tree(params, dev(ids), dev(ps), kp, dev(one * k), dev(one), dev(emit), nxt)
+        bad = False
+        for b in range(batch):
+            try:
+                tok, par, _ = O.build_prune_tree(op, ids[b], same[b], 501, n_depths=k)
+            except KeyError:
+                bad, refused = True, refused + 1
+                assert int(nxt.n_nodes[b]) == 0 and int(nxt.n_rows[b]) == 0
+                continue
+            built += 1
+            n = int(nxt.n_nodes[b])
+            assert n == len(tok), (rnd, b)
+            assert nxt.tok[b * rows:b * rows + n].tolist() == tok.tolist(), (rnd, b)
+            check_block(nxt, b, tok, par, k, 1)
+            assert nxt.parent[b * rows:b * rows + n].tolist() == par.tolist(), (rnd, b)
+        assert eng.device_status() == (B.DEV_BAD_TREE if bad else 0)
+    print(f"built {built}, refused {refused}", flush=True)
+    assert built >= 3
+
+
+def test_build_static_tree_ignores_list_values(B, tiny_engine):
+    """A fixed tree takes its entries by place: its shape does not depend on the values beside them."""
+    shape, w, eng = tiny_engine
+    rng = np.random.default_rng(8)
+    k, kp, widths = 3, 6, [4, 3, 2]
+    ids, ps = random_lists(rng, k, kp, 500)
+    dev = lambda a: torch.as_tensor(a).cuda()
+    one = np.ones(1, dtype=np.int32)
+    emit = np.full((1, B.MAX_MASKS + 1), 501, dtype=np.int32)
+    tok, par, _ = O.build_prune_tree(O.TreeParams(B=10, k=k, K=4, expand_width=1, static_widths=widths), ids, ps, 501, n_depths=k)
+    for value in (ps, np.full_like(ps, np.nan), ps * 30, -ps):
+        nxt = B.BlockBuffers(1, 10 + k, k, 1)
+        eng.build_prune_tree(B.tree_params(10, k, 4, 1, True, False, 1, widths), dev(ids[None]), dev(value[None].astype(np.float32)), kp,
+                             dev(one * k), dev(one), dev(emit), nxt)
+        assert eng.device_status() == 0
+        n = int(nxt.n_nodes[0])
+        assert nxt.tok[:n].tolist() == tok.tolist() and nxt.parent[:n].tolist() == par.tolist()
+
+
 # ---------------------------------------------------------------------------------------- verify + KV commit
 def test_verify_accept_and_kv_commit(B, tiny_engine):
     shape, w, eng = tiny_engine
