@@ -12,7 +12,7 @@
 //     that at least K' and few more of its 64 lane maxima reach; what reaches it is ranked at once.
 // Pass 2 (k_topk_merge): one wave per row merges the segment statistics (online-softmax rule) and
 // the segments' sorted lists (at most 64 segments, one per lane: K' rounds of a wave-wide best-head
-// search); p = exp(v - max) / sum in fp32.
+// search); p = min(1, exp(v - max) / sum) in fp32.
 #include <algorithm>
 #include <mutex>
 
@@ -259,7 +259,10 @@ __global__ __launch_bounds__(64) void k_topk_merge(const float* __restrict__ seg
   }
   if (lane < kp) {
     ids[(size_t)row * kp + lane] = out_i;
-    probs[(size_t)row * kp + lane] = out_i >= 0 ? expf(out_v - gmax) / tot : 0.f;
+    // the sum's own term at the maximum, exp2(fma(m, log2 e, -round(m log2 e))), can lie a few units in the last place
+    // below 1: a row with nearly all probability on one token would hand out more than 1.  NaN stays NaN.
+    const float p = expf(out_v - gmax) / tot;
+    probs[(size_t)row * kp + lane] = out_i < 0 ? 0.f : (p > 1.f ? 1.f : p);
   }
 }
 

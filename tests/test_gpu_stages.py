@@ -167,6 +167,24 @@ def test_softmax_topk_adversarial_orders_and_masked_logits(B):
     check_topk(ids.cpu().numpy(), ps.cpu().numpy(), to_np(many), 10, 1e-6)
 
 
+def test_softmax_topk_never_hands_out_more_than_one(B):
+    """Rows with all but a vanishing share of the probability on one token (maxima 15 to 40 over a floor of -30):
+    the first probability is 1 to rounding and never above it, and the tree built from such lists is one."""
+    rows, vocab, kp = 256, 4096, 10
+    top = torch.linspace(15.0, 40.0, rows)
+    logits = torch.full((rows, vocab), -30.0) + synth.normal_like((rows, vocab), 1.0, 22, 0, "cpu", torch.float32)
+    logits[torch.arange(rows), (torch.arange(rows) * 37) % vocab] = top
+    ids, ps = B.softmax_topk(logits.cuda(), kp)
+    ids, ps = ids.cpu().numpy(), ps.cpu().numpy()
+    assert ids[:, 0].tolist() == ((np.arange(rows) * 37) % vocab).tolist()
+    # round(m log2 e) is off by at most half a unit in the last place of values below 64, 2^-19, i.e. 1.33e-6 of the
+    # term; the exponentials and the division add 3 * 2^-24 each at most
+    assert ps.max() <= 1.0 and ps[:, 0].min() > 1 - 2e-6
+    check_topk(ids[::16], ps[::16], logits[::16].numpy(), kp, 1e-6)
+    for r in range(0, rows, 4):
+        O.build_prune_tree(O.TreeParams(B=64, k=4, K=8, expand_width=0), ids[r:r + 4], ps[r:r + 4], 1, n_depths=4)
+
+
 # ---------------------------------------------------------------------------------------- engine fixture
 @pytest.fixture(scope="module")
 def tiny_engine(B):

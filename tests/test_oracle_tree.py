@@ -251,3 +251,30 @@ def test_short_lists_and_depth_limit():
     assert tok.tolist() == [0, 1, 2]
     tok, parent, _ = O.build_prune_tree(O.TreeParams(B=20, k=2, K=5), ids, ps, 0, n_depths=0)
     assert tok.tolist() == [0] and parent.tolist() == [-1]
+
+
+def test_fp32_softmax_of_peaked_rows_keeps_the_tree_closed_when_capped():
+    """The device sums exp2(fma(v, log2 e, -round(m log2 e))) in fp32: at the maximum that term can lie below 1, so
+    that on a peaked row the quotient exceeds 1, a child outranks its parent and the cut at B - 1 leaves a node without
+    its parent (the oracle's KeyError).  Capped at 1, every selection is closed."""
+    rng = np.random.default_rng(4)
+    log2e = np.float32(1.4426950408889634)
+    k, kp = 4, 10
+    above = orphans = 0
+    for draw in range(120):
+        ids = np.stack([rng.choice(500, kp, replace=False) for _ in range(k)])
+        ps = np.zeros((k, kp), dtype=np.float32)
+        for i in range(k):
+            m = np.float32(rng.uniform(15.0, 40.0))
+            v = np.concatenate([[m], np.sort(m - rng.uniform(17.5, 25.0, kp - 1))[::-1]]).astype(np.float32)
+            shift = np.float32(m * log2e)
+            terms = np.exp2((v.astype(np.longdouble) * np.longdouble(log2e) - shift).astype(np.float32))
+            ps[i] = np.exp((v - m).astype(np.float32)) / terms.sum(dtype=np.float32)
+        above += int((ps > 1).any())
+        params = O.TreeParams(B=64, k=k, K=8, expand_width=0, prune_parent=True)
+        try:
+            O.build_prune_tree(params, ids, ps, 501, n_depths=k)
+        except KeyError:
+            orphans += 1
+        O.build_prune_tree(params, ids, np.minimum(ps, np.float32(1)), 501, n_depths=k)
+    assert above > 20 and orphans > 5
