@@ -216,7 +216,7 @@ __global__ void k_mask_rows(BlockDev b, const int32_t* star_row, const int32_t* 
 // breaks ties and orders rows, is what the creation index records.
 // A list entry above 1 (or NaN) voids the second premise: then every candidate is created and stays in the pool
 // that the selections choose from, as Alg. 1 is written ("wide" below).
-constexpr int MAX_CAND = MAXC + ESP_MAX_TREE_NODES;
+constexpr int MAX_CAND = MAXC + ESP_MAX_TREE_NODES + 4;
 struct TreeLds {
   // every candidate created, by creation index (0 = the root)
   int32_t tok[MAXC];
@@ -225,9 +225,9 @@ struct TreeLds {
   uint8_t used[MAXC];           // has been in the node set N
   // the kept candidates, sorted, followed by a depth's new ones: probability and creation index; two
   // buffers, a selection writes the other one
-  float prob[2][MAX_CAND];
+  __align__(16) float prob[2][MAX_CAND];
   int32_t cre[2][MAX_CAND];
-  float pick_p[ESP_MAX_TREE_NODES];        // survivors of a selection, in list order
+  __align__(16) float pick_p[ESP_MAX_TREE_NODES + 4];   // survivors of a selection, in list order
   int32_t pick[ESP_MAX_TREE_NODES];
   int32_t expand[ESP_MAX_TREE_NODES];      // list places of the kept candidates to expand next, in order
   __align__(16) uint32_t order[ESP_MAX_TREE_NODES];   // depth << 16 | creation index of the kept nodes
@@ -236,6 +236,7 @@ struct TreeLds {
   int16_t row_of[MAXC];                    // creation index -> row, -1: not in the tree
   int32_t list_id[ESP_MAX_MASKS * ESP_MAX_TOPK];   // the sequence's Top-K' lists, staged once
   float list_p[ESP_MAX_MASKS * ESP_MAX_TOPK];
+  uint64_t count[2][4];                    // pick_best: per-wave counts
   int32_t n_cand, n_keep, kept_buf;        // n_keep -1: more candidates or nodes than there is room for
   int32_t orphan;                          // a kept node whose parent is not
   __align__(16) int32_t odd[4];            // per wave: an entry outside [0, 1] among those it staged
@@ -243,57 +244,90 @@ struct TreeLds {
   int32_t n_cre, n_pool;                   // wide: candidates created + 1, candidates not used yet
 };
 
-// How many of n fp32 values >= 0 in LDS reach `bound` (compared as bit patterns); one wave.
-__device__ __forceinline__ int count_reaching(const float* v, int n, uint32_t bound, int lane) {
-  int cnt = 0;
-#pragma unroll 1
-  for (int j = 0; j < n; j += 64)
-    cnt += __popcll(__builtin_amdgcn_ballot_w64(j + lane < n && __float_as_uint(v[min(j + lane, n - 1)]) >= bound));
-  return cnt;
-}
-
-// One wave, for more candidates than a workgroup has threads: the T best (T <= 255) of the n in buffer
-// `from`, unsorted but in list order, to s.pick / pick_p.  The T-th largest probability is found bit by
-// bit from the top: a count (ballot, popcount) of the values that reach the prefix with the bit set.
-__device__ void pick_best(TreeLds& s, int from, int n, int T, int lane) {
+// The whole workgroup, for more candidates than it has threads: the T best (T <= 255) of the n in buffer
+// `from`, unsorted but in list order, to s.pick / pick_p.  The T-th largest probability (as a bit pattern) is found
+// two bits at a time from the top: each wave counts, over its quarter of the list, the values that reach the three
+// prefixes with those bits set (ballot, popcount), and the four waves' counts meet in LDS, one barrier a step.
+// Up to PICK_REGS * 256 candidates a step reads no LDS but the counts.  With the ranking below, the build at B = 256,
+// k = 3, K = 12: 37 us; 70 us with one wave that counts bit by bit over LDS and ranks by lane reads, 42 us with
+// a histogram over all candidates.
+constexpr int PICK_REGS = 5;
+__device__ void pick_best(TreeLds& s, int from, int n, int T) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int quarter = ((n + 255) >> 8) << 6;               // whole groups of 64
+  const int j0 = wave * quarter, j1 = min(n, j0 + quarter);
   const float* v = s.prob[from];
+  auto bits_at = [&](int j) {                              // 0 past the quarter's end: never counted
+    const uint32_t u = __float_as_uint(v[min(j + lane, n - 1)]);
+    return j + lane < j1 ? u : 0u;
+  };
+  uint32_t held[PICK_REGS];
+#pragma unroll
+  for (int r = 0; r < PICK_REGS; ++r) held[r] = bits_at(j0 + 64 * r);
   uint32_t bound = 0;
-  int reach = n;
+  int reach = n, turn = 0;
 #pragma unroll 1
-  for (int bit = 30; bit >= 0 && reach != T; --bit) {
-    const uint32_t b = bound | (1u << bit);
-    const int cnt = count_reaching(v, n, b, lane);
-    if (cnt >= T) { bound = b; reach = cnt; }
+  for (int shift = 30;; shift -= 2, turn ^= 1) {
+    // last of all, how many lie above the bound and how many are equal to it
+    const bool done = reach == T || shift < 0;
+    const uint32_t a = done ? max(bound, 1u) : bound | 1u << shift, b = done ? bound + 1 : bound | 2u << shift,
+                   c = done ? ~0u : bound | 3u << shift;
+    int na = 0, nb = 0, nc = 0;
+    auto count = [&](uint32_t u) {
+      na += __popcll(__builtin_amdgcn_ballot_w64(u >= a));
+      nb += __popcll(__builtin_amdgcn_ballot_w64(u >= b));
+      nc += __popcll(__builtin_amdgcn_ballot_w64(u >= c));
+    };
+#pragma unroll
+    for (int r = 0; r < PICK_REGS; ++r)
+      if (64 * r < quarter) count(held[r]);
+#pragma unroll 1
+    for (int j = j0 + 64 * PICK_REGS; j < j1; j += 64) count(bits_at(j));
+    if (lane == 0) s.count[turn][wave] = (uint64_t)na | (uint64_t)nb << 16 | (uint64_t)nc << 32;
+    __syncthreads();
+    if (done) break;
+    const uint64_t all = s.count[turn][0] + s.count[turn][1] + s.count[turn][2] + s.count[turn][3];
+    const uint32_t ab = __builtin_amdgcn_readfirstlane((uint32_t)all);
+    na = ab & 0xffff, nb = ab >> 16, nc = __builtin_amdgcn_readfirstlane((uint32_t)(all >> 32));
+    if (nc >= T) { bound |= 3u << shift; reach = nc; }
+    else if (nb >= T) { bound |= 2u << shift; reach = nb; }
+    else if (na >= T) { bound |= 1u << shift; reach = na; }
   }
-  int room = reach == T ? n : T - count_reaching(v, n, bound + 1, lane);   // how many of those equal to the bound fit
-  int base = 0;
+  // of those equal to the bound the first in list order are taken
+  if (threadIdx.x < 3) s.pick_p[T + threadIdx.x] = __int_as_float(-1);
+  int gt = 0, gt_before = 0, eq_before = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const int g = (int)(s.count[turn][w] >> 16) & 0xffff;
+    const int e = (bound ? (int)s.count[turn][w] & 0xffff : max(min(n, (w + 1) * quarter) - w * quarter, 0)) - g;
+    gt += g;
+    if (w < wave) { gt_before += g; eq_before += e; }
+  }
+  int room = T - gt - eq_before, base = gt_before + min(eq_before, T - gt);
 #pragma unroll 1
-  for (int j = 0; j < n; j += 64) {
-    const int i = j + lane;
-    const float p = i < n ? v[i] : -1.f;
-    const uint32_t u = __float_as_uint(p);
-    const bool eq = i < n && u == bound, gt = i < n && u > bound;
-    const unsigned long long be = __builtin_amdgcn_ballot_w64(eq);
-    const bool sel = gt || (eq && lanes_below(be) < room);
+  for (int j = j0; j < j1; j += 64) {
+    const bool in = j + lane < j1;
+    const uint32_t u = bits_at(j);
+    const unsigned long long be = __builtin_amdgcn_ballot_w64(in && u == bound);
+    const bool sel = in && (u > bound || (u == bound && lanes_below(be) < room));
     room -= __popcll(be);
     const unsigned long long bs = __builtin_amdgcn_ballot_w64(sel);
     const int at = base + lanes_below(bs);
-    if (sel) { s.pick[at] = s.cre[from][i]; s.pick_p[at] = p; }
+    if (sel) { s.pick[at] = s.cre[from][j + lane]; s.pick_p[at] = __uint_as_float(u); }
     base += __popcll(bs);
   }
 }
 
 // The whole workgroup: of the n candidates of buffer `from` the T best (T <= 255), sorted by (probability
 // descending, creation ascending), to the other buffer; returns how many.  A thread per candidate
-// counts the better ones: the others' probabilities come from a register of the wave lane by lane, so a
-// comparison is three instructions and no LDS access.  Candidates of equal probability lie in creation
-// order in both buffers.
+// counts the better ones, four at a time from one LDS read that all lanes share.  Candidates of equal probability
+// lie in creation order in both buffers; behind the last one lie three entries worse than anything (-1).
 __device__ int keep_best(TreeLds& s, int from, int n, int T) {
-  const int tid = threadIdx.x, lane = tid & 63, a0 = tid & ~63;
+  const int tid = threadIdx.x, a0 = tid & ~63;
   const bool pick = n > 256;
   const int m = pick ? T : n;
   if (pick) {
-    if (tid < 64) pick_best(s, from, n, T, lane);
+    pick_best(s, from, n, T);
     __syncthreads();
   }
   const float* v = pick ? s.pick_p : s.prob[from];
@@ -301,18 +335,18 @@ __device__ int keep_best(TreeLds& s, int from, int n, int T) {
   if (a0 < m) {                                            // wave-uniform
     const int32_t p = tid < m ? __float_as_int(v[tid]) : 0x7fffffff;      // >= 0.0: ordered as integers
     int rank = 0;
-#pragma unroll 1
-    for (int b0 = 0; b0 < m; b0 += 64) {
-      const int32_t o64 = b0 + lane < m ? __float_as_int(v[b0 + lane]) : -1;   // padding: worse than anything
-      const int32_t reach = b0 < a0 ? p - 1 : p;           // equal ones before this candidate are better
-      if (b0 == a0) {
-#pragma unroll 8
-        for (int l = 0; l < 64; ++l) rank += __builtin_amdgcn_readlane(o64, l) > p - (l < lane ? 1 : 0) ? 1 : 0;
-      } else {
-#pragma unroll 8
-        for (int l = 0; l < 64; ++l) rank += __builtin_amdgcn_readlane(o64, l) > reach ? 1 : 0;
+    // equal ones before this candidate are better: [0, a0) all lie before it, [a0, a0 + 64) may
+    auto better = [&](int b0, int b1, auto before) {
+#pragma unroll 2
+      for (int b = b0; b < b1; b += 4) {
+        const u32x4_t o = *reinterpret_cast<const u32x4_t*>(v + b);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) rank += (int32_t)o[e] > p - (before(b + e) ? 1 : 0) ? 1 : 0;
       }
-    }
+    };
+    better(0, min(a0, m), [](int) { return true; });
+    better(a0, min(a0 + 64, m), [&](int b) { return b < tid; });
+    better(a0 + 64, m, [](int) { return false; });
     if (tid < m && rank < T) { s.prob[from ^ 1][rank] = __int_as_float(p); s.cre[from ^ 1][rank] = c[tid]; }
   }
   return min(m, T);
@@ -322,7 +356,7 @@ __device__ int keep_best(TreeLds& s, int from, int n, int T) {
 // instead of workgroup barriers), the workgroup sorts.  Leaves the kept candidates in
 // s.cre[s.kept_buf][0..s.n_keep).  Latency is all there is to it: the code is kept in small loops on
 // purpose (it runs once per launch, so instruction fetch costs more than arithmetic).  B = 64, k = 4,
-// K = 8: the call takes 16 us; 36 us with every candidate created and a histogram per selection.
+// K = 8: the call takes 14.7 us; 36 us with every candidate created and a histogram per selection.
 template <bool wide>
 __device__ void grow_tree(TreeLds& s, const esp_tree_params& p, int root_tok, int kp, int depth_limit) {
   const int lane = threadIdx.x & 63;
@@ -359,12 +393,17 @@ __device__ void grow_tree(TreeLds& s, const esp_tree_params& p, int root_tok, in
         uint32_t make = 0;
         int taken = 0;
 #pragma unroll 1
-        for (int c = 0; c < nv; ++c) {
-          const int t = __builtin_amdgcn_readlane(id, c);
-          const float q = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lp), c));
-          const bool ok = live && taken < want && !(drop_parent && t == ptok) && !(drop_last && i >= 2 && t == root_tok);
-          taken += ok ? 1 : 0;
-          if (ok && __float_as_int(child_prob(pp, q)) > floor_p) make |= 1u << c;
+        for (int c = 0, c1 = min(nv, want);; c1 = min(nv, c1 + 1)) {
+#pragma unroll 1
+          for (; c < c1; ++c) {
+            const int t = __builtin_amdgcn_readlane(id, c);
+            const float q = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lp), c));
+            const bool ok = live && taken < want && !(drop_parent && t == ptok) && !(drop_last && i >= 2 && t == root_tok);
+            taken += ok ? 1 : 0;
+            if (ok && __float_as_int(child_prob(pp, q)) > floor_p) make |= 1u << c;
+          }
+          // more entries only where one was dropped
+          if (c >= nv || __builtin_amdgcn_ballot_w64(live && taken < want) == 0ull) break;
         }
         const int cnt = __popc(make);
         int off = 0, tot = 0;
@@ -393,6 +432,7 @@ __device__ void grow_tree(TreeLds& s, const esp_tree_params& p, int root_tok, in
         n += tot;
         n_cre += tot;
       }
+      if (lane < 3 && n >= 0) s.prob[dst][n + lane] = __int_as_float(-1);
       if (lane == 0) { s.n_cand = n; if (wide) s.n_cre = n_cre; }
     }
     __syncthreads();
@@ -413,6 +453,7 @@ __device__ void grow_tree(TreeLds& s, const esp_tree_params& p, int root_tok, in
         if (last) {                   // the tree is chosen from all candidates, used ones included
           n = s.n_cre - 1;
           for (int c = threadIdx.x; c < n; c += 256) { s.prob[0][c] = s.all_p[c + 1]; s.cre[0][c] = c + 1; }
+          if (threadIdx.x < 3) s.prob[0][n + threadIdx.x] = __int_as_float(-1);
           __syncthreads();
         }
       }

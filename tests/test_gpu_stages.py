@@ -262,9 +262,11 @@ def test_block_from_tree_long_chains(B, tiny_engine, n):
         check_block(blk, b, np.full(n, b + 1), np.asarray(par), 0, 0)
 
 
-@pytest.mark.parametrize("Bn,k,K,kp", [(256, 2, 32, 32), (200, 3, 10, 12), (65, 5, 8, 10), (1, 2, 4, 6)])
+@pytest.mark.parametrize("Bn,k,K,kp", [(256, 2, 32, 32), (256, 3, 12, 12), (200, 3, 10, 12), (256, 8, 2, 32), (65, 5, 8, 10),
+                                         (1, 2, 4, 6)])
 def test_build_prune_tree_large_and_smallest(B, tiny_engine, Bn, k, K, kp):
-    """More candidates than threads of the builder (its threshold path), the largest tree and the root alone."""
+    """More candidates than threads of the builder (its threshold search), more than that holds in registers
+    ((256, 3, 12, 12): 1871), lists longer than what a node takes of them, the largest tree and the root alone."""
     shape, w, eng = tiny_engine
     rng = np.random.default_rng(Bn)
     ids, ps = random_lists(rng, k, kp, 500)
@@ -373,9 +375,9 @@ def test_build_prune_tree_bit_exact(B, tiny_engine, Bn, k, K, kp, width, layout,
 
 def test_build_prune_tree_with_every_probability_tied(B, tiny_engine):
     """All list entries carry the same probability (a power of two, so the products are exact and
-    equal per depth): every selection is decided by creation order alone, and the hundreds of
-    candidates that share one probability defeat the histogram shortcut of the selection, so the
-    full sort behind it runs.  Bit-exact against the oracle."""
+    equal per depth): every selection is decided by creation order alone.  (Children that do not beat the
+    last of a full set are not created, so that at most 110 candidates meet here; the next test goes past 256.)
+    Bit-exact against the oracle."""
     shape, w, eng = tiny_engine
     Bn, k, K, kp, layout = 96, 5, 10, 12, 0
     batch = 2
@@ -401,6 +403,39 @@ def test_build_prune_tree_with_every_probability_tied(B, tiny_engine):
         assert n == len(tok)
         assert nxt.tok[r0:r0 + n].tolist() == tok.tolist()
         assert nxt.parent[r0:r0 + n].tolist() == par.tolist()
+
+
+@pytest.mark.parametrize("Bn,k,K,kp,better", [(200, 2, 32, 32, 0), (200, 2, 32, 32, 5), (129, 2, 20, 20, 3), (256, 2, 32, 32, 31),
+                                              (40, 2, 17, 17, 0), (256, 3, 12, 12, 2)])
+def test_build_prune_tree_cut_inside_a_tied_run(B, tiny_engine, Bn, k, K, kp, better):
+    """More candidates than the builder has threads (its threshold search), with the cut at B - 1 inside a run of
+    equal probabilities: the first created of them stay.  `better` entries of the second list lie above the
+    run; rows 1 and 2 of the batch have a zero tail and distinct values instead."""
+    shape, w, eng = tiny_engine
+    batch, rows = 3, Bn + k
+    rng = np.random.default_rng(Bn + better)
+    ids = np.stack([np.stack([rng.permutation(500)[:kp] for _ in range(k)]) for _ in range(batch)]).astype(np.int32)
+    ps = np.full((batch, k, kp), 2.0 ** -5, dtype=np.float32)
+    ps[0, 1, :better] = 2.0 ** -4
+    ps[1, :, kp // 2:] = 0.0
+    for i in range(k):
+        ps[2, i] = np.sort(rng.uniform(0.01, 0.03, kp))[::-1]
+    # until the last depth the set is not full, so that all children are created (less the parent's own token)
+    assert sum(kp * (kp - 1) ** i for i in range(k - 1)) < Bn - 1 and sum(kp * (kp - 1) ** i for i in range(k)) > 256
+    emit = np.full((batch, B.MAX_MASKS + 1), 501, dtype=np.int32)
+    one = np.ones(batch, dtype=np.int32)
+    dev = lambda a: torch.as_tensor(a).cuda()
+    nxt = B.BlockBuffers(batch, rows, k, 1)
+    print(f"tied run B={Bn} K={K} better={better}", flush=True)
+    eng.build_prune_tree(B.tree_params(Bn, k, K, 0, True, False, 1), dev(ids), dev(ps), kp, dev(one * k), dev(one), dev(emit), nxt)
+    assert eng.device_status() == 0
+    for b in range(batch):
+        tok, par, _ = O.build_prune_tree(O.TreeParams(B=Bn, k=k, K=K, expand_width=0, prune_parent=True), ids[b], ps[b], 501,
+                                         n_depths=k)
+        n = int(nxt.n_nodes[b])
+        assert n == len(tok)
+        assert nxt.tok[b * rows:b * rows + n].tolist() == tok.tolist()
+        assert nxt.parent[b * rows:b * rows + n].tolist() == par.tolist()
 
 
 @pytest.mark.parametrize("Bn,k,K,kp,layout", [(64, 4, 8, 10, 1), (96, 5, 10, 12, 0), (5, 3, 4, 4, 1)])
