@@ -167,6 +167,30 @@ def test_softmax_topk_adversarial_orders_and_masked_logits(B):
     check_topk(ids.cpu().numpy(), ps.cpu().numpy(), to_np(many), 10, 1e-6)
 
 
+@pytest.mark.parametrize("rows,vocab,kp", [(1, 2048, 10), (3, 32000, 10), (70, 4100, 31), (2, 151936, 5)])
+def test_softmax_topk_finite_masks(B, rows, vocab, kp):
+    """Large finite masks that fill every logit of one lane (four columns of each 256), whole ranges of the row,
+    or all but a few columns; rows without a positive value, with both zeros, and with values to 1e31 (ids only)."""
+    print(f"topk masks rows={rows} vocab={vocab} kp={kp}", flush=True)
+    col = np.arange(vocab)
+    lane = (col // 4) % 64 == 5
+    base = to_np(synth.normal_like((rows, vocab), 2.0, 23, rows, "cpu", torch.float32)).astype(np.float32)
+    kinds = {"lane": lambda v: np.where(lane, -1e9, v),
+             "tail": lambda v: np.where(col >= vocab - 300, -1e9, v), "few left": lambda v: np.where(col >= kp + 3, -1e9, v),
+             "negative": lambda v: -np.abs(v) - 1, "relu": lambda v: np.maximum(v, -0.0),
+             "spread": lambda v: np.where(col % 97 == 0, v * 1e30, v)}
+    for name, f in kinds.items():
+        logits = f(base).astype(np.float32)
+        ids, ps = B.softmax_topk(torch.as_tensor(logits).cuda(), kp)
+        ids, ps = ids.cpu().numpy(), ps.cpu().numpy()
+        for r in range(0, rows, 23):
+            want_ids = np.lexsort((col, -logits[r].astype(np.float64)))[:kp]    # the oracle ties what underflows to 0
+            _, want_ps = O.softmax_topk(logits[r], kp)
+            assert ids[r].tolist() == want_ids.tolist(), (name, r)
+            if name != "spread":
+                np.testing.assert_allclose(ps[r], want_ps, rtol=1e-5, atol=1e-30, err_msg=name)
+
+
 def test_softmax_topk_never_hands_out_more_than_one(B):
     """Rows with all but a vanishing share of the probability on one token (maxima 15 to 40 over a floor of -30):
     the first probability is 1 to rounding and never above it, and the tree built from such lists is one."""
