@@ -169,7 +169,9 @@ __global__ __launch_bounds__(256) void k_topk_stream(const float* __restrict__ l
     for (int i = 1; i < PER_LANE; ++i) bmax = fmaxf(bmax, cur[i]);
     const float m_new = fmaxf(m, bmax);
     if (m_new > -INFINITY) {
-      const float mb = m_new * LOG2E_F;
+      // Over a large finite mask (1e30, the type's lowest value) the rounded product is off by more than the
+      // exponents exp2 can take: a lane that holds nothing else adds 0, not infinity.
+      const float mb = fmaxf(m_new * LOG2E_F, -0x1p31f);
       float acc = s * __builtin_amdgcn_exp2f(m * LOG2E_F - mb);   // m = -inf: 0
 #pragma unroll
       for (int i = 0; i < PER_LANE; ++i) acc += __builtin_amdgcn_exp2f(fmaf(cur[i], LOG2E_F, -mb));

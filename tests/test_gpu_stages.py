@@ -175,7 +175,9 @@ def test_softmax_topk_finite_masks(B, rows, vocab, kp):
     col = np.arange(vocab)
     lane = (col // 4) % 64 == 5
     base = to_np(synth.normal_like((rows, vocab), 2.0, 23, rows, "cpu", torch.float32)).astype(np.float32)
-    kinds = {"lane": lambda v: np.where(lane, -1e9, v),
+    lowest = np.finfo(np.float32).min
+    kinds = {"lane": lambda v: np.where(lane, -1e9, v), "lane, lowest": lambda v: np.where(lane, lowest, v),
+             "row, lowest": lambda v: np.where(col > 0, lowest, v), "half, 1e30": lambda v: np.where(col < vocab // 2, -1e30, v),
              "tail": lambda v: np.where(col >= vocab - 300, -1e9, v), "few left": lambda v: np.where(col >= kp + 3, -1e9, v),
              "negative": lambda v: -np.abs(v) - 1, "relu": lambda v: np.maximum(v, -0.0),
              "spread": lambda v: np.where(col % 97 == 0, v * 1e30, v)}
@@ -189,6 +191,18 @@ def test_softmax_topk_finite_masks(B, rows, vocab, kp):
             assert ids[r].tolist() == want_ids.tolist(), (name, r)
             if name != "spread":
                 np.testing.assert_allclose(ps[r], want_ps, rtol=1e-5, atol=1e-30, err_msg=name)
+
+
+def test_softmax_topk_nan_row_says_so(B):
+    """A NaN among the logits makes the row's probabilities NaN wherever it lies, also far from the row's maximum;
+    other rows are untouched."""
+    logits = synth.normal_like((6, 32000), 2.0, 24, 0, "cpu", torch.float32).clone()
+    want = O.softmax_topk(logits[5].numpy(), 8)
+    logits[:4, 11] = 400.0
+    logits[0, 0], logits[1, 31999], logits[2, 5000], logits[3, 17] = (float("nan"),) * 4
+    ids, ps = B.softmax_topk(logits.cuda(), 8)
+    assert bool(torch.isnan(ps[:4]).all()) and not bool(torch.isnan(ps[4:]).any())
+    assert ids[5].tolist() == want[0].tolist()
 
 
 def test_softmax_topk_never_hands_out_more_than_one(B):
