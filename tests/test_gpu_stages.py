@@ -677,6 +677,54 @@ def test_qk_norm_sum_order(B, head_dim):
     assert np.array_equal(k, v * (inv * gain))
 
 
+@pytest.mark.parametrize("dtype,head_dim,d_model,hq,hkv,qk_norm", [
+    ("bf16", 64, 512, 3, 1, False), ("bf16", 64, 1024, 6, 2, True), ("bf16", 64, 1536, 3, 3, True), ("bf16", 64, 2048, 2, 1, False),
+    ("bf16", 64, 2560, 5, 1, True), ("bf16", 64, 3072, 3, 1, True), ("bf16", 64, 3584, 3, 3, False), ("bf16", 64, 4096, 3, 1, True),
+    ("bf16", 128, 512, 3, 1, True), ("bf16", 128, 3584, 3, 3, True), ("f32", 64, 128, 3, 1, True), ("f32", 128, 128, 3, 3, False),
+    ("f32", 128, 192, 5, 1, True)])
+def test_qkv_epilogue_forms(B, dtype, head_dim, d_model, hq, hkv, qk_norm):
+    """One layer against the oracle for every form of the QKV epilogue: head widths, types, QK-norm, and the 1 to 8
+    split-K parts that d_model / 512 gives the bf16 projection.  Odd numbers of heads leave the last workgroup partial;
+    two sequences of different length leave padding rows."""
+    shape = small_shape(d_model=d_model, n_q_heads=hq, n_kv_heads=hkv, head_dim=head_dim, d_ff=128, vocab=256, n_layers=1,
+                        qk_norm=qk_norm, dtype=dtype)
+    w = synth.make_weights(shape, seed=7, unit_gains=False)
+    m = oracle_model(shape, w)
+    k, layout, lens = 2, 0, [70, 5]
+    trees = [synth.make_random_tree(n, 4, shape.vocab, seed=60 + n) for n in (9, 6)]
+    rows = 9 * (k + 1) + 2
+    print(f"qkv epilogue {dtype} hd={head_dim} d={d_model} heads {hq}/{hkv} qk_norm={qk_norm}", flush=True)
+    eng = B.Engine(shape, w, 2, rows, 256)
+    blk = B.BlockBuffers(2, rows, k, layout)
+    blk.upload_trees([t.tolist() for t, _ in trees], [p.tolist() for _, p in trees])
+    eng.block_from_tree(blk)
+    kv = B.KvCache(shape, [128, 64])
+    old = []
+    for b, n in enumerate(lens):
+        old.append([synth.normal_like((n, hkv, head_dim), 1.0, 80 + b, i, "cuda", eng.dt) for i in (0, 1)])
+        eng.kv_store(kv, 0, b, 0, *old[b])
+    kv.set_len(lens)
+    masks = synth.normal_like((k, d_model), 0.02, 81, 0, "cuda", eng.dt)
+    hidden = torch.zeros((2 * rows, d_model), dtype=eng.dt, device="cuda")
+    eng.tree_forward(blk, masks, kv, hidden, None)
+    assert eng.device_status() == 0
+    for b, n in enumerate(lens):
+        ob = O.make_block(trees[b][0].numpy(), trees[b][1].numpy(), k, layout)
+        R = ob.n_rows
+        kc, vc = ([to_np(t)] for t in old[b])
+        _, want_h, want_k, want_v = O.tree_forward(m, ob, to_np(masks), kc, vc, n, want_logits_rows=[0])
+        got_k, got_v = eng.kv_load(kv, 0, b, n, R)
+        for what, got, want in (("hidden", hidden[b * rows:b * rows + R], want_h), ("k", got_k, want_k[0]), ("v", got_v, want_v[0])):
+            err = rel_err_rows(to_np(got).reshape(R, -1), np.asarray(want).reshape(R, -1))
+            assert err < TOL[dtype], (what, b, err)
+        # old rows and the slots behind the block are untouched
+        before = eng.kv_load(kv, 0, b, 0, n)
+        assert all(torch.equal(x, y) for x, y in zip(before, old[b]))
+        after = eng.kv_load(kv, 0, b, n + R, kv.caps[b] - n - R)
+        assert all(bool((x == 0).all()) for x in after)
+    eng.close()
+
+
 # ---------------------------------------------------------------------------------------- attention
 def run_attention_case(B, shape, eng, n_nodes, k, layout, cache_lens, seed):
     batch = len(cache_lens)
