@@ -9,11 +9,13 @@
 //     j-th best).  A block is only looked at when its maximum reaches the current K'-th value,
 //     which after the first block is rare (about K' ln(n/K') times per n logits), so the common
 //     path per logit is one max, one fma, one exp and one add.  The first block is filtered by a bound
-//     that at least K' and few more of its 64 lane maxima reach; what reaches it is ranked at once.
+//     that at least K' of its 64 lane maxima reach, and at most two more unless maxima are equal; up to 64
+//     logits that reach it are ranked at once, more (ties) are inserted one by one like those of later blocks.
 // Pass 2 (k_topk_merge): one wave per row merges the segment statistics (online-softmax rule) and
 // the segments' sorted lists (at most 64 segments, one per lane: K' rounds of a wave-wide best-head
 // search); p = min(1, exp(v - max) / sum) in fp32.
 #include <algorithm>
+#include <climits>
 #include <mutex>
 
 #include "esp_internal.h"
@@ -80,27 +82,35 @@ __device__ __forceinline__ float wave_sum_dpp(float x) {
   return wave_reduce_dpp(x, 0.f, [](float a, float b) { return a + b; });
 }
 
-// A bound that at least kp of the 64 lane values reach and, by bisection, at most two more unless values are
-// equal; -inf when fewer than kp are finite.  lanes = how many reach it, top = the wave's maximum.  The bisection
-// runs over the values' bit patterns (in their order): over the values themselves a single lane of large finite
-// masks (-1e9) uses up all steps, every logit of the block reaches the bound and is inserted one by one
-// (64 rows of 128256: 41 us against 13).
-__device__ __forceinline__ int ordered(int bits) { return bits ^ ((bits >> 31) & 0x7fffffff); }   // its own inverse
+// A bound that at least kp of the 64 lane values reach and, unless values are equal, at most two more; -inf when
+// fewer than kp are finite.  lanes = how many reach it, top = the wave's maximum.  The distance below the top is
+// found to a factor of eight first and then by bisection: over the values' whole range a single lane of large
+// finite masks (-1e9) uses up all halvings, every logit of the block reaches the bound and is inserted one by
+// one (64 rows of 128256: 41 us against 13).
 __device__ __forceinline__ float low_bound(float x, float top, int kp, int& lanes) {
-  const bool finite = x > -INFINITY;
-  lanes = __popcll(__builtin_amdgcn_ballot_w64(finite));
-  if (lanes < kp) return -INFINITY;
-  int lo = ordered(__float_as_int(-wave_max_dpp(finite ? -x : -INFINITY))), hi = ordered(__float_as_int(top));
+  lanes = 0;
+  if (__popcll(__builtin_amdgcn_ballot_w64(x > -INFINITY)) < kp) return -INFINITY;
+  float width = 8.f, lo = top - width, hi = top;
 #pragma unroll 1
-  while ((unsigned)hi - (unsigned)lo > 1u) {
-    const int mid = (int)((unsigned)lo + (((unsigned)hi - (unsigned)lo) >> 1));
-    const int reach = __popcll(__builtin_amdgcn_ballot_w64(x >= __int_as_float(ordered(mid))));
-    if (reach < kp) { hi = mid; continue; }
-    lo = mid;
-    lanes = reach;
-    if (reach <= kp + 2) break;
+  while ((lanes = __popcll(__builtin_amdgcn_ballot_w64(x >= lo))) < kp) {
+    if (!(width < 1e37f)) return -INFINITY;              // infinities, or the whole range of the type
+    hi = lo;
+    width *= 8.f;
+    lo = top - width;
   }
-  return __int_as_float(ordered(lo));
+#pragma unroll 1
+  for (int it = 0; it < 16 && lanes > kp + 2; ++it) {
+    const float mid = 0.5f * (lo + hi);
+    const int reach = __popcll(__builtin_amdgcn_ballot_w64(x >= mid));
+    if (reach >= kp) { lo = mid; lanes = reach; } else hi = mid;
+  }
+  return lo;
+}
+
+// the next larger value; NaN, which nothing reaches, after infinity
+__device__ __forceinline__ float next_above(float x) {
+  const int bits = __float_as_int(x);
+  return bits == INT_MIN ? __int_as_float(1) : __int_as_float(bits >= 0 ? bits + 1 : bits - 1);
 }
 
 // Offer the values of one register slot (one per lane) to the list: every lane whose value
@@ -158,7 +168,9 @@ __global__ __launch_bounds__(256) void k_topk_stream(const float* __restrict__ l
   LaneList L;
   list_init(L);
   float m = -INFINITY, s = 0.f;       // lane-local running maximum and sum of 2^((v - m) log2 e)
-  float floor_bound = -INFINITY, bound = -INFINITY;
+  // gate: what a block's maximum has to reach to be looked at.  A later block's ids are higher than all listed ones,
+  // so there it has to exceed the bound (rows of one repeated value: 4.2 ms for 1024 rows of 128256 without that)
+  float floor_bound = -INFINITY, bound = -INFINITY, gate = -INFINITY;
   if (nblocks > 0) load_block(0, nxt);
   for (int b = 0; b < nblocks; ++b) {
 #pragma unroll
@@ -181,7 +193,7 @@ __global__ __launch_bounds__(256) void k_topk_stream(const float* __restrict__ l
     if (b == 0) {
       int lanes;
       floor_bound = low_bound(bmax, wave_max_dpp(bmax), kp, lanes);
-      bound = floor_bound;
+      bound = gate = floor_bound;
       // the values that reach the bound (kp or a few more) are collected in LDS and ranked together
       // (not where most lanes are tied at it: equal values by the thousand are offered below)
       int n = 0;
@@ -209,13 +221,15 @@ __global__ __launch_bounds__(256) void k_topk_stream(const float* __restrict__ l
         L.last_v = readlane_f(L.v, kp - 1);
         L.last_id = __builtin_amdgcn_readlane(L.id, kp - 1);
         bound = fmaxf(floor_bound, L.last_v);
+        gate = next_above(bound);
         continue;
       }
     }
-    if (__builtin_amdgcn_ballot_w64(bmax >= bound) != 0ull) {
+    if (__builtin_amdgcn_ballot_w64(bmax >= gate) != 0ull) {
       const int base = start + b * BLOCK + lane * 4;
 #pragma unroll
       for (int i = 0; i < PER_LANE; ++i) offer(L, cur[i], base + (i >> 2) * 256 + (i & 3), bound, floor_bound, kp, lane);
+      gate = next_above(bound);
     }
   }
   // wave-wide statistics in the natural-exponent convention: sum of exp(v - max)
@@ -277,11 +291,13 @@ __global__ __launch_bounds__(64) void k_topk_merge(const float* __restrict__ seg
   }
 }
 
-// Segments per row.  Up to 4096 waves (four per SIMD, all resident at once) a wave gets a single block:
-// every load of the launch is then in flight from the start (64 rows of 128256: 14.8 us against 16.8 us
-// with two blocks a wave; 23.3 us before the bound by bisection and the ranked first block).  Beyond that
-// the fixed cost per wave counts and about 2048 waves walk several blocks each (256 rows: 33.4 us
-// against 36.3 us with 4096 waves).
+// Segments per row, at most 64 (the merge gives each a lane).  Where that makes up to 4096 waves (four per SIMD,
+// all resident at once), a row of up to 64 blocks (131072 logits) gets a wave per block: every load of the launch is
+// then in flight from the start (64 rows of 128256: 14.8 us against 16.8 us with two blocks a wave).  Longer rows
+// get two blocks a wave at any row count (151936: 38 segments; 64 rows 18.3 us).  With more waves than that the
+// fixed cost per wave counts and about 2048 waves walk several blocks each (256 rows: 33.4 us against 36.3 us with
+// 4096 waves).  Between, only 64 and 256 rows were compared: at 128256 the rule turns at 66 rows, and 65 rows take
+// 12.8 us where 80 take 19.4 us.
 int topk_segments(int rows, int vocab, int* seg_len) {
   const int max_seg = std::min(64, (vocab + BLOCK - 1) / BLOCK);   // the merge gives each segment a lane
   const int waves = (int64_t)rows * max_seg <= 4096 ? 4096 : 2048;

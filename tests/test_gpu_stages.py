@@ -193,6 +193,26 @@ def test_softmax_topk_finite_masks(B, rows, vocab, kp):
                 np.testing.assert_allclose(ps[r], want_ps, rtol=1e-5, atol=1e-30, err_msg=name)
 
 
+def test_softmax_topk_ties_across_blocks(B):
+    """Equal values in later blocks of a segment do not displace listed ones, a larger one does, and equal ones of the
+    same block go by id; negative values, zeros of both signs, infinity among them."""
+    rows, vocab, kp = 300, 20000, 6                        # several blocks a wave
+    for value in (-3.5, 0.0, -0.0, 2.0, -1e9):
+        logits = torch.full((rows, vocab), value)
+        logits[1::3, 9000] = value + abs(value) * 0.25 + 1
+        logits[2::3, [17000, 16900]] = value + abs(value) * 0.25 + 1
+        logits[2::3, 5] = -0.0 if value == 0 else value
+        ids, ps = B.softmax_topk(logits.cuda(), kp)
+        assert ids[0].tolist() == [0, 1, 2, 3, 4, 5]
+        assert ids[1].tolist() == [9000, 0, 1, 2, 3, 4]
+        assert ids[2].tolist() == [16900, 17000, 0, 1, 2, 3]
+        assert bool((ids[3:] == ids[:3].repeat(rows // 3 - 1, 1)).all())
+    few = torch.full((rows, vocab), float("-inf"))
+    few[:, [19000, 18999, 3000]] = torch.finfo(torch.float32).min
+    ids, _ = B.softmax_topk(few.cuda(), kp)
+    assert bool((ids == torch.tensor([3000, 18999, 19000, -1, -1, -1], device="cuda", dtype=torch.int32)).all())
+
+
 def test_softmax_topk_nan_row_says_so(B):
     """A NaN among the logits makes the row's probabilities NaN wherever it lies, also far from the row's maximum;
     other rows are untouched."""
