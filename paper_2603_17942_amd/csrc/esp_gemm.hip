@@ -253,10 +253,9 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
   // nothing): with a fixed number of loads in flight the compiler can wait for exactly the chunk it
   // needs.  The last group is code of its own that loads nothing: its refills would be D chunks of
   // repeated reads a workgroup (the O projection has 8 of its own), waited for by nobody but queued
-  // before the next kernel's.  Without them, relative to one common earlier build timed in the same run:
-  // one-row step 1.022 -> 1.031 times as fast, 30 rows 1.022 -> 1.041, 68 rows 1.009 -> 1.016, 101 rows of the
-  // Qwen3 shape 1.006 -> 1.018.  (Deeper rings on top, 8 chunks at <= 64 rows and 6 above, are slower:
-  // 1.000, 1.019, 0.969 and 0.971.)
+  // before the next kernel's.  With and without them, both in one run: step of one row 3562 -> 3535 us (runs of one side
+  // differ by 1.8 %), 30 rows 3782 -> 3716, 68 rows 4709 -> 4658, 101 rows of the Qwen3 shape 5978 -> 5904.  (Deeper
+  // rings, 8 chunks at <= 64 rows and 6 above, were slower by 2 to 5 %.)
   const int c_last = max(c_end - 1, c_begin);
   const u32x4_t zero4 = {0u, 0u, 0u, 0u};
   // prologue: chunks c_begin .. c_begin+D-1
