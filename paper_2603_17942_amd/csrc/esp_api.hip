@@ -10,7 +10,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline size_t elt(int dtype) { return dtype == ESP_F32 ? 4 : 2; }
 
 struct WsLayout {
-  size_t h, xn, q, attn_out, act, gemm_out, attn_part, rope_tab, logits, topk_scratch, idx_a, idx_b, idx_c, idx_d, status, total;
+  size_t h, xn, q, attn_out, act, gemm_out, attn_part, rope_tab, logits, topk_scratch, idx_a, idx_b, idx_c, idx_d, live, status, total;
   size_t gemm_out_floats, attn_part_floats, logits_rows;
 };
 
@@ -73,6 +73,7 @@ WsLayout ws_layout(const esp_model_desc* m, int max_batch, int max_rows, int64_t
   w.idx_b = take(std::max<size_t>(M, (size_t)max_batch * ESP_MAX_MASKS) * 4);
   w.idx_c = take(std::max<size_t>(M, (size_t)max_batch * ESP_MAX_MASKS) * 4);
   w.idx_d = take(std::max<size_t>(M, (size_t)max_batch * ESP_MAX_MASKS) * 4);
+  w.live = take((2 * M + 2 * (size_t)max_batch + 2) * 4);   // live_rows, packed_row, seq_row0, seq_node0, n_live
   w.status = take(256);
   w.total = off;
   return w;
@@ -240,6 +241,11 @@ esp_status esp_create(const esp_model_desc* m, const esp_weights* w, int32_t max
   c->topk_scratch = (float*)(c->ws + L.topk_scratch);
   c->idx_a = (int32_t*)(c->ws + L.idx_a); c->idx_b = (int32_t*)(c->ws + L.idx_b);
   c->idx_c = (int32_t*)(c->ws + L.idx_c); c->idx_d = (int32_t*)(c->ws + L.idx_d);
+  c->live_rows = (int32_t*)(c->ws + L.live);
+  c->packed_row = c->live_rows + (size_t)max_batch * max_rows;
+  c->seq_row0 = c->packed_row + (size_t)max_batch * max_rows;
+  c->seq_node0 = c->seq_row0 + max_batch;
+  c->n_live = c->seq_node0 + max_batch;
   c->status = (int32_t*)(c->ws + L.status);
   c->gemm_out_floats = L.gemm_out_floats; c->attn_part_floats = L.attn_part_floats; c->logits_rows = L.logits_rows;
   if (hipMemsetAsync(c->status, 0, 256, c->stream) != hipSuccess) {
@@ -345,13 +351,24 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
     if (gemm_plan(dt, Mlm, m.vocab, d).splits != 1) return ESP_ESHAPE;
   }
 
+  // Ragged batches: only the rows that are there go through the layers, packed together (the row counts live on the
+  // device).  Up to 128 rows the projections are weight streams and padding costs nothing; one sequence has no
+  // padding to speak of.  16 sequences of 36 to 128 tree nodes, 1630 of 2112 rows there (8B shape): step 37.1 -> 32.7 ms.
+  const bool packed = pk && blk->batch > 1 && M > 128;
+  const int32_t* m_live = nullptr;
   { ESP_PROF(ESP_SITE_GLUE);
+  if (packed) {
+    ESP_HIP(launch_live_rows(s, bd, kd, nodes_bound(blk), c->live_rows, c->packed_row, c->seq_row0, c->seq_node0, c->n_live));
+    bd.live_rows = c->live_rows; bd.packed_row = c->packed_row; bd.seq_row0 = c->seq_row0;
+    bd.seq_node0 = c->seq_node0; bd.n_live = c->n_live;
+    m_live = c->n_live;
+  }
   ESP_HIP(launch_embed(s, dt, bd, kd, c->embed, mask_embed, c->h, d, m.vocab, c->rope_tab, hd, m.rope_theta,
                        c->status, c->mask_per_seq ? (size_t)blk->k_masks * d : 0));
-  ESP_HIP(launch_residual_norm(s, dt, c->h, nullptr, 0, M, d, c->norm_attn[0], m.rms_eps, c->xn)); }
+  ESP_HIP(launch_residual_norm(s, dt, c->h, nullptr, 0, M, d, c->norm_attn[0], m.rms_eps, c->xn, m_live)); }
   for (int l = 0; l < m.n_layers; ++l) {
     { ESP_PROF_KERNEL(ESP_SITE_GEMM_LAYER, dt == ESP_BF16);
-      ESP_HIP(launch_gemm(s, dt, c->xn, nullptr, c->wqkv[l], c->gemm_out, M, nqkv, d, p_qkv, pk)); }
+      ESP_HIP(launch_gemm(s, dt, c->xn, nullptr, c->wqkv[l], c->gemm_out, M, nqkv, d, p_qkv, pk, 0, m_live)); }
     { ESP_PROF(ESP_SITE_GLUE);
       ESP_HIP(launch_qkv_post(s, dt, bd, kd, l, c->gemm_out, p_qkv.splits, M, hq, hkv, hd, m.qk_norm, c->q_norm[l],
                               c->k_norm[l], m.rms_eps, c->rope_tab, c->q)); }
@@ -360,12 +377,12 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
     { ESP_PROF(ESP_SITE_ATTN_MERGE);
       ESP_HIP(launch_attn_merge(s, dt, bd, kd, hq, hkv, hd, c->attn_part, ap, c->attn_out)); }
     { ESP_PROF_KERNEL(ESP_SITE_GEMM_LAYER, dt == ESP_BF16);
-      ESP_HIP(launch_gemm(s, dt, c->attn_out, nullptr, c->wo[l], c->gemm_out, M, d, hq * hd, p_o, pk)); }
+      ESP_HIP(launch_gemm(s, dt, c->attn_out, nullptr, c->wo[l], c->gemm_out, M, d, hq * hd, p_o, pk, 0, m_live)); }
     { ESP_PROF(ESP_SITE_GLUE);
-      ESP_HIP(launch_residual_norm(s, dt, c->h, c->gemm_out, p_o.splits, M, d, c->norm_mlp[l], m.rms_eps, c->xn)); }
+      ESP_HIP(launch_residual_norm(s, dt, c->h, c->gemm_out, p_o.splits, M, d, c->norm_mlp[l], m.rms_eps, c->xn, m_live)); }
     if (dt == ESP_BF16) {   // gate/up projection with the SwiGLU in its epilogue (interleaved weight rows)
       ESP_PROF_KERNEL(ESP_SITE_GEMM_LAYER, true);
-      ESP_HIP(launch_gemm_swiglu(s, c->xn, c->wgu[l], c->act, M, ff, d));
+      ESP_HIP(launch_gemm_swiglu(s, c->xn, c->wgu[l], c->act, M, ff, d, m_live));
     } else {
       { ESP_PROF(ESP_SITE_GEMM_LAYER);
         ESP_HIP(launch_gemm(s, dt, c->xn, nullptr, c->wgu[l], c->gemm_out, M, 2 * ff, d, p_gu, pk)); }
@@ -373,11 +390,12 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
         ESP_HIP(launch_swiglu(s, dt, c->gemm_out, p_gu.splits, M, ff, c->act)); }
     }
     { ESP_PROF_KERNEL(ESP_SITE_GEMM_LAYER, dt == ESP_BF16);
-      ESP_HIP(launch_gemm(s, dt, c->act, nullptr, c->wdown[l], c->gemm_out, M, d, ff, p_dn, pk)); }
+      ESP_HIP(launch_gemm(s, dt, c->act, nullptr, c->wdown[l], c->gemm_out, M, d, ff, p_dn, pk, 0, m_live)); }
     const bool last = l + 1 == m.n_layers;
     { ESP_PROF(ESP_SITE_GLUE);
       ESP_HIP(launch_residual_norm(s, dt, c->h, c->gemm_out, p_dn.splits, M, d,
-                                   last ? c->final_norm : c->norm_attn[l + 1], m.rms_eps, last ? hidden_out : c->xn)); }
+                                   last ? c->final_norm : c->norm_attn[l + 1], m.rms_eps, last ? hidden_out : c->xn, last ? nullptr : m_live,
+                                   last ? bd.packed_row : nullptr)); }
   }
   // LM head + argmax at the tree rows (Sec. 2 Eq. 3 needs the base model's own next token there)
   if (logits_dbg) {
@@ -419,7 +437,7 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
       // arg-max in the GEMM epilogue: the [rows, vocab] logits are never written
       ESP_PROF(ESP_SITE_LM_HEAD);
       ESP_HIP(launch_gemm_argmax(s, hidden_out, c->idx_a, c->lm_head, Mn, m.vocab, d, c->logits, node_argmax,
-                                 c->idx_b, 0, nullptr, nullptr, Mn, draw_list, c->sample_seed));
+                                 c->idx_b, 0, nullptr, nullptr, Mn, draw_list, c->sample_seed, packed ? c->n_live + 1 : nullptr));
     } else {
       { ESP_PROF(ESP_SITE_LM_HEAD);
         ESP_HIP(launch_gemm(s, dt, hidden_out, c->idx_a, c->lm_head, c->logits, Mn, m.vocab, d, p_lm, pk)); }

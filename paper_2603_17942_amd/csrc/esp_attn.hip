@@ -48,7 +48,7 @@ __global__ __launch_bounds__(64) void k_attn_generic(BlockDev b, KvDev kv, int l
   const T* vp = (const T*)kv.v + kv_plane(layer, kvh, hkv, kv.capacity, HD);
   const int64_t base = kv.base[seq];
   const float scale = LOG2E / sqrtf((float)HD);
-  for (int d = lane; d < HD; d += 64) qs[d] = to_f32(q[((size_t)row * hq + h) * HD + d]) * scale;
+  for (int d = lane; d < HD; d += 64) qs[d] = to_f32(q[(act_row(b, seq, r) * hq + h) * HD + d]) * scale;
   __syncthreads();
   const uint64_t* anc = b.anc + (size_t)row * b.anc_words;
   float m = NEG_BIG, l = 0.f;
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(64 * RING_MAX_WAVES) void k_attn_ring(BlockDev b, K
   issue_tile(0);
   bf16x8_t qf[8];
   {
-    const bf16_t* qp = q + (row * hq + h) * HD + 8 * lg;
+    const bf16_t* qp = q + (act_row(b, seq, r) * hq + h) * HD + 8 * lg;
 #pragma unroll
     for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8_t*>(qp + 16 * s);
     asm volatile("" : "+v"(qf[0]), "+v"(qf[1]), "+v"(qf[2]), "+v"(qf[3]), "+v"(qf[4]), "+v"(qf[5]), "+v"(qf[6]), "+v"(qf[7])
@@ -451,12 +451,12 @@ __global__ __launch_bounds__(256) void k_attn_merge(BlockDev b, KvDev kv, int hq
   const int row = item / hq;
   const int seq = row / b.rows_per_seq, r = row % b.rows_per_seq;
   const int nr = b.n_rows[seq];
-  T* dst = out + (size_t)item * hd + d;
   f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
   if (!seq_ok(kv, seq, nr, b.rows_per_seq) || r >= nr) {
-    store4(dst, acc);
+    if (!b.seq_row0) store4(out + (size_t)item * hd + d, acc);
     return;
   }
+  T* dst = out + (act_row(b, seq, r) * hq + item % hq) * hd + d;
   const size_t item0 = (size_t)item * nsplit;
   float mx = NEG_BIG;
   for (int s = 0; s < nsplit; ++s) mx = fmaxf(mx, part_ml[(item0 + s) * 2]);
@@ -494,8 +494,8 @@ __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, i
   const bool ok = seq_ok(kv, seq, nr, b.rows_per_seq);
   const int col = threadIdx.x & 31, grp = threadIdx.x >> 5;
   const int c = ct * 32 + col;                      // column within the kv group
-  const bool in_block = c < b.rows_per_seq * G;     // has an output row at all
   const bool live = ok && c < nr * G;
+  const bool in_block = b.seq_row0 ? live : c < b.rows_per_seq * G;     // has an output row at all
   const size_t t0 = (size_t)tile * nsplit;
   float ms[PER], ls[PER];
   float mx = NEG_BIG;
@@ -543,7 +543,7 @@ __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, i
     acc *= inv;
   }
   const int r = c / G, h = kvh * G + c % G;
-  store4(out + (((size_t)seq * b.rows_per_seq + r) * hq + h) * HD + f0, acc);
+  store4(out + (act_row(b, seq, r) * hq + h) * HD + f0, acc);
 }
 
 }  // namespace

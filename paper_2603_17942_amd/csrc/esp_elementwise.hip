@@ -34,6 +34,51 @@ __device__ __forceinline__ float block_sum_256(float v, float* red) {
 }
 
 // ---- block assembly (Sec. 3.1, Sec. 3.3): h0 rows and the per-row rotary table ---------------
+// Packed rows of a batch (BlockDev): one workgroup per sequence adds up the row counts of the sequences before it
+// and writes its own rows' places.  A sequence that is not valid (or a count that does not fit) has no rows; its tree
+// rows follow the block alone, as in k_node_rows.
+__global__ __launch_bounds__(256) void k_live_rows(BlockDev b, KvDev kv, int max_nodes, int32_t* live_rows,
+                                                   int32_t* packed_row, int32_t* seq_row0, int32_t* seq_node0,
+                                                   int32_t* n_live) {
+  __shared__ float red[4];
+  const int seq = blockIdx.x;
+  auto rows_of = [&](int s) {
+    const int nr = b.n_rows[s];
+    return nr <= b.rows_per_seq && seq_ok(kv, s, nr) ? nr : 0;
+  };
+  auto nodes_of = [&](int s) {
+    const int nn = b.n_nodes[s];
+    return nn >= 0 && nn <= b.n_rows[s] && b.n_rows[s] <= b.rows_per_seq ? min(nn, max_nodes) : 0;
+  };
+  float r0 = 0.f, q0 = 0.f;             // counts below 2^24: exact
+  for (int s = threadIdx.x; s < seq; s += 256) {
+    r0 += (float)rows_of(s);
+    q0 += (float)nodes_of(s);
+  }
+  const int first = (int)block_sum_256(r0, red), node0 = (int)block_sum_256(q0, red);
+  const int nr = rows_of(seq);
+  for (int r = threadIdx.x; r < b.rows_per_seq; r += 256) {
+    const int row = seq * b.rows_per_seq + r;
+    packed_row[row] = r < nr ? first + r : -1;
+    if (r < nr) live_rows[first + r] = row;
+  }
+  if (threadIdx.x == 0) {
+    seq_row0[seq] = first;
+    seq_node0[seq] = node0;
+    if (seq + 1 == b.batch) {
+      n_live[0] = first + nr;
+      n_live[1] = node0 + nodes_of(seq);
+    }
+  }
+}
+
+hipError_t launch_live_rows(hipStream_t st, const BlockDev& b, const KvDev& kv, int max_nodes, int32_t* live_rows, int32_t* packed_row,
+                            int32_t* seq_row0, int32_t* seq_node0, int32_t* n_live) {
+  hipLaunchKernelGGL(k_live_rows, dim3(b.batch), dim3(256), 0, st, b, kv, max_nodes, live_rows, packed_row, seq_row0,
+                     seq_node0, n_live);
+  return hipGetLastError();
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void k_embed(BlockDev b, KvDev kv, const T* __restrict__ embed,
                                                const T* __restrict__ mask_embed, float* __restrict__ h, int d,
@@ -45,6 +90,8 @@ __global__ __launch_bounds__(256) void k_embed(BlockDev b, KvDev kv, const T* __
   const bool ok = seq_ok(kv, seq, nr) && nr <= b.rows_per_seq;
   if (r == 0 && threadIdx.x == 0 && !ok) atomicOr(status, ESP_DEV_LEN_OVER_BOUND);
   const bool live = ok && r < nr;
+  if (b.packed_row && !live) return;
+  const size_t at = b.packed_row ? (size_t)b.packed_row[row] : (size_t)row;
   const T* src = nullptr;
   if (live) {
     int j = b.mask_j[row];
@@ -59,15 +106,15 @@ __global__ __launch_bounds__(256) void k_embed(BlockDev b, KvDev kv, const T* __
       }
     }
   }
-  float* hr = h + (size_t)row * d;
+  float* hr = h + at * d;
   for (int i = threadIdx.x; i < d; i += blockDim.x) hr[i] = src ? to_f32(src[i]) : 0.f;
   const int half = hd >> 1;
   for (int i = threadIdx.x; i < half; i += blockDim.x) {
     // angle in double: positions reach 1e4..1e5 where an fp32 product loses the fraction
     double pos = live ? (double)(kv.len[seq] + b.depth[row]) : 0.0;
     double ang = pos * pow((double)theta, -2.0 * (double)i / (double)hd);
-    rope_tab[((size_t)row * half + i) * 2 + 0] = (float)cos(ang);
-    rope_tab[((size_t)row * half + i) * 2 + 1] = (float)sin(ang);
+    rope_tab[(at * half + i) * 2 + 0] = (float)cos(ang);
+    rope_tab[(at * half + i) * 2 + 1] = (float)sin(ang);
   }
 }
 
@@ -118,11 +165,24 @@ __device__ __forceinline__ f32x4_t add_splits(f32x4_t v, const float* __restrict
 template <typename T, int S>
 __global__ __launch_bounds__(1024) void k_residual_norm(float* __restrict__ h, const float* __restrict__ part,
                                                         size_t split_stride, int d, const T* __restrict__ gain,
-                                                        float eps, T* __restrict__ xn) {
+                                                        float eps, T* __restrict__ xn, const int32_t* __restrict__ n_live,
+                                                        const int32_t* __restrict__ packed_row) {
   __shared__ float red[16];
-  const size_t row = blockIdx.x;
-  float* hr = h + row * d;
+  const size_t row_out = blockIdx.x;
   const int d4 = d >> 2, tid = threadIdx.x, step = blockDim.x;
+  size_t row = row_out;
+  if (packed_row) {                  // back to block rows
+    const int at = packed_row[row_out];
+    if (at < 0) {
+      const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+      for (int i = tid; i < d4; i += step) Pack4<T>::store(xn + row_out * d + 4 * i, zero);
+      return;
+    }
+    row = (size_t)at;
+  } else if (n_live && (int)row >= *n_live) {
+    return;
+  }
+  float* hr = h + row * d;
   f32x4_t keep = {0.f, 0.f, 0.f, 0.f}, g0 = keep;    // this thread's first column and its gain
   if (tid < d4) g0 = Pack4<T>::load(gain + 4 * tid);
   float ss = 0.f;
@@ -141,7 +201,7 @@ __global__ __launch_bounds__(1024) void k_residual_norm(float* __restrict__ h, c
   for (int i = tid; i < d4; i += step) {
     const f32x4_t v = i == tid ? keep : *reinterpret_cast<const f32x4_t*>(hr + 4 * i);   // written by this thread above
     const f32x4_t g = i == tid ? g0 : Pack4<T>::load(gain + 4 * i);
-    Pack4<T>::store(xn + row * d + 4 * i, v * inv * g);
+    Pack4<T>::store(xn + row_out * d + 4 * i, v * inv * g);
   }
 }
 
@@ -160,19 +220,20 @@ __global__ __launch_bounds__(1024) void k_residual_norm(float* __restrict__ h, c
   }
 
 hipError_t launch_residual_norm(hipStream_t st, int dtype, float* h, const float* part, int splits, int M,
-                                int d, const void* gain, float eps, void* xn_out) {
+                                int d, const void* gain, float eps, void* xn_out, const int32_t* n_live,
+                                const int32_t* packed_row) {
   const dim3 grid(M), block(std::min(1024, ((d >> 2) + 63) & ~63));
   const size_t stride = (size_t)M * d;
   if (splits == 0) {
     ESP_DISPATCH(dtype, hipLaunchKernelGGL((k_residual_norm<T, 0>), grid, block, 0, st, h, part, stride, d,
-                                           (const T*)gain, eps, (T*)xn_out));
+                                           (const T*)gain, eps, (T*)xn_out, n_live, packed_row));
   } else if (dtype == ESP_F32) {   // the fp32 GEMM splits K inside a workgroup
     if (splits != 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_residual_norm<float, 1>), grid, block, 0, st, h, part, stride, d, (const float*)gain, eps,
-                       (float*)xn_out);
+                       (float*)xn_out, n_live, packed_row);
   } else {
     ESP_SPLITS(splits, hipLaunchKernelGGL((k_residual_norm<bf16_t, S>), grid, block, 0, st, h, part, stride, d,
-                                          (const bf16_t*)gain, eps, (bf16_t*)xn_out));
+                                          (const bf16_t*)gain, eps, (bf16_t*)xn_out, n_live, packed_row));
   }
   return hipGetLastError();
 }
@@ -186,7 +247,8 @@ __global__ __launch_bounds__(256) void k_qkv_post(BlockDev b, KvDev kv, int laye
                                                   const T* __restrict__ qg, const T* __restrict__ kg, float eps,
                                                   const float* __restrict__ rope_tab, T* __restrict__ q_out) {
   constexpr int LPH = HD / 8, HALF = HD / 2;
-  const int row = blockIdx.y;
+  const int row = blockIdx.y;                       // of the activations
+  if (b.n_live && row >= *b.n_live) return;
   const int hidx = (blockIdx.x * 256 + threadIdx.x) / LPH;
   const int f0 = (threadIdx.x % LPH) * 4;
   const int n_heads = hq + 2 * hkv;
@@ -195,7 +257,8 @@ __global__ __launch_bounds__(256) void k_qkv_post(BlockDev b, KvDev kv, int laye
   f32x4_t x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
   x0 = add_splits<S>(x0, part + c0, split_stride);
   x1 = add_splits<S>(x1, part + c0 + HALF, split_stride);
-  const int seq = row / b.rows_per_seq, r = row % b.rows_per_seq;
+  const int brow = b.live_rows ? b.live_rows[row] : row;
+  const int seq = brow / b.rows_per_seq, r = brow % b.rows_per_seq;
   const int nr = b.n_rows[seq];
   const bool live = seq_ok(kv, seq, nr) && nr <= b.rows_per_seq && r < nr;
   const int64_t slot = (int64_t)kv.base[seq] + kv.len[seq] + r;
@@ -356,7 +419,8 @@ hipError_t launch_argmax(hipStream_t st, const float* logits, size_t row_stride,
   return hipGetLastError();
 }
 
-// gather lists for the LM head over node rows: logical row m = seq*max_nodes + i
+// gather lists for the LM head over node rows: logical row m = seq*max_nodes + i; in a batch with packed rows the
+// tree rows that are there come first, one after the other, and the rest of the lists is marked unused
 __global__ void k_node_rows(BlockDev b, int max_nodes, int32_t* a_rows, int32_t* out_rows,
                             const int32_t* __restrict__ kv_len, int32_t* pos_list) {
   int m = blockIdx.x * blockDim.x + threadIdx.x;
@@ -365,8 +429,13 @@ __global__ void k_node_rows(BlockDev b, int max_nodes, int32_t* a_rows, int32_t*
   int nn = b.n_nodes[seq];
   bool live = i < nn && nn <= b.n_rows[seq] && b.n_rows[seq] <= b.rows_per_seq;
   const int row = seq * b.rows_per_seq + (live ? i : 0);
+  if (b.seq_node0) {
+    if (m >= b.n_live[1]) { a_rows[m] = 0; out_rows[m] = -1; if (pos_list) pos_list[m] = 0; }
+    if (!live) return;
+    m = b.seq_node0[seq] + i;
+  }
   a_rows[m] = row;
-  out_rows[m] = live ? seq * b.rows_per_seq + i : -1;
+  out_rows[m] = live ? row : -1;
   if (pos_list) pos_list[m] = kv_len[seq] + b.depth[row] + 1;
 }
 

@@ -54,11 +54,21 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
                                                const int32_t* __restrict__ a_rows, const bf16_t* __restrict__ W,
                                                float* __restrict__ out, int M, int N, int K, int splits,
                                                int m_tiles, int n_tiles, int a_ld, float* __restrict__ out2,
-                                               const int32_t* __restrict__ draw_pos, uint32_t seed) {
+                                               const int32_t* __restrict__ draw_pos, uint32_t seed,
+                                               const int32_t* __restrict__ m_live) {
+  // m_live: only the first *m_live rows are there (packed rows of a ragged batch).  The grid was sized for M; the
+  // tiles that are there take its first workgroups and the others have nothing to do.  Strides stay those of M.
+  const int M_ld = M;
+  if (m_live) {
+    M = min(*m_live, M);
+    if (M <= 0) return;
+    m_tiles = (M + WM * MT * 32 - 1) / (WM * MT * 32);
+  }
   // XCD-aware logical id: consecutive hardware ids go to different XCDs, so give each XCD a
   // contiguous range of tiles (tiles sharing weight rows then share an L2).
   const int total = m_tiles * n_tiles * splits;
   const int per_xcd = (total + 7) >> 3;
+  if ((int)(blockIdx.x >> 3) >= per_xcd) return;
   const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (logical >= total) return;
   const int mi = logical % m_tiles;
@@ -334,7 +344,7 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
 
   // epilogue: lane holds column n, rows 8*(v/4) + 4*lg + v%4 of each 32x32 tile
   if (EPI == 0 || EPI == 3) {
-    float* o = out + (size_t)z * M * N;
+    float* o = out + (size_t)z * M_ld * N;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       const int n = n0 + nb * 32 + lr;
@@ -419,8 +429,8 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
       const int m = mt0 + rl;
       float* pairs = EPI == 3 ? out2 : out;
       if (m < M) {
-        pairs[((size_t)ni * M + m) * 2 + 0] = bv;
-        pairs[((size_t)ni * M + m) * 2 + 1] = __int_as_float(bj);
+        pairs[((size_t)ni * M_ld + m) * 2 + 0] = bv;
+        pairs[((size_t)ni * M_ld + m) * 2 + 1] = __int_as_float(bj);
       }
     }
   } else if (EPI == 1 || EPI == 3) {
@@ -469,8 +479,8 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
       const int m = mt0 + rl;
       float* pairs = EPI == 3 ? out2 : out;
       if (m < M) {
-        pairs[((size_t)ni * M + m) * 2 + 0] = best;
-        pairs[((size_t)ni * M + m) * 2 + 1] = __int_as_float(bi);
+        pairs[((size_t)ni * M_ld + m) * 2 + 0] = best;
+        pairs[((size_t)ni * M_ld + m) * 2 + 1] = __int_as_float(bi);
       }
     }
   }
@@ -525,20 +535,20 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const bf16_t* __restrict__ A,
                                                    const bf16_t* __restrict__ W, float* __restrict__ out, int M,
                                                    int N, int K, int splits, int m_tiles, int n_tiles, int a_ld,
                                                    float* __restrict__ out2, const int32_t* __restrict__ draw_pos,
-                                                   uint32_t seed) {
+                                                   uint32_t seed, const int32_t* __restrict__ m_live) {
   extern __shared__ __align__(16) unsigned char lds[];   // 2 buffers of MT*32 rows * A_ROW_BYTES
   gemm_bf16_body<MT, NB, D, TILED, 1, EPI>(lds, A, a_rows, W, out, M, N, K, splits, m_tiles, n_tiles, a_ld, out2,
-                                           draw_pos, seed);
+                                           draw_pos, seed, m_live);
 }
 
 template <int MT, int NB, int D, bool TILED, int EPI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gemm_bf16_big(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ a_rows, const bf16_t* __restrict__ W,
     float* __restrict__ out, int M, int N, int K, int splits, int m_tiles, int n_tiles, int a_ld,
-    float* __restrict__ out2) {
+    float* __restrict__ out2, const int32_t* __restrict__ m_live) {
   extern __shared__ __align__(16) unsigned char lds[];
   gemm_bf16_body<MT, NB, D, TILED, 1, EPI>(lds, A, a_rows, W, out, M, N, K, splits, m_tiles, n_tiles, a_ld, out2,
-                                           nullptr, 0u);
+                                           nullptr, 0u, m_live);
 }
 
 // Large tile with the LDS ring: one workgroup of eight waves per CU owns (almost) the whole LDS;
@@ -552,10 +562,10 @@ template <int MT, int NB, int EPI>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_bf16_ring(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ a_rows, const bf16_t* __restrict__ W,
     float* __restrict__ out, int M, int N, int K, int splits, int m_tiles, int n_tiles, int a_ld,
-    float* __restrict__ out2, const int32_t* __restrict__ draw_pos, uint32_t seed) {
+    float* __restrict__ out2, const int32_t* __restrict__ draw_pos, uint32_t seed, const int32_t* __restrict__ m_live) {
   extern __shared__ __align__(16) unsigned char lds[];
   gemm_bf16_body<MT, NB, 2, true, 1, EPI, RING_STAGES>(lds, A, a_rows, W, out, M, N, K, splits, m_tiles, n_tiles, a_ld,
-                                                      out2, draw_pos, seed);
+                                                      out2, draw_pos, seed, m_live);
 }
 
 // ---- fp32: one 32 x 32 tile per workgroup, its eight waves split K (v_mfma_f32_32x32x2_f32) --------
@@ -673,7 +683,7 @@ void launch_kernel(Kern kern, dim3 grid, dim3 block, size_t lds, hipStream_t st,
 template <int MT, int NB, bool TILED = true, int D = (MT * NB >= 8 ? 2 : 4), int EPI = 0>
 hipError_t launch_bf16(hipStream_t st, const void* A, const int32_t* a_rows, const void* W, float* out, int M,
                        int N, int K, const GemmPlan& p, int a_ld = 0, float* out2 = nullptr,
-                       const int32_t* draw_pos = nullptr, uint32_t seed = 0) {
+                       const int32_t* draw_pos = nullptr, uint32_t seed = 0, const int32_t* m_live = nullptr) {
   int total = p.m_tiles * p.n_tiles * p.splits;
   int per_xcd = (total + 7) / 8;
   size_t lds = 2 * (size_t)MT * 32 * A_ROW_BYTES;
@@ -683,13 +693,13 @@ hipError_t launch_bf16(hipStream_t st, const void* A, const int32_t* a_rows, con
     if (attr != hipSuccess) return attr;
     const size_t ring_bytes = ring_lds_bytes<MT, NB>();
     launch_kernel(kern, dim3(per_xcd * 8), dim3(512), ring_bytes, st, (const bf16_t*)A, a_rows, (const bf16_t*)W, out,
-                  M, N, K, p.splits, p.m_tiles, p.n_tiles, a_ld, out2, draw_pos, seed);
+                  M, N, K, p.splits, p.m_tiles, p.n_tiles, a_ld, out2, draw_pos, seed, m_live);
   } else if constexpr (MT * NB >= 8)
     launch_kernel(k_gemm_bf16_big<MT, NB, D, TILED, EPI>, dim3(per_xcd * 8), dim3(256), lds, st, (const bf16_t*)A,
-                  a_rows, (const bf16_t*)W, out, M, N, K, p.splits, p.m_tiles, p.n_tiles, a_ld, out2);
+                  a_rows, (const bf16_t*)W, out, M, N, K, p.splits, p.m_tiles, p.n_tiles, a_ld, out2, m_live);
   else
     launch_kernel(k_gemm_bf16<MT, NB, D, TILED, EPI>, dim3(per_xcd * 8), dim3(256), lds, st, (const bf16_t*)A, a_rows,
-                  (const bf16_t*)W, out, M, N, K, p.splits, p.m_tiles, p.n_tiles, a_ld, out2, draw_pos, seed);
+                  (const bf16_t*)W, out, M, N, K, p.splits, p.m_tiles, p.n_tiles, a_ld, out2, draw_pos, seed, m_live);
   return hipGetLastError();
 }
 
@@ -787,7 +797,7 @@ size_t gemm_argmax_scratch_floats(int M, int N) { return (size_t)((N + 127) / 12
 hipError_t launch_gemm_argmax(hipStream_t st, const void* A, const int32_t* a_rows, const void* W, int M, int N,
                               int K, float* scratch, int32_t* out, const int32_t* out_index, int a_ld,
                               float* logits_out, const int32_t* arg_rows, int n_arg, const int32_t* draw_pos,
-                              uint32_t seed) {
+                              uint32_t seed, const int32_t* m_live) {
   GemmPlan p = gemm_plan(ESP_BF16, M, N, K);
   hipError_t e = hipErrorInvalidValue;
   // without logits_out: pairs only (the logits are never written); with it: the fp32 logits of all M
@@ -795,15 +805,15 @@ hipError_t launch_gemm_argmax(hipStream_t st, const void* A, const int32_t* a_ro
 #define ESP_AMAX_CASE(MT_)                                                                                     \
   case MT_:                                                                                                    \
     e = logits_out ? launch_bf16<MT_, 1, true, 4, 3>(st, A, a_rows, W, logits_out, M, N, K, p, a_ld, scratch,  \
-                                                     draw_pos, seed)                                           \
+                                                     draw_pos, seed, m_live)                                   \
                    : launch_bf16<MT_, 1, true, 4, 1>(st, A, a_rows, W, scratch, M, N, K, p, a_ld, nullptr,     \
-                                                     draw_pos, seed);                                          \
+                                                     draw_pos, seed, m_live);                                          \
     break;
   if (p.nb == 2) {   // many rows: large tiles, pairs only
     if (logits_out) return hipErrorInvalidValue;
-    if (p.mt == 3) e = launch_bf16<3, 2, true, 4, 1>(st, A, a_rows, W, scratch, M, N, K, p, a_ld, nullptr, draw_pos, seed);
-    else if (p.mt == 4) e = launch_bf16<4, 2, true, 2, 1>(st, A, a_rows, W, scratch, M, N, K, p, a_ld, nullptr, draw_pos, seed);
-    else if (p.mt == 5) e = launch_bf16<5, 2, true, 2, 1>(st, A, a_rows, W, scratch, M, N, K, p, a_ld, nullptr, draw_pos, seed);
+    if (p.mt == 3) e = launch_bf16<3, 2, true, 4, 1>(st, A, a_rows, W, scratch, M, N, K, p, a_ld, nullptr, draw_pos, seed, m_live);
+    else if (p.mt == 4) e = launch_bf16<4, 2, true, 2, 1>(st, A, a_rows, W, scratch, M, N, K, p, a_ld, nullptr, draw_pos, seed, m_live);
+    else if (p.mt == 5) e = launch_bf16<5, 2, true, 2, 1>(st, A, a_rows, W, scratch, M, N, K, p, a_ld, nullptr, draw_pos, seed, m_live);
   } else {
     switch (p.mt) {
       ESP_AMAX_CASE(1)
@@ -821,14 +831,16 @@ hipError_t launch_gemm_argmax(hipStream_t st, const void* A, const int32_t* a_ro
 
 // Fused gate/up projection + SwiGLU (bf16, packed weights whose rows alternate in blocks of 32
 // between gate and up): act[M][ff] = silu(A Wg^T) * (A Wu^T), one pass over K per workgroup.
-hipError_t launch_gemm_swiglu(hipStream_t st, const void* A, const void* W, void* act, int M, int ff, int K) {
+hipError_t launch_gemm_swiglu(hipStream_t st, const void* A, const void* W, void* act, int M, int ff, int K,
+                              const int32_t* m_live) {
   if (M <= 0) return hipSuccess;
   GemmPlan p = gemm_plan(ESP_BF16, M, 2 * ff, K);
   p.splits = 1;
   float* out = reinterpret_cast<float*>(act);
 #define ESP_GU_CASE(MT_, NB_)                                                                           \
   if (p.mt == MT_ && p.nb == NB_)                                                                       \
-    return launch_bf16<MT_, NB_, true, (MT_ * NB_ >= 8 ? 2 : 4), 2>(st, A, nullptr, W, out, M, 2 * ff, K, p);
+    return launch_bf16<MT_, NB_, true, (MT_ * NB_ >= 8 ? 2 : 4), 2>(st, A, nullptr, W, out, M, 2 * ff, K, p, 0, nullptr, \
+                                                                    nullptr, 0u, m_live);
   ESP_GU_CASE(1, 1)
   ESP_GU_CASE(2, 1)
   ESP_GU_CASE(3, 1)
@@ -848,7 +860,7 @@ hipError_t launch_pack_weight(hipStream_t st, const void* src, void* dst, int N,
 }
 
 hipError_t launch_gemm(hipStream_t st, int dtype, const void* A, const int32_t* a_rows, const void* W,
-                       float* out, int M, int N, int K, const GemmPlan& p, bool w_packed, int a_ld) {
+                       float* out, int M, int N, int K, const GemmPlan& p, bool w_packed, int a_ld, const int32_t* m_live) {
   if (M <= 0) return hipSuccess;
   if (dtype == ESP_F32) {
     const bool vec = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0;
@@ -858,8 +870,8 @@ hipError_t launch_gemm(hipStream_t st, int dtype, const void* A, const int32_t* 
   }
 #define ESP_GEMM_CASE(MT_, NB_)                                                                  \
   if (p.mt == MT_ && p.nb == NB_)                                                                \
-    return w_packed ? launch_bf16<MT_, NB_, true>(st, A, a_rows, W, out, M, N, K, p, a_ld)       \
-                    : launch_bf16<MT_, NB_, false>(st, A, a_rows, W, out, M, N, K, p, a_ld);
+    return w_packed ? launch_bf16<MT_, NB_, true>(st, A, a_rows, W, out, M, N, K, p, a_ld, nullptr, nullptr, 0u, m_live) \
+                    : launch_bf16<MT_, NB_, false>(st, A, a_rows, W, out, M, N, K, p, a_ld, nullptr, nullptr, 0u, m_live);
   ESP_GEMM_CASE(1, 1)
   ESP_GEMM_CASE(2, 1)
   ESP_GEMM_CASE(3, 1)

@@ -112,13 +112,16 @@ GemmPlan gemm_plan(int dtype, int M, int N, int K);
 inline size_t gemm_out_elems(const GemmPlan& p, int M, int N) { return (size_t)p.splits * M * N; }
 // out: fp32 [splits][M][N].  a_rows (device, may be null): physical row of A for logical row m.
 // w_packed: W is in the streaming layout written by launch_pack_weight (bf16 only).
+// m_live (device, may be null; bf16 only): how many of the M rows there are; the others are neither computed nor written.
 hipError_t launch_gemm(hipStream_t st, int dtype, const void* A, const int32_t* a_rows, const void* W,
-                       float* out, int M, int N, int K, const GemmPlan& p, bool w_packed, int a_ld = 0);
+                       float* out, int M, int N, int K, const GemmPlan& p, bool w_packed, int a_ld = 0,
+                       const int32_t* m_live = nullptr);
 // a_ld == 0: A is row-major [rows][K]; a_ld > 0 (bf16 only): A is chunk-major [K/64][a_ld][64]
 hipError_t launch_pack_weight(hipStream_t st, const void* src, void* dst, int N, int K);
 // one-time kernel attributes of the GEMM kernels (dynamic LDS limits); call before the first launch
 hipError_t gemm_prepare();
-hipError_t launch_gemm_swiglu(hipStream_t st, const void* A, const void* W, void* act, int M, int ff, int K);
+hipError_t launch_gemm_swiglu(hipStream_t st, const void* A, const void* W, void* act, int M, int ff, int K,
+                              const int32_t* m_live = nullptr);
 // LM head with the arg-max taken in the GEMM epilogue (bf16, packed weights, <= 128 rows, one split)
 bool gemm_argmax_supported(int dtype, int M, int N, int K, bool with_logits);
 size_t gemm_argmax_scratch_floats(int M, int N);
@@ -127,14 +130,24 @@ size_t gemm_argmax_scratch_floats(int M, int N);
 hipError_t launch_gemm_argmax(hipStream_t st, const void* A, const int32_t* a_rows, const void* W, int M, int N,
                               int K, float* scratch, int32_t* out, const int32_t* out_index, int a_ld,
                               float* logits_out, const int32_t* arg_rows, int n_arg,
-                              const int32_t* draw_pos = nullptr, uint32_t seed = 0);   // draw_pos: per GEMM row
+                              const int32_t* draw_pos = nullptr, uint32_t seed = 0,   // draw_pos: per GEMM row
+                              const int32_t* m_live = nullptr);
 
 // ---- elementwise / glue (esp_elementwise.hip) ----------------------------------------------
 struct BlockDev {   // device-side view of esp_block + esp_kv scalars, passed by value
   int batch, rows_per_seq, k_masks, layout, anc_words;
   const int32_t *n_rows, *n_nodes, *tok, *parent, *depth, *mask_j, *attach;
   const uint64_t* anc;
+  // Live rows of a ragged batch packed together (all null: row m of the activations is block row m).
+  // live_rows[m]: block row of packed row m; packed_row[block row]: its packed row, -1 for a row that is not
+  // there; seq_row0[seq]: first packed row of a sequence; n_live[0] rows, n_live[1] tree rows; seq_node0: n_live's
+  // second count up to a sequence.
+  const int32_t *live_rows = nullptr, *packed_row = nullptr, *seq_row0 = nullptr, *seq_node0 = nullptr, *n_live = nullptr;
 };
+// where row r of a sequence sits in the activations
+__device__ __forceinline__ size_t act_row(const BlockDev& b, int seq, int r) {
+  return b.seq_row0 ? (size_t)b.seq_row0[seq] + r : (size_t)seq * b.rows_per_seq + r;
+}
 struct KvDev {
   void *k, *v;
   int32_t* len;
@@ -143,11 +156,17 @@ struct KvDev {
   int len_bound;
 };
 
+// fills the arrays of a BlockDev's packed rows (one int per block row in live_rows and packed_row, one per sequence
+// in seq_row0 and seq_node0, two in n_live) from the row counts, which only the device knows
+hipError_t launch_live_rows(hipStream_t st, const BlockDev& b, const KvDev& kv, int max_nodes, int32_t* live_rows, int32_t* packed_row,
+                            int32_t* seq_row0, int32_t* seq_node0, int32_t* n_live);
 hipError_t launch_embed(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, const void* embed,
                         const void* mask_embed, float* h, int d, int vocab, float* rope_tab, int hd,
                         float theta, int32_t* status, size_t mask_seq_stride);
+// n_live (nullable): rows there are.  packed_row (nullable): row m of xn_out comes from row packed_row[m], or is zero
 hipError_t launch_residual_norm(hipStream_t st, int dtype, float* h, const float* part, int splits, int M,
-                                int d, const void* gain, float eps, void* xn_out);
+                                int d, const void* gain, float eps, void* xn_out, const int32_t* n_live = nullptr,
+                                const int32_t* packed_row = nullptr);
 hipError_t launch_qkv_post(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, int layer,
                            const float* part, int splits, int M, int hq, int hkv, int hd, int qk_norm,
                            const void* qg, const void* kg, float eps, const float* rope_tab, void* q_out);
@@ -247,6 +266,7 @@ struct esp_ctx {
   float* topk_scratch;
   int32_t* idx_a;    // [Mmax] gather rows
   int32_t* idx_b;    // [Mmax]
+  int32_t *live_rows, *packed_row, *seq_row0, *seq_node0, *n_live;   // packed rows of a ragged batch (BlockDev)
   int32_t* status;   // device status word
   size_t gemm_out_floats, attn_part_floats, logits_rows;
   // optional launch-site timing with HIP events (esp_profile_enable / esp_profile_read)

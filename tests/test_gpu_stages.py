@@ -745,6 +745,54 @@ def test_qkv_epilogue_forms(B, dtype, head_dim, d_model, hq, hkv, qk_norm):
     eng.close()
 
 
+# ---------------------------------------------------------------------------- packed rows of a batch
+@pytest.mark.parametrize("head_dim,counts,sample", [(128, [14, 1, 5], False), (128, [1, 14, 3, 14, 9, 2], True), (64, [2, 14, 8, 1], True),
+                                                    (128, [1, 1, 1, 1], False)])
+def test_packed_rows_of_a_ragged_batch(B, head_dim, counts, sample):
+    """Above 128 block rows a batch's live rows go through the layers packed together.  A row's sums do not depend on
+    the rows beside it (one split-K part and one key split at these sizes), so every sequence comes out bit for bit as
+    it does alone, with its rows where they were; rows that are not there are zero, also in the K/V cache."""
+    shape = small_shape(d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=head_dim, d_ff=384, vocab=1024, n_layers=2, qk_norm=True,
+                        dtype="bf16")
+    w = synth.make_weights(shape, seed=9, unit_gains=False)
+    k, layout, batch = 3, 0, len(counts)
+    rows = 14 * (k + 1)
+    lens = [(37 * b + 5) % 61 for b in range(batch)]
+    print(f"packed rows hd={head_dim} counts={counts} sample={sample}", flush=True)
+    masks = synth.normal_like((batch, k, 256), 0.02, 91, 0, "cuda", torch.bfloat16)
+
+    def forward(which):
+        n = len(which)
+        eng = B.Engine(shape, w, n, rows, 256)
+        eng.set_sampling(sample, 5)
+        blk = B.BlockBuffers(n, rows, k, layout)
+        trees = [synth.make_random_tree(counts[b], 4, shape.vocab, seed=70 + b) for b in which]
+        blk.upload_trees([t.tolist() for t, _ in trees], [p.tolist() for _, p in trees])
+        eng.block_from_tree(blk)
+        kv = B.KvCache(shape, [128] * n)
+        for i, b in enumerate(which):
+            if lens[b]:
+                for layer in range(2):
+                    kf, vf = (synth.normal_like((lens[b], 2, head_dim), 1.0, 92 + b, 2 * layer + j, "cuda", torch.bfloat16) for j in (0, 1))
+                    eng.kv_store(kv, layer, i, 0, kf, vf)
+        kv.set_len([lens[b] for b in which])
+        hidden = torch.full((n * rows, 256), 7.0, dtype=torch.bfloat16, device="cuda")
+        nxt = torch.full((n * rows,), -7, dtype=torch.int32, device="cuda")
+        eng.tree_forward(blk, masks[which].contiguous() if n > 1 else masks[which[0]], kv, hidden, nxt)
+        assert eng.device_status() == 0
+        planes = [torch.stack([torch.stack(eng.kv_load(kv, layer, i, 0, 128)) for layer in range(2)]) for i in range(n)]
+        eng.close()
+        return hidden.reshape(n, rows, 256), nxt.reshape(n, rows), planes
+
+    hidden, nxt, planes = forward(list(range(batch)))
+    for b in range(batch):
+        h1, n1, p1 = forward([b])
+        live = counts[b] * (k + 1)
+        assert torch.equal(hidden[b, :live], h1[0, :live]) and bool((hidden[b, live:] == 0).all()), b
+        assert torch.equal(nxt[b], n1[0]), b
+        assert torch.equal(planes[b], p1[0]) and bool((planes[b][:, :, lens[b] + live:] == 0).all()), b
+
+
 # ---------------------------------------------------------------------------------------- attention
 def run_attention_case(B, shape, eng, n_nodes, k, layout, cache_lens, seed):
     batch = len(cache_lens)
