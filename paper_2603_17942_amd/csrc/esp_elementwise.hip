@@ -492,24 +492,62 @@ hipError_t launch_kv_copy(hipStream_t st, int dtype, const KvDev& kv, int layer,
 }
 
 // ---- mask vectors (Sec. 3.1 Eq. 4 and Eq. 5) -----------------------------------------------------------
-template <typename T>
-__global__ void k_mask_mean(const T* __restrict__ embed, const int32_t* __restrict__ tokens, int n, int k, int d,
-                            int vocab, T* __restrict__ mask_embed) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= d) return;
-  float acc = 0.f;
-  for (int t = 0; t < n; ++t) {
-    int id = tokens[t];
-    if (id >= 0 && id < vocab) acc += to_f32(embed[(size_t)id * d + i]);
+// Mean of the prompt's token embeddings.  A workgroup owns 64 features: 16 lanes of four features side by side (a
+// 128-byte line of a bf16 row) times 64 groups of tokens, each with eight rows in flight, added up through LDS in group
+// order.  The time is that of the gather: 2049 tokens of d = 4096 took 896 us with a thread per feature walking all tokens.
+// VEC: rows start at a multiple of the four features' size.
+constexpr int MEAN_GROUPS = 64, MEAN_U = 8;
+template <typename T, bool VEC>
+__global__ __launch_bounds__(1024) void k_mask_mean(const T* __restrict__ embed, const int32_t* __restrict__ tokens, int n, int k,
+                                                    int d, int vocab, T* __restrict__ mask_embed) {
+  __shared__ f32x4_t part[MEAN_GROUPS][16];
+  const int lane = threadIdx.x & 15, grp = threadIdx.x >> 4;
+  const int i = blockIdx.x * 64 + lane * 4;          // d is a multiple of 4
+  const bool in = i < d;
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  for (int t0 = grp; t0 < n; t0 += MEAN_GROUPS * MEAN_U) {
+    int id[MEAN_U];
+#pragma unroll
+    for (int u = 0; u < MEAN_U; ++u) {
+      const int t = t0 + u * MEAN_GROUPS;
+      id[u] = t < n ? tokens[t] : -1;
+    }
+    f32x4_t x[MEAN_U];
+#pragma unroll
+    for (int u = 0; u < MEAN_U; ++u) {
+      x[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      if (in && id[u] >= 0 && id[u] < vocab) {
+        const T* row = embed + (size_t)id[u] * d + i;
+        if constexpr (VEC) {
+          x[u] = Pack4<T>::load(row);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[u][e] = to_f32(row[e]);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < MEAN_U; ++u) acc += x[u];
   }
-  T v = from_f32<T>(acc / (float)n);
-  for (int j = 0; j < k; ++j) mask_embed[(size_t)j * d + i] = v;
+  part[grp][lane] = acc;
+  __syncthreads();
+  if (grp != 0 || !in) return;
+  f32x4_t sum = part[0][lane];
+  for (int g = 1; g < MEAN_GROUPS; ++g) sum += part[g][lane];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const T v = from_f32<T>(sum[e] / (float)n);
+    for (int j = 0; j < k; ++j) mask_embed[(size_t)j * d + i + e] = v;
+  }
 }
 
 hipError_t launch_mask_mean(hipStream_t st, int dtype, const void* embed, const int32_t* tokens, int n, int k,
                             int d, int vocab, void* mask_embed) {
-  ESP_DISPATCH(dtype, hipLaunchKernelGGL(k_mask_mean<T>, dim3((d + 255) / 256), dim3(256), 0, st, (const T*)embed,
-                                         tokens, n, k, d, vocab, (T*)mask_embed));
+  ESP_DISPATCH(dtype, {
+    const bool vec = (uintptr_t)embed % (4 * sizeof(T)) == 0;
+    hipLaunchKernelGGL((vec ? k_mask_mean<T, true> : k_mask_mean<T, false>), dim3((d + 63) / 64), dim3(1024), 0, st,
+                       (const T*)embed, tokens, n, k, d, vocab, (T*)mask_embed);
+  });
   return hipGetLastError();
 }
 

@@ -886,6 +886,31 @@ def test_attn_tree_bf16_other_head_groupings(B, hq, hkv, n_nodes, k, layout, cac
     assert err < 2e-2
 
 
+@pytest.mark.parametrize("which,offset", [("tiny", 0), ("tiny", 1), ("bf16", 0), ("bf16", 1)])
+def test_mask_mean(B, which, offset):
+    """Eq. 4 at prompt lengths around the 64 token groups of eight rows, with d not a multiple of a workgroup's 64
+    features, ids outside the vocabulary (they add nothing), and a table that starts off a vector's alignment.  fp32 sums
+    of values below 5 sigma: n 2^-24 relative to the largest partial sum at most, far below the tolerances."""
+    dt = torch.float32 if which == "tiny" else torch.bfloat16
+    shape = small_shape(d_model=192 + 4 if which == "tiny" else 320, head_dim=64, d_ff=128,
+                        dtype="f32" if which == "tiny" else "bf16", vocab=512)
+    w = synth.make_weights(shape, seed=6, device="cuda")
+    store = torch.zeros(shape.vocab * shape.d_model + offset, dtype=dt, device="cuda")
+    w["embed"] = store[offset:].view(shape.vocab, shape.d_model).copy_(w["embed"].to("cuda"))
+    eng = B.Engine(shape, w, 1, 8, 64)
+    table = to_np(w["embed"])
+    for n in (1, 2, 63, 64, 65, 511, 512, 513, 1500):
+        tok = synth.uniform_ints(n, 2 * shape.vocab, 8, n).to("cuda", torch.int32) - shape.vocab // 2
+        out = torch.full((3, shape.d_model), 9.0, dtype=dt, device="cuda")
+        eng.mask_mean(tok, 3, out)
+        ids = tok.cpu().numpy()
+        want = table[ids[(ids >= 0) & (ids < shape.vocab)]].sum(0) / n
+        got = to_np(out)
+        assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+        assert np.max(np.abs(got[0] - want)) <= (1e-6 if which == "tiny" else 2.0 ** -8) * max(np.max(np.abs(want)), 1e-30), n
+    eng.close()
+
+
 @pytest.mark.parametrize("which", ["tiny", "bf16"])
 def test_mask_last_k_and_gaussian_inits(B, tiny_engine, bf16_engine, which):
     """Sec. 4 mask-design variants a (last k prompt tokens) and b (Gaussian fit of the embedding
