@@ -73,7 +73,7 @@ WsLayout ws_layout(const esp_model_desc* m, int max_batch, int max_rows, int64_t
   w.idx_b = take(std::max<size_t>(M, (size_t)max_batch * ESP_MAX_MASKS) * 4);
   w.idx_c = take(std::max<size_t>(M, (size_t)max_batch * ESP_MAX_MASKS) * 4);
   w.idx_d = take(std::max<size_t>(M, (size_t)max_batch * ESP_MAX_MASKS) * 4);
-  w.live = take((2 * M + 2 * (size_t)max_batch + 2) * 4);   // live_rows, packed_row, seq_row0, seq_node0, n_live
+  w.live = take(BlockDev::packed_ints(M, max_batch) * 4);
   w.status = take(256);
   w.total = off;
   return w;
@@ -241,11 +241,7 @@ esp_status esp_create(const esp_model_desc* m, const esp_weights* w, int32_t max
   c->topk_scratch = (float*)(c->ws + L.topk_scratch);
   c->idx_a = (int32_t*)(c->ws + L.idx_a); c->idx_b = (int32_t*)(c->ws + L.idx_b);
   c->idx_c = (int32_t*)(c->ws + L.idx_c); c->idx_d = (int32_t*)(c->ws + L.idx_d);
-  c->live_rows = (int32_t*)(c->ws + L.live);
-  c->packed_row = c->live_rows + (size_t)max_batch * max_rows;
-  c->seq_row0 = c->packed_row + (size_t)max_batch * max_rows;
-  c->seq_node0 = c->seq_row0 + max_batch;
-  c->n_live = c->seq_node0 + max_batch;
+  c->packed = (int32_t*)(c->ws + L.live);
   c->status = (int32_t*)(c->ws + L.status);
   c->gemm_out_floats = L.gemm_out_floats; c->attn_part_floats = L.attn_part_floats; c->logits_rows = L.logits_rows;
   if (hipMemsetAsync(c->status, 0, 256, c->stream) != hipSuccess) {
@@ -358,10 +354,9 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
   const int32_t* m_live = nullptr;
   { ESP_PROF(ESP_SITE_GLUE);
   if (packed) {
-    ESP_HIP(launch_live_rows(s, bd, kd, nodes_bound(blk), c->live_rows, c->packed_row, c->seq_row0, c->seq_node0, c->n_live));
-    bd.live_rows = c->live_rows; bd.packed_row = c->packed_row; bd.seq_row0 = c->seq_row0;
-    bd.seq_node0 = c->seq_node0; bd.n_live = c->n_live;
-    m_live = c->n_live;
+    bd.packed = c->packed;
+    ESP_HIP(launch_live_rows(s, bd, kd, nodes_bound(blk)));
+    m_live = bd.n_live();
   }
   ESP_HIP(launch_embed(s, dt, bd, kd, c->embed, mask_embed, c->h, d, m.vocab, c->rope_tab, hd, m.rope_theta,
                        c->status, c->mask_per_seq ? (size_t)blk->k_masks * d : 0));
@@ -395,7 +390,7 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
     { ESP_PROF(ESP_SITE_GLUE);
       ESP_HIP(launch_residual_norm(s, dt, c->h, c->gemm_out, p_dn.splits, M, d,
                                    last ? c->final_norm : c->norm_attn[l + 1], m.rms_eps, last ? hidden_out : c->xn, last ? nullptr : m_live,
-                                   last ? bd.packed_row : nullptr)); }
+                                   last && packed ? bd.packed_row() : nullptr)); }
   }
   // LM head + argmax at the tree rows (Sec. 2 Eq. 3 needs the base model's own next token there)
   if (logits_dbg) {
@@ -437,7 +432,7 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
       // arg-max in the GEMM epilogue: the [rows, vocab] logits are never written
       ESP_PROF(ESP_SITE_LM_HEAD);
       ESP_HIP(launch_gemm_argmax(s, hidden_out, c->idx_a, c->lm_head, Mn, m.vocab, d, c->logits, node_argmax,
-                                 c->idx_b, 0, nullptr, nullptr, Mn, draw_list, c->sample_seed, packed ? c->n_live + 1 : nullptr));
+                                 c->idx_b, 0, nullptr, nullptr, Mn, draw_list, c->sample_seed, packed ? m_live + 1 : nullptr));
     } else {
       { ESP_PROF(ESP_SITE_LM_HEAD);
         ESP_HIP(launch_gemm(s, dt, hidden_out, c->idx_a, c->lm_head, c->logits, Mn, m.vocab, d, p_lm, pk)); }

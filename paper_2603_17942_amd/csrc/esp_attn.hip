@@ -30,7 +30,7 @@ __device__ __forceinline__ bool seq_ok(const KvDev& kv, int seq, int n_rows, int
 }
 
 // --------------------------------------------------------------------------------------------------
-template <typename T, int HD>
+template <typename T, int HD, bool PACKED>
 __global__ __launch_bounds__(64) void k_attn_generic(BlockDev b, KvDev kv, int layer, int hq, int hkv,
                                                      const T* __restrict__ q, float* __restrict__ part_o,
                                                      float* __restrict__ part_ml, int nsplit, int tps) {
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(64) void k_attn_generic(BlockDev b, KvDev kv, int l
   const T* vp = (const T*)kv.v + kv_plane(layer, kvh, hkv, kv.capacity, HD);
   const int64_t base = kv.base[seq];
   const float scale = LOG2E / sqrtf((float)HD);
-  for (int d = lane; d < HD; d += 64) qs[d] = to_f32(q[(act_row(b, seq, r) * hq + h) * HD + d]) * scale;
+  for (int d = lane; d < HD; d += 64) qs[d] = to_f32(q[(act_row<PACKED>(b, seq, r) * hq + h) * HD + d]) * scale;
   __syncthreads();
   const uint64_t* anc = b.anc + (size_t)row * b.anc_words;
   float m = NEG_BIG, l = 0.f;
@@ -257,7 +257,7 @@ __device__ __forceinline__ void ring_unit(bool masked, const unsigned char* kst,
 }
 
 // LPW: 1 KB wave-loads per loading wave and tile (the first 32 / LPW waves of the workgroup load)
-template <int LPW>
+template <int LPW, bool PACKED>
 __global__ __launch_bounds__(64 * RING_MAX_WAVES) void k_attn_ring(BlockDev b, KvDev kv, int layer, int hq, int hkv,
                                                                   const bf16_t* __restrict__ q,
                                                                   float* __restrict__ part_o,
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(64 * RING_MAX_WAVES) void k_attn_ring(BlockDev b, K
   issue_tile(0);
   bf16x8_t qf[8];
   {
-    const bf16_t* qp = q + (act_row(b, seq, r) * hq + h) * HD + 8 * lg;
+    const bf16_t* qp = q + (act_row<PACKED>(b, seq, r) * hq + h) * HD + 8 * lg;
 #pragma unroll
     for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8_t*>(qp + 16 * s);
     asm volatile("" : "+v"(qf[0]), "+v"(qf[1]), "+v"(qf[2]), "+v"(qf[3]), "+v"(qf[4]), "+v"(qf[5]), "+v"(qf[6]), "+v"(qf[7])
@@ -439,7 +439,7 @@ __device__ __forceinline__ void store4(bf16_t* dst, f32x4_t v) {
 
 // Merge of the per-split partials, in split order.  hd/4 threads per (row, head) item, four
 // features each; a 256-thread workgroup takes 256/(hd/4) items.
-template <typename T>
+template <typename T, bool PACKED>
 __global__ __launch_bounds__(256) void k_attn_merge(BlockDev b, KvDev kv, int hq, int hd,
                                                     const float* __restrict__ part_o,
                                                     const float* __restrict__ part_ml, int nsplit,
@@ -453,10 +453,10 @@ __global__ __launch_bounds__(256) void k_attn_merge(BlockDev b, KvDev kv, int hq
   const int nr = b.n_rows[seq];
   f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
   if (!seq_ok(kv, seq, nr, b.rows_per_seq) || r >= nr) {
-    if (!b.seq_row0) store4(out + (size_t)item * hd + d, acc);
+    if (!PACKED) store4(out + (size_t)item * hd + d, acc);
     return;
   }
-  T* dst = out + (act_row(b, seq, r) * hq + item % hq) * hd + d;
+  T* dst = out + (act_row<PACKED>(b, seq, r) * hq + item % hq) * hd + d;
   const size_t item0 = (size_t)item * nsplit;
   float mx = NEG_BIG;
   for (int s = 0; s < nsplit; ++s) mx = fmaxf(mx, part_ml[(item0 + s) * 2]);
@@ -477,7 +477,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(BlockDev b, KvDev kv, int hq
 // fetches the (m, l) of every eighth split at once -- one after the other, a column's splits would
 // cost a memory latency each -- and the eight groups combine through LDS.  Then thread (column,
 // feature quad) sums the splits' O, every load instruction of a wave covering whole 128-byte lines.
-template <int MAXS>
+template <int MAXS, bool PACKED>
 __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, int hq, int hkv,
                                                          const float* __restrict__ part_o,
                                                          const float* __restrict__ part_ml, int nsplit,
@@ -495,7 +495,7 @@ __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, i
   const int col = threadIdx.x & 31, grp = threadIdx.x >> 5;
   const int c = ct * 32 + col;                      // column within the kv group
   const bool live = ok && c < nr * G;
-  const bool in_block = b.seq_row0 ? live : c < b.rows_per_seq * G;     // has an output row at all
+  const bool in_block = PACKED ? live : c < b.rows_per_seq * G;     // has an output row at all
   const size_t t0 = (size_t)tile * nsplit;
   float ms[PER], ls[PER];
   float mx = NEG_BIG;
@@ -543,7 +543,7 @@ __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, i
     acc *= inv;
   }
   const int r = c / G, h = kvh * G + c % G;
-  store4(out + (act_row(b, seq, r) * hq + h) * HD + f0, acc);
+  store4(out + (act_row<PACKED>(b, seq, r) * hq + h) * HD + f0, acc);
 }
 
 }  // namespace
@@ -552,11 +552,12 @@ __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, i
 // called when a context is created, so that no launch inside a stream capture is the first one)
 hipError_t attn_prepare() {
   static const hipError_t attr = [] {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_ring<4>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, RING_LDS_BYTES);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_ring<8>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               RING_LDS_BYTES);
+    for (const void* k : {reinterpret_cast<const void*>(k_attn_ring<4, false>), reinterpret_cast<const void*>(k_attn_ring<8, false>),
+                          reinterpret_cast<const void*>(k_attn_ring<4, true>), reinterpret_cast<const void*>(k_attn_ring<8, true>)}) {
+      const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, RING_LDS_BYTES);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   }();
   return attr;
 }
@@ -618,6 +619,7 @@ size_t attn_partial_floats(int dtype, int batch, int rows_per_seq, int hq, int h
 hipError_t launch_attn(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, int layer, int hq, int hkv,
                        int hd, const void* q, float* partials, const AttnPlan& p) {
   const int M = b.batch * b.rows_per_seq;
+  const bool packed = b.packed != nullptr;
   float* part_o = partials;
   float* part_ml = partials + (size_t)M * hq * p.nsplit * hd;
   if (dtype == ESP_BF16 && hd == 128) {
@@ -627,23 +629,21 @@ hipError_t launch_attn(hipStream_t st, int dtype, const BlockDev& b, const KvDev
     const hipError_t attr = attn_prepare();
     if (attr != hipSuccess) return attr;
     const dim3 grid(((total_wg + 7) / 8) * 8), block(64 * g.waves);
-    if (g.waves >= 8)
-      hipLaunchKernelGGL(k_attn_ring<4>, grid, block, RING_LDS_BYTES, st, b, kv, layer, hq, hkv, (const bf16_t*)q, part_o,
-                         part_ml, p.nsplit, p.tiles_per_split, g.q_tiles, g.ct_wg, g.n_full);
-    else
-      hipLaunchKernelGGL(k_attn_ring<8>, grid, block, RING_LDS_BYTES, st, b, kv, layer, hq, hkv, (const bf16_t*)q, part_o,
-                         part_ml, p.nsplit, p.tiles_per_split, g.q_tiles, g.ct_wg, g.n_full);
+    const auto kern = g.waves >= 8 ? (packed ? k_attn_ring<4, true> : k_attn_ring<4, false>)
+                                   : (packed ? k_attn_ring<8, true> : k_attn_ring<8, false>);
+    hipLaunchKernelGGL(kern, grid, block, RING_LDS_BYTES, st, b, kv, layer, hq, hkv, (const bf16_t*)q, part_o, part_ml, p.nsplit,
+                       p.tiles_per_split, g.q_tiles, g.ct_wg, g.n_full);
   } else {
-    dim3 grid(M, hq, p.nsplit);
-    if (dtype == ESP_F32 && hd == 64)
-      hipLaunchKernelGGL((k_attn_generic<float, 64>), grid, dim3(64), 0, st, b, kv, layer, hq, hkv, (const float*)q,
+    const dim3 grid(M, hq, p.nsplit);
+    if (dtype == ESP_F32 && hd == 64)         // fp32 batches are not packed
+      hipLaunchKernelGGL((k_attn_generic<float, 64, false>), grid, dim3(64), 0, st, b, kv, layer, hq, hkv, (const float*)q,
                          part_o, part_ml, p.nsplit, p.tiles_per_split);
     else if (dtype == ESP_F32 && hd == 128)
-      hipLaunchKernelGGL((k_attn_generic<float, 128>), grid, dim3(64), 0, st, b, kv, layer, hq, hkv,
+      hipLaunchKernelGGL((k_attn_generic<float, 128, false>), grid, dim3(64), 0, st, b, kv, layer, hq, hkv,
                          (const float*)q, part_o, part_ml, p.nsplit, p.tiles_per_split);
     else if (dtype == ESP_BF16 && hd == 64)
-      hipLaunchKernelGGL((k_attn_generic<bf16_t, 64>), grid, dim3(64), 0, st, b, kv, layer, hq, hkv,
-                         (const bf16_t*)q, part_o, part_ml, p.nsplit, p.tiles_per_split);
+      hipLaunchKernelGGL((packed ? k_attn_generic<bf16_t, 64, true> : k_attn_generic<bf16_t, 64, false>), grid, dim3(64), 0, st, b,
+                         kv, layer, hq, hkv, (const bf16_t*)q, part_o, part_ml, p.nsplit, p.tiles_per_split);
     else
       return hipErrorInvalidValue;
   }
@@ -652,17 +652,16 @@ hipError_t launch_attn(hipStream_t st, int dtype, const BlockDev& b, const KvDev
 
 hipError_t launch_attn_merge(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, int hq, int hkv, int hd,
                              const float* partials, const AttnPlan& p, void* out) {
+  const bool packed = b.packed != nullptr;
   if (dtype == ESP_BF16 && hd == 128) {
     const RingGeometry g = ring_geometry(b.rows_per_seq * (hq / hkv));
     const int n_ct = g.q_tiles * g.ct_wg;
     const float* part_o = partials;
     const float* part_ml = partials + (size_t)b.batch * hkv * n_ct * p.nsplit * (32 * hd);
     const dim3 grid(b.batch * hkv * n_ct * 4);
-    if (p.nsplit <= 64)
-      hipLaunchKernelGGL(k_attn_merge_ring<64>, grid, dim3(256), 0, st, b, kv, hq, hkv, part_o, part_ml, p.nsplit, n_ct,
-                         (bf16_t*)out);
-    else
-      return hipErrorInvalidValue;
+    if (p.nsplit > 64) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((packed ? k_attn_merge_ring<64, true> : k_attn_merge_ring<64, false>), grid, dim3(256), 0, st, b, kv, hq, hkv,
+                       part_o, part_ml, p.nsplit, n_ct, (bf16_t*)out);
     return hipGetLastError();
   }
   const int M = b.batch * b.rows_per_seq;
@@ -671,10 +670,10 @@ hipError_t launch_attn_merge(hipStream_t st, int dtype, const BlockDev& b, const
   const int n_items = M * hq, per_wg = 256 / (hd / 4);
   const dim3 grid((n_items + per_wg - 1) / per_wg);
   if (dtype == ESP_F32)
-    hipLaunchKernelGGL(k_attn_merge<float>, grid, dim3(256), 0, st, b, kv, hq, hd, part_o, part_ml, p.nsplit,
+    hipLaunchKernelGGL((k_attn_merge<float, false>), grid, dim3(256), 0, st, b, kv, hq, hd, part_o, part_ml, p.nsplit,
                        (float*)out, n_items);
   else
-    hipLaunchKernelGGL(k_attn_merge<bf16_t>, grid, dim3(256), 0, st, b, kv, hq, hd, part_o, part_ml, p.nsplit,
+    hipLaunchKernelGGL((packed ? k_attn_merge<bf16_t, true> : k_attn_merge<bf16_t, false>), grid, dim3(256), 0, st, b, kv, hq, hd, part_o, part_ml, p.nsplit,
                        (bf16_t*)out, n_items);
   return hipGetLastError();
 }

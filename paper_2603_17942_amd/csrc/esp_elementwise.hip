@@ -37,9 +37,7 @@ __device__ __forceinline__ float block_sum_256(float v, float* red) {
 // Packed rows of a batch (BlockDev): one workgroup per sequence adds up the row counts of the sequences before it
 // and writes its own rows' places.  A sequence that is not valid (or a count that does not fit) has no rows; its tree
 // rows follow the block alone, as in k_node_rows.
-__global__ __launch_bounds__(256) void k_live_rows(BlockDev b, KvDev kv, int max_nodes, int32_t* live_rows,
-                                                   int32_t* packed_row, int32_t* seq_row0, int32_t* seq_node0,
-                                                   int32_t* n_live) {
+__global__ __launch_bounds__(256) void k_live_rows(BlockDev b, KvDev kv, int max_nodes) {
   __shared__ float red[4];
   const int seq = blockIdx.x;
   auto rows_of = [&](int s) {
@@ -59,27 +57,25 @@ __global__ __launch_bounds__(256) void k_live_rows(BlockDev b, KvDev kv, int max
   const int nr = rows_of(seq);
   for (int r = threadIdx.x; r < b.rows_per_seq; r += 256) {
     const int row = seq * b.rows_per_seq + r;
-    packed_row[row] = r < nr ? first + r : -1;
-    if (r < nr) live_rows[first + r] = row;
+    b.packed_row()[row] = r < nr ? first + r : -1;
+    if (r < nr) b.live_rows()[first + r] = row;
   }
   if (threadIdx.x == 0) {
-    seq_row0[seq] = first;
-    seq_node0[seq] = node0;
+    b.seq_row0()[seq] = first;
+    b.seq_node0()[seq] = node0;
     if (seq + 1 == b.batch) {
-      n_live[0] = first + nr;
-      n_live[1] = node0 + nodes_of(seq);
+      b.n_live()[0] = first + nr;
+      b.n_live()[1] = node0 + nodes_of(seq);
     }
   }
 }
 
-hipError_t launch_live_rows(hipStream_t st, const BlockDev& b, const KvDev& kv, int max_nodes, int32_t* live_rows, int32_t* packed_row,
-                            int32_t* seq_row0, int32_t* seq_node0, int32_t* n_live) {
-  hipLaunchKernelGGL(k_live_rows, dim3(b.batch), dim3(256), 0, st, b, kv, max_nodes, live_rows, packed_row, seq_row0,
-                     seq_node0, n_live);
+hipError_t launch_live_rows(hipStream_t st, const BlockDev& b, const KvDev& kv, int max_nodes) {
+  hipLaunchKernelGGL(k_live_rows, dim3(b.batch), dim3(256), 0, st, b, kv, max_nodes);
   return hipGetLastError();
 }
 
-template <typename T>
+template <typename T, bool PACKED>
 __global__ __launch_bounds__(256) void k_embed(BlockDev b, KvDev kv, const T* __restrict__ embed,
                                                const T* __restrict__ mask_embed, float* __restrict__ h, int d,
                                                int vocab, float* __restrict__ rope_tab, int hd, float theta,
@@ -90,8 +86,8 @@ __global__ __launch_bounds__(256) void k_embed(BlockDev b, KvDev kv, const T* __
   const bool ok = seq_ok(kv, seq, nr) && nr <= b.rows_per_seq;
   if (r == 0 && threadIdx.x == 0 && !ok) atomicOr(status, ESP_DEV_LEN_OVER_BOUND);
   const bool live = ok && r < nr;
-  if (b.packed_row && !live) return;
-  const size_t at = b.packed_row ? (size_t)b.packed_row[row] : (size_t)row;
+  if (PACKED && !live) return;
+  const size_t at = PACKED ? (size_t)b.packed_row()[row] : (size_t)row;
   const T* src = nullptr;
   if (live) {
     int j = b.mask_j[row];
@@ -122,7 +118,7 @@ hipError_t launch_embed(hipStream_t st, int dtype, const BlockDev& b, const KvDe
                         const void* mask_embed, float* h, int d, int vocab, float* rope_tab, int hd,
                         float theta, int32_t* status, size_t mask_seq_stride) {
   int M = b.batch * b.rows_per_seq;
-  ESP_DISPATCH(dtype, hipLaunchKernelGGL(k_embed<T>, dim3(M), dim3(256), 0, st, b, kv, (const T*)embed,
+  ESP_DISPATCH(dtype, hipLaunchKernelGGL((b.packed ? k_embed<T, true> : k_embed<T, false>), dim3(M), dim3(256), 0, st, b, kv, (const T*)embed,
                                          (const T*)mask_embed, h, d, vocab, rope_tab, hd, theta, status,
                                          mask_seq_stride));
   return hipGetLastError();
@@ -162,25 +158,24 @@ __device__ __forceinline__ f32x4_t add_splits(f32x4_t v, const float* __restrict
   return v;
 }
 
-template <typename T, int S>
+// PACKED 1: only the first *live rows are there; 2: row m of xn comes from row live[m], or is zero (back to block rows).
+template <typename T, int S, int PACKED>
 __global__ __launch_bounds__(1024) void k_residual_norm(float* __restrict__ h, const float* __restrict__ part,
                                                         size_t split_stride, int d, const T* __restrict__ gain,
-                                                        float eps, T* __restrict__ xn, const int32_t* __restrict__ n_live,
-                                                        const int32_t* __restrict__ packed_row) {
+                                                        float eps, T* __restrict__ xn, const int32_t* __restrict__ live) {
   __shared__ float red[16];
   const size_t row_out = blockIdx.x;
   const int d4 = d >> 2, tid = threadIdx.x, step = blockDim.x;
   size_t row = row_out;
-  if (packed_row) {                  // back to block rows
-    const int at = packed_row[row_out];
+  if (PACKED == 1 && (int)row >= *live) return;
+  if (PACKED == 2) {
+    const int at = live[row_out];
     if (at < 0) {
       const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
       for (int i = tid; i < d4; i += step) Pack4<T>::store(xn + row_out * d + 4 * i, zero);
       return;
     }
     row = (size_t)at;
-  } else if (n_live && (int)row >= *n_live) {
-    return;
   }
   float* hr = h + row * d;
   f32x4_t keep = {0.f, 0.f, 0.f, 0.f}, g0 = keep;    // this thread's first column and its gain
@@ -224,31 +219,39 @@ hipError_t launch_residual_norm(hipStream_t st, int dtype, float* h, const float
                                 const int32_t* packed_row) {
   const dim3 grid(M), block(std::min(1024, ((d >> 2) + 63) & ~63));
   const size_t stride = (size_t)M * d;
-  if (splits == 0) {
-    ESP_DISPATCH(dtype, hipLaunchKernelGGL((k_residual_norm<T, 0>), grid, block, 0, st, h, part, stride, d,
-                                           (const T*)gain, eps, (T*)xn_out, n_live, packed_row));
-  } else if (dtype == ESP_F32) {   // the fp32 GEMM splits K inside a workgroup
-    if (splits != 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_residual_norm<float, 1>), grid, block, 0, st, h, part, stride, d, (const float*)gain, eps,
-                       (float*)xn_out, n_live, packed_row);
+#define ESP_NORM(T_, S_, P_, LIVE_)                                                                                      \
+  hipLaunchKernelGGL((k_residual_norm<T_, S_, P_>), grid, block, 0, st, h, part, stride, d, (const T_*)gain, eps, (T_*)xn_out, \
+                     (const int32_t*)(LIVE_))
+  if (dtype == ESP_F32) {          // the fp32 GEMM splits K inside a workgroup; fp32 batches are not packed
+    if (splits > 1 || n_live || packed_row) return hipErrorInvalidValue;
+    if (splits == 0) ESP_NORM(float, 0, 0, nullptr);
+    else ESP_NORM(float, 1, 0, nullptr);
+  } else if (splits == 0) {
+    if (packed_row) ESP_NORM(bf16_t, 0, 2, packed_row);
+    else if (n_live) ESP_NORM(bf16_t, 0, 1, n_live);
+    else ESP_NORM(bf16_t, 0, 0, nullptr);
+  } else if (packed_row) {
+    ESP_SPLITS(splits, ESP_NORM(bf16_t, S, 2, packed_row));
+  } else if (n_live) {
+    ESP_SPLITS(splits, ESP_NORM(bf16_t, S, 1, n_live));
   } else {
-    ESP_SPLITS(splits, hipLaunchKernelGGL((k_residual_norm<bf16_t, S>), grid, block, 0, st, h, part, stride, d,
-                                          (const bf16_t*)gain, eps, (bf16_t*)xn_out, n_live, packed_row));
+    ESP_SPLITS(splits, ESP_NORM(bf16_t, S, 0, nullptr));
   }
+#undef ESP_NORM
   return hipGetLastError();
 }
 
 // ---- QKV epilogue: split-K reduce, optional per-head RMSNorm, rotary, KV append ----------------
 // hd/8 lanes per (row, head): a lane owns the features 4 i .. 4 i + 3 of both halves of the head, i.e. four
 // rotary pairs, as two 16-byte pieces of every partial; all 2 S loads are in flight at once.
-template <typename T, int HD, int S>
+template <typename T, int HD, int S, bool PACKED>
 __global__ __launch_bounds__(256) void k_qkv_post(BlockDev b, KvDev kv, int layer, const float* __restrict__ part,
                                                   size_t split_stride, int hq, int hkv, int qk_norm,
                                                   const T* __restrict__ qg, const T* __restrict__ kg, float eps,
                                                   const float* __restrict__ rope_tab, T* __restrict__ q_out) {
   constexpr int LPH = HD / 8, HALF = HD / 2;
   const int row = blockIdx.y;                       // of the activations
-  if (b.n_live && row >= *b.n_live) return;
+  if (PACKED && row >= *b.n_live()) return;
   const int hidx = (blockIdx.x * 256 + threadIdx.x) / LPH;
   const int f0 = (threadIdx.x % LPH) * 4;
   const int n_heads = hq + 2 * hkv;
@@ -257,7 +260,7 @@ __global__ __launch_bounds__(256) void k_qkv_post(BlockDev b, KvDev kv, int laye
   f32x4_t x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
   x0 = add_splits<S>(x0, part + c0, split_stride);
   x1 = add_splits<S>(x1, part + c0 + HALF, split_stride);
-  const int brow = b.live_rows ? b.live_rows[row] : row;
+  const int brow = PACKED ? b.live_rows()[row] : row;
   const int seq = brow / b.rows_per_seq, r = brow % b.rows_per_seq;
   const int nr = b.n_rows[seq];
   const bool live = seq_ok(kv, seq, nr) && nr <= b.rows_per_seq && r < nr;
@@ -329,17 +332,19 @@ hipError_t launch_qkv_post(hipStream_t st, int dtype, const BlockDev& b, const K
   const int n_heads = hq + 2 * hkv;
   const dim3 grid((n_heads * (hd / 8) + 255) / 256, M);
   const size_t stride = (size_t)M * n_heads * hd;
-#define ESP_QKV_POST(T_, HD_, S_)                                                                                     \
-  hipLaunchKernelGGL((k_qkv_post<T_, HD_, S_>), grid, dim3(256), 0, st, b, kv, layer, part, stride, hq, hkv, qk_norm, \
+#define ESP_QKV_POST(T_, HD_, S_, P_)                                                                                     \
+  hipLaunchKernelGGL((k_qkv_post<T_, HD_, S_, P_>), grid, dim3(256), 0, st, b, kv, layer, part, stride, hq, hkv, qk_norm, \
                      (const T_*)qg, (const T_*)kg, eps, rope_tab, (T_*)q_out)
   if (dtype == ESP_F32) {
     if (splits != 1) return hipErrorInvalidValue;
-    if (hd == 64) ESP_QKV_POST(float, 64, 1);
-    else ESP_QKV_POST(float, 128, 1);
+    if (hd == 64) ESP_QKV_POST(float, 64, 1, false);
+    else ESP_QKV_POST(float, 128, 1, false);
   } else if (hd == 64) {
-    ESP_SPLITS(splits, ESP_QKV_POST(bf16_t, 64, S));
+    if (b.packed) { ESP_SPLITS(splits, ESP_QKV_POST(bf16_t, 64, S, true)); }
+    else { ESP_SPLITS(splits, ESP_QKV_POST(bf16_t, 64, S, false)); }
   } else {
-    ESP_SPLITS(splits, ESP_QKV_POST(bf16_t, 128, S));
+    if (b.packed) { ESP_SPLITS(splits, ESP_QKV_POST(bf16_t, 128, S, true)); }
+    else { ESP_SPLITS(splits, ESP_QKV_POST(bf16_t, 128, S, false)); }
   }
 #undef ESP_QKV_POST
   return hipGetLastError();
@@ -429,10 +434,10 @@ __global__ void k_node_rows(BlockDev b, int max_nodes, int32_t* a_rows, int32_t*
   int nn = b.n_nodes[seq];
   bool live = i < nn && nn <= b.n_rows[seq] && b.n_rows[seq] <= b.rows_per_seq;
   const int row = seq * b.rows_per_seq + (live ? i : 0);
-  if (b.seq_node0) {
-    if (m >= b.n_live[1]) { a_rows[m] = 0; out_rows[m] = -1; if (pos_list) pos_list[m] = 0; }
+  if (b.packed) {
+    if (m >= b.n_live()[1]) { a_rows[m] = 0; out_rows[m] = -1; if (pos_list) pos_list[m] = 0; }
     if (!live) return;
-    m = b.seq_node0[seq] + i;
+    m = b.seq_node0()[seq] + i;
   }
   a_rows[m] = row;
   out_rows[m] = live ? row : -1;

@@ -58,8 +58,9 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
                                                const int32_t* __restrict__ m_live) {
   // m_live: only the first *m_live rows are there (packed rows of a ragged batch).  The grid was sized for M; the
   // tiles that are there take its first workgroups and the others have nothing to do.  Strides stay those of M.
+  // (Large tiles only: up to 128 rows there is one row tile.)
   const int M_ld = M;
-  if (m_live) {
+  if (RING > 0 && m_live) {
     M = min(*m_live, M);
     if (M <= 0) return;
     m_tiles = (M + WM * MT * 32 - 1) / (WM * MT * 32);
@@ -68,7 +69,7 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
   // contiguous range of tiles (tiles sharing weight rows then share an L2).
   const int total = m_tiles * n_tiles * splits;
   const int per_xcd = (total + 7) >> 3;
-  if ((int)(blockIdx.x >> 3) >= per_xcd) return;
+  if (RING > 0 && (int)(blockIdx.x >> 3) >= per_xcd) return;
   const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (logical >= total) return;
   const int mi = logical % m_tiles;
@@ -535,20 +536,20 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const bf16_t* __restrict__ A,
                                                    const bf16_t* __restrict__ W, float* __restrict__ out, int M,
                                                    int N, int K, int splits, int m_tiles, int n_tiles, int a_ld,
                                                    float* __restrict__ out2, const int32_t* __restrict__ draw_pos,
-                                                   uint32_t seed, const int32_t* __restrict__ m_live) {
+                                                   uint32_t seed) {
   extern __shared__ __align__(16) unsigned char lds[];   // 2 buffers of MT*32 rows * A_ROW_BYTES
   gemm_bf16_body<MT, NB, D, TILED, 1, EPI>(lds, A, a_rows, W, out, M, N, K, splits, m_tiles, n_tiles, a_ld, out2,
-                                           draw_pos, seed, m_live);
+                                           draw_pos, seed, nullptr);
 }
 
 template <int MT, int NB, int D, bool TILED, int EPI>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gemm_bf16_big(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ a_rows, const bf16_t* __restrict__ W,
     float* __restrict__ out, int M, int N, int K, int splits, int m_tiles, int n_tiles, int a_ld,
-    float* __restrict__ out2, const int32_t* __restrict__ m_live) {
+    float* __restrict__ out2) {
   extern __shared__ __align__(16) unsigned char lds[];
   gemm_bf16_body<MT, NB, D, TILED, 1, EPI>(lds, A, a_rows, W, out, M, N, K, splits, m_tiles, n_tiles, a_ld, out2,
-                                           nullptr, 0u, m_live);
+                                           nullptr, 0u, nullptr);
 }
 
 // Large tile with the LDS ring: one workgroup of eight waves per CU owns (almost) the whole LDS;
@@ -696,10 +697,10 @@ hipError_t launch_bf16(hipStream_t st, const void* A, const int32_t* a_rows, con
                   M, N, K, p.splits, p.m_tiles, p.n_tiles, a_ld, out2, draw_pos, seed, m_live);
   } else if constexpr (MT * NB >= 8)
     launch_kernel(k_gemm_bf16_big<MT, NB, D, TILED, EPI>, dim3(per_xcd * 8), dim3(256), lds, st, (const bf16_t*)A,
-                  a_rows, (const bf16_t*)W, out, M, N, K, p.splits, p.m_tiles, p.n_tiles, a_ld, out2, m_live);
+                  a_rows, (const bf16_t*)W, out, M, N, K, p.splits, p.m_tiles, p.n_tiles, a_ld, out2);
   else
     launch_kernel(k_gemm_bf16<MT, NB, D, TILED, EPI>, dim3(per_xcd * 8), dim3(256), lds, st, (const bf16_t*)A, a_rows,
-                  (const bf16_t*)W, out, M, N, K, p.splits, p.m_tiles, p.n_tiles, a_ld, out2, draw_pos, seed, m_live);
+                  (const bf16_t*)W, out, M, N, K, p.splits, p.m_tiles, p.n_tiles, a_ld, out2, draw_pos, seed);
   return hipGetLastError();
 }
 

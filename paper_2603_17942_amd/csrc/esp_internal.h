@@ -138,15 +138,23 @@ struct BlockDev {   // device-side view of esp_block + esp_kv scalars, passed by
   int batch, rows_per_seq, k_masks, layout, anc_words;
   const int32_t *n_rows, *n_nodes, *tok, *parent, *depth, *mask_j, *attach;
   const uint64_t* anc;
-  // Live rows of a ragged batch packed together (all null: row m of the activations is block row m).
-  // live_rows[m]: block row of packed row m; packed_row[block row]: its packed row, -1 for a row that is not
-  // there; seq_row0[seq]: first packed row of a sequence; n_live[0] rows, n_live[1] tree rows; seq_node0: n_live's
-  // second count up to a sequence.
-  const int32_t *live_rows = nullptr, *packed_row = nullptr, *seq_row0 = nullptr, *seq_node0 = nullptr, *n_live = nullptr;
+  // Live rows of a ragged batch packed together (null: row m of the activations is block row m).  The kernels that use
+  // them have an instantiation without (PACKED false): looking at a null pointer first cost a short launch 0.2 us.
+  int32_t* packed = nullptr;
+  __host__ __device__ size_t rows() const { return (size_t)batch * rows_per_seq; }
+  // block row of packed row m; packed row of a block row (-1: not there); first packed row of a sequence; tree rows
+  // before a sequence; [0] rows and [1] tree rows of the batch
+  __host__ __device__ int32_t* live_rows() const { return packed; }
+  __host__ __device__ int32_t* packed_row() const { return packed + rows(); }
+  __host__ __device__ int32_t* seq_row0() const { return packed + 2 * rows(); }
+  __host__ __device__ int32_t* seq_node0() const { return packed + 2 * rows() + batch; }
+  __host__ __device__ int32_t* n_live() const { return packed + 2 * rows() + 2 * batch; }
+  static size_t packed_ints(size_t rows, size_t batch) { return 2 * rows + 2 * batch + 2; }
 };
 // where row r of a sequence sits in the activations
+template <bool PACKED>
 __device__ __forceinline__ size_t act_row(const BlockDev& b, int seq, int r) {
-  return b.seq_row0 ? (size_t)b.seq_row0[seq] + r : (size_t)seq * b.rows_per_seq + r;
+  return PACKED ? (size_t)b.seq_row0()[seq] + r : (size_t)seq * b.rows_per_seq + r;
 }
 struct KvDev {
   void *k, *v;
@@ -156,10 +164,8 @@ struct KvDev {
   int len_bound;
 };
 
-// fills the arrays of a BlockDev's packed rows (one int per block row in live_rows and packed_row, one per sequence
-// in seq_row0 and seq_node0, two in n_live) from the row counts, which only the device knows
-hipError_t launch_live_rows(hipStream_t st, const BlockDev& b, const KvDev& kv, int max_nodes, int32_t* live_rows, int32_t* packed_row,
-                            int32_t* seq_row0, int32_t* seq_node0, int32_t* n_live);
+// fills b.packed from the row counts, which only the device knows
+hipError_t launch_live_rows(hipStream_t st, const BlockDev& b, const KvDev& kv, int max_nodes);
 hipError_t launch_embed(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, const void* embed,
                         const void* mask_embed, float* h, int d, int vocab, float* rope_tab, int hd,
                         float theta, int32_t* status, size_t mask_seq_stride);
@@ -266,7 +272,7 @@ struct esp_ctx {
   float* topk_scratch;
   int32_t* idx_a;    // [Mmax] gather rows
   int32_t* idx_b;    // [Mmax]
-  int32_t *live_rows, *packed_row, *seq_row0, *seq_node0, *n_live;   // packed rows of a ragged batch (BlockDev)
+  int32_t* packed;   // packed rows of a ragged batch (BlockDev)
   int32_t* status;   // device status word
   size_t gemm_out_floats, attn_part_floats, logits_rows;
   // optional launch-site timing with HIP events (esp_profile_enable / esp_profile_read)
