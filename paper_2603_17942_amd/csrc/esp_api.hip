@@ -58,10 +58,8 @@ WsLayout ws_layout(const esp_model_desc* m, int max_batch, int max_rows, int64_t
   go = std::max(go, gemm_out_elems(gemm_plan(m->dtype, (int)M, d, ff), (int)M, d));
   w.gemm_out_floats = go;
   w.gemm_out = take(go * 4);
-  int lb = (int)std::min<int64_t>(max_kv_len, 0x7fffffff);
-  AttnPlan ap = attn_plan(max_batch, max_rows, hq, hkv, lb);
   // a call may use fewer rows / shorter bound and hence another split count: size for the worst
-  size_t apf = attn_partial_floats(m->dtype, max_batch, max_rows, hq, hkv, hd, std::max(ap.nsplit, 64));
+  size_t apf = attn_partial_floats_bound(m->dtype, max_batch, max_rows, hq, hkv, hd);
   w.attn_part_floats = apf;
   w.attn_part = take(apf * 4);
   w.rope_tab = take(M * (size_t)hd * 4);
@@ -336,8 +334,8 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
   if (gemm_out_elems(p_qkv, M, nqkv) > c->gemm_out_floats || gemm_out_elems(p_o, M, d) > c->gemm_out_floats ||
       gemm_out_elems(p_gu, M, 2 * ff) > c->gemm_out_floats || gemm_out_elems(p_dn, M, d) > c->gemm_out_floats)
     return ESP_ECAPACITY;
-  const AttnPlan ap = attn_plan(blk->batch, blk->rows_per_seq, hq, hkv, kv->len_bound);
-  if (attn_partial_floats(dt, blk->batch, blk->rows_per_seq, hq, hkv, hd, ap.nsplit) > c->attn_part_floats)
+  const AttnPlan ap = attn_plan(dt, hd, blk->batch, blk->rows_per_seq, hq, hkv, kv->len_bound);
+  if (attn_partial_floats(dt, blk->batch, blk->rows_per_seq, hq, hkv, hd, ap) > c->attn_part_floats)
     return ESP_ECAPACITY;
   // the LM-head passes below need an unsplit plan (their epilogues see whole rows): refuse before
   // anything is launched, so that no K/V has been appended when the call fails
@@ -705,8 +703,8 @@ esp_status esp_attn_tree(esp_ctx* c, const esp_block* blk, const esp_kv* kv, int
   if (st != ESP_OK) return st;
   if (layer < 0 || layer >= c->m.n_layers) return ESP_EINVAL;
   const esp_model_desc& m = c->m;
-  const AttnPlan ap = attn_plan(blk->batch, blk->rows_per_seq, m.n_q_heads, m.n_kv_heads, kv->len_bound);
-  if (attn_partial_floats(m.dtype, blk->batch, blk->rows_per_seq, m.n_q_heads, m.n_kv_heads, m.head_dim, ap.nsplit) >
+  const AttnPlan ap = attn_plan(m.dtype, m.head_dim, blk->batch, blk->rows_per_seq, m.n_q_heads, m.n_kv_heads, kv->len_bound);
+  if (attn_partial_floats(m.dtype, blk->batch, blk->rows_per_seq, m.n_q_heads, m.n_kv_heads, m.head_dim, ap) >
       c->attn_part_floats)
     return ESP_ECAPACITY;
   { ESP_PROF(ESP_SITE_ATTN);

@@ -563,57 +563,94 @@ hipError_t attn_prepare() {
 }
 
 namespace {
-// Geometry of the ring kernel for `cols` query columns per kv head.  A column tile is 32 columns; a
-// workgroup owns ct_wg of them (as few workgroups per kv head and split as twelve waves allow, the
-// tiles spread evenly).  Its first n_full tiles get a wave each; each of the others is worked by two
-// waves, one per half of every key tile, when that evens out the load of the four SIMDs (waves go
-// to SIMDs round-robin, and the SIMD with the most matrix work sets the pace): ct_wg = 9 gives
-// SIMD loads of 5, 5, 4, 4 half-tiles instead of 6, 4, 4, 4.  At least four waves (they carry the loads).
-struct RingGeometry { int q_tiles, ct_wg, n_full, waves; };
-RingGeometry ring_geometry(int cols) {
-  RingGeometry g;
-  const int ct = (cols + 31) / 32;
-  g.q_tiles = (ct + RING_MAX_WAVES - 1) / RING_MAX_WAVES;
-  g.ct_wg = (ct + g.q_tiles - 1) / g.q_tiles;
-  const int rem = g.ct_wg & 3;
-  const int n_split = ((rem == 1 || rem == 2) && g.ct_wg > 4 && g.ct_wg + rem <= RING_MAX_WAVES) ? rem : 0;
-  g.n_full = g.ct_wg - n_split;
-  g.waves = std::max(4, g.n_full + 2 * n_split);
-  return g;
+// Waves of a workgroup with ct_wg column tiles and tps key tiles.  A wave has a whole column tile, or the even or odd
+// half of each of its key tiles; the SIMD with the most half-tiles sets the pace (waves go to SIMDs round-robin).  Two
+// waves share a column tile where that evens the SIMDs out: ct_wg = 9 gives loads of 5, 5, 4, 4 half-tiles instead of
+// 6, 4, 4, 4; with one or two column tiles it puts idle SIMDs to work, where there are key tiles enough to make up for
+// the exchange at the end (68 rows, 2048 keys, two column tiles: 20.1 -> 18.2 us; one key tile: 10.7 -> 11.3).  At least
+// four waves (they carry the loads).
+struct RingGeometry { int n_full, waves; };
+RingGeometry ring_geometry(int ct_wg, int tps) {
+  const int rem = ct_wg & 3;
+  int paired = 0;
+  if (ct_wg <= 2) paired = tps >= 3 ? ct_wg : 0;
+  else if ((rem == 1 || rem == 2) && ct_wg > 4 && ct_wg + rem <= RING_MAX_WAVES) paired = rem;
+  return {ct_wg - paired, std::max(4, ct_wg + paired)};
 }
-}  // namespace
+// most partial column tiles (column tiles x splits) of a plan, per sequence and kv head: what the workspace holds
+int ring_tiles_bound(int cols) {
+  const int ct = (cols + 31) / 32, q = (ct + RING_MAX_WAVES - 1) / RING_MAX_WAVES;
+  return q * ((ct + q - 1) / q) * 64;
+}
 
-AttnPlan attn_plan(int batch, int rows_per_seq, int hq, int hkv, int len_bound) {
-  // Splits of the key range.  A workgroup (one per CU) owns the query columns of one kv head -- or a
-  // share of them when they exceed twelve waves -- and one split; every split writes a partial
-  // (m, l, O) per query row and head that the merge kernel reads back, so: as few splits as fill the
-  // 256 CUs once, no second, mostly empty round, and a few tiles of 64 keys per split at least.
-  // Cost model per candidate: rounds over the CUs times (tiles per split + a fixed per-workgroup
-  // cost of about four tiles).
-  AttnPlan p;
-  const int nt = (len_bound + rows_per_seq + 63) / 64;
-  const int G = hq / hkv;
-  const int base = ring_geometry(rows_per_seq * G).q_tiles * hkv * batch;
+// Splits of the key range alone: rounds over the CUs x (tiles + about four tiles' time of a workgroup's own).
+void plan_splits(AttnPlan& p, int base, int nt) {
   int best = 1, best_cost = 1 << 30;
   for (int ns = 1; ns <= 64; ++ns) {
     const int tps = (nt + ns - 1) / ns;
     if (ns > 1 && tps < 2) break;
     if ((nt + tps - 1) / tps != ns) continue;             // same partition as a smaller count
-    const int rounds = (base * ns + 255) / 256;
-    const int cost = rounds * (tps + 4);
+    const int cost = (base * ns + 255) / 256 * (tps + 4);
     if (cost < best_cost) { best_cost = cost; best = ns; }
   }
   p.tiles_per_split = (nt + best - 1) / best;
   p.nsplit = (nt + p.tiles_per_split - 1) / p.tiles_per_split;
+}
+}  // namespace
+
+AttnPlan attn_plan(int dtype, int hd, int batch, int rows_per_seq, int hq, int hkv, int len_bound) {
+  AttnPlan p;
+  const int nt = (len_bound + rows_per_seq + 63) / 64;
+  const int cols = rows_per_seq * (hq / hkv), ct = (cols + 31) / 32;
+  p.q_tiles = (ct + RING_MAX_WAVES - 1) / RING_MAX_WAVES;
+  p.ct_wg = (ct + p.q_tiles - 1) / p.q_tiles;
+  plan_splits(p, p.q_tiles * hkv * batch, nt);
+  if (dtype != ESP_BF16 || hd != 128) return p;
+  // Column tiles per workgroup (one workgroup per CU) and splits of the key range together.  More column tiles share
+  // each key tile's loads; more splits fill the CUs, but every one costs a partial (m, l, O) per column tile (16 KB,
+  // written and read back).  Cost of a candidate in units of 10 ns: the two launches + rounds over the CUs x (start and
+  // end of a workgroup + its key tiles x the time of one: the SIMD with the most half-tiles, or the loads of 32 KB with
+  // that many CUs at it) + merge per partial column tile.  Fitted to 7200 measured candidates of 240 shapes (1 to 512 rows, 64 to 32768 keys,
+  // batches of 1 to 16; model within 7 %).  The plan above (as many column tiles as twelve waves hold) stays unless the
+  // model sees 4 % in another: over the 240 shapes 0.948 of its time on average, 5 of them slower by 5 to 7 % (five
+  // sequences of 200 rows on short caches among them), the others by at most 2 %.
+  // Attention and merge of a layer: 90 rows on 2048 keys 26.6 -> 19.6 us, 132 rows on 1000 keys 24.5 -> 17.6.
+  static const int tile_time[RING_MAX_WAVES] = {84, 70, 104, 110, 120, 126, 138, 150, 165, 175, 208, 218};
+  auto cost = [&](int q, int c, int ns, int tps) {
+    const int64_t groups = (int64_t)q * hkv * batch, rounds = (groups * ns + 255) / 256;
+    const bool short_unpaired = c <= 2 && tps < 3;
+    const int64_t tile = std::max<int64_t>(short_unpaired ? 104 : tile_time[c - 1], 80 * std::min<int64_t>(groups * ns, 256) / 256);
+    return 880 + rounds * ((short_unpaired ? 160 : 180) + tps * tile) + groups * c * ns * 55 / 100;
+  };
+  int64_t best_cost = cost(p.q_tiles, p.ct_wg, p.nsplit, p.tiles_per_split) * 96 / 100;
+  for (int want = std::min(ct, RING_MAX_WAVES); want >= 1; --want) {
+    const int q = (ct + want - 1) / want, c = (ct + q - 1) / q;
+    if (c != want) continue;                              // the same tiling as with fewer
+    const int most = std::min(64, ring_tiles_bound(cols) / (q * c));
+    for (int ns = 1; ns <= most && ns <= nt; ++ns) {
+      const int tps = (nt + ns - 1) / ns;
+      if (ns > 1 && tps < 2 && ct < 3) break;             // (one row, 400 keys: 10.6 us in four splits, 11.1 in seven)
+      if ((nt + tps - 1) / tps != ns) continue;           // same partition as a smaller count
+      const int64_t t = cost(q, c, ns, tps);
+      if (t < best_cost) {
+        best_cost = t;
+        p.nsplit = ns; p.tiles_per_split = tps; p.q_tiles = q; p.ct_wg = c;
+      }
+      if ((int64_t)q * hkv * batch * ns > 16 * 256) break;   // more splits even out nothing any more
+    }
+  }
   return p;
 }
 
-size_t attn_partial_floats(int dtype, int batch, int rows_per_seq, int hq, int hkv, int hd, int nsplit) {
-  if (dtype == ESP_BF16 && hd == 128) {   // ring layout: whole column tiles of 32
-    const RingGeometry g = ring_geometry(rows_per_seq * (hq / hkv));
-    return (size_t)batch * hkv * g.q_tiles * g.ct_wg * nsplit * (32 * (hd + 2));
-  }
-  return (size_t)batch * rows_per_seq * hq * nsplit * (hd + 2);
+size_t attn_partial_floats_bound(int dtype, int batch, int rows_per_seq, int hq, int hkv, int hd) {
+  if (dtype == ESP_BF16 && hd == 128)   // ring layout: whole column tiles of 32
+    return (size_t)batch * hkv * ring_tiles_bound(rows_per_seq * (hq / hkv)) * (32 * (hd + 2));
+  return (size_t)batch * rows_per_seq * hq * 64 * (hd + 2);
+}
+
+size_t attn_partial_floats(int dtype, int batch, int rows_per_seq, int hq, int hkv, int hd, const AttnPlan& p) {
+  if (dtype == ESP_BF16 && hd == 128) return (size_t)batch * hkv * p.q_tiles * p.ct_wg * p.nsplit * (32 * (hd + 2));
+  return (size_t)batch * rows_per_seq * hq * p.nsplit * (hd + 2);
 }
 
 hipError_t launch_attn(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, int layer, int hq, int hkv,
@@ -623,16 +660,16 @@ hipError_t launch_attn(hipStream_t st, int dtype, const BlockDev& b, const KvDev
   float* part_o = partials;
   float* part_ml = partials + (size_t)M * hq * p.nsplit * hd;
   if (dtype == ESP_BF16 && hd == 128) {
-    const RingGeometry g = ring_geometry(b.rows_per_seq * (hq / hkv));
-    part_ml = partials + (size_t)b.batch * hkv * g.q_tiles * g.ct_wg * p.nsplit * (32 * hd);
-    const int total_wg = g.q_tiles * hkv * b.batch * p.nsplit;
+    const RingGeometry g = ring_geometry(p.ct_wg, p.tiles_per_split);
+    part_ml = partials + (size_t)b.batch * hkv * p.q_tiles * p.ct_wg * p.nsplit * (32 * hd);
+    const int total_wg = p.q_tiles * hkv * b.batch * p.nsplit;
     const hipError_t attr = attn_prepare();
     if (attr != hipSuccess) return attr;
     const dim3 grid(((total_wg + 7) / 8) * 8), block(64 * g.waves);
     const auto kern = g.waves >= 8 ? (packed ? k_attn_ring<4, true> : k_attn_ring<4, false>)
                                    : (packed ? k_attn_ring<8, true> : k_attn_ring<8, false>);
     hipLaunchKernelGGL(kern, grid, block, RING_LDS_BYTES, st, b, kv, layer, hq, hkv, (const bf16_t*)q, part_o, part_ml, p.nsplit,
-                       p.tiles_per_split, g.q_tiles, g.ct_wg, g.n_full);
+                       p.tiles_per_split, p.q_tiles, p.ct_wg, g.n_full);
   } else {
     const dim3 grid(M, hq, p.nsplit);
     if (dtype == ESP_F32 && hd == 64)         // fp32 batches are not packed
@@ -654,8 +691,7 @@ hipError_t launch_attn_merge(hipStream_t st, int dtype, const BlockDev& b, const
                              const float* partials, const AttnPlan& p, void* out) {
   const bool packed = b.packed != nullptr;
   if (dtype == ESP_BF16 && hd == 128) {
-    const RingGeometry g = ring_geometry(b.rows_per_seq * (hq / hkv));
-    const int n_ct = g.q_tiles * g.ct_wg;
+    const int n_ct = p.q_tiles * p.ct_wg;
     const float* part_o = partials;
     const float* part_ml = partials + (size_t)b.batch * hkv * n_ct * p.nsplit * (32 * hd);
     const dim3 grid(b.batch * hkv * n_ct * 4);

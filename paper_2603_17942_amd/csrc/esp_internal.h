@@ -199,10 +199,15 @@ hipError_t launch_mask_ema(hipStream_t st, int dtype, const void* embed, const i
                            const int32_t* emit_tok, float lambda, int k, int d, int vocab, void* mask_embed, int n_seq);
 
 // ---- attention (esp_attn.hip) ------------------------------------------------------------------
-struct AttnPlan { int nsplit; int tiles_per_split; };
-AttnPlan attn_plan(int batch, int rows_per_seq, int hq, int hkv, int len_bound);
+struct AttnPlan {
+  int nsplit = 1, tiles_per_split = 1;   // splits of the key range, 64-key tiles in each
+  int q_tiles = 1, ct_wg = 1;            // ring kernel: workgroups per kv head and split, column tiles in each
+};
+AttnPlan attn_plan(int dtype, int hd, int batch, int rows_per_seq, int hq, int hkv, int len_bound);
 hipError_t attn_prepare();   // one-time kernel attributes (dynamic LDS limit)
-size_t attn_partial_floats(int dtype, int batch, int rows_per_seq, int hq, int hkv, int hd, int nsplit);
+size_t attn_partial_floats(int dtype, int batch, int rows_per_seq, int hq, int hkv, int hd, const AttnPlan& p);
+// what any plan for up to that many sequences and rows needs
+size_t attn_partial_floats_bound(int dtype, int batch, int rows_per_seq, int hq, int hkv, int hd);
 hipError_t launch_attn(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, int layer, int hq,
                        int hkv, int hd, const void* q, float* partials, const AttnPlan& p);
 hipError_t launch_attn_merge(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, int hq, int hkv, int hd,

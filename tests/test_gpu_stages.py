@@ -864,6 +864,15 @@ def test_attn_tree_bf16_mfma(B, bf16_engine, n_nodes, k, layout, cache_lens):
     assert err < 2e-2
 
 
+@pytest.mark.parametrize("n_nodes,cache_lens", [(1, [900]), (7, [193]), (9, [1500, 3]), (16, [700]), (23, [64]), (31, [2100])])
+def test_attn_tree_bf16_few_columns(B, bf16_engine, n_nodes, cache_lens):
+    """One to four column tiles a kv head, in splits of one to many key tiles: with and without two waves sharing a
+    column tile."""
+    shape, w, eng = bf16_engine
+    print(f"attn bf16 few columns n={n_nodes} L={cache_lens}", flush=True)
+    assert run_attention_case(B, shape, eng, n_nodes, 0, 0, cache_lens, seed=75) < 2e-2
+
+
 # ------------------------------------------------------------------------- mask initialisations
 @pytest.mark.parametrize("hq,hkv,n_nodes,k,layout,cache_lens", [
     (2, 2, 40, 3, 0, [515]),            # no grouping: one query head per kv head
