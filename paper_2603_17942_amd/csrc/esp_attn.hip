@@ -30,7 +30,28 @@ __device__ __forceinline__ bool seq_ok(const KvDev& kv, int seq, int n_rows, int
 }
 
 // --------------------------------------------------------------------------------------------------
-template <typename T, int HD, bool PACKED>
+// eight consecutive elements of the cache (one 16-byte or two) as floats; VEC: the planes are 16-byte aligned
+template <bool VEC, typename T>
+__device__ __forceinline__ void load8(const T* p, float (&v)[8]) {
+  if constexpr (VEC && sizeof(T) == 4) {
+    const f32x4_t a = *reinterpret_cast<const f32x4_t*>(p), b = *reinterpret_cast<const f32x4_t*>(p + 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
+  } else if constexpr (VEC) {
+    const bf16x8_t a = *reinterpret_cast<const bf16x8_t*>(p);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = (float)a[e];
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = to_f32(p[e]);
+  }
+}
+
+// One wave per (row, head, split); a lane has one key of a tile for the scores and HD / 64 features for the output.  The
+// tile's K and V sit in fragment order, eight features of a key or eight keys of a feature side by side: all of them are
+// in flight before the first is used (a load an element was 14.5 us at 60 rows and 188 keys, and with them one split of
+// three tiles; now 5.6 in three splits).  Sums run over features and keys in ascending order.
+template <typename T, int HD, bool PACKED, bool VEC>
 __global__ __launch_bounds__(64) void k_attn_generic(BlockDev b, KvDev kv, int layer, int hq, int hkv,
                                                      const T* __restrict__ q, float* __restrict__ part_o,
                                                      float* __restrict__ part_ml, int nsplit, int tps) {
@@ -58,6 +79,17 @@ __global__ __launch_bounds__(64) void k_attn_generic(BlockDev b, KvDev kv, int l
   for (int t = t0; t < t1; ++t) {
     const int key = t * 64 + lane;
     bool valid = key < total;
+    float kf[HD / 8][8];
+    if (valid) {
+#pragma unroll
+      for (int g = 0; g < HD / 8; ++g) load8<VEC>(kp + k_off(base + key, 8 * g, HD), kf[g]);
+    }
+    float vf[HD / 64][8][8];                    // [.][piece: block, step, half][key 8 (e / 4) + e % 4 of it]
+#pragma unroll
+    for (int i = 0; i < HD / 64; ++i)
+#pragma unroll
+      for (int c = 0; c < 8; ++c)               // (the whole tile lies inside the plane: sequences own 64-aligned slots)
+        load8<VEC>(vp + v_off(base + t * 64 + (c >> 2) * 32 + ((c >> 1) & 1) * 16 + (c & 1) * 4, lane + 64 * i, HD), vf[i][c]);
     if (valid && key >= L) {
       int c = key - L;
       valid = (anc[c >> 6] >> (c & 63)) & 1ull;
@@ -65,7 +97,8 @@ __global__ __launch_bounds__(64) void k_attn_generic(BlockDev b, KvDev kv, int l
     float s = NEG_BIG;
     if (valid) {
       float acc = 0.f;
-      for (int d = 0; d < HD; ++d) acc = fmaf(to_f32(kp[k_off(base + key, d, HD)]), qs[d], acc);
+#pragma unroll
+      for (int d = 0; d < HD; ++d) acc = fmaf(kf[d >> 3][d & 7], qs[d], acc);
       s = acc;
     }
     float m_new = fmaxf(m, wave_max(s));
@@ -75,11 +108,15 @@ __global__ __launch_bounds__(64) void k_attn_generic(BlockDev b, KvDev kv, int l
     m = m_new;
     ps[lane] = p;
     __syncthreads();
-    const int nk = min(64, total - t * 64);
+    const int nk = min(64, total - t * 64);     // entries past the sequence are not touched: cache memory may hold anything
 #pragma unroll
     for (int i = 0; i < HD / 64; ++i) {
       float a = o[i] * alpha;
-      for (int kk = 0; kk < nk; ++kk) a = fmaf(ps[kk], to_f32(vp[v_off(base + t * 64 + kk, lane + 64 * i, HD)]), a);
+#pragma unroll
+      for (int kk = 0; kk < 64; ++kk) {
+        const int c = (kk >> 5) * 4 + ((kk >> 4) & 1) * 2 + ((kk >> 2) & 1), e = ((kk >> 3) & 1) * 4 + (kk & 3);
+        a = fmaf(ps[kk], kk < nk ? vf[i][c][e] : 0.f, a);
+      }
       o[i] = a;
     }
     __syncthreads();
@@ -602,10 +639,17 @@ AttnPlan attn_plan(int dtype, int hd, int batch, int rows_per_seq, int hq, int h
   AttnPlan p;
   const int nt = (len_bound + rows_per_seq + 63) / 64;
   const int cols = rows_per_seq * (hq / hkv), ct = (cols + 31) / 32;
+  if (dtype != ESP_BF16 || hd != 128) {
+    // generic kernel: one wave per (row, head, split) and a tile a split, as long as that is no more than 16 waves a CU
+    const int64_t waves = (int64_t)batch * rows_per_seq * hq;
+    const int ns = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(nt, 64), 4096 / waves));
+    p.tiles_per_split = (nt + ns - 1) / ns;
+    p.nsplit = (nt + p.tiles_per_split - 1) / p.tiles_per_split;
+    return p;
+  }
   p.q_tiles = (ct + RING_MAX_WAVES - 1) / RING_MAX_WAVES;
   p.ct_wg = (ct + p.q_tiles - 1) / p.q_tiles;
   plan_splits(p, p.q_tiles * hkv * batch, nt);
-  if (dtype != ESP_BF16 || hd != 128) return p;
   // Column tiles per workgroup (one workgroup per CU) and splits of the key range together.  More column tiles share
   // each key tile's loads; more splits fill the CUs, but every one costs a partial (m, l, O) per column tile (16 KB,
   // written and read back).  Cost of a candidate in units of 10 ns: the two launches + rounds over the CUs x (start and
@@ -629,7 +673,7 @@ AttnPlan attn_plan(int dtype, int hd, int batch, int rows_per_seq, int hq, int h
     const int most = std::min(64, ring_tiles_bound(cols) / (q * c));
     for (int ns = 1; ns <= most && ns <= nt; ++ns) {
       const int tps = (nt + ns - 1) / ns;
-      if (ns > 1 && tps < 2 && ct < 3) break;             // (one row, 400 keys: 10.6 us in four splits, 11.1 in seven)
+      if (ns > 1 && tps < 2) break;                       // (one row, 400 keys: 10.6 us in four splits, 11.1 in seven)
       if ((nt + tps - 1) / tps != ns) continue;           // same partition as a smaller count
       const int64_t t = cost(q, c, ns, tps);
       if (t < best_cost) {
@@ -672,15 +716,15 @@ hipError_t launch_attn(hipStream_t st, int dtype, const BlockDev& b, const KvDev
                        p.tiles_per_split, p.q_tiles, p.ct_wg, g.n_full);
   } else {
     const dim3 grid(M, hq, p.nsplit);
-    if (dtype == ESP_F32 && hd == 64)         // fp32 batches are not packed
-      hipLaunchKernelGGL((k_attn_generic<float, 64, false>), grid, dim3(64), 0, st, b, kv, layer, hq, hkv, (const float*)q,
-                         part_o, part_ml, p.nsplit, p.tiles_per_split);
-    else if (dtype == ESP_F32 && hd == 128)
-      hipLaunchKernelGGL((k_attn_generic<float, 128, false>), grid, dim3(64), 0, st, b, kv, layer, hq, hkv,
-                         (const float*)q, part_o, part_ml, p.nsplit, p.tiles_per_split);
-    else if (dtype == ESP_BF16 && hd == 64)
-      hipLaunchKernelGGL((packed ? k_attn_generic<bf16_t, 64, true> : k_attn_generic<bf16_t, 64, false>), grid, dim3(64), 0, st, b,
-                         kv, layer, hq, hkv, (const bf16_t*)q, part_o, part_ml, p.nsplit, p.tiles_per_split);
+    const bool vec = (((uintptr_t)kv.k | (uintptr_t)kv.v) & 15) == 0;
+#define ESP_GENERIC(T_, HD_, P_)                                                                                             \
+  hipLaunchKernelGGL((vec ? k_attn_generic<T_, HD_, P_, true> : k_attn_generic<T_, HD_, P_, false>), grid, dim3(64), 0, st, b, kv, \
+                     layer, hq, hkv, (const T_*)q, part_o, part_ml, p.nsplit, p.tiles_per_split)
+    if (dtype == ESP_F32 && hd == 64) ESP_GENERIC(float, 64, false);   // fp32 batches are not packed
+    else if (dtype == ESP_F32 && hd == 128) ESP_GENERIC(float, 128, false);
+    else if (dtype == ESP_BF16 && hd == 64 && packed) ESP_GENERIC(bf16_t, 64, true);
+    else if (dtype == ESP_BF16 && hd == 64) ESP_GENERIC(bf16_t, 64, false);
+#undef ESP_GENERIC
     else
       return hipErrorInvalidValue;
   }

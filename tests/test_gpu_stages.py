@@ -844,6 +844,28 @@ def test_attn_tree_f32(B, tiny_engine, n_nodes, k, layout, cache_lens):
     assert err < 1e-4
 
 
+@pytest.mark.parametrize("dtype,head_dim,offset", [("f32", 64, 1), ("f32", 128, 0), ("f32", 128, 1), ("bf16", 64, 0), ("bf16", 64, 1)])
+def test_attn_tree_generic_forms(B, monkeypatch, dtype, head_dim, offset):
+    """The generic attention kernel at both types and head widths, with caches that start off a 16-byte boundary, splits of
+    one and of several key tiles, and a last tile with one key."""
+    class Shifted(B.KvCache):
+        def __init__(self, *a):
+            super().__init__(*a)
+            n = self.k.numel()
+            self.k, self.v = (torch.full((n + offset,), float("nan"), dtype=t.dtype, device="cuda")[offset:].view(t.shape)
+                              for t in (self.k, self.v))
+    monkeypatch.setattr(B, "KvCache", Shifted)
+    shape = small_shape(d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=head_dim, d_ff=128, vocab=512, n_layers=2, dtype=dtype)
+    w = synth.make_weights(shape, seed=5)
+    for n_nodes, k, layout, lens in [(11, 3, 0, [148, 64]), (1, 0, 0, [1000]), (90, 4, 0, [700]), (3, 2, 1, [64 - 5, 0])]:
+        rows = n_nodes * (k + 1) if layout == 0 else n_nodes + k
+        eng = B.Engine(shape, w, max_batch=len(lens), max_rows_per_seq=rows, max_kv_len=max(lens) + rows + 64)
+        print(f"attn generic {dtype} hd={head_dim} offset={offset} n={n_nodes} L={lens}", flush=True)
+        err = run_attention_case(B, shape, eng, n_nodes, k, layout, lens, seed=61)
+        eng.close()
+        assert err < TOL[dtype]
+
+
 @pytest.fixture(scope="module")
 def bf16_engine(B):
     shape = small_shape(d_model=256, n_q_heads=8, n_kv_heads=2, head_dim=128, d_ff=384, vocab=1024, n_layers=2,
