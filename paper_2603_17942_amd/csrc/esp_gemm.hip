@@ -569,6 +569,203 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                                                       out2, draw_pos, seed, m_live);
 }
 
+// ---- gate/up projection on a wide tile ------------------------------------------------------------------
+// Four waves, one per SIMD with all 512 registers, in 2 x 2: MT x NB tiles of 32 x 32 each, 4 x 4 (256 x 256 a workgroup)
+// or 3 x 5 (192 x 320).  A workgroup's bytes per flop are 0.77 of the 5 x 2 tile's and a wave's fragment reads per matrix
+// instruction 0.7 (the large GEMMs run against the chip's power: the clock falls as the matrix cores fill up, and what
+// moves less data runs at the higher clock), and a launch that needs two rounds of 5 x 2 or 4 x 2 tiles often needs one of
+// these.  Both operands go through LDS as in the ring kernel above: three chunks of activations and four half chunks of
+// weights, 152 to 160 KB, two chunks and three half chunks ahead.  The waves issue their own loads, one every three or
+// four matrix instructions, and read the fragments of the next 16-wide step during the first three quarters of a step, so
+// that none is under way at the barrier; the barrier at the start of a half chunk's last step says that the next half
+// chunk has landed and that nobody reads the one before any more.
+// MI355X, K = 4096, rotating weights: 512 rows x 28672 117 -> 103 us (ring: 448 tiles of 4 x 2, two rounds; here 224), 576
+// rows x 24576 124 -> 102 us (384 tiles of 5 x 2; here 231 of 3 x 5), 1024 rows x 28672 244 -> 203 us.
+template <int MT, int NB>
+struct WideTile {
+  static constexpr int ROWS = 2 * MT * 32, BLOCKS = 2 * NB;          // of a workgroup: rows, 32-column blocks
+  static constexpr int A_STAGE = 2 * MT * 4096, W_STAGE = BLOCKS * 2048;   // a chunk of activations, half a chunk of weights
+  static constexpr int A_STAGES = 3, W_STAGES = 4;
+  static constexpr int ACT_LD = NB * 64 + 16;                        // bytes of a result row in LDS
+  static constexpr size_t LDS = A_STAGES * A_STAGE + W_STAGES * W_STAGE;
+  static_assert(LDS <= 160 * 1024 && (size_t)ROWS * ACT_LD + (NB & 1) * 2 * MT * 4096 <= LDS, "fits the CU");
+};
+
+template <int MT, int NB>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gemm_swiglu_wide(
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, bf16_t* __restrict__ act, int M, int N, int K, int m_tiles,
+    int n_tiles, const int32_t* __restrict__ m_live) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  using T = WideTile<MT, NB>;
+  if (m_live) {                                          // packed rows of a ragged batch, as in the kernels above
+    M = min(*m_live, M);
+    if (M <= 0) return;
+    m_tiles = (M + T::ROWS - 1) / T::ROWS;
+  }
+  const int total = m_tiles * n_tiles;
+  const int per_xcd = (total + 7) >> 3;
+  if ((int)(blockIdx.x >> 3) >= per_xcd) return;
+  const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (logical >= total) return;
+  const int mi = logical % m_tiles, ni = logical / m_tiles;
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lg = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+  const int mt0 = mi * T::ROWS;
+  const int blk0 = ni * T::BLOCKS, nblk = N >> 5;
+  const int nc = K / KC;                                 // at least one
+
+  f32x16_t acc[MT][NB];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+  auto swz = [](int r) { return (r & 7) ^ ((r >> 3) & 1); };
+  const uint32_t lds0 = (uint32_t)(uintptr_t)lds, ldsw = lds0 + T::A_STAGES * T::A_STAGE;
+  // activations: quarter-tiles (8 rows x 128 bytes) wave, wave + 4, ... of the workgroup's 8 MT
+  uint32_t aoff[2 * MT];
+#pragma unroll
+  for (int j = 0; j < 2 * MT; ++j) {
+    const int rt = 8 * wave + (lane >> 3);
+    const int m = min(mt0 + j * 32 + rt, M - 1);
+    aoff[j] = (uint32_t)(((size_t)m * K + 8 * ((lane & 7) ^ swz(rt))) * 2);
+  }
+  const unsigned char* a_base = reinterpret_cast<const unsigned char*>(A);
+  // weights: wave brings 1 KB pieces wave, wave + 4, ... of the half chunk's [block][2 steps]
+  const size_t W_CHUNK = (size_t)nblk * 4096;
+  const unsigned char* w_src[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const int piece = wave + 4 * j, blk = min(blk0 + (piece >> 1), nblk - 1);   // clamped: computed, never stored
+    w_src[j] = reinterpret_cast<const unsigned char*>(W) + (size_t)blk * 4096 + (piece & 1) * 1024;
+  }
+  const uint32_t lane16 = (uint32_t)lane * 16;
+  auto load_a = [&](int j, int c, int stage) {
+    load_to_lds16_sbase<0>(a_base + (size_t)min(c, nc - 1) * (KC * 2), aoff[j], lds0 + stage * T::A_STAGE + (wave + 4 * j) * 1024);
+  };
+  auto load_w = [&](int j, int h, int stage) {
+    const int hh = min(h, 2 * nc - 1);
+    load_to_lds16_sbase<0>(w_src[j] + (size_t)(hh >> 1) * W_CHUNK + (hh & 1) * 2048, lane16, ldsw + stage * T::W_STAGE + (wave + 4 * j) * 1024);
+  };
+  // this lane's fragments; an odd NB leaves a last pair of blocks, gate in wave column 0 and up in wave column 1
+  int a_rd[4];
+#pragma unroll
+  for (int st = 0; st < 4; ++st) a_rd[st] = wm * (MT * 4096) + lr * 128 + (((4 * lg + st) ^ swz(lr)) << 4);
+  auto wblk = [&](int j) { return NB % 2 == 0 ? wn * NB + j : j < NB - 1 ? wn * (NB - 1) + j : 2 * (NB - 1) + wn; };
+  bf16x8_t af[2][MT], wf[2][NB];
+  auto read_frag = [&](int buf, int astage, int wstage, int st, int i) {
+    if (i < MT) af[buf][i] = *reinterpret_cast<const bf16x8_t*>(lds + astage * T::A_STAGE + i * 4096 + a_rd[st]);
+    else wf[buf][i - MT] = *reinterpret_cast<const bf16x8_t*>(lds + T::A_STAGES * T::A_STAGE + wstage * T::W_STAGE +
+                                                              wblk(i - MT) * 2048 + (st & 1) * 1024 + lane16);
+  };
+#pragma unroll
+  for (int j = 0; j < NB; ++j) load_w(j, 0, 0);
+#pragma unroll
+  for (int j = 0; j < 2 * MT; ++j) load_a(j, 0, 0);
+#pragma unroll
+  for (int j = 0; j < NB; ++j) load_w(j, 1, 1);
+#pragma unroll
+  for (int j = 0; j < 2 * MT; ++j) load_a(j, 1, 1);
+#pragma unroll
+  for (int j = 0; j < NB; ++j) load_w(j, 2, 2);
+  // Loads retire in order.  A half chunk h issues the weights of h + 3 in its first step and half of the activations of
+  // chunk c + 2 in its second (past the end: the last ones again, into stages nobody reads), so at the wait in h's second
+  // step the loads younger than the weights of h + 1 are two halves of activations and two half chunks of weights; in the
+  // second half of chunk c the activations of c + 1 have to be there as well, and one half of activations is younger.
+  wait_loads_but<2 * MT + 2 * NB>();
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < MT + NB; ++i) read_frag(0, 0, 0, 0, i);
+  constexpr int SLOTS = MT * NB, READS = MT + NB;
+  int as = 0, ws = 0;                                    // stages of the current chunk and half
+  for (int c = 0; c < nc; ++c) {
+    const int as_next = as + 1 == T::A_STAGES ? 0 : as + 1, as_free = as == 0 ? T::A_STAGES - 1 : as - 1;
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      const int ws_next = (ws + 1) & 3, ws_free = (ws + 3) & 3;
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) {
+        const int st = 2 * hf + s2;
+        if (s2 == 1) {
+          if (hf == 0) wait_loads_but<2 * MT + 2 * NB>();
+          else wait_loads_but<MT + 2 * NB>();
+          __syncthreads();
+        }
+        const int loads = s2 == 0 ? NB : MT;
+#pragma unroll
+        for (int k = 0; k < SLOTS; ++k) {
+          // fragments of the next step in the first three quarters of this one, loads spread evenly
+#pragma unroll
+          for (int q = 0; q < READS; ++q)
+            if (q * (SLOTS * 3 / 4) / READS == k) {
+              if (s2 == 0) read_frag((st + 1) & 1, as, ws, st + 1, q);
+              else read_frag((st + 1) & 1, hf == 0 ? as : as_next, ws_next, (st + 1) & 3, q);
+            }
+#pragma unroll
+          for (int q = 0; q < loads; ++q)
+            if ((2 * q + 1) * SLOTS / (2 * loads) == k) {
+              if (s2 == 0) load_w(q, 2 * c + hf + 3, ws_free);
+              else load_a(hf * MT + q, c + 2, as_free);
+            }
+          __builtin_amdgcn_sched_barrier(0);
+          acc[k / NB][k % NB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[st & 1][k / NB], wf[st & 1][k % NB], acc[k / NB][k % NB], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      ws = ws_next;
+    }
+    as = as_next;
+  }
+  wait_loads_but<0>();
+  __syncthreads();                                       // the LDS is free
+
+  // SwiGLU (even blocks gate, odd ones up), rounded to bf16 into LDS as [row][column], stored 16 bytes a lane.  The odd pair
+  // changes hands row tile by row tile: wave column 0 computes the first (MT + 1) / 2, column 1 the others.
+  unsigned char* tile = lds;
+  float* ex = reinterpret_cast<float*>(lds + (size_t)T::ROWS * T::ACT_LD) + (size_t)wm * MT * 1024;
+  constexpr int EX_SPLIT = (MT + 1) / 2;
+  if (NB & 1) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+      if ((i < EX_SPLIT) == (wn == 1)) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) ex[(i * 16 + v) * 64 + lane] = acc[i][NB - 1][v];
+      }
+    __syncthreads();
+  }
+  auto put = [&](int i, int v, int pair, float g, float u) {
+    const int rl = wm * (MT * 32) + i * 32 + 8 * (v >> 2) + 4 * lg + (v & 3);
+    *reinterpret_cast<bf16_t*>(tile + (size_t)rl * T::ACT_LD + pair * 64 + lr * 2) = (bf16_t)silu_mul(g, u);
+  };
+#pragma unroll
+  for (int p = 0; p < NB / 2; ++p)
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) put(i, v, wn * (NB / 2) + p, acc[i][2 * p][v], acc[i][2 * p + 1][v]);
+  if (NB & 1) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+      if ((i < EX_SPLIT) == (wn == 0)) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const float mine = acc[i][NB - 1][v], other = ex[(i * 16 + v) * 64 + lane];
+          put(i, v, NB - 1, wn == 0 ? mine : other, wn == 0 ? other : mine);
+        }
+      }
+  }
+  __syncthreads();
+  const int ff = N >> 1, per_row = NB * 4;               // 16-byte pieces of a row, four to a pair of blocks
+  for (int e = tid; e < T::ROWS * per_row; e += 256) {
+    const int rl = e / per_row, piece = e % per_row, m = mt0 + rl;
+    const u32x4_t x = *reinterpret_cast<const u32x4_t*>(tile + (size_t)rl * T::ACT_LD + piece * 16);
+    if (m < M && blk0 + (piece >> 2) * 2 < nblk)
+      *reinterpret_cast<u32x4_t*>(act + (size_t)m * ff + (blk0 >> 1) * 32 + piece * 8) = x;
+  }
+}
+
 // ---- fp32: one 32 x 32 tile per workgroup, its eight waves split K (v_mfma_f32_32x32x2_f32) --------
 // The fp32 models are small (256 x 256 to 4096 x 256 weights): latency is the bound, so a tile is as
 // small as a matrix instruction, every wave has an eighth of K to itself and issues its loads up front
@@ -670,6 +867,13 @@ hipError_t ring_allow_lds() {
   return attr;
 }
 
+template <int MT, int NB>
+hipError_t wide_allow_lds() {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_swiglu_wide<MT, NB>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)WideTile<MT, NB>::LDS);
+  return attr;
+}
+
 // launch, with a profiling scope's events attached to the kernel when there are any
 template <typename Kern, typename... Args>
 void launch_kernel(Kern kern, dim3 grid, dim3 block, size_t lds, hipStream_t st, Args... args) {
@@ -715,6 +919,8 @@ hipError_t gemm_prepare() {
   if (e == hipSuccess) e = ring_allow_lds<5, 2, 2>();
   if (e == hipSuccess) e = ring_allow_lds<4, 2, 1>();
   if (e == hipSuccess) e = ring_allow_lds<5, 2, 1>();
+  if (e == hipSuccess) e = wide_allow_lds<4, 4>();
+  if (e == hipSuccess) e = wide_allow_lds<3, 5>();
   return e;
 }
 
@@ -830,6 +1036,25 @@ hipError_t launch_gemm_argmax(hipStream_t st, const void* A, const int32_t* a_ro
   return hipGetLastError();
 }
 
+namespace {
+// Rounds over the CUs times a round's time, in units of 10 ns: chunks x the time of one + start and epilogue.  Measured over
+// 129 to 2112 rows at N = 28672 and 24576, K = 4096: a round takes 63 to 66 us with 5 x 2 tiles, 57 with 4 x 2, 54 with
+// 3 x 2, 97 to 103 with the wide ones, which therefore pay where they save rounds: 352 to 512 rows (113..126 -> 97..104),
+// 1024 x 28672 (244 -> 203), 544 to 576 x 24576 (123 -> 103); elsewhere the others are up to twice as fast.
+int64_t rounds_cost(int tiles, int chunks, int chunk, int fixed) { return (int64_t)((tiles + 255) / 256) * ((int64_t)chunks * chunk + fixed); }
+
+template <int MT, int NB>
+hipError_t launch_swiglu_wide(hipStream_t st, const void* A, const void* W, void* act, int M, int N, int K, const int32_t* m_live) {
+  using T = WideTile<MT, NB>;
+  const hipError_t attr = wide_allow_lds<MT, NB>();
+  if (attr != hipSuccess) return attr;
+  const int m_tiles = (M + T::ROWS - 1) / T::ROWS, n_tiles = ((N >> 5) + T::BLOCKS - 1) / T::BLOCKS;
+  launch_kernel(k_gemm_swiglu_wide<MT, NB>, dim3((m_tiles * n_tiles + 7) / 8 * 8), dim3(256), T::LDS, st, (const bf16_t*)A,
+                (const bf16_t*)W, (bf16_t*)act, M, N, K, m_tiles, n_tiles, m_live);
+  return hipGetLastError();
+}
+}  // namespace
+
 // Fused gate/up projection + SwiGLU (bf16, packed weights whose rows alternate in blocks of 32
 // between gate and up): act[M][ff] = silu(A Wg^T) * (A Wu^T), one pass over K per workgroup.
 hipError_t launch_gemm_swiglu(hipStream_t st, const void* A, const void* W, void* act, int M, int ff, int K,
@@ -837,6 +1062,17 @@ hipError_t launch_gemm_swiglu(hipStream_t st, const void* A, const void* W, void
   if (M <= 0) return hipSuccess;
   GemmPlan p = gemm_plan(ESP_BF16, M, 2 * ff, K);
   p.splits = 1;
+  if (p.nb == 2) {
+    // of a ragged batch the host knows an upper bound only: three quarters of it as a guess
+    const int rows = m_live ? (3 * M + 3) / 4 : M, chunks = K / KC, blocks = (2 * ff) >> 5;
+    const GemmPlan r = gemm_plan(ESP_BF16, rows, 2 * ff, K);
+    const int64_t ring = rounds_cost(r.m_tiles * r.n_tiles, chunks, r.mt >= 5 ? 90 : r.mt == 4 ? 80 : 74, 650);
+    const int64_t w44 = rounds_cost((rows + 255) / 256 * ((blocks + 7) / 8), chunks, 142, 900);
+    const int64_t w35 = rounds_cost((rows + 191) / 192 * ((blocks + 9) / 10), chunks, 142, 900);
+    if (std::min(w44, w35) * 100 < ring * 95 && (uintptr_t)act % 16 == 0 && ff % 8 == 0)   // the result is stored 16 bytes at a time
+      return w44 <= w35 ? launch_swiglu_wide<4, 4>(st, A, W, act, M, 2 * ff, K, m_live)
+                        : launch_swiglu_wide<3, 5>(st, A, W, act, M, 2 * ff, K, m_live);
+  }
   float* out = reinterpret_cast<float*>(act);
 #define ESP_GU_CASE(MT_, NB_)                                                                           \
   if (p.mt == MT_ && p.nb == NB_)                                                                       \

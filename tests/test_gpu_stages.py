@@ -1,6 +1,8 @@
 """Stage parity on the GPU: each C-ABI entry point against the oracle on the same seeded
 inputs.  Integer / index work must be bit-exact; floating point within the stated tolerance
 (row-wise max |diff| / max |oracle|: 2e-2 for bf16 inputs, 1e-4 for fp32)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -87,6 +89,39 @@ def test_gemm_argmax_epilogue(B, M, N, K):
     assert np.array_equal(got, want), np.nonzero(got != want)[0][:8]
     ties = int(sum((logits[i] == logits[i].max()).sum() > 1 for i in range(M)))
     assert ties >= 1
+
+
+@pytest.mark.parametrize("M,ff,K,live", [
+    (353, 14336, 64, None), (512, 14336, 128, None), (511, 14336, 704, None), (1024, 14336, 192, None), (993, 14368, 64, None),   # 4 x 4 tiles
+    (576, 12288, 64, None), (545, 12288, 128, None), (571, 12288, 1088, None), (570, 12320, 192, None),                           # 3 x 5 tiles
+    (700, 14336, 192, 520), (700, 14336, 64, 1), (760, 12288, 128, 760),                                                # live rows of a batch
+    (320, 14336, 128, None), (640, 1056, 64, None), (1, 96, 64, None)])                                                 # other tiles
+def test_gemm_swiglu(B, M, ff, K, live):
+    """The gate/up projection with the SwiGLU in its epilogue, at the sizes where the wide tiles take it (remainders of rows
+    and of columns, one to many chunks of K, an odd number of them) and beside them.  The products are exact in fp32; the sums'
+    order and the hardware's exp and reciprocal (1 ulp each) leave 2e-6 of the row's largest value before the bf16 rounding
+    of half an ulp of eight bits (2^-8).  Rows that are not live stay as they were."""
+    fn = B.load_library()._Z18launch_gemm_swigluP12ihipStream_tPKvS2_PviiiPKi
+    fn.argtypes = [ctypes.c_void_p] * 4 + [ctypes.c_int] * 3 + [ctypes.c_void_p]
+    print(f"swiglu M={M} ff={ff} K={K} live={live}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + ff + K)
+    a = torch.randn(M, K, device="cuda", generator=g).bfloat16()
+    wg, wu = (torch.randn(ff, K, device="cuda", generator=g).mul_(K ** -0.5).bfloat16() for _ in range(2))
+    w = torch.stack([wg.view(ff // 32, 32, K), wu.view(ff // 32, 32, K)], 1).reshape(2 * ff, K).contiguous()   # blocks of 32 alternate
+    packed = B.pack_weight(w)
+    act = torch.full((M + 1, ff), -7.0, dtype=torch.bfloat16, device="cuda")
+    n_live = None if live is None else torch.tensor([live], dtype=torch.int32, device="cuda")
+    assert fn(torch.cuda.current_stream().cuda_stream, a.data_ptr(), packed.data_ptr(), act.data_ptr(), M, ff, K,
+              None if n_live is None else n_live.data_ptr()) == 0
+    rows = M if live is None else live
+    gate, up = a[:rows].double() @ wg.double().T, a[:rows].double() @ wu.double().T
+    want = gate / (1 + torch.exp(-gate)) * up
+    err = (act[:rows].double() - want).abs()
+    assert bool((err <= want.abs() * 2.0 ** -8 + 2e-6 * want.abs().amax(1, keepdim=True)).all()), float((err / want.abs().clamp_min(1e-9)).max())
+    assert bool((act[M:] == -7).all())
+    if live is not None and live < M:
+        assert bool((act[live:] == -7).all())
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (13, 4096, 256), (52, 688, 256), (52, 256, 688), (70, 130, 77)])
