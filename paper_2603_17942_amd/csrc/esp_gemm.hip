@@ -49,7 +49,8 @@ constexpr int A_ROW_BYTES = 144;  // 128 B of bf16 + 16 B pad: conflict-free ds_
 // 2 SwiGLU of interleaved gate/up column blocks to bf16, 3 fp32 tile to out and arg-max pairs to out2
 // RING > 0 (packed weights only): both operands ride a ring of RING chunk stages in LDS, filled
 // by load_to_lds16 two chunks ahead of their use; RING == 0: register rings of depth D.
-template <int MT, int NB, int D, bool TILED, int WM, int EPI, int RING = 0>   // D even; WM wave groups along M
+// NT_W (ring only): weights by nontemporal loads.
+template <int MT, int NB, int D, bool TILED, int WM, int EPI, int RING = 0, bool NT_W = false>   // D even; WM wave groups along M
 __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t* __restrict__ A,
                                                const int32_t* __restrict__ a_rows, const bf16_t* __restrict__ W,
                                                float* __restrict__ out, int M, int N, int K, int splits,
@@ -148,10 +149,10 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
         const unsigned char* src = w_base[nb] + (size_t)c * W_CHUNK;
         const uint32_t dst = sb + A_STAGE + (lw * NB + nb) * 4096;
         // the constant is added to the global and to the LDS address alike
-        if (st == 0) load_to_lds16_sbase<0>(src, lane16, dst);
-        else if (st == 1) load_to_lds16_sbase<1024>(src, lane16, dst);
-        else if (st == 2) load_to_lds16_sbase<2048>(src, lane16, dst);
-        else load_to_lds16_sbase<3072>(src, lane16, dst);
+        if (st == 0) load_to_lds16_sbase<0, NT_W>(src, lane16, dst);
+        else if (st == 1) load_to_lds16_sbase<1024, NT_W>(src, lane16, dst);
+        else if (st == 2) load_to_lds16_sbase<2048, NT_W>(src, lane16, dst);
+        else load_to_lds16_sbase<3072, NT_W>(src, lane16, dst);
       }
     };
     // The loads are issued by four waves of their own.  (Issued by the computing waves between their
@@ -569,13 +570,13 @@ constexpr int RING_STAGES = 3;
 template <int MT, int NB>
 constexpr size_t ring_lds_bytes() { return (size_t)RING_STAGES * (MT * 4096 + 4 * NB * 4096); }
 
-template <int MT, int NB, int EPI>
+template <int MT, int NB, int EPI, bool NT_W>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_bf16_ring(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ a_rows, const bf16_t* __restrict__ W,
     float* __restrict__ out, int M, int N, int K, int splits, int m_tiles, int n_tiles, int a_ld,
     float* __restrict__ out2, const int32_t* __restrict__ draw_pos, uint32_t seed, const int32_t* __restrict__ m_live) {
   extern __shared__ __align__(16) unsigned char lds[];
-  gemm_bf16_body<MT, NB, 2, true, 1, EPI, RING_STAGES>(lds, A, a_rows, W, out, M, N, K, splits, m_tiles, n_tiles, a_ld,
+  gemm_bf16_body<MT, NB, 2, true, 1, EPI, RING_STAGES, NT_W>(lds, A, a_rows, W, out, M, N, K, splits, m_tiles, n_tiles, a_ld,
                                                       out2, draw_pos, seed, m_live);
 }
 
@@ -655,9 +656,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   auto load_a = [&](int j, int c, int stage) {
     load_to_lds16_sbase<0>(a_base + (size_t)min(c, nc - 1) * (KC * 2), aoff[j], lds0 + stage * T::A_STAGE + (wave + 4 * j) * 1024);
   };
-  auto load_w = [&](int j, int h, int stage) {
+  auto load_w = [&](int j, int h, int stage) {           // nontemporal, as the ring's with few row tiles (launch_bf16)
     const int hh = min(h, 2 * nc - 1);
-    load_to_lds16_sbase<0>(w_src[j] + (size_t)(hh >> 1) * W_CHUNK + (hh & 1) * 2048, lane16, ldsw + stage * T::W_STAGE + (wave + 4 * j) * 1024);
+    load_to_lds16_sbase<0, true>(w_src[j] + (size_t)(hh >> 1) * W_CHUNK + (hh & 1) * 2048, lane16, ldsw + stage * T::W_STAGE + (wave + 4 * j) * 1024);
   };
   // this lane's fragments; an odd NB leaves a last pair of blocks, gate in wave column 0 and up in wave column 1
   int a_rd[4];
@@ -871,9 +872,14 @@ __global__ void k_pack_weight(const bf16_t* __restrict__ src, bf16_t* __restrict
 // a stream capture is the first one).
 template <int MT, int NB, int EPI>
 hipError_t ring_allow_lds() {
-  static const hipError_t attr =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_bf16_ring<MT, NB, EPI>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring_lds_bytes<MT, NB>());
+  static const hipError_t attr = [] {
+    for (const void* k : {reinterpret_cast<const void*>(k_gemm_bf16_ring<MT, NB, EPI, false>),
+                          reinterpret_cast<const void*>(k_gemm_bf16_ring<MT, NB, EPI, true>)}) {
+      const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring_lds_bytes<MT, NB>());
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }();
   return attr;
 }
 
@@ -903,7 +909,10 @@ hipError_t launch_bf16(hipStream_t st, const void* A, const int32_t* a_rows, con
   int per_xcd = (total + 7) / 8;
   size_t lds = 2 * (size_t)MT * 32 * A_ROW_BYTES;
   if constexpr (MT * NB >= 8 && TILED) {
-    auto kern = k_gemm_bf16_ring<MT, NB, EPI>;
+    // Nontemporal weights where few row tiles share them.  A step of 320 rows (two) 7511 -> 7387 us, 576 rows of the Qwen3
+    // shape (four) 12227 -> 12105, prefill of 2049 tokens in chunks of 512 (four) 37.17 -> 36.64 ms; with 14 row tiles (16
+    // ragged sequences) 33.83 -> 34.00 ms, so not there.
+    auto kern = p.m_tiles <= 4 ? k_gemm_bf16_ring<MT, NB, EPI, true> : k_gemm_bf16_ring<MT, NB, EPI, false>;
     const hipError_t attr = ring_allow_lds<MT, NB, EPI>();
     if (attr != hipSuccess) return attr;
     const size_t ring_bytes = ring_lds_bytes<MT, NB>();

@@ -52,15 +52,22 @@ __device__ __forceinline__ void load_to_lds16(const void* g, uint32_t lds_addr) 
 // The same with a wave-uniform base address (scalar registers) plus a per-lane byte offset and a
 // constant offset IMM, which the hardware adds to the global address and to the LDS address alike
 // (piece j of a run: IMM = j KB, lds_addr the address of piece 0): one vector register for any
-// number of pieces.
-template <int IMM>
+// number of pieces.  NT: nontemporal, for data that one workgroup (or a few at the same time) reads once.
+template <int IMM, bool NT = false>
 __device__ __forceinline__ void load_to_lds16_sbase(const void* sbase, uint32_t lane_off, uint32_t lds_addr) {
   uint32_t keep;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3 offset:%4\n\ts_mov_b32 m0, %0"
-      : "=&s"(keep)
-      : "s"(lds_addr), "v"(lane_off), "s"(sbase), "n"(IMM)
-      : "memory");
+  if constexpr (NT)
+    asm volatile(
+        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3 offset:%4 nt\n\ts_mov_b32 m0, %0"
+        : "=&s"(keep)
+        : "s"(lds_addr), "v"(lane_off), "s"(sbase), "n"(IMM)
+        : "memory");
+  else
+    asm volatile(
+        "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3 offset:%4\n\ts_mov_b32 m0, %0"
+        : "=&s"(keep)
+        : "s"(lds_addr), "v"(lane_off), "s"(sbase), "n"(IMM)
+        : "memory");
 }
 template <int N_YOUNGER>
 __device__ __forceinline__ void wait_loads_but() {
