@@ -13,6 +13,7 @@
 // Generic path (k_attn_generic): one wave per (row, head, split), any dtype / head_dim multiple of
 // 64; used by the fp32 tiny configuration.
 #include <algorithm>
+#include <type_traits>
 
 #include "esp_internal.h"
 
@@ -293,8 +294,9 @@ __device__ __forceinline__ void ring_unit(bool masked, const unsigned char* kst,
   __builtin_amdgcn_s_setprio(0);
 }
 
-// LPW: 1 KB wave-loads per loading wave and tile (the first 32 / LPW waves of the workgroup load)
-template <int LPW, bool PACKED>
+// LPW: 1 KB wave-loads per loading wave and tile (the first 32 / LPW waves of the workgroup load).  NT: K and V by
+// nontemporal loads.
+template <int LPW, bool PACKED, bool NT>
 __global__ __launch_bounds__(64 * RING_MAX_WAVES) void k_attn_ring(BlockDev b, KvDev kv, int layer, int hq, int hkv,
                                                                   const bf16_t* __restrict__ q,
                                                                   float* __restrict__ part_o,
@@ -366,15 +368,15 @@ __global__ __launch_bounds__(64 * RING_MAX_WAVES) void k_attn_ring(BlockDev b, K
     if (!loader) return;
     const unsigned char* src = src0 + (size_t)(t0 + i) * K_TILE_BYTES;
     const uint32_t dst = lds0 + (i & 3) * STAGE_BYTES + piece0 * 1024;
-    load_to_lds16_sbase<0>(src, lane_off, dst);
-    load_to_lds16_sbase<1024>(src, lane_off, dst);
-    load_to_lds16_sbase<2048>(src, lane_off, dst);
-    load_to_lds16_sbase<3072>(src, lane_off, dst);
+    load_to_lds16_sbase<0, NT>(src, lane_off, dst);
+    load_to_lds16_sbase<1024, NT>(src, lane_off, dst);
+    load_to_lds16_sbase<2048, NT>(src, lane_off, dst);
+    load_to_lds16_sbase<3072, NT>(src, lane_off, dst);
     if (LPW == 8) {
-      load_to_lds16_sbase<0>(src + 4096, lane_off, dst + 4096);
-      load_to_lds16_sbase<1024>(src + 4096, lane_off, dst + 4096);
-      load_to_lds16_sbase<2048>(src + 4096, lane_off, dst + 4096);
-      load_to_lds16_sbase<3072>(src + 4096, lane_off, dst + 4096);
+      load_to_lds16_sbase<0, NT>(src + 4096, lane_off, dst + 4096);
+      load_to_lds16_sbase<1024, NT>(src + 4096, lane_off, dst + 4096);
+      load_to_lds16_sbase<2048, NT>(src + 4096, lane_off, dst + 4096);
+      load_to_lds16_sbase<3072, NT>(src + 4096, lane_off, dst + 4096);
     }
   };
   // Q^T fragments: lane = query column, 8 features per k-step at 16 s + 8 lg.  The compiler places
@@ -589,8 +591,10 @@ __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, i
 // called when a context is created, so that no launch inside a stream capture is the first one)
 hipError_t attn_prepare() {
   static const hipError_t attr = [] {
-    for (const void* k : {reinterpret_cast<const void*>(k_attn_ring<4, false>), reinterpret_cast<const void*>(k_attn_ring<8, false>),
-                          reinterpret_cast<const void*>(k_attn_ring<4, true>), reinterpret_cast<const void*>(k_attn_ring<8, true>)}) {
+    for (const void* k : {reinterpret_cast<const void*>(k_attn_ring<4, false, false>), reinterpret_cast<const void*>(k_attn_ring<8, false, false>),
+                          reinterpret_cast<const void*>(k_attn_ring<4, true, false>), reinterpret_cast<const void*>(k_attn_ring<8, true, false>),
+                          reinterpret_cast<const void*>(k_attn_ring<4, false, true>), reinterpret_cast<const void*>(k_attn_ring<8, false, true>),
+                          reinterpret_cast<const void*>(k_attn_ring<4, true, true>), reinterpret_cast<const void*>(k_attn_ring<8, true, true>)}) {
       const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, RING_LDS_BYTES);
       if (e != hipSuccess) return e;
     }
@@ -710,8 +714,15 @@ hipError_t launch_attn(hipStream_t st, int dtype, const BlockDev& b, const KvDev
     const hipError_t attr = attn_prepare();
     if (attr != hipSuccess) return attr;
     const dim3 grid(((total_wg + 7) / 8) * 8), block(64 * g.waves);
-    const auto kern = g.waves >= 8 ? (packed ? k_attn_ring<4, true> : k_attn_ring<4, false>)
-                                   : (packed ? k_attn_ring<8, true> : k_attn_ring<8, false>);
+    // Nontemporal where a key tile is read by one workgroup only: steps of one row on 2048 keys 3286 -> 3221 us, 68 rows on
+    // 32768 keys 5738 -> 5671; 16 sequences of one row on 4096 keys, eight layers, 1487 -> 1432.  Where several workgroups
+    // read it, 50 and 80 rows got 1 % slower with it and the others stayed the same.
+    const auto pick = [&](auto nt) {
+      constexpr bool NT = decltype(nt)::value;
+      return g.waves >= 8 ? (packed ? k_attn_ring<4, true, NT> : k_attn_ring<4, false, NT>)
+                          : (packed ? k_attn_ring<8, true, NT> : k_attn_ring<8, false, NT>);
+    };
+    const auto kern = p.q_tiles == 1 ? pick(std::true_type{}) : pick(std::false_type{});
     hipLaunchKernelGGL(kern, grid, block, RING_LDS_BYTES, st, b, kv, layer, hq, hkv, (const bf16_t*)q, part_o, part_ml, p.nsplit,
                        p.tiles_per_split, p.q_tiles, p.ct_wg, g.n_full);
   } else {
