@@ -65,6 +65,21 @@ def test_gemm_bf16_ring_depth(B, M, chunks):
     assert rel_err_rows(got, to_np(a) @ to_np(w).T) < 1e-5      # fp32 sums of at most 1664 exact products
 
 
+@pytest.mark.parametrize("M", [64, 65, 96, 128, 640, 641])
+def test_gemm_bf16_cache_policy_edges(B, M):
+    """Both sides of the two lines at which accesses become nontemporal: stores of the partials from three row tiles of 32 on
+    (65 rows), weights up to four row tiles of 160 (640 rows).  Row-major weights are loaded the ordinary way and add in the
+    same order."""
+    N, K = 544, 512
+    print(f"gemm bf16 cache policy M={M} N={N} K={K}", flush=True)
+    a = synth.normal_like((M, K), 1.0, 14, 0, "cuda", torch.bfloat16)
+    w = synth.normal_like((N, K), 0.05, 14, 1, "cuda", torch.bfloat16)
+    wp = B.pack_weight(w)
+    got = B.gemm(a, wp, packed=True).cpu().numpy()
+    assert np.array_equal(got, B.gemm(a, w).cpu().numpy())
+    assert rel_err_rows(got, to_np(a) @ to_np(w).T) < 1e-5      # fp32 sums of 512 exact products
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 512, 128), (68, 4096, 256), (128, 1056, 192), (129, 768, 256), (320, 4096, 512),
                                    (200, 2048, 128), (1344, 1280, 256), (700, 33 * 32, 192), (180, 512, 64)])
 def test_gemm_argmax_epilogue(B, M, N, K):
