@@ -353,7 +353,7 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
   { ESP_PROF(ESP_SITE_GLUE);
   if (packed) {
     bd.packed = c->packed;
-    ESP_HIP(launch_live_rows(s, bd, kd, nodes_bound(blk)));
+    ESP_HIP(launch_live_rows(s, bd, kd, nodes_bound(blk), gate_up_rule(M, ff, d, c->act, true)));
     m_live = bd.n_live();
   }
   ESP_HIP(launch_embed(s, dt, bd, kd, c->embed, mask_embed, c->h, d, m.vocab, c->rope_tab, hd, m.rope_theta,

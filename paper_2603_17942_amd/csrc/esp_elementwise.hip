@@ -37,7 +37,7 @@ __device__ __forceinline__ float block_sum_256(float v, float* red) {
 // Packed rows of a batch (BlockDev): one workgroup per sequence adds up the row counts of the sequences before it
 // and writes its own rows' places.  A sequence that is not valid (or a count that does not fit) has no rows; its tree
 // rows follow the block alone, as in k_node_rows.
-__global__ __launch_bounds__(256) void k_live_rows(BlockDev b, KvDev kv, int max_nodes) {
+__global__ __launch_bounds__(256) void k_live_rows(BlockDev b, KvDev kv, int max_nodes, GateUpRule gate_up) {
   __shared__ float red[4];
   const int seq = blockIdx.x;
   auto rows_of = [&](int s) {
@@ -66,12 +66,14 @@ __global__ __launch_bounds__(256) void k_live_rows(BlockDev b, KvDev kv, int max
     if (seq + 1 == b.batch) {
       b.n_live()[0] = first + nr;
       b.n_live()[1] = node0 + nodes_of(seq);
+      const int tile = gate_up.tile(first + nr);
+      for (int t = 0; t < GU_TILES; ++t) b.n_live()[2 + t] = t == tile ? first + nr : 0;
     }
   }
 }
 
-hipError_t launch_live_rows(hipStream_t st, const BlockDev& b, const KvDev& kv, int max_nodes) {
-  hipLaunchKernelGGL(k_live_rows, dim3(b.batch), dim3(256), 0, st, b, kv, max_nodes);
+hipError_t launch_live_rows(hipStream_t st, const BlockDev& b, const KvDev& kv, int max_nodes, const GateUpRule& gate_up) {
+  hipLaunchKernelGGL(k_live_rows, dim3(b.batch), dim3(256), 0, st, b, kv, max_nodes, gate_up);
   return hipGetLastError();
 }
 

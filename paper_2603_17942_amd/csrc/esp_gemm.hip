@@ -893,7 +893,7 @@ hipError_t wide_allow_lds() {
 // launch, with a profiling scope's events attached to the kernel when there are any
 template <typename Kern, typename... Args>
 void launch_kernel(Kern kern, dim3 grid, dim3 block, size_t lds, hipStream_t st, Args... args) {
-  if (g_launch_events.start) {
+  if (g_launch_events.start || g_launch_events.stop) {
     hipExtLaunchKernelGGL(kern, grid, block, (uint32_t)lds, st, g_launch_events.start, g_launch_events.stop, 0, args...);
     g_launch_events = LaunchEvents{};
   } else {
@@ -1056,12 +1056,6 @@ hipError_t launch_gemm_argmax(hipStream_t st, const void* A, const int32_t* a_ro
 }
 
 namespace {
-// Rounds over the CUs times a round's time, in units of 10 ns: chunks x the time of one + start and epilogue.  Measured over
-// 129 to 2112 rows at N = 28672 and 24576, K = 4096: a round takes 63 to 66 us with 5 x 2 tiles, 57 with 4 x 2, 54 with
-// 3 x 2, 97 to 103 with the wide ones, which therefore pay where they save rounds: 352 to 512 rows (113..126 -> 97..104),
-// 1024 x 28672 (244 -> 203), 544 to 576 x 24576 (123 -> 103); elsewhere the others are up to twice as fast.
-int64_t rounds_cost(int tiles, int chunks, int chunk, int fixed) { return (int64_t)((tiles + 255) / 256) * ((int64_t)chunks * chunk + fixed); }
-
 template <int MT, int NB>
 hipError_t launch_swiglu_wide(hipStream_t st, const void* A, const void* W, void* act, int M, int N, int K, const int32_t* m_live) {
   using T = WideTile<MT, NB>;
@@ -1074,38 +1068,55 @@ hipError_t launch_swiglu_wide(hipStream_t st, const void* A, const void* W, void
 }
 }  // namespace
 
+GateUpRule gate_up_rule(int M, int ff, int K, const void* act, bool ragged) {
+  const GemmPlan p = gemm_plan(ESP_BF16, M, 2 * ff, K);
+  GateUpRule r;
+  r.mt = p.mt; r.chunks = K / KC; r.blocks = (2 * ff) >> 5;
+  if (p.nb != 2 || (uintptr_t)act % 16 || ff % 8) return r;      // the wide tiles store 16 bytes at a time
+  constexpr unsigned all = (1u << GU_TILES) - 1;
+  r.plan_percent = ragged ? 108 : 95;
+  r.launched = 1u << r.tile(M, all);
+  if (ragged)                                                    // (every tile ends at a multiple of 32 rows)
+    for (int rows = (2 * M / 3) & ~31; rows < M; rows += 32) r.launched |= 1u << r.tile(std::max(rows, 1), all);
+  return r;
+}
+unsigned gate_up_tiles(int M, int ff, int K, const void* act, bool ragged) { return gate_up_rule(M, ff, K, act, ragged).launched; }
+
 // Fused gate/up projection + SwiGLU (bf16, packed weights whose rows alternate in blocks of 32
 // between gate and up): act[M][ff] = silu(A Wg^T) * (A Wu^T), one pass over K per workgroup.
 hipError_t launch_gemm_swiglu(hipStream_t st, const void* A, const void* W, void* act, int M, int ff, int K,
-                              const int32_t* m_live) {
+                              const int32_t* live) {
   if (M <= 0) return hipSuccess;
   GemmPlan p = gemm_plan(ESP_BF16, M, 2 * ff, K);
   p.splits = 1;
-  if (p.nb == 2) {
-    // of a ragged batch the host knows an upper bound only: three quarters of it as a guess
-    const int rows = m_live ? (3 * M + 3) / 4 : M, chunks = K / KC, blocks = (2 * ff) >> 5;
-    const GemmPlan r = gemm_plan(ESP_BF16, rows, 2 * ff, K);
-    const int64_t ring = rounds_cost(r.m_tiles * r.n_tiles, chunks, r.mt >= 5 ? 90 : r.mt == 4 ? 80 : 74, 650);
-    const int64_t w44 = rounds_cost((rows + 255) / 256 * ((blocks + 7) / 8), chunks, 142, 900);
-    const int64_t w35 = rounds_cost((rows + 191) / 192 * ((blocks + 9) / 10), chunks, 142, 900);
-    if (std::min(w44, w35) * 100 < ring * 95 && (uintptr_t)act % 16 == 0 && ff % 8 == 0)   // the result is stored 16 bytes at a time
-      return w44 <= w35 ? launch_swiglu_wide<4, 4>(st, A, W, act, M, 2 * ff, K, m_live)
-                        : launch_swiglu_wide<3, 5>(st, A, W, act, M, 2 * ff, K, m_live);
-  }
   float* out = reinterpret_cast<float*>(act);
+  auto launch = [&](int tile, const int32_t* m_live) -> hipError_t {
+    if (tile == GU_256x256) return launch_swiglu_wide<4, 4>(st, A, W, act, M, 2 * ff, K, m_live);
+    if (tile == GU_192x320) return launch_swiglu_wide<3, 5>(st, A, W, act, M, 2 * ff, K, m_live);
 #define ESP_GU_CASE(MT_, NB_)                                                                           \
   if (p.mt == MT_ && p.nb == NB_)                                                                       \
     return launch_bf16<MT_, NB_, true, (MT_ * NB_ >= 8 ? 2 : 4), 2>(st, A, nullptr, W, out, M, 2 * ff, K, p, 0, nullptr, \
                                                                     nullptr, 0u, m_live);
-  ESP_GU_CASE(1, 1)
-  ESP_GU_CASE(2, 1)
-  ESP_GU_CASE(3, 1)
-  ESP_GU_CASE(4, 1)
-  ESP_GU_CASE(3, 2)
-  ESP_GU_CASE(4, 2)
-  ESP_GU_CASE(5, 2)
+    ESP_GU_CASE(1, 1)
+    ESP_GU_CASE(2, 1)
+    ESP_GU_CASE(3, 1)
+    ESP_GU_CASE(4, 1)
+    ESP_GU_CASE(3, 2)
+    ESP_GU_CASE(4, 2)
+    ESP_GU_CASE(5, 2)
 #undef ESP_GU_CASE
-  return hipErrorInvalidValue;
+    return hipErrorInvalidValue;
+  };
+  const unsigned tiles = gate_up_tiles(M, ff, K, act, live != nullptr);
+  if ((tiles & (tiles - 1)) == 0) return launch(__builtin_ctz(tiles), live);
+  const LaunchEvents span = g_launch_events;             // a profiling span covers all of them
+  for (int t = 0; t < GU_TILES; ++t) {
+    if (!((tiles >> t) & 1u)) continue;
+    g_launch_events = LaunchEvents{(tiles & ((1u << t) - 1)) == 0 ? span.start : nullptr, (tiles >> (t + 1)) == 0 ? span.stop : nullptr};
+    const hipError_t e = launch(t, live + 2 + t);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_pack_weight(hipStream_t st, const void* src, void* dst, int N, int K) {

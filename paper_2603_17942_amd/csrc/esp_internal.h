@@ -127,8 +127,42 @@ hipError_t launch_gemm(hipStream_t st, int dtype, const void* A, const int32_t* 
 hipError_t launch_pack_weight(hipStream_t st, const void* src, void* dst, int N, int K);
 // one-time kernel attributes of the GEMM kernels (dynamic LDS limits); call before the first launch
 hipError_t gemm_prepare();
+// Tile of the gate/up projection: gemm_plan's, or, above 128 rows, a wide one of 256 x 256 or 192 x 320 where that saves
+// rounds over the 256 CUs.  Cost: rounds times a round's time, in units of 10 ns: chunks x the time of one + start and
+// epilogue.  Measured over 129 to 2112 rows at N = 28672 and 24576, K = 4096: a round takes 63 to 66 us with 5 x 2 tiles, 57
+// with 4 x 2, 54 with 3 x 2, 97 to 103 with the wide ones, which therefore pay where they save rounds: 352 to 512 rows
+// (113..126 -> 97..104), 1024 x 28672 (244 -> 203), 544 to 576 x 24576 (123 -> 103); elsewhere the others are up to twice as
+// fast.
+// Of a batch of M block rows only the device knows how many are there: the host launches every tile that a number from two
+// thirds of M up asks for, the device (k_live_rows) hands the rows to the best of these, and the others end at once (1.6 us).
+// One tile, taken for a guess of three quarters: 640 rows all there took 180 us at N = 28672 (256 x 256 in two rounds) where the
+// ring takes 135, 400 all there 130 in two rounds of the ring.  Among launched tiles a wide one is taken also where the cost is
+// level: 641 to 960 of 1344 rows, two rounds of 256 x 256 against three of the ring, 15 to 25 us faster a layer.
+enum GateUpTile { GU_PLAN = 0, GU_256x256 = 1, GU_192x320 = 2, GU_TILES = 3 };
+struct GateUpRule {
+  int mt = 1, chunks = 0, blocks = 0;      // row tiles of 32 of gemm_plan's tile; chunks of 64 of K; column blocks of 32
+  unsigned launched = 1u << GU_PLAN;       // bit t: tile t is launched
+  int plan_percent = 95;                   // weight of the plan's tile
+  __host__ __device__ GateUpTile tile(int rows) const { return tile(rows, launched); }
+  __host__ __device__ GateUpTile tile(int rows, unsigned among) const {
+    const int per[GU_TILES] = {32 * mt, 256, 192}, cols[GU_TILES] = {8, 8, 10};
+    const int chunk[GU_TILES] = {mt >= 5 ? 90 : mt == 4 ? 80 : 74, 142, 142}, fixed[GU_TILES] = {650, 900, 900};
+    int best = GU_PLAN;
+    int64_t best_cost = INT64_MAX;
+    for (int t = 0; t < GU_TILES; ++t) {
+      if (!((among >> t) & 1u)) continue;
+      const int64_t n = (int64_t)((rows + per[t] - 1) / per[t]) * ((blocks + cols[t] - 1) / cols[t]);
+      const int64_t cost = (n + 255) / 256 * ((int64_t)chunks * chunk[t] + fixed[t]) * (t == GU_PLAN ? plan_percent : 100);
+      if (cost < best_cost) { best_cost = cost; best = t; }
+    }
+    return (GateUpTile)best;
+  }
+};
+GateUpRule gate_up_rule(int M, int ff, int K, const void* act, bool ragged);
+unsigned gate_up_tiles(int M, int ff, int K, const void* act, bool ragged);   // what launch_gemm_swiglu launches
+// live (device, may be null): BlockDev::n_live of a batch with packed rows
 hipError_t launch_gemm_swiglu(hipStream_t st, const void* A, const void* W, void* act, int M, int ff, int K,
-                              const int32_t* m_live = nullptr);
+                              const int32_t* live = nullptr);
 // LM head with the arg-max taken in the GEMM epilogue (bf16, packed weights, <= 128 rows, one split)
 bool gemm_argmax_supported(int dtype, int M, int N, int K, bool with_logits);
 size_t gemm_argmax_scratch_floats(int M, int N);
@@ -150,13 +184,13 @@ struct BlockDev {   // device-side view of esp_block + esp_kv scalars, passed by
   int32_t* packed = nullptr;
   __host__ __device__ size_t rows() const { return (size_t)batch * rows_per_seq; }
   // block row of packed row m; packed row of a block row (-1: not there); first packed row of a sequence; tree rows
-  // before a sequence; [0] rows and [1] tree rows of the batch
+  // before a sequence; [0] rows and [1] tree rows of the batch, [2 + t] rows that gate/up tile t computes (all or none)
   __host__ __device__ int32_t* live_rows() const { return packed; }
   __host__ __device__ int32_t* packed_row() const { return packed + rows(); }
   __host__ __device__ int32_t* seq_row0() const { return packed + 2 * rows(); }
   __host__ __device__ int32_t* seq_node0() const { return packed + 2 * rows() + batch; }
   __host__ __device__ int32_t* n_live() const { return packed + 2 * rows() + 2 * batch; }
-  static size_t packed_ints(size_t rows, size_t batch) { return 2 * rows + 2 * batch + 2; }
+  static size_t packed_ints(size_t rows, size_t batch) { return 2 * rows + 2 * batch + 2 + GU_TILES; }
 };
 // where row r of a sequence sits in the activations
 template <bool PACKED>
@@ -172,7 +206,7 @@ struct KvDev {
 };
 
 // fills b.packed from the row counts, which only the device knows
-hipError_t launch_live_rows(hipStream_t st, const BlockDev& b, const KvDev& kv, int max_nodes);
+hipError_t launch_live_rows(hipStream_t st, const BlockDev& b, const KvDev& kv, int max_nodes, const GateUpRule& gate_up);
 hipError_t launch_embed(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, const void* embed,
                         const void* mask_embed, float* h, int d, int vocab, float* rope_tab, int hd,
                         float theta, int32_t* status, size_t mask_seq_stride);

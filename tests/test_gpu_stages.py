@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 import torch
 
-from util import O, oracle_model, small_shape, synth, to_np
+from util import O, internal, oracle_model, small_shape, synth, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -106,19 +106,27 @@ def test_gemm_argmax_epilogue(B, M, N, K):
     assert ties >= 1
 
 
-@pytest.mark.parametrize("M,ff,K,live", [
-    (353, 14336, 64, None), (512, 14336, 128, None), (511, 14336, 704, None), (1024, 14336, 192, None), (993, 14368, 64, None),   # 4 x 4 tiles
-    (576, 12288, 64, None), (545, 12288, 128, None), (571, 12288, 1088, None), (570, 12320, 192, None),                           # 3 x 5 tiles
-    (700, 14336, 192, 520), (700, 14336, 64, 1), (760, 12288, 128, 760),                                                # live rows of a batch
-    (320, 14336, 128, None), (640, 1056, 64, None), (1, 96, 64, None)])                                                 # other tiles
-def test_gemm_swiglu(B, M, ff, K, live):
-    """The gate/up projection with the SwiGLU in its epilogue, at the sizes where the wide tiles take it (remainders of rows
-    and of columns, one to many chunks of K, an odd number of them) and beside them.  The products are exact in fp32; the sums'
+@pytest.mark.parametrize("M,ff,K,live,tile", [
+    (353, 14336, 64, None, 1), (512, 14336, 128, None, 1), (511, 14336, 704, None, 1), (1024, 14336, 192, None, 1), (993, 14368, 64, None, 1),
+    (576, 12288, 64, None, 2), (545, 12288, 128, None, 2), (571, 12288, 1088, None, 2), (570, 12320, 192, None, 2),
+    (700, 14336, 192, 520, 0), (700, 14336, 64, 1, 0),                                               # live rows of a batch, one tile
+    (512, 14336, 192, 385, 1), (512, 14336, 64, 1, 1), (512, 14336, 64, 256, 1), (512, 14336, 64, 257, 1), (512, 14336, 64, 512, 1),
+    (640, 14336, 192, 0, 1), (640, 14336, 192, 300, 1), (640, 14336, 192, 512, 1), (640, 14336, 192, 640, 1),   # two tiles launched
+    (640, 14336, 192, 513, 0), (640, 14336, 64, 1, 0), (640, 14336, 64, 640, 0),
+    (560, 12288, 128, 1, 2), (560, 12288, 128, 193, 2), (560, 12288, 128, 560, 2), (560, 12288, 128, 512, 1),
+    (640, 12288, 128, 500, 1), (640, 12288, 128, 570, 2), (640, 12288, 128, 640, 0), (760, 12288, 128, 760, 0),
+    (320, 14336, 128, None, 0), (640, 1056, 64, None, 0), (1, 96, 64, None, 0)])
+def test_gemm_swiglu(B, M, ff, K, live, tile):
+    """The gate/up projection with the SwiGLU in its epilogue, on gemm_plan's tiles (tile 0) and on the wide ones of 256 x 256
+    (1) and 192 x 320 (2): remainders of rows and of columns, one to many chunks of K, an odd number of them, and of a batch
+    any number of live rows.  The tile is the one that the sizes ask for, or, in a batch that several are launched for, the
+    one that is handed the rows, so a case that would run on another fails.  The products are exact in fp32; the sums'
     order and the hardware's exp and reciprocal (1 ulp each) leave 2e-6 of the row's largest value before the bf16 rounding
     of half an ulp of eight bits (2^-8).  Rows that are not live stay as they were."""
-    fn = B.load_library()._Z18launch_gemm_swigluP12ihipStream_tPKvS2_PviiiPKi
-    fn.argtypes = [ctypes.c_void_p] * 4 + [ctypes.c_int] * 3 + [ctypes.c_void_p]
-    print(f"swiglu M={M} ff={ff} K={K} live={live}", flush=True)
+    c = ctypes
+    fn = internal("launch_gemm_swiglu", *[c.c_void_p] * 4, *[c.c_int] * 3, c.c_void_p)
+    tiles = internal("gate_up_tiles", c.c_int, c.c_int, c.c_int, c.c_void_p, c.c_bool, restype=c.c_uint)
+    print(f"swiglu M={M} ff={ff} K={K} live={live} tile={tile}", flush=True)
     g = torch.Generator(device="cuda")
     g.manual_seed(M + ff + K)
     a = torch.randn(M, K, device="cuda", generator=g).bfloat16()
@@ -126,17 +134,19 @@ def test_gemm_swiglu(B, M, ff, K, live):
     w = torch.stack([wg.view(ff // 32, 32, K), wu.view(ff // 32, 32, K)], 1).reshape(2 * ff, K).contiguous()   # blocks of 32 alternate
     packed = B.pack_weight(w)
     act = torch.full((M + 1, ff), -7.0, dtype=torch.bfloat16, device="cuda")
-    n_live = None if live is None else torch.tensor([live], dtype=torch.int32, device="cuda")
+    launched = tiles(M, ff, K, act.data_ptr(), live is not None)
+    assert launched == 1 << tile or (live is not None and launched & (1 << tile)), bin(launched)
+    # rows and tree rows of the batch, then what each tile computes
+    counts = None if live is None else torch.tensor([live, 0] + [live if t == tile else 0 for t in range(3)], dtype=torch.int32, device="cuda")
     assert fn(torch.cuda.current_stream().cuda_stream, a.data_ptr(), packed.data_ptr(), act.data_ptr(), M, ff, K,
-              None if n_live is None else n_live.data_ptr()) == 0
+              None if counts is None else counts.data_ptr()) == 0
     rows = M if live is None else live
-    gate, up = a[:rows].double() @ wg.double().T, a[:rows].double() @ wu.double().T
-    want = gate / (1 + torch.exp(-gate)) * up
-    err = (act[:rows].double() - want).abs()
-    assert bool((err <= want.abs() * 2.0 ** -8 + 2e-6 * want.abs().amax(1, keepdim=True)).all()), float((err / want.abs().clamp_min(1e-9)).max())
-    assert bool((act[M:] == -7).all())
-    if live is not None and live < M:
-        assert bool((act[live:] == -7).all())
+    if rows:
+        gate, up = a[:rows].double() @ wg.double().T, a[:rows].double() @ wu.double().T
+        want = gate / (1 + torch.exp(-gate)) * up
+        err = (act[:rows].double() - want).abs()
+        assert bool((err <= want.abs() * 2.0 ** -8 + 2e-6 * want.abs().amax(1, keepdim=True)).all()), float((err / want.abs().clamp_min(1e-9)).max())
+    assert bool((act[rows:] == -7).all())
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (13, 4096, 256), (52, 688, 256), (52, 256, 688), (70, 130, 77)])

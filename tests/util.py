@@ -1,5 +1,7 @@
 """Shared test plumbing: turn synthetic torch inputs into the oracle's containers."""
+import ctypes
 import os
+import subprocess
 import sys
 
 import numpy as np
@@ -10,7 +12,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 from oracle import esp_oracle as O  # noqa: E402
-from paper_2603_17942_amd import synth  # noqa: E402
+from paper_2603_17942_amd import binding, synth  # noqa: E402
 
 
 def to_np(t):
@@ -26,6 +28,17 @@ def oracle_model(shape: synth.ModelShape, weights: dict, layers=None) -> O.Model
          "layers": [{k: to_np(v) for k, v in weights["layers"][l].items()} for l in range(n_layers)]}
     return O.Model(n_layers, shape.d_model, shape.n_q_heads, shape.n_kv_heads, shape.head_dim,
                    shape.d_ff, shape.vocab, shape.rope_theta, shape.rms_eps, shape.qk_norm, w)
+
+
+def internal(name, *argtypes, restype=ctypes.c_int):
+    """A C++ function of the built library that is not part of the C ABI, by its plain name."""
+    prefix = f"_Z{len(name)}{name}"
+    out = subprocess.run(["nm", "-D", "--defined-only", binding.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    found = [s for s in (line.split()[-1] for line in out.splitlines()) if s.startswith(prefix)]
+    assert len(found) == 1, (name, found)
+    fn = getattr(binding.load_library(), found[0])
+    fn.argtypes, fn.restype = list(argtypes), restype
+    return fn
 
 
 def small_shape(**kw) -> synth.ModelShape:
