@@ -1073,11 +1073,10 @@ GateUpRule gate_up_rule(int M, int ff, int K, const void* act, bool ragged) {
   GateUpRule r;
   r.mt = p.mt; r.chunks = K / KC; r.blocks = (2 * ff) >> 5;
   if (p.nb != 2 || (uintptr_t)act % 16 || ff % 8) return r;      // the wide tiles store 16 bytes at a time
-  constexpr unsigned all = (1u << GU_TILES) - 1;
-  r.plan_percent = ragged ? 108 : 95;
-  r.launched = 1u << r.tile(M, all);
+  r.ragged = ragged;
+  r.launched = 1u << r.tile(M, false);
   if (ragged)                                                    // (every tile ends at a multiple of 32 rows)
-    for (int rows = (2 * M / 3) & ~31; rows < M; rows += 32) r.launched |= 1u << r.tile(std::max(rows, 1), all);
+    for (int rows = (2 * M / 3) & ~31; rows < M; rows += 32) r.launched |= 1u << r.tile(std::max(rows, 1), false);
   return r;
 }
 unsigned gate_up_tiles(int M, int ff, int K, const void* act, bool ragged) { return gate_up_rule(M, ff, K, act, ragged).launched; }

@@ -136,26 +136,33 @@ hipError_t gemm_prepare();
 // Of a batch of M block rows only the device knows how many are there: the host launches every tile that a number from two
 // thirds of M up asks for, the device (k_live_rows) hands the rows to the best of these, and the others end at once (1.6 us).
 // One tile, taken for a guess of three quarters: 640 rows all there took 180 us at N = 28672 (256 x 256 in two rounds) where the
-// ring takes 135, 400 all there 130 in two rounds of the ring.  Among launched tiles a wide one is taken also where the cost is
-// level: 641 to 960 of 1344 rows, two rounds of 256 x 256 against three of the ring, 15 to 25 us faster a layer.
+// ring takes 135, 400 all there 130 in two rounds of the ring.  There the last round counts by how full it is, since rounds
+// alone call two of 256 x 256 and three of the ring level: N = 28672, 660 to 768 rows 187 to 190 against 187 to 192 us (and 15 us
+// less in a step, whose other launches the ring's ordinary weight loads slow down), 769 to 960 rows 203 against 193 to 200.
 enum GateUpTile { GU_PLAN = 0, GU_256x256 = 1, GU_192x320 = 2, GU_TILES = 3 };
 struct GateUpRule {
   int mt = 1, chunks = 0, blocks = 0;      // row tiles of 32 of gemm_plan's tile; chunks of 64 of K; column blocks of 32
+  bool ragged = false;
   unsigned launched = 1u << GU_PLAN;       // bit t: tile t is launched
-  int plan_percent = 95;                   // weight of the plan's tile
-  __host__ __device__ GateUpTile tile(int rows) const { return tile(rows, launched); }
-  __host__ __device__ GateUpTile tile(int rows, unsigned among) const {
+  // the tile for that many rows, of all (what to launch) or of the launched ones
+  __host__ __device__ GateUpTile tile(int rows, bool of_launched) const {
+    int64_t round[GU_TILES], n[GU_TILES], whole[GU_TILES], filled[GU_TILES];
     const int per[GU_TILES] = {32 * mt, 256, 192}, cols[GU_TILES] = {8, 8, 10};
-    const int chunk[GU_TILES] = {mt >= 5 ? 90 : mt == 4 ? 80 : 74, 142, 142}, fixed[GU_TILES] = {650, 900, 900};
-    int best = GU_PLAN;
-    int64_t best_cost = INT64_MAX;
     for (int t = 0; t < GU_TILES; ++t) {
-      if (!((among >> t) & 1u)) continue;
-      const int64_t n = (int64_t)((rows + per[t] - 1) / per[t]) * ((blocks + cols[t] - 1) / cols[t]);
-      const int64_t cost = (n + 255) / 256 * ((int64_t)chunks * chunk[t] + fixed[t]) * (t == GU_PLAN ? plan_percent : 100);
-      if (cost < best_cost) { best_cost = cost; best = t; }
+      round[t] = t == GU_PLAN ? (int64_t)chunks * (mt >= 5 ? 90 : mt == 4 ? 80 : 74) + 650 : (int64_t)chunks * 142 + 900;
+      n[t] = (int64_t)((rows + per[t] - 1) / per[t]) * ((blocks + cols[t] - 1) / cols[t]);
+      whole[t] = (n[t] + 255) / 256 * round[t];
+      const int64_t before = n[t] > 0 ? (n[t] - 1) / 256 : 0;        // rounds before the last, which takes so many per cent of one:
+      filled[t] = round[t] * (before * 25600 + (t == GU_PLAN ? 95 : 78) * 256 + (t == GU_PLAN ? 44 : 36) * (n[t] - 256 * before));
     }
-    return (GateUpTile)best;
+    const bool plan = !of_launched || (launched >> GU_PLAN & 1u), w44 = !of_launched || (launched >> GU_256x256 & 1u),
+               w35 = !of_launched || (launched >> GU_192x320 & 1u);
+    if (!w44 && !w35) return GU_PLAN;
+    const int64_t* c = of_launched ? filled : whole;
+    const GateUpTile w = w44 && (!w35 || c[GU_256x256] <= c[GU_192x320]) ? GU_256x256 : GU_192x320;
+    if (!plan) return w;
+    if (!ragged) return whole[w] * 100 < whole[GU_PLAN] * 95 ? w : GU_PLAN;
+    return filled[w] * 100 < filled[GU_PLAN] * 98 ? w : GU_PLAN;
   }
 };
 GateUpRule gate_up_rule(int M, int ff, int K, const void* act, bool ragged);
