@@ -26,3 +26,39 @@ def test_gate_up_tiles(m, ff, full, batch):
     assert tiles(m, ff, 4096, None, False) == full
     assert tiles(m, ff, 4096, None, True) == batch
     assert tiles(m, ff, 4096, 8, True) == 0b001             # results off the 16-byte alignment of the wide tiles' stores
+
+
+class AttnPlan(C.Structure):
+    _fields_ = [("nsplit", C.c_int), ("tiles_per_split", C.c_int), ("q_tiles", C.c_int), ("ct_wg", C.c_int)]
+
+
+def attn_plan(dtype, hd, batch, rows, hq, hkv, keys):
+    p = internal("attn_plan", *[C.c_int] * 7, restype=AttnPlan)(dtype, hd, batch, rows, hq, hkv, keys)
+    return p.q_tiles, p.ct_wg, p.nsplit, p.tiles_per_split
+
+
+@pytest.mark.parametrize("dtype,hd", [(binding.ESP_F32, 64), (binding.ESP_F32, 128), (binding.ESP_BF16, 64)])
+def test_generic_attention_splits_grow_with_the_root_of_the_tiles(dtype, hd):
+    """The generic kernel's merge walks the splits one after the other: with few rows a long cache is not cut into a key tile
+    each (63 splits at 4000 keys took twice as long as 16), a short one is; many rows fill the chip without splits."""
+    for keys, splits in [(0, 1), (60, 1), (64, 2), (188, 3), (319, 5), (1000, 8), (4000, 16), (16000, 32), (63999, 63)]:
+        _, _, ns, tps = attn_plan(dtype, hd, 1, 1, 4, 2, keys)
+        nt = (keys + 1 + 63) // 64
+        assert ns == splits and (ns - 1) * tps < nt <= ns * tps, (keys, ns, tps)
+    assert attn_plan(dtype, hd, 4, 300, 4, 2, 4000)[2] == 1
+
+
+def test_ring_attention_plans_fit_their_workspace():
+    """Whatever the plan, its partials fit what a context reserves for its largest batch and block."""
+    c = C
+    need = internal("attn_partial_floats", *[c.c_int] * 6, c.POINTER(AttnPlan), restype=c.c_size_t)
+    bound = internal("attn_partial_floats_bound", *[c.c_int] * 6, restype=c.c_size_t)
+    fn = internal("attn_plan", *[c.c_int] * 7, restype=AttnPlan)
+    for dtype, hd, hq, hkv in [(binding.ESP_BF16, 128, 32, 8), (binding.ESP_BF16, 128, 16, 2), (binding.ESP_F32, 64, 4, 2)]:
+        for batch in (1, 2, 5, 16):
+            for rows in (1, 7, 50, 101, 320, 576):
+                most = bound(dtype, batch, 576, hq, hkv, hd)
+                for keys in (0, 300, 2048, 9000, 32768):
+                    p = fn(dtype, hd, batch, rows, hq, hkv, keys)
+                    assert 1 <= p.nsplit <= 64 and p.nsplit * p.tiles_per_split * 64 >= keys + rows
+                    assert need(dtype, batch, rows, hq, hkv, hd, p) <= most, (dtype, batch, rows, keys)
