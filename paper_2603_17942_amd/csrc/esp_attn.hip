@@ -662,18 +662,24 @@ AttnPlan attn_plan(int dtype, int hd, int batch, int rows_per_seq, int hq, int h
   // each key tile's loads; more splits fill the CUs, but every one costs a partial (m, l, O) per column tile (16 KB,
   // written and read back).  Cost of a candidate in units of 10 ns: the two launches + rounds over the CUs x (start and
   // end of a workgroup + its key tiles x the time of one: the SIMD with the most half-tiles, or the loads of 32 KB with
-  // that many CUs at it) + merge per partial column tile.  Fitted to 7200 measured candidates of 240 shapes (1 to 512 rows, 64 to 32768 keys,
-  // batches of 1 to 16; model within 7 %).  The plan above (as many column tiles as twelve waves hold) stays unless the
-  // model sees 4 % in another: over the 240 shapes 0.948 of its time on average, 5 of them slower by 5 to 7 % (five
-  // sequences of 200 rows on short caches among them), the others by at most 2 %.
+  // that many CUs at it) + merge per partial column tile.  Fitted to 7200 measured candidates of 240 shapes (1 to 512 rows,
+  // 64 to 32768 keys, batches of 1 to 16; model within 7 %).  The plan above (as many column tiles as twelve waves hold)
+  // stays unless the model sees 4 % in another.  Where the model was too hopeful, against measured times of 469 shapes with the
+  // cache out of the last-level cache: one or two column tiles take longer with all CUs at it; and a single split with four or
+  // more column tiles, which leaves all masked key tiles of a column to one wave, was 3 to 11 % slower than the plan above where
+  // that is one round too (five sequences of 200 rows on 600 keys 38.6 us, 35.1 in two splits; three of 320 on 256 keys 35.4, 30.3), and
+  // with nearly every CU on one long split 25 us of 260 (eight sequences of 200 rows on 8192 keys, in a step).  Over the
+  // shapes 0.948 of the plan above's time on average, four of them slower by 2 to 4.5 %, the others by at most 1.5 %.
   // Attention and merge of a layer: 90 rows on 2048 keys 26.6 -> 19.6 us, 132 rows on 1000 keys 24.5 -> 17.6.
   static const int tile_time[RING_MAX_WAVES] = {84, 70, 104, 110, 120, 126, 138, 150, 165, 175, 208, 218};
   auto cost = [&](int q, int c, int ns, int tps) {
-    const int64_t groups = (int64_t)q * hkv * batch, rounds = (groups * ns + 255) / 256;
+    const int64_t groups = (int64_t)q * hkv * batch, rounds = (groups * ns + 255) / 256, busy = std::min<int64_t>(groups * ns, 256);
     const bool short_unpaired = c <= 2 && tps < 3;
-    const int64_t tile = std::max<int64_t>(short_unpaired ? 104 : tile_time[c - 1], 80 * std::min<int64_t>(groups * ns, 256) / 256);
+    const int64_t tile = std::max<int64_t>(short_unpaired ? 104 : tile_time[c - 1] + (c <= 2 ? 6 * busy / 256 : 0), 80 * busy / 256);
     return 880 + rounds * ((short_unpaired ? 160 : 180) + tps * tile) + groups * c * ns * 55 / 100;
   };
+  const int64_t base_wg = (int64_t)p.q_tiles * hkv * batch * p.nsplit;
+  const bool base_split = p.nsplit > 1;
   int64_t best_cost = cost(p.q_tiles, p.ct_wg, p.nsplit, p.tiles_per_split) * 96 / 100;
   for (int want = std::min(ct, RING_MAX_WAVES); want >= 1; --want) {
     const int q = (ct + want - 1) / want, c = (ct + q - 1) / q;
@@ -683,7 +689,11 @@ AttnPlan attn_plan(int dtype, int hd, int batch, int rows_per_seq, int hq, int h
       const int tps = (nt + ns - 1) / ns;
       if (ns > 1 && tps < 2) break;                       // (one row, 400 keys: 10.6 us in four splits, 11.1 in seven)
       if ((nt + tps - 1) / tps != ns) continue;           // same partition as a smaller count
-      const int64_t t = cost(q, c, ns, tps);
+      int64_t t = cost(q, c, ns, tps);
+      if (ns == 1 && c >= 4 && base_split) {
+        if (base_wg <= 256 && tps >= 5) continue;
+        if (tps > 64 && (int64_t)q * hkv * batch > 240) t = t * 103 / 100;
+      }
       if (t < best_cost) {
         best_cost = t;
         p.nsplit = ns; p.tiles_per_split = tps; p.q_tiles = q; p.ct_wg = c;
