@@ -59,9 +59,10 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
                                                const int32_t* __restrict__ m_live) {
   // m_live: only the first *m_live rows are there (packed rows of a ragged batch).  The grid was sized for M; the
   // tiles that are there take its first workgroups and the others have nothing to do.  Strides stay those of M.
-  // (Large tiles only: up to 128 rows there is one row tile.)
+  // (Above 128 rows only: up to there a launch has one row tile, and no batch is packed.)
+  constexpr bool LIVE = TILED && NB == 2;
   const int M_ld = M;
-  if (RING > 0 && m_live) {
+  if (LIVE && m_live) {
     M = min(*m_live, M);
     if (M <= 0) return;
     m_tiles = (M + WM * MT * 32 - 1) / (WM * MT * 32);
@@ -70,7 +71,7 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
   // contiguous range of tiles (tiles sharing weight rows then share an L2).
   const int total = m_tiles * n_tiles * splits;
   const int per_xcd = (total + 7) >> 3;
-  if (RING > 0 && (int)(blockIdx.x >> 3) >= per_xcd) return;
+  if (LIVE && (int)(blockIdx.x >> 3) >= per_xcd) return;
   const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (logical >= total) return;
   const int mi = logical % m_tiles;
@@ -238,8 +239,8 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
   }
   const size_t W_CHUNK = TILED ? (size_t)(N >> 5) * 256 : KC * 2 / 16;   // u32x4_t between chunks of a lane's stream
   constexpr int W_STEP = TILED ? 64 : 1;               // u32x4_t between the steps of a chunk
-  // The weights of a small-row launch pass once (one row tile): nontemporal loads keep them from pushing the activations,
-  // the partial sums and one another out of the caches.  One row 3478 -> 3263 us a step, 30 rows 3590 -> 3530, 68 rows
+  // The weights of a small-row launch pass once (up to 128 rows are one row tile, 161 to 192 are two, side by side): nontemporal
+  // loads keep them from pushing the activations, the partial sums and one another out of the caches.  One row 3478 -> 3263 us a step, 30 rows 3590 -> 3530, 68 rows
   // 4462 -> 4416 (two runs of one side differ by 0.1 to 0.7 %).  Row-major weights are read in pieces of a line: not those.
   auto load_w = [](const u32x4_t* p) { return TILED ? __builtin_nontemporal_load(p) : *p; };
 
@@ -547,10 +548,10 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const bf16_t* __restrict__ A,
                                                    const bf16_t* __restrict__ W, float* __restrict__ out, int M,
                                                    int N, int K, int splits, int m_tiles, int n_tiles, int a_ld,
                                                    float* __restrict__ out2, const int32_t* __restrict__ draw_pos,
-                                                   uint32_t seed) {
+                                                   uint32_t seed, const int32_t* __restrict__ m_live) {
   extern __shared__ __align__(16) unsigned char lds[];   // 2 buffers of MT*32 rows * A_ROW_BYTES
   gemm_bf16_body<MT, NB, D, TILED, 1, EPI>(lds, A, a_rows, W, out, M, N, K, splits, m_tiles, n_tiles, a_ld, out2,
-                                           draw_pos, seed, nullptr);
+                                           draw_pos, seed, m_live);
 }
 
 template <int MT, int NB, int D, bool TILED, int EPI>
@@ -923,7 +924,7 @@ hipError_t launch_bf16(hipStream_t st, const void* A, const int32_t* a_rows, con
                   a_rows, (const bf16_t*)W, out, M, N, K, p.splits, p.m_tiles, p.n_tiles, a_ld, out2);
   else
     launch_kernel(k_gemm_bf16<MT, NB, D, TILED, EPI>, dim3(per_xcd * 8), dim3(256), lds, st, (const bf16_t*)A, a_rows,
-                  (const bf16_t*)W, out, M, N, K, p.splits, p.m_tiles, p.n_tiles, a_ld, out2, draw_pos, seed);
+                  (const bf16_t*)W, out, M, N, K, p.splits, p.m_tiles, p.n_tiles, a_ld, out2, draw_pos, seed, m_live);
   return hipGetLastError();
 }
 

@@ -119,7 +119,8 @@ GemmPlan gemm_plan(int dtype, int M, int N, int K);
 inline size_t gemm_out_elems(const GemmPlan& p, int M, int N) { return (size_t)p.splits * M * N; }
 // out: fp32 [splits][M][N].  a_rows (device, may be null): physical row of A for logical row m.
 // w_packed: W is in the streaming layout written by launch_pack_weight (bf16 only).
-// m_live (device, may be null; bf16 only): how many of the M rows there are; the others are neither computed nor written.
+// m_live (device, may be null; bf16, packed weights and more than 128 rows only): how many of the M rows there are; row tiles
+// without any are left out, rows past them are not written.
 hipError_t launch_gemm(hipStream_t st, int dtype, const void* A, const int32_t* a_rows, const void* W,
                        float* out, int M, int N, int K, const GemmPlan& p, bool w_packed, int a_ld = 0,
                        const int32_t* m_live = nullptr);

@@ -80,6 +80,32 @@ def test_gemm_bf16_cache_policy_edges(B, M):
     assert rel_err_rows(got, to_np(a) @ to_np(w).T) < 1e-5      # fp32 sums of 512 exact products
 
 
+class GemmPlan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("splits", "mt", "nb", "m_tiles", "n_tiles", "wm")]
+
+
+@pytest.mark.parametrize("M,N,K,live", [(161, 320, 1024, 1), (161, 320, 1024, 96), (192, 544, 512, 97), (192, 320, 2048, 192), (192, 320, 512, 0),
+                                        (129, 256, 2048, 100), (320, 512, 4096, 160), (320, 512, 4096, 161), (640, 256, 4096, 481), (1344, 256, 2048, 700)])
+def test_gemm_bf16_live_rows(B, M, N, K, live):
+    """Packed rows of a batch on every tile above 128 rows, in several split-K parts: the rows that are there get what they get
+    alone (each part's sums run over K in the same order), parts keep the stride of all M rows, no other row is written."""
+    c = ctypes
+    plan = internal("gemm_plan", *[c.c_int] * 4, restype=GemmPlan)(B.ESP_BF16, M, N, K)
+    fn = internal("launch_gemm", c.c_void_p, c.c_int, c.c_void_p, c.c_void_p, c.c_void_p, c.c_void_p, *[c.c_int] * 3, c.POINTER(GemmPlan),
+                  c.c_bool, c.c_int, c.c_void_p)
+    print(f"gemm live rows M={M} N={N} K={K} live={live} mt={plan.mt} splits={plan.splits}", flush=True)
+    assert plan.nb == 2 and (plan.splits > 1 or K < 1024)
+    a = synth.normal_like((M, K), 1.0, 15, 0, "cuda", torch.bfloat16)
+    wp = B.pack_weight(synth.normal_like((N, K), 0.05, 15, 1, "cuda", torch.bfloat16))
+    n = torch.tensor([live], dtype=torch.int32, device="cuda")
+    got, want = (torch.full((plan.splits, M, N), -7.0, device="cuda") for _ in range(2))
+    for out, m_live in ((want, None), (got, n.data_ptr())):
+        assert fn(torch.cuda.current_stream().cuda_stream, B.ESP_BF16, a.data_ptr(), None, wp.data_ptr(), out.data_ptr(), M, N, K, plan, True, 0,
+                  m_live) == 0
+    assert torch.equal(got[:, :live], want[:, :live]) and bool((got[:, live:] == -7).all())
+    assert rel_err_rows(want.sum(0).cpu().numpy(), B.gemm(a, wp, packed=True).cpu().numpy()) < 1e-6
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 512, 128), (68, 4096, 256), (128, 1056, 192), (129, 768, 256), (320, 4096, 512),
                                    (200, 2048, 128), (1344, 1280, 256), (700, 33 * 32, 192), (180, 512, 64)])
 def test_gemm_argmax_epilogue(B, M, N, K):
