@@ -832,12 +832,15 @@ def test_qkv_epilogue_forms(B, dtype, head_dim, d_model, hq, hkv, qk_norm):
 
 
 # ---------------------------------------------------------------------------- packed rows of a batch
-@pytest.mark.parametrize("head_dim,counts,sample", [(128, [14, 1, 5], False), (128, [1, 14, 3, 14, 9, 2], True), (64, [2, 14, 8, 1], True),
-                                                    (128, [1, 1, 1, 1], False)])
-def test_packed_rows_of_a_ragged_batch(B, head_dim, counts, sample):
+@pytest.mark.parametrize("head_dim,counts,sample,invalid", [
+    (128, [14, 1, 5], False, []), (128, [1, 14, 3, 14, 9, 2], True, []), (64, [2, 14, 8, 1], True, []), (128, [1, 1, 1, 1], False, []),
+    (128, [14, 2, 9, 14, 1, 7, 3, 14, 14, 5, 1, 12], True, []), (128, [3, 14, 6, 2], False, [0, 2]), (64, [4, 1, 14], False, [0, 1, 2])])
+def test_packed_rows_of_a_ragged_batch(B, head_dim, counts, sample, invalid):
     """Above 128 block rows a batch's live rows go through the layers packed together.  A row's sums do not depend on
     the rows beside it (one split-K part and one key split at these sizes), so every sequence comes out bit for bit as
-    it does alone, with its rows where they were; rows that are not there are zero, also in the K/V cache."""
+    it does alone, with its rows where they were; rows that are not there are zero, also in the K/V cache.  A sequence longer
+    than the bound has no rows and sets the status, also where no sequence is left; twelve sequences' tree rows take the
+    large-tile arg-max."""
     shape = small_shape(d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=head_dim, d_ff=384, vocab=1024, n_layers=2, qk_norm=True,
                         dtype="bf16")
     w = synth.make_weights(shape, seed=9, unit_gains=False)
@@ -862,10 +865,13 @@ def test_packed_rows_of_a_ragged_batch(B, head_dim, counts, sample):
                     kf, vf = (synth.normal_like((lens[b], 2, head_dim), 1.0, 92 + b, 2 * layer + j, "cuda", torch.bfloat16) for j in (0, 1))
                     eng.kv_store(kv, layer, i, 0, kf, vf)
         kv.set_len([lens[b] for b in which])
+        for i, b in enumerate(which):
+            if b in invalid:
+                kv.len[i] = kv.len_bound + 1
         hidden = torch.full((n * rows, 256), 7.0, dtype=torch.bfloat16, device="cuda")
         nxt = torch.full((n * rows,), -7, dtype=torch.int32, device="cuda")
         eng.tree_forward(blk, masks[which].contiguous() if n > 1 else masks[which[0]], kv, hidden, nxt)
-        assert eng.device_status() == 0
+        assert (eng.device_status() != 0) == any(b in invalid for b in which)
         planes = [torch.stack([torch.stack(eng.kv_load(kv, layer, i, 0, 128)) for layer in range(2)]) for i in range(n)]
         eng.close()
         return hidden.reshape(n, rows, 256), nxt.reshape(n, rows), planes
@@ -873,18 +879,55 @@ def test_packed_rows_of_a_ragged_batch(B, head_dim, counts, sample):
     hidden, nxt, planes = forward(list(range(batch)))
     for b in range(batch):
         h1, n1, p1 = forward([b])
-        live = counts[b] * (k + 1)
+        live = 0 if b in invalid else counts[b] * (k + 1)
         assert torch.equal(hidden[b, :live], h1[0, :live]) and bool((hidden[b, live:] == 0).all()), b
         assert torch.equal(nxt[b], n1[0]), b
         assert torch.equal(planes[b], p1[0]) and bool((planes[b][:, :, lens[b] + live:] == 0).all()), b
+
+
+@pytest.mark.parametrize("counts", [[80, 80], [80, 40], [80, 1], [60, 68]])
+def test_packed_rows_with_two_gate_up_tiles(B, counts):
+    """Two sequences of up to 320 rows, for which two gate/up tiles are launched and the number of live rows decides between
+    them.  Each sequence alone takes other split-K parts: equal to the tolerance of bf16 models.  A profiling span covers both
+    launches."""
+    shape = small_shape(d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=64, d_ff=14336, vocab=512, n_layers=2, dtype="bf16")
+    tiles = internal("gate_up_tiles", ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_bool, restype=ctypes.c_uint)
+    assert tiles(640, 14336, 256, None, True) == 0b011
+    w = synth.make_weights(shape, seed=9, unit_gains=False)
+    k, rows = 3, 320
+    print(f"packed rows, two gate/up tiles, counts={counts}", flush=True)
+    masks = synth.normal_like((k, 256), 0.02, 91, 0, "cuda", torch.bfloat16)
+
+    def forward(which):
+        n = len(which)
+        eng = B.Engine(shape, w, n, rows, 512)
+        blk = B.BlockBuffers(n, rows, k, 0)
+        trees = [synth.make_random_tree(counts[b], 4, shape.vocab, seed=70 + b) for b in which]
+        blk.upload_trees([t.tolist() for t, _ in trees], [p.tolist() for _, p in trees])
+        eng.block_from_tree(blk)
+        kv = B.KvCache(shape, [rows] * n)
+        kv.set_len([0] * n)
+        hidden = torch.full((n * rows, 256), 7.0, dtype=torch.bfloat16, device="cuda")
+        eng.profile_enable(["gemm_layer"])
+        eng.tree_forward(blk, masks, kv, hidden, torch.zeros(n * rows, dtype=torch.int32, device="cuda"))
+        spans, ms = eng.profile_read("gemm_layer")
+        assert eng.device_status() == 0 and spans == 4 * shape.n_layers and 0 < ms < 1000
+        eng.close()
+        return to_np(hidden).reshape(n, rows, 256)
+
+    both = forward([0, 1])
+    for b in (0, 1):
+        live = counts[b] * (k + 1)
+        assert rel_err_rows(both[b, :live], forward([b])[0, :live]) < TOL["bf16"]
+        assert np.all(both[b, live:] == 0)
 
 
 # ---------------------------------------------------------------------------------------- attention
 def run_attention_case(B, shape, eng, n_nodes, k, layout, cache_lens, seed):
     batch = len(cache_lens)
     if k == 0:   # prefill-like chain block: row i sees rows 0..i
-        trees = [(torch.arange(n_nodes - 3 * b, dtype=torch.int32) % shape.vocab,
-                  torch.arange(-1, n_nodes - 3 * b - 1, dtype=torch.int32)) for b in range(batch)]
+        sizes = [max(n_nodes - 3 * b, 1) for b in range(batch)]
+        trees = [(torch.arange(n, dtype=torch.int32) % shape.vocab, torch.arange(-1, n - 1, dtype=torch.int32)) for n in sizes]
     else:
         trees = [synth.make_random_tree(n_nodes - 3 * b, max(k, 2), shape.vocab, seed=seed + b)
                  for b in range(batch)]
@@ -974,11 +1017,31 @@ def test_attn_tree_bf16_mfma(B, bf16_engine, n_nodes, k, layout, cache_lens):
 
 @pytest.mark.parametrize("n_nodes,cache_lens", [(1, [900]), (7, [193]), (9, [1500, 3]), (16, [700]), (23, [64]), (31, [2100])])
 def test_attn_tree_bf16_few_columns(B, bf16_engine, n_nodes, cache_lens):
-    """One to four column tiles a kv head, in splits of one to many key tiles: with and without two waves sharing a
-    column tile."""
+    """One to four column tiles a kv head, in splits of two key tiles: one or two column tiles without waves that share one."""
     shape, w, eng = bf16_engine
     print(f"attn bf16 few columns n={n_nodes} L={cache_lens}", flush=True)
     assert run_attention_case(B, shape, eng, n_nodes, 0, 0, cache_lens, seed=75) < 2e-2
+
+
+class AttnPlan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("nsplit", "tiles_per_split", "q_tiles", "ct_wg")]
+
+
+@pytest.mark.parametrize("n_nodes,ct_wg,cache_lens", [
+    (1, 1, [4096, 30, 700, 1, 2111]), (1, 1, [63, 64, 65, 1500, 1, 127, 128, 3000, 700, 5, 640, 2000, 33, 900, 1200, 4096]),
+    (7, 1, [1500, 3, 64, 800, 129, 1400, 1000, 190]), (12, 2, [2000, 1, 700, 1300, 61]), (9, 2, [4096, 129, 64]), (68, 2, [2048])])
+def test_attn_tree_bf16_paired_columns(B, n_nodes, ct_wg, cache_lens):
+    """One or two column tiles a workgroup in splits of three and more key tiles: two waves share a column tile, the other
+    waves of four (with one column tile, two) only load.  Lengths leave splits empty, with one key and partly masked."""
+    shape = small_shape(d_model=512, n_q_heads=32, n_kv_heads=8, head_dim=128, d_ff=128, vocab=512, n_layers=1, dtype="bf16")
+    bound = max(cache_lens)
+    p = internal("attn_plan", *[ctypes.c_int] * 7, restype=AttnPlan)(B.ESP_BF16, 128, len(cache_lens), n_nodes, 32, 8, bound)
+    print(f"attn bf16 paired n={n_nodes} L={cache_lens} splits={p.nsplit}x{p.tiles_per_split}", flush=True)
+    assert p.ct_wg == ct_wg and p.tiles_per_split >= 3
+    eng = B.Engine(shape, synth.make_weights(shape, seed=5), max_batch=len(cache_lens), max_rows_per_seq=n_nodes, max_kv_len=bound + n_nodes + 64)
+    err = run_attention_case(B, shape, eng, n_nodes, 0, 0, cache_lens, seed=77)
+    eng.close()
+    assert err < 2e-2
 
 
 # ------------------------------------------------------------------------- mask initialisations
