@@ -728,9 +728,9 @@ hipError_t launch_attn(hipStream_t st, int dtype, const BlockDev& b, const KvDev
     const hipError_t attr = attn_prepare();
     if (attr != hipSuccess) return attr;
     const dim3 grid(((total_wg + 7) / 8) * 8), block(64 * g.waves);
-    // Nontemporal where a key tile is read by one workgroup only: steps of one row on 2048 keys 3286 -> 3221 us, 68 rows on
-    // 32768 keys 5738 -> 5671; 16 sequences of one row on 4096 keys, eight layers, 1487 -> 1432.  Where several workgroups
-    // read it, 50 and 80 rows got 1 % slower with it and the others stayed the same.
+    // Nontemporal where a key tile is read by one workgroup only.  Eight layers of the 8B shape, this alone: one row on 32768 keys
+    // 994 -> 952 us, 68 rows 1357 -> 1341, 16 sequences of one row on 8192 keys 1717 -> 1626; up to 2048 keys within 1 %.  Where
+    // several workgroups read a tile, 50 and 80 rows got 1 % slower with it and the others stayed the same.
     const auto pick = [&](auto nt) {
       constexpr bool NT = decltype(nt)::value;
       return g.waves >= 8 ? (packed ? k_attn_ring<4, true, NT> : k_attn_ring<4, false, NT>)

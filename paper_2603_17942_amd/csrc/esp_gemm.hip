@@ -240,8 +240,9 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
   const size_t W_CHUNK = TILED ? (size_t)(N >> 5) * 256 : KC * 2 / 16;   // u32x4_t between chunks of a lane's stream
   constexpr int W_STEP = TILED ? 64 : 1;               // u32x4_t between the steps of a chunk
   // The weights of a small-row launch pass once (up to 128 rows are one row tile, 161 to 192 are two, side by side): nontemporal
-  // loads keep them from pushing the activations, the partial sums and one another out of the caches.  One row 3478 -> 3263 us a step, 30 rows 3590 -> 3530, 68 rows
-  // 4462 -> 4416 (two runs of one side differ by 0.1 to 0.7 %).  Row-major weights are read in pieces of a line: not those.
+  // loads keep them from pushing the activations, the partial sums and one another out of the caches.  Eight layers of the
+  // 8B shape on 2048 keys, this alone: one row 843 -> 779 us, 30 rows 886 -> 834, 68 rows 1055 -> 1014, 128 rows 1260 -> 1230 (two
+  // runs of one side differ by 0.3 %).  Row-major weights are read in pieces of a line: not those.
   auto load_w = [](const u32x4_t* p) { return TILED ? __builtin_nontemporal_load(p) : *p; };
 
   // activation staging: thread handles MT pieces of 16 B; piece p -> row p/8, 16-byte column p%8
@@ -351,8 +352,9 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
 
   // epilogue: lane holds column n, rows 8*(v/4) + 4*lg + v%4 of each 32x32 tile
   if (EPI == 0 || EPI == 3) {
-    // Split-K partials of 65 to 128 rows go past the caches on their way out: 68 rows 4366 -> 4281 us a step, 101 rows of the
-    // Qwen3 shape 5647 -> 5555.  At one row, where they are 0.1 MB, that is 3 % slower; with large tiles it is neither.
+    // Split-K partials of 65 to 128 rows go past the caches on their way out: eight layers of the 8B shape on 2048 keys, this
+    // alone, 65 rows 1025 -> 1008 us, 101 rows 1178 -> 1158, 128 rows 1253 -> 1230.  At one row, where they are 0.1 MB, it is 3 %
+    // slower; with large tiles it is neither.
     constexpr bool NT_OUT = EPI == 0 && RING == 0 && NB == 1 && MT >= 3;
     float* o = out + (size_t)z * M_ld * N;
 #pragma unroll
@@ -657,7 +659,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   auto load_a = [&](int j, int c, int stage) {
     load_to_lds16_sbase<0>(a_base + (size_t)min(c, nc - 1) * (KC * 2), aoff[j], lds0 + stage * T::A_STAGE + (wave + 4 * j) * 1024);
   };
-  auto load_w = [&](int j, int h, int stage) {           // nontemporal, as the ring's with few row tiles (launch_bf16)
+  // nontemporal at any number of row tiles: 512 rows (two) 104.2 -> 102.7 us at N = 28672, 1312 (six) 296 and 298
+  auto load_w = [&](int j, int h, int stage) {
     const int hh = min(h, 2 * nc - 1);
     load_to_lds16_sbase<0, true>(w_src[j] + (size_t)(hh >> 1) * W_CHUNK + (hh & 1) * 2048, lane16, ldsw + stage * T::W_STAGE + (wave + 4 * j) * 1024);
   };
