@@ -350,14 +350,17 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
   // padding to speak of.  16 sequences of 36 to 128 tree nodes, 1630 of 2112 rows there (8B shape): step 37.1 -> 32.7 ms.
   const bool packed = pk && blk->batch > 1 && M > 128;
   const int32_t* m_live = nullptr;
+  PackedEnd end;
   { ESP_PROF(ESP_SITE_GLUE);
   if (packed) {
+    end.rows[0] = (bf16_t*)c->xn; end.rows[1] = (bf16_t*)c->attn_out; end.rows[2] = (bf16_t*)c->act;
+    end.width[0] = d; end.width[1] = hq * hd; end.width[2] = ff;
     bd.packed = c->packed;
     ESP_HIP(launch_live_rows(s, bd, kd, nodes_bound(blk), gate_up_rule(M, ff, d, c->act, true)));
     m_live = bd.n_live();
   }
   ESP_HIP(launch_embed(s, dt, bd, kd, c->embed, mask_embed, c->h, d, m.vocab, c->rope_tab, hd, m.rope_theta,
-                       c->status, c->mask_per_seq ? (size_t)blk->k_masks * d : 0));
+                       c->status, c->mask_per_seq ? (size_t)blk->k_masks * d : 0, end));
   ESP_HIP(launch_residual_norm(s, dt, c->h, nullptr, 0, M, d, c->norm_attn[0], m.rms_eps, c->xn, m_live)); }
   for (int l = 0; l < m.n_layers; ++l) {
     { ESP_PROF_KERNEL(ESP_SITE_GEMM_LAYER, dt == ESP_BF16);

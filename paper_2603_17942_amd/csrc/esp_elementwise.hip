@@ -77,12 +77,26 @@ hipError_t launch_live_rows(hipStream_t st, const BlockDev& b, const KvDev& kv, 
   return hipGetLastError();
 }
 
+// PACKED: the row behind the live ones in the projections' inputs is set to zero; no kernel of the layers writes it, and the row
+// tiles load it for every row that is not there.  (A copy of the last live row keeps the matrix cores as busy as a real one, zeros
+// do not, and the card is at its power limit in the large tiles: eight layers of the 8B shape on 2048 keys, 172 rows of 318 there
+// 1930 -> 1672 us, 273 of 448 2142 -> 1902.  A zero row for each instead cost the loads of it: 64 of 224 rows 1392 -> 1448.)
 template <typename T, bool PACKED>
 __global__ __launch_bounds__(256) void k_embed(BlockDev b, KvDev kv, const T* __restrict__ embed,
                                                const T* __restrict__ mask_embed, float* __restrict__ h, int d,
                                                int vocab, float* __restrict__ rope_tab, int hd, float theta,
-                                               int32_t* status, size_t mask_seq_stride) {
+                                               int32_t* status, size_t mask_seq_stride, PackedEnd end) {
   const int row = blockIdx.x;
+  if (PACKED) {
+    if (row == b.n_live()[0]) {
+      const u32x4_t zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        u32x4_t* dst = reinterpret_cast<u32x4_t*>(end.rows[t] + (size_t)row * end.width[t]);
+        for (int i = threadIdx.x; i < end.width[t] / 8; i += blockDim.x) dst[i] = zero;
+      }
+    }
+  }
   const int seq = row / b.rows_per_seq, r = row % b.rows_per_seq;
   const int nr = b.n_rows[seq];
   const bool ok = seq_ok(kv, seq, nr) && nr <= b.rows_per_seq;
@@ -118,11 +132,11 @@ __global__ __launch_bounds__(256) void k_embed(BlockDev b, KvDev kv, const T* __
 
 hipError_t launch_embed(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, const void* embed,
                         const void* mask_embed, float* h, int d, int vocab, float* rope_tab, int hd,
-                        float theta, int32_t* status, size_t mask_seq_stride) {
+                        float theta, int32_t* status, size_t mask_seq_stride, const PackedEnd& end) {
   int M = b.batch * b.rows_per_seq;
   ESP_DISPATCH(dtype, hipLaunchKernelGGL((b.packed ? k_embed<T, true> : k_embed<T, false>), dim3(M), dim3(256), 0, st, b, kv, (const T*)embed,
                                          (const T*)mask_embed, h, d, vocab, rope_tab, hd, theta, status,
-                                         mask_seq_stride));
+                                         mask_seq_stride, end));
   return hipGetLastError();
 }
 

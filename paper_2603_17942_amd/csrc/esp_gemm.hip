@@ -59,7 +59,8 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
                                                const int32_t* __restrict__ m_live) {
   // m_live: only the first *m_live rows are there (packed rows of a ragged batch).  The grid was sized for M; the
   // tiles that are there take its first workgroups and the others have nothing to do.  Strides stay those of M.
-  // (Above 128 rows only: up to there a launch has one row tile, and no batch is packed.)
+  // (Above 128 rows only: up to there a launch has one row tile, and no batch is packed.)  Every row of
+  // the last tile that is not there is loaded from the first of them, in which the forward pass keeps zeros (launch_embed).
   constexpr bool LIVE = TILED && NB == 2;
   const int M_ld = M;
   if (LIVE && m_live) {
@@ -67,6 +68,7 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
     if (M <= 0) return;
     m_tiles = (M + WM * MT * 32 - 1) / (WM * MT * 32);
   }
+  const int m_last = LIVE ? min(M, M_ld - 1) : M - 1;
   // XCD-aware logical id: consecutive hardware ids go to different XCDs, so give each XCD a
   // contiguous range of tiles (tiles sharing weight rows then share an L2).
   const int total = m_tiles * n_tiles * splits;
@@ -123,7 +125,7 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
     for (int j = 0; j < MT; ++j) {
       const int pr = lw + 4 * j;                          // row tile pr / 4, rows 8 (pr % 4) .. + 7 of it
       const int rt = 8 * (pr & 3) + (lane >> 3);
-      int m = min(mt0 + (pr >> 2) * 32 + rt, M - 1);
+      int m = min(mt0 + (pr >> 2) * 32 + rt, m_last);
       if (a_rows) m = max(a_rows[m], 0);
       aoff[j] = (uint32_t)(((a_ld > 0 ? (size_t)m * KC : (size_t)m * K) + 8 * ((lane & 7) ^ swz(rt))) * 2);
     }
@@ -252,7 +254,7 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
   for (int i = 0; i < MT; ++i) {
     int p = tid + 256 * WM * i;
     int r = p >> 3, c16 = p & 7;
-    int m = min(mt0 + r, M - 1);
+    int m = min(mt0 + r, m_last);
     if (a_rows) m = max(a_rows[m], 0);
     ap[i] = A + (a_ld > 0 ? (size_t)m * KC : (size_t)m * K) + c16 * 8;
     a_lds[i] = r * A_ROW_BYTES + c16 * 16;
@@ -611,11 +613,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     int n_tiles, const int32_t* __restrict__ m_live) {
   extern __shared__ __align__(16) unsigned char lds[];
   using T = WideTile<MT, NB>;
+  const int M_ld = M;
   if (m_live) {                                          // packed rows of a ragged batch, as in the kernels above
     M = min(*m_live, M);
     if (M <= 0) return;
     m_tiles = (M + T::ROWS - 1) / T::ROWS;
   }
+  const int m_last = min(M, M_ld - 1);
   const int total = m_tiles * n_tiles;
   const int per_xcd = (total + 7) >> 3;
   if ((int)(blockIdx.x >> 3) >= per_xcd) return;
@@ -643,7 +647,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
   for (int j = 0; j < 2 * MT; ++j) {
     const int rt = 8 * wave + (lane >> 3);
-    const int m = min(mt0 + j * 32 + rt, M - 1);
+    const int m = min(mt0 + j * 32 + rt, m_last);
     aoff[j] = (uint32_t)(((size_t)m * K + 8 * ((lane & 7) ^ swz(rt))) * 2);
   }
   const unsigned char* a_base = reinterpret_cast<const unsigned char*>(A);

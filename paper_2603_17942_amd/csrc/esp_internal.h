@@ -120,7 +120,7 @@ inline size_t gemm_out_elems(const GemmPlan& p, int M, int N) { return (size_t)p
 // out: fp32 [splits][M][N].  a_rows (device, may be null): physical row of A for logical row m.
 // w_packed: W is in the streaming layout written by launch_pack_weight (bf16 only).
 // m_live (device, may be null; bf16, packed weights and more than 128 rows only): how many of the M rows there are; row tiles
-// without any are left out, rows past them are not written.
+// without any are left out, rows past them are not written; the others of a row tile are computed from A's row m_live.
 hipError_t launch_gemm(hipStream_t st, int dtype, const void* A, const int32_t* a_rows, const void* W,
                        float* out, int M, int N, int K, const GemmPlan& p, bool w_packed, int a_ld = 0,
                        const int32_t* m_live = nullptr);
@@ -215,9 +215,14 @@ struct KvDev {
 
 // fills b.packed from the row counts, which only the device knows
 hipError_t launch_live_rows(hipStream_t st, const BlockDev& b, const KvDev& kv, int max_nodes, const GateUpRule& gate_up);
+// inputs of the projections (bf16, width a multiple of 8), of which the row behind a packed batch's live ones is zeroed
+struct PackedEnd {
+  bf16_t* rows[3] = {};
+  int width[3] = {};
+};
 hipError_t launch_embed(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, const void* embed,
                         const void* mask_embed, float* h, int d, int vocab, float* rope_tab, int hd,
-                        float theta, int32_t* status, size_t mask_seq_stride);
+                        float theta, int32_t* status, size_t mask_seq_stride, const PackedEnd& end);
 // n_live (nullable): rows there are.  packed_row (nullable): row m of xn_out comes from row packed_row[m], or is zero
 hipError_t launch_residual_norm(hipStream_t st, int dtype, float* h, const float* part, int splits, int M,
                                 int d, const void* gain, float eps, void* xn_out, const int32_t* n_live = nullptr,

@@ -838,7 +838,8 @@ def test_qkv_epilogue_forms(B, dtype, head_dim, d_model, hq, hkv, qk_norm):
 def test_packed_rows_of_a_ragged_batch(B, head_dim, counts, sample, invalid):
     """Above 128 block rows a batch's live rows go through the layers packed together.  A row's sums do not depend on
     the rows beside it (one split-K part and one key split at these sizes), so every sequence comes out bit for bit as
-    it does alone, with its rows where they were; rows that are not there are zero, also in the K/V cache.  A sequence longer
+    it does alone, with its rows where they were; rows that are not there are zero, also in the K/V cache, and so is the row
+    behind the live ones in what goes into the projections, which stands for all of them there.  A sequence longer
     than the bound has no rows and sets the status, also where no sequence is left; twelve sequences' tree rows take the
     large-tile arg-max."""
     shape = small_shape(d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=head_dim, d_ff=384, vocab=1024, n_layers=2, qk_norm=True,
@@ -873,6 +874,10 @@ def test_packed_rows_of_a_ragged_batch(B, head_dim, counts, sample, invalid):
         eng.tree_forward(blk, masks[which].contiguous() if n > 1 else masks[which[0]], kv, hidden, nxt)
         assert (eng.device_status() != 0) == any(b in invalid for b in which)
         planes = [torch.stack([torch.stack(eng.kv_load(kv, layer, i, 0, 128)) for layer in range(2)]) for i in range(n)]
+        if n > 1:   # the workspace begins with the fp32 residual rows, then the rows that go into the projections
+            live = sum(counts[b] * (k + 1) for b in which if b not in invalid)
+            xn = eng.workspace[eng._ws_off + n * rows * 256 * 4:][:n * rows * 256 * 2].view(torch.bfloat16).reshape(n * rows, 256)
+            assert bool((xn[live:live + 1] == 0).all()) and bool((xn[:live] != 0).any(1).all())
         eng.close()
         return hidden.reshape(n, rows, 256), nxt.reshape(n, rows), planes
 
