@@ -31,13 +31,6 @@ esp_status check_model(const esp_model_desc* m) {
   return ESP_OK;
 }
 
-int max_splits_of(const esp_model_desc* m, int M) {
-  int nqkv = (m->n_q_heads + 2 * m->n_kv_heads) * m->head_dim;
-  int s = 1;
-  s = std::max(s, gemm_plan(m->dtype, M, nqkv, m->d_model).splits);
-  return s;
-}
-
 WsLayout ws_layout(const esp_model_desc* m, int max_batch, int max_rows, int64_t max_kv_len) {
   WsLayout w{};
   const size_t M = (size_t)max_batch * max_rows;
@@ -51,14 +44,13 @@ WsLayout ws_layout(const esp_model_desc* m, int max_batch, int max_rows, int64_t
   w.q = take(M * (size_t)hq * hd * e);
   w.attn_out = take(M * (size_t)hq * hd * e);
   w.act = take(M * (size_t)ff * e);
-  size_t go = 0;
-  go = std::max(go, gemm_out_elems(gemm_plan(m->dtype, (int)M, nqkv, d), (int)M, nqkv));
-  go = std::max(go, gemm_out_elems(gemm_plan(m->dtype, (int)M, d, hq * hd), (int)M, d));
-  go = std::max(go, gemm_out_elems(gemm_plan(m->dtype, (int)M, 2 * ff, d), (int)M, 2 * ff));
-  go = std::max(go, gemm_out_elems(gemm_plan(m->dtype, (int)M, d, ff), (int)M, d));
+  // a call may use fewer rows / a shorter bound and hence another split count: size for the worst
+  const int rows = (int)M;
+  size_t go = std::max(M * 2 * ff, gemm_out_elems_bound(m->dtype, rows, nqkv, d));
+  go = std::max(go, gemm_out_elems_bound(m->dtype, rows, d, hq * hd));
+  go = std::max(go, gemm_out_elems_bound(m->dtype, rows, d, ff));
   w.gemm_out_floats = go;
   w.gemm_out = take(go * 4);
-  // a call may use fewer rows / shorter bound and hence another split count: size for the worst
   size_t apf = attn_partial_floats_bound(m->dtype, max_batch, max_rows, hq, hkv, hd);
   w.attn_part_floats = apf;
   w.attn_part = take(apf * 4);
@@ -327,12 +319,14 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
   KvDev kd = to_dev(kv);
   const bool pk = dt == ESP_BF16;   // bf16 matrices arrive in the streaming layout
 
-  const GemmPlan p_qkv = gemm_plan(dt, M, nqkv, d);
-  const GemmPlan p_o = gemm_plan(dt, M, d, hq * hd);
-  const GemmPlan p_gu = gemm_plan(dt, M, 2 * ff, d);
-  const GemmPlan p_dn = gemm_plan(dt, M, d, ff);
+  // Ragged batches: only the rows that are there go through the layers, packed together (the row counts live on the
+  // device).  Up to 128 rows the projections are weight streams and padding costs nothing; one sequence has no
+  // padding to speak of.  16 sequences of 36 to 128 tree nodes, 1630 of 2112 rows there (8B shape): step 37.1 -> 32.7 ms.
+  const bool packed = pk && blk->batch > 1 && M > 128;
+  auto plan = [&](int N, int K) { return packed ? batch_gemm_plan(M, N, K) : gemm_plan(dt, M, N, K); };
+  const GemmPlan p_qkv = plan(nqkv, d), p_o = plan(d, hq * hd), p_dn = plan(d, ff);
   if (gemm_out_elems(p_qkv, M, nqkv) > c->gemm_out_floats || gemm_out_elems(p_o, M, d) > c->gemm_out_floats ||
-      gemm_out_elems(p_gu, M, 2 * ff) > c->gemm_out_floats || gemm_out_elems(p_dn, M, d) > c->gemm_out_floats)
+      (!pk && (size_t)M * 2 * ff > c->gemm_out_floats) || gemm_out_elems(p_dn, M, d) > c->gemm_out_floats)
     return ESP_ECAPACITY;
   const AttnPlan ap = attn_plan(dt, hd, blk->batch, blk->rows_per_seq, hq, hkv, kv->len_bound);
   if (attn_partial_floats(dt, blk->batch, blk->rows_per_seq, hq, hkv, hd, ap) > c->attn_part_floats)
@@ -342,13 +336,9 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
   if (logits_dbg || node_argmax) {
     const int Mlm = logits_dbg ? M : blk->batch * nodes_bound(blk);
     if (!logits_dbg && (size_t)Mlm > c->logits_rows) return ESP_ECAPACITY;
-    if (gemm_plan(dt, Mlm, m.vocab, d).splits != 1) return ESP_ESHAPE;
+    if (!gemm_whole_rows(dt, Mlm, m.vocab, d)) return ESP_ESHAPE;
   }
 
-  // Ragged batches: only the rows that are there go through the layers, packed together (the row counts live on the
-  // device).  Up to 128 rows the projections are weight streams and padding costs nothing; one sequence has no
-  // padding to speak of.  16 sequences of 36 to 128 tree nodes, 1630 of 2112 rows there (8B shape): step 37.1 -> 32.7 ms.
-  const bool packed = pk && blk->batch > 1 && M > 128;
   const int32_t* m_live = nullptr;
   PackedEnd end;
   { ESP_PROF(ESP_SITE_GLUE);
@@ -381,9 +371,9 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
       ESP_HIP(launch_gemm_swiglu(s, c->xn, c->wgu[l], c->act, M, ff, d, m_live));
     } else {
       { ESP_PROF(ESP_SITE_GEMM_LAYER);
-        ESP_HIP(launch_gemm(s, dt, c->xn, nullptr, c->wgu[l], c->gemm_out, M, 2 * ff, d, p_gu, pk)); }
+        ESP_HIP(launch_gemm(s, dt, c->xn, nullptr, c->wgu[l], c->gemm_out, M, 2 * ff, d, gemm_plan(dt, M, 2 * ff, d), pk)); }
       { ESP_PROF(ESP_SITE_GLUE);
-        ESP_HIP(launch_swiglu(s, dt, c->gemm_out, p_gu.splits, M, ff, c->act)); }
+        ESP_HIP(launch_swiglu(s, dt, c->gemm_out, 1, M, ff, c->act)); }
     }
     { ESP_PROF_KERNEL(ESP_SITE_GEMM_LAYER, dt == ESP_BF16);
       ESP_HIP(launch_gemm(s, dt, c->act, nullptr, c->wdown[l], c->gemm_out, M, d, ff, p_dn, pk, 0, m_live)); }
@@ -395,8 +385,7 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
   }
   // LM head + argmax at the tree rows (Sec. 2 Eq. 3 needs the base model's own next token there)
   if (logits_dbg) {
-    const GemmPlan p_lm = gemm_plan(dt, M, m.vocab, d);
-    if (p_lm.splits != 1) return ESP_ESHAPE;
+    const GemmPlan p_lm = whole_row_plan(dt, M, m.vocab, d);
     { ESP_PROF(ESP_SITE_LM_HEAD);
       ESP_HIP(launch_gemm(s, dt, hidden_out, nullptr, c->lm_head, logits_dbg, M, m.vocab, d, p_lm, pk)); }
     if (node_argmax) {
@@ -410,8 +399,7 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
     const int nb = nodes_bound(blk);
     const int Mn = blk->batch * nb;
     if ((size_t)Mn > c->logits_rows) return ESP_ECAPACITY;
-    const GemmPlan p_lm = gemm_plan(dt, Mn, m.vocab, d);
-    if (p_lm.splits != 1) return ESP_ESHAPE;
+    const GemmPlan p_lm = whole_row_plan(dt, Mn, m.vocab, d);
     const int32_t* draw_list = c->sample_on ? c->idx_d : nullptr;   // draw positions per node-list entry
     { ESP_PROF(ESP_SITE_GLUE);
       ESP_HIP(launch_node_rows(s, bd, nb, c->idx_a, c->idx_b, kd.len, c->idx_d));
@@ -481,8 +469,8 @@ esp_status esp_mask_topk(esp_ctx* c, const esp_block* blk, const int32_t* star_r
     return ESP_OK;
   }
   c->lm_cache_hidden = nullptr;          // c->logits is about to be overwritten
-  const GemmPlan p_lm = gemm_plan(m.dtype, rows, m.vocab, m.d_model);
-  if (p_lm.splits != 1) return ESP_ESHAPE;
+  if (!gemm_whole_rows(m.dtype, rows, m.vocab, m.d_model)) return ESP_ESHAPE;
+  const GemmPlan p_lm = whole_row_plan(m.dtype, rows, m.vocab, m.d_model);
   float* lg = logits_out ? logits_out : c->logits;
   { ESP_PROF(ESP_SITE_LM_HEAD);
     ESP_HIP(launch_gemm(s, m.dtype, hidden, c->idx_a, c->lm_head, lg, rows, m.vocab, m.d_model, p_lm, m.dtype == ESP_BF16)); }
@@ -667,6 +655,9 @@ esp_status esp_gemm(void* stream, int32_t dtype, const void* A, const void* W, i
   if (dtype == ESP_BF16 && (N % 32 || K % 64)) return ESP_ESHAPE;
   if (w_packed && dtype != ESP_BF16) return ESP_EDTYPE;
   GemmPlan p = gemm_plan(dtype, M, N, K);
+  // a product that fills the CUs without split-K takes no scratch if there is none
+  if (p.splits > 1 && (!partials || partial_bytes < gemm_out_elems(p, M, N) * 4) && gemm_whole_rows(dtype, M, N, K))
+    p = whole_row_plan(dtype, M, N, K);
   hipStream_t s = (hipStream_t)stream;
   if (p.splits == 1) {
     ESP_HIP(launch_gemm(s, dtype, A, nullptr, W, C, M, N, K, p, w_packed != 0));

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(256) void k_live_rows(BlockDev b, KvDev kv, int max
     if (seq + 1 == b.batch) {
       b.n_live()[0] = first + nr;
       b.n_live()[1] = node0 + nodes_of(seq);
-      const int tile = gate_up.tile(first + nr, true);
+      const int tile = gate_up.cheapest_launched(first + nr);
       for (int t = 0; t < GU_TILES; ++t) b.n_live()[2 + t] = t == tile ? first + nr : 0;
     }
   }

@@ -35,24 +35,15 @@ __device__ __forceinline__ float wave_max(float v) {
 }
 
 // ---- direct global -> LDS loads --------------------------------------------------------------
-// One 16-byte piece per lane from global memory straight into LDS (no register hop): the lane
-// supplies its own global address, the wave's 64 pieces land at lds_addr + 16 * lane.  Issued as
-// text so that the compiler's wait-count bookkeeping knows nothing of it: the LDS rings of the GEMM
-// and attention kernels count their own loads (they retire in order) and would otherwise be
+// One 16-byte piece per lane from global memory straight into LDS (no register hop): a wave-uniform base address (scalar
+// registers) plus a per-lane byte offset, the wave's 64 pieces land at lds_addr + 16 * lane.  The constant offset IMM is added to
+// the global address and to the LDS address alike (piece j of a run: IMM = j KB, lds_addr the address of piece 0), so one vector
+// register serves any number of pieces.  Issued as text so that the compiler's wait-count bookkeeping knows nothing of it: the
+// LDS rings of the GEMM and attention kernels count their own loads (they retire in order) and would otherwise be
 // drained before every LDS read.
 // M0 (the LDS base of the transfer) is put back to what it held before, so the statement leaves no
-// register changed that the compiler might rely on.
-__device__ __forceinline__ void load_to_lds16(const void* g, uint32_t lds_addr) {
-  uint32_t keep;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0"
-               : "=&s"(keep)
-               : "s"(lds_addr), "v"(g)
-               : "memory");
-}
-// The same with a wave-uniform base address (scalar registers) plus a per-lane byte offset and a
-// constant offset IMM, which the hardware adds to the global address and to the LDS address alike
-// (piece j of a run: IMM = j KB, lds_addr the address of piece 0): one vector register for any
-// number of pieces.  NT: nontemporal, for data that one workgroup (or a few at the same time) reads once.
+// register changed that the compiler might rely on.  NT: nontemporal, for data that one workgroup (or a few at the same time)
+// reads once.
 template <int IMM, bool NT = false>
 __device__ __forceinline__ void load_to_lds16_sbase(const void* sbase, uint32_t lane_off, uint32_t lds_addr) {
   uint32_t keep;
@@ -108,15 +99,37 @@ __host__ __device__ __forceinline__ size_t v_off(int64_t slot, int d, int hd) {
 
 // ---- GEMM -----------------------------------------------------------------------------------
 struct GemmPlan {
-  int splits;        // split-K factor; a function of (N, K) and of the tile class (<=128 rows or more)
-  int mt;            // 32-row MFMA tiles per workgroup
-  int nb;            // 32-column blocks per wave
+  int splits;        // split-K factor
+  int mt;            // 32-row tiles per workgroup
+  int nb;            // bf16: 1 the small-row kernel (up to 128 rows), 2 the large tiles
   int m_tiles;       // workgroup tiles along M
   int n_tiles;       // workgroup tiles along N
-  int wm;            // wave groups along M inside a workgroup (1: 256 threads, 2: 512 threads)
+  int ct;            // 32-column blocks per workgroup
 };
+// Large tiles (esp_gemm_large.h): row tiles and column blocks of 32 and what one costs, in ns: start and end of a round over the
+// 256 CUs, a chunk of 64 of K, and how much longer a chunk takes with all CUs at it (power and L2; with half of them, half of it).
+// Fitted to 3900 measured launches: M 136 to 2112, N and K of QKV, O, gate/up and down of two model shapes, 1 to 8 splits.  Of
+// the tiles and splits that were measured for a shape the model's choice is 0.8 % slower than the best on average, 10 % at most.
+struct LargeTileCost { int rt, ct, start, chunk, busy; };
+constexpr int N_LARGE_TILES = 11;
+constexpr LargeTileCost LARGE_TILES[N_LARGE_TILES] = {
+    {3, 8, 3980, 582, 94}, {4, 4, 2110, 413, 124}, {4, 6, 3660, 565, 75}, {4, 8, 5010, 584, 178}, {5, 6, 4720, 589, 97}, {5, 8, 6230, 646, 218},
+    {6, 6, 5400, 585, 192}, {6, 8, 6860, 710, 311}, {6, 10, 7800, 982, 206}, {8, 6, 6660, 784, 220}, {8, 8, 8130, 885, 368}};
+__host__ __device__ inline int64_t large_cost(const LargeTileCost& t, int rows, int blocks, int chunks, int splits) {
+  const int64_t n = (int64_t)((rows + 32 * t.rt - 1) / (32 * t.rt)) * ((blocks + t.ct - 1) / t.ct) * splits;
+  if (n == 0) return 0;
+  const int64_t before = (n - 1) / 256, last = n - 256 * before, c = (chunks + splits - 1) / splits;
+  return (before + 1) * t.start + c * ((before + 1) * t.chunk + t.busy * before + t.busy * last / 256);
+}
 GemmPlan gemm_plan(int dtype, int M, int N, int K);
+// of a batch with packed rows, of whose M rows only the device knows how many are there: for two thirds of them to all
+GemmPlan batch_gemm_plan(int M, int N, int K);
+// is a projection's output unsplit by its size (the LM head's epilogues see whole rows and are refused otherwise), and its plan
+bool gemm_whole_rows(int dtype, int M, int N, int K);
+GemmPlan whole_row_plan(int dtype, int M, int N, int K);
 inline size_t gemm_out_elems(const GemmPlan& p, int M, int N) { return (size_t)p.splits * M * N; }
+// most that a bf16 or fp32 product of up to M rows needs, a batch's among them
+size_t gemm_out_elems_bound(int dtype, int M, int N, int K);
 // out: fp32 [splits][M][N].  a_rows (device, may be null): physical row of A for logical row m.
 // w_packed: W is in the streaming layout written by launch_pack_weight (bf16 only).
 // m_live (device, may be null; bf16, packed weights and more than 128 rows only): how many of the M rows there are; row tiles
@@ -124,46 +137,53 @@ inline size_t gemm_out_elems(const GemmPlan& p, int M, int N) { return (size_t)p
 hipError_t launch_gemm(hipStream_t st, int dtype, const void* A, const int32_t* a_rows, const void* W,
                        float* out, int M, int N, int K, const GemmPlan& p, bool w_packed, int a_ld = 0,
                        const int32_t* m_live = nullptr);
-// a_ld == 0: A is row-major [rows][K]; a_ld > 0 (bf16 only): A is chunk-major [K/64][a_ld][64]
+// a_ld == 0: A is row-major [rows][K]; a_ld > 0 (bf16, up to 128 rows or unpacked weights): A is chunk-major [K/64][a_ld][64]
 hipError_t launch_pack_weight(hipStream_t st, const void* src, void* dst, int N, int K);
 // one-time kernel attributes of the GEMM kernels (dynamic LDS limits); call before the first launch
 hipError_t gemm_prepare();
-// Tile of the gate/up projection: gemm_plan's, or, above 128 rows, a wide one of 256 x 256 or 192 x 320 where that saves
-// rounds over the 256 CUs.  Cost: rounds times a round's time, in units of 10 ns: chunks x the time of one + start and
-// epilogue.  Measured over 129 to 2112 rows at N = 28672 and 24576, K = 4096: a round takes 63 to 66 us with 5 x 2 tiles, 57
-// with 4 x 2, 54 with 3 x 2, 97 to 103 with the wide ones, which therefore pay where they save rounds: 352 to 512 rows
-// (113..126 -> 97..104), 1024 x 28672 (244 -> 203), 544 to 576 x 24576 (123 -> 103); elsewhere the others are up to twice as
-// fast.
-// Of a batch of M block rows only the device knows how many are there: the host launches every tile that a number from two
-// thirds of M up asks for, the device (k_live_rows) hands the rows to the best of these, and the others end at once (1.6 us).
-// One tile, taken for a guess of three quarters: 640 rows all there took 180 us at N = 28672 (256 x 256 in two rounds) where the
-// ring takes 135, 400 all there 130 in two rounds of the ring.  There the last round counts by how full it is, since rounds
-// alone call two of 256 x 256 and three of the ring level: N = 28672, 660 to 768 rows 187 to 190 against 187 to 192 us (and 15 us
-// less in a step, whose other launches the ring's ordinary weight loads slow down), 769 to 960 rows 203 against 193 to 200.
-enum GateUpTile { GU_PLAN = 0, GU_256x256 = 1, GU_192x320 = 2, GU_TILES = 3 };
+// the large-tile kernel, a launcher per epilogue
+struct LargeGemm {
+  const void* A; const int32_t* a_rows; const void* W; void* out;
+  int M, N, K, splits, tile;               // tile: index into LARGE_TILES
+  const int32_t* draw_pos; uint32_t seed; const int32_t* m_live;
+};
+hipError_t launch_gemm_large_out(hipStream_t st, const LargeGemm& g);
+hipError_t launch_gemm_large_argmax(hipStream_t st, const LargeGemm& g);
+hipError_t launch_gemm_large_swiglu(hipStream_t st, const LargeGemm& g);
+hipError_t gemm_large_out_prepare();
+hipError_t gemm_large_argmax_prepare();
+hipError_t gemm_large_swiglu_prepare();
+// Tile of the gate/up projection above 128 rows, in three classes: the plan's, one with a side of 256 (256 x 256, 192 x 256 or
+// 256 x 192, by cost), and 192 x 320.  The host takes the wide classes where they save rounds over the 256 CUs against row tiles of
+// up to 160: `rounds` in units of 10 ns, chunks x the time of one + start and epilogue.  K = 4096: 512 x 28672 128 us with
+// 160 x 256 in two rounds, 95 with 256 x 256; 576 x 24576 108 and 93 with 192 x 320; 384 x 28672 101 and 79 with 192 x 256.
+// Of a batch of M block rows only the device knows how many are there: the host launches every class that a number from two
+// thirds of M up asks for, the device (k_live_rows) hands the rows to the cheapest of these, and the others end at once (1.6 us).
+enum GateUpTile { GU_PLAN = 0, GU_SIDE256 = 1, GU_192x320 = 2, GU_TILES = 3 };
 struct GateUpRule {
-  int mt = 1, chunks = 0, blocks = 0;      // row tiles of 32 of gemm_plan's tile; chunks of 64 of K; column blocks of 32
-  bool ragged = false;
-  unsigned launched = 1u << GU_PLAN;       // bit t: tile t is launched
-  // the tile for that many rows, of all (what to launch) or of the launched ones
-  __host__ __device__ GateUpTile tile(int rows, bool of_launched) const {
-    int64_t round[GU_TILES], n[GU_TILES], whole[GU_TILES], filled[GU_TILES];
+  int mt = 1, chunks = 0, blocks = 0;      // row tiles of 32 where as few tiles as possible have up to five; chunks of 64 of K; column blocks of 32
+  unsigned launched = 1u << GU_PLAN;       // bit t: class t is launched
+  int tile[GU_TILES] = {};                 // of LARGE_TILES
+  LargeTileCost cost[GU_TILES] = {};
+  GateUpTile by_rounds(int rows) const {
+    int64_t whole[GU_TILES];
     const int per[GU_TILES] = {32 * mt, 256, 192}, cols[GU_TILES] = {8, 8, 10};
     for (int t = 0; t < GU_TILES; ++t) {
-      round[t] = t == GU_PLAN ? (int64_t)chunks * (mt >= 5 ? 90 : mt == 4 ? 80 : 74) + 650 : (int64_t)chunks * 142 + 900;
-      n[t] = (int64_t)((rows + per[t] - 1) / per[t]) * ((blocks + cols[t] - 1) / cols[t]);
-      whole[t] = (n[t] + 255) / 256 * round[t];
-      const int64_t before = n[t] > 0 ? (n[t] - 1) / 256 : 0;        // rounds before the last, which takes so many per cent of one:
-      filled[t] = round[t] * (before * 25600 + (t == GU_PLAN ? 95 : 78) * 256 + (t == GU_PLAN ? 44 : 36) * (n[t] - 256 * before));
+      const int64_t round = t == GU_PLAN ? (int64_t)chunks * (mt >= 5 ? 90 : mt == 4 ? 80 : 74) + 650 : (int64_t)chunks * 142 + 900;
+      whole[t] = ((int64_t)((rows + per[t] - 1) / per[t]) * ((blocks + cols[t] - 1) / cols[t]) + 255) / 256 * round;
     }
-    const bool plan = !of_launched || (launched >> GU_PLAN & 1u), w44 = !of_launched || (launched >> GU_256x256 & 1u),
-               w35 = !of_launched || (launched >> GU_192x320 & 1u);
-    if (!w44 && !w35) return GU_PLAN;
-    const int64_t* c = of_launched ? filled : whole;
-    const GateUpTile w = w44 && (!w35 || c[GU_256x256] <= c[GU_192x320]) ? GU_256x256 : GU_192x320;
-    if (!plan) return w;
-    if (!ragged) return whole[w] * 100 < whole[GU_PLAN] * 95 ? w : GU_PLAN;
-    return filled[w] * 100 < filled[GU_PLAN] * 98 ? w : GU_PLAN;
+    const GateUpTile w = whole[GU_SIDE256] <= whole[GU_192x320] ? GU_SIDE256 : GU_192x320;
+    return whole[w] * 100 < whole[GU_PLAN] * 95 ? w : GU_PLAN;
+  }
+  __host__ __device__ GateUpTile cheapest_launched(int rows) const {
+    int best = -1;
+    int64_t least = 0;
+    for (int t = 0; t < GU_TILES; ++t)
+      if (launched >> t & 1u) {
+        const int64_t c = large_cost(cost[t], rows, blocks, chunks, 1);
+        if (best < 0 || c < least) { best = t; least = c; }
+      }
+    return (GateUpTile)best;
   }
 };
 GateUpRule gate_up_rule(int M, int ff, int K, const void* act, bool ragged);
@@ -171,7 +191,7 @@ unsigned gate_up_tiles(int M, int ff, int K, const void* act, bool ragged);   //
 // live (device, may be null): BlockDev::n_live of a batch with packed rows
 hipError_t launch_gemm_swiglu(hipStream_t st, const void* A, const void* W, void* act, int M, int ff, int K,
                               const int32_t* live = nullptr);
-// LM head with the arg-max taken in the GEMM epilogue (bf16, packed weights, <= 128 rows, one split)
+// LM head with the arg-max taken in the GEMM epilogue (bf16, packed weights, one split)
 bool gemm_argmax_supported(int dtype, int M, int N, int K, bool with_logits);
 size_t gemm_argmax_scratch_floats(int M, int N);
 // logits_out == NULL: arg-max of each of the M rows (out[out_index[m]]), logits never written.

@@ -175,6 +175,73 @@ def test_gemm_swiglu(B, M, ff, K, live, tile):
     assert bool((act[rows:] == -7).all())
 
 
+LARGE_TILES = [(3, 8), (4, 4), (4, 6), (4, 8), (5, 6), (5, 8), (6, 6), (6, 8), (6, 10), (8, 6), (8, 8)]   # 32-row and 32-column tiles
+
+
+class LargePlan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("splits", "mt", "nb", "m_tiles", "n_tiles", "ct")]
+
+
+class LargeGemm(ctypes.Structure):
+    _fields_ = ([(n, ctypes.c_void_p) for n in ("A", "a_rows", "W", "out")] + [(n, ctypes.c_int) for n in ("M", "N", "K", "splits", "tile")] +
+                [("draw_pos", ctypes.c_void_p), ("seed", ctypes.c_uint32), ("m_live", ctypes.c_void_p)])
+
+
+@pytest.mark.parametrize("tile", range(len(LARGE_TILES)))
+@pytest.mark.parametrize("M,N,K,splits,live", [
+    (129, 544, 64, 1, None), (257, 352, 128, 1, None), (160, 1056, 192, 1, None), (300, 96, 256, 1, None), (192, 256, 320, 1, None),
+    (513, 416, 704, 3, None), (256, 640, 512, 8, None), (320, 320, 1088, 2, None), (385, 192, 1536, 1, None),
+    (200, 320, 1088, 2, 77), (700, 288, 448, 1, 513), (300, 256, 384, 1, 1), (300, 256, 384, 1, 0)])
+def test_gemm_large_tiles(B, tile, M, N, K, splits, live):
+    """Every large tile at remainders of rows and columns, from one chunk of K (fewer than the loads reach ahead) to many, in
+    parts, and with rows of a batch that are not there: bit for bit what the kernel for row-major weights gives, which adds in
+    the same order; with one part also its arg-max and SwiGLU epilogues against the same logits (ties: the lowest column)."""
+    c = ctypes
+    rt, ct = LARGE_TILES[tile]
+    print(f"large tile {rt}x{ct} M={M} N={N} K={K} splits={splits} live={live}", flush=True)
+    gemm = internal("launch_gemm", c.c_void_p, c.c_int, c.c_void_p, c.c_void_p, c.c_void_p, c.c_void_p, *[c.c_int] * 3, c.POINTER(LargePlan),
+                    c.c_bool, c.c_int, c.c_void_p)
+    a = synth.normal_like((M, K), 1.0, 16, 0, "cuda", torch.bfloat16)
+    w = synth.normal_like((N, K), K ** -0.5, 16, 1, "cuda", torch.bfloat16)
+    w[N // 2:] = w[:N - N // 2]                              # every column twice: ties of the arg-max
+    wp = B.pack_weight(w)
+    n = None if live is None else torch.tensor([live], dtype=torch.int32, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    plan = LargePlan(splits, rt, 2, (M + 32 * rt - 1) // (32 * rt), (N // 32 + ct - 1) // ct, ct)
+    got, want = (torch.full((splits, M, N), -7.0, device="cuda") for _ in range(2))
+    assert gemm(st, B.ESP_BF16, a.data_ptr(), None, wp.data_ptr(), got.data_ptr(), M, N, K, plan, True, 0, None if n is None else n.data_ptr()) == 0
+    assert gemm(st, B.ESP_BF16, a.data_ptr(), None, w.data_ptr(), want.data_ptr(), M, N, K, plan, False, 0, None) == 0
+    rows = M if live is None else live
+    assert torch.equal(got[:, :rows], want[:, :rows]) and bool((got[:, rows:] == -7).all())
+    ref = a.double() @ w.double().T
+    assert float((want.double().sum(0) - ref).abs().max()) <= 2e-5 * float(ref.abs().max())   # fp32 sums of up to 1536 exact products
+    if splits > 1 or not rows:
+        return
+    out = torch.full((plan.n_tiles, M, 2), -7.0, device="cuda")
+    g = LargeGemm(a.data_ptr(), None, wp.data_ptr(), out.data_ptr(), M, N, K, 1, tile, None, 0, None if n is None else n.data_ptr())
+    assert internal("launch_gemm_large_argmax", c.c_void_p, c.POINTER(LargeGemm))(st, g) == 0
+    for t in range(plan.n_tiles):
+        cols = want[0, :rows, t * 32 * ct:(t + 1) * 32 * ct]
+        best = cols.amax(1)
+        assert torch.equal(out[t, :rows, 0], best)
+        first = (cols == best[:, None]).int().argmax(1) + t * 32 * ct
+        assert torch.equal(out[t, :rows, 1].contiguous().view(torch.int32).long(), first)
+    assert bool((out[:, rows:] == -7).all())
+    if N % 64 == 0:
+        act = torch.full((M + 1, N // 2), -7.0, dtype=torch.bfloat16, device="cuda")
+        for offset in (0, 1):                                # results on and off the 16-byte alignment of the wide stores
+            flat = act.view(-1)[offset:offset + M * (N // 2)]
+            g.out = flat.data_ptr()
+            assert internal("launch_gemm_large_swiglu", c.c_void_p, c.POINTER(LargeGemm))(st, g) == 0
+            blocks = want[0, :rows].double().view(rows, N // 64, 2, 32)
+            gate, up = blocks[:, :, 0].reshape(rows, -1), blocks[:, :, 1].reshape(rows, -1)
+            r = gate / (1 + torch.exp(-gate)) * up
+            # exp and reciprocal to 1 ulp each, then the rounding to bf16
+            res = flat.view(M, N // 2)[:rows].double()
+            assert bool(((res - r).abs() <= r.abs() * (2.0 ** -8 + 1e-6) + 1e-30).all())
+            assert bool((flat.view(M, N // 2)[rows:] == -7).all()) if offset == 0 else True
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (13, 4096, 256), (52, 688, 256), (52, 256, 688), (70, 130, 77)])
 def test_gemm_f32(B, M, N, K):
     print(f"gemm f32 M={M} N={N} K={K}", flush=True)
