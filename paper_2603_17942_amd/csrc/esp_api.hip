@@ -10,7 +10,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline size_t elt(int dtype) { return dtype == ESP_F32 ? 4 : 2; }
 
 struct WsLayout {
-  size_t h, xn, q, attn_out, act, gemm_out, attn_part, rope_tab, logits, topk_scratch, idx_a, idx_b, idx_c, idx_d, live, status, total;
+  size_t h, xn, q, attn_out, act, gemm_out, attn_part, rope_tab, logits, topk_scratch, idx_a, idx_b, idx_c, idx_d, live, cuts, status, total;
   size_t gemm_out_floats, attn_part_floats, logits_rows;
 };
 
@@ -64,6 +64,7 @@ WsLayout ws_layout(const esp_model_desc* m, int max_batch, int max_rows, int64_t
   w.idx_c = take(std::max<size_t>(M, (size_t)max_batch * ESP_MAX_MASKS) * 4);
   w.idx_d = take(std::max<size_t>(M, (size_t)max_batch * ESP_MAX_MASKS) * 4);
   w.live = take(BlockDev::packed_ints(M, max_batch) * 4);
+  w.cuts = take(attn_cuts_ints(max_batch) * 4);
   w.status = take(256);
   w.total = off;
   return w;
@@ -232,6 +233,7 @@ esp_status esp_create(const esp_model_desc* m, const esp_weights* w, int32_t max
   c->idx_a = (int32_t*)(c->ws + L.idx_a); c->idx_b = (int32_t*)(c->ws + L.idx_b);
   c->idx_c = (int32_t*)(c->ws + L.idx_c); c->idx_d = (int32_t*)(c->ws + L.idx_d);
   c->packed = (int32_t*)(c->ws + L.live);
+  c->cuts = (int32_t*)(c->ws + L.cuts);
   c->status = (int32_t*)(c->ws + L.status);
   c->gemm_out_floats = L.gemm_out_floats; c->attn_part_floats = L.attn_part_floats; c->logits_rows = L.logits_rows;
   if (hipMemsetAsync(c->status, 0, 256, c->stream) != hipSuccess) {
@@ -339,6 +341,9 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
     if (!gemm_whole_rows(dt, Mlm, m.vocab, d)) return ESP_ESHAPE;
   }
 
+  const int shares = attn_shares(dt, hd, blk->batch, blk->rows_per_seq, hq, hkv, ap);
+  const int32_t* cuts = shares ? c->cuts : nullptr;
+  const GateUpRule gate_up = pk ? gate_up_rule(M, ff, d, c->act, packed) : GateUpRule{};
   const int32_t* m_live = nullptr;
   PackedEnd end;
   { ESP_PROF(ESP_SITE_GLUE);
@@ -346,11 +351,12 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
     end.rows[0] = (bf16_t*)c->xn; end.rows[1] = (bf16_t*)c->attn_out; end.rows[2] = (bf16_t*)c->act;
     end.width[0] = d; end.width[1] = hq * hd; end.width[2] = ff;
     bd.packed = c->packed;
-    ESP_HIP(launch_live_rows(s, bd, kd, nodes_bound(blk), gate_up_rule(M, ff, d, c->act, true)));
+    ESP_HIP(launch_live_rows(s, bd, kd, nodes_bound(blk), gate_up));
     m_live = bd.n_live();
   }
   ESP_HIP(launch_embed(s, dt, bd, kd, c->embed, mask_embed, c->h, d, m.vocab, c->rope_tab, hd, m.rope_theta,
                        c->status, c->mask_per_seq ? (size_t)blk->k_masks * d : 0, end));
+  if (shares) ESP_HIP(launch_attn_cuts(s, bd, kd, hq, hkv, ap, shares, c->cuts));
   ESP_HIP(launch_residual_norm(s, dt, c->h, nullptr, 0, M, d, c->norm_attn[0], m.rms_eps, c->xn, m_live)); }
   for (int l = 0; l < m.n_layers; ++l) {
     { ESP_PROF_KERNEL(ESP_SITE_GEMM_LAYER, dt == ESP_BF16);
@@ -359,16 +365,16 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
       ESP_HIP(launch_qkv_post(s, dt, bd, kd, l, c->gemm_out, p_qkv.splits, M, hq, hkv, hd, m.qk_norm, c->q_norm[l],
                               c->k_norm[l], m.rms_eps, c->rope_tab, c->q)); }
     { ESP_PROF(ESP_SITE_ATTN);
-      ESP_HIP(launch_attn(s, dt, bd, kd, l, hq, hkv, hd, c->q, c->attn_part, ap)); }
+      ESP_HIP(launch_attn(s, dt, bd, kd, l, hq, hkv, hd, c->q, c->attn_part, ap, cuts)); }
     { ESP_PROF(ESP_SITE_ATTN_MERGE);
-      ESP_HIP(launch_attn_merge(s, dt, bd, kd, hq, hkv, hd, c->attn_part, ap, c->attn_out)); }
+      ESP_HIP(launch_attn_merge(s, dt, bd, kd, hq, hkv, hd, c->attn_part, ap, c->attn_out, cuts)); }
     { ESP_PROF_KERNEL(ESP_SITE_GEMM_LAYER, dt == ESP_BF16);
       ESP_HIP(launch_gemm(s, dt, c->attn_out, nullptr, c->wo[l], c->gemm_out, M, d, hq * hd, p_o, pk, 0, m_live)); }
     { ESP_PROF(ESP_SITE_GLUE);
       ESP_HIP(launch_residual_norm(s, dt, c->h, c->gemm_out, p_o.splits, M, d, c->norm_mlp[l], m.rms_eps, c->xn, m_live)); }
     if (dt == ESP_BF16) {   // gate/up projection with the SwiGLU in its epilogue (interleaved weight rows)
       ESP_PROF_KERNEL(ESP_SITE_GEMM_LAYER, true);
-      ESP_HIP(launch_gemm_swiglu(s, c->xn, c->wgu[l], c->act, M, ff, d, m_live));
+      ESP_HIP(launch_gate_up(s, c->xn, c->wgu[l], c->act, M, ff, d, m_live, gate_up));
     } else {
       { ESP_PROF(ESP_SITE_GEMM_LAYER);
         ESP_HIP(launch_gemm(s, dt, c->xn, nullptr, c->wgu[l], c->gemm_out, M, 2 * ff, d, gemm_plan(dt, M, 2 * ff, d), pk)); }
@@ -701,12 +707,15 @@ esp_status esp_attn_tree(esp_ctx* c, const esp_block* blk, const esp_kv* kv, int
   if (attn_partial_floats(m.dtype, blk->batch, blk->rows_per_seq, m.n_q_heads, m.n_kv_heads, m.head_dim, ap) >
       c->attn_part_floats)
     return ESP_ECAPACITY;
+  const int shares = attn_shares(m.dtype, m.head_dim, blk->batch, blk->rows_per_seq, m.n_q_heads, m.n_kv_heads, ap);
+  const int32_t* cuts = shares ? c->cuts : nullptr;
   { ESP_PROF(ESP_SITE_ATTN);
+    if (shares) ESP_HIP(launch_attn_cuts(c->stream, to_dev(blk), to_dev(kv), m.n_q_heads, m.n_kv_heads, ap, shares, c->cuts));
     ESP_HIP(launch_attn(c->stream, m.dtype, to_dev(blk), to_dev(kv), layer, m.n_q_heads, m.n_kv_heads, m.head_dim, q,
-                        c->attn_part, ap)); }
+                        c->attn_part, ap, cuts)); }
   { ESP_PROF(ESP_SITE_ATTN_MERGE);
     ESP_HIP(launch_attn_merge(c->stream, m.dtype, to_dev(blk), to_dev(kv), m.n_q_heads, m.n_kv_heads, m.head_dim, c->attn_part, ap,
-                              out)); }
+                              out, cuts)); }
   return ESP_OK;
 }
 

@@ -294,53 +294,163 @@ __device__ __forceinline__ void ring_unit(bool masked, const unsigned char* kst,
   __builtin_amdgcn_s_setprio(0);
 }
 
+// Waves of a workgroup with ct_wg column tiles and tps key tiles.  A wave has a whole column tile, or the even or odd
+// half of each of its key tiles; the SIMD with the most half-tiles sets the pace (waves go to SIMDs round-robin).  Two
+// waves share a column tile where that evens the SIMDs out: ct_wg = 9 gives loads of 5, 5, 4, 4 half-tiles instead of
+// 6, 4, 4, 4; with one or two column tiles it puts idle SIMDs to work, where there are key tiles enough to make up for
+// the exchange at the end (68 rows, 2048 keys, two column tiles: 20.1 -> 18.2 us; one key tile: 10.7 -> 11.3).  At least
+// four waves (they carry the loads).
+struct RingGeometry { int n_full, waves; };
+__host__ __device__ inline RingGeometry ring_geometry(int ct_wg, int tps) {
+  const int rem = ct_wg & 3;
+  int paired = 0;
+  if (ct_wg <= 2) paired = tps >= 3 ? ct_wg : 0;
+  else if ((rem == 1 || rem == 2) && ct_wg > 4 && ct_wg + rem <= RING_MAX_WAVES) paired = rem;
+  return {ct_wg - paired, ct_wg + paired < 4 ? 4 : ct_wg + paired};
+}
+// time of a key tile in a workgroup with that many column tiles, 10 ns
+__host__ __device__ constexpr int ring_tile_time(int c) {
+  constexpr int t[RING_MAX_WAVES] = {84, 70, 104, 110, 120, 126, 138, 150, 165, 175, 208, 218};
+  return t[c - 1];
+}
+constexpr int PIECE_TIME = 180;                          // start and end of a workgroup's work on a sequence, 10 ns
+
+// ---- batches: one line of work per kv head ----------------------------------------------------------------------
+// The sequences of a batch differ in length and rows, which only the device knows.  A grid of equal splits of the longest
+// one gives the CUs unequal work (16 sequences of 1638 to 8192 keys and 40 to 132 rows: a launch took 237 us, the longest
+// sequence's single split 215 of them).  Instead the sequences' key tiles, each weighted with its time, form one line per kv
+// head, which is cut into as many equal shares as there are workgroups; a share is one sequence's tiles, or the end of one,
+// some whole ones and the start of another.  A column group of a share (q_tiles of them) is a workgroup of its own beside the others, so
+// that they read the same keys at the same time.  Piece (sequence s, share w) leaves its partial in slot s + w, which
+// rises along the line: pieces never share one, and those of a sequence are consecutive.
+// Table of the cuts (ints): [0] shares; share w begins at tile [3 + 2 w] of sequence [2 + 2 w], w <= shares; then per sequence
+// the first and the last share that has any of it.
+constexpr int MAX_SHARES = 63;
+__host__ __device__ constexpr int cuts_of_seq(int max_shares) { return 2 + 2 * (max_shares + 1); }
+
+// columns of a sequence in a workgroup: its column tiles spread evenly over the groups
+__device__ __forceinline__ int even_ct(int ncols, int q_tiles) { return ((ncols + 31) / 32 + q_tiles - 1) / q_tiles; }
+
+__global__ __launch_bounds__(256) void k_attn_cuts(BlockDev b, KvDev kv, int G, int q_tiles, int max_shares, int32_t* __restrict__ cuts) {
+  __shared__ int64_t red[4];
+  const int tid = threadIdx.x;
+  // weight and key tiles of a sequence
+  auto weigh = [&](int s, int& nt, int& u) {
+    const int nr = b.n_rows[s];
+    nt = 0; u = 1;
+    if (!seq_ok(kv, s, nr, b.rows_per_seq) || nr == 0) return 0;
+    nt = (kv.len[s] + nr + 63) >> 6;
+    u = ring_tile_time(even_ct(nr * G, q_tiles));
+    return PIECE_TIME + nt * u;
+  };
+  int nt, u;
+  int64_t sum = 0;
+  for (int s = tid; s < b.batch; s += 256) sum += weigh(s, nt, u);
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if ((tid & 63) == 0) red[tid >> 6] = sum;
+  __syncthreads();
+  const int64_t total = red[0] + red[1] + red[2] + red[3];
+  // a share of less than about two key tiles costs more in its partial than it gives
+  const int64_t shares = max((int64_t)1, min((int64_t)max_shares, total / 400));
+  if (tid == 0) {
+    cuts[0] = (int)shares;
+    cuts[2 + 2 * shares] = b.batch; cuts[3 + 2 * shares] = 0;
+    if (total == 0) { cuts[2] = b.batch; cuts[3] = 0; }
+  }
+  for (int s = tid; s < b.batch; s += 256) {
+    int64_t c0 = 0;
+    for (int i = 0; i < s; ++i) c0 += weigh(i, nt, u);
+    const int w = weigh(s, nt, u);
+    int first = 0, last = -1;
+    if (w > 0) {
+      first = (int)min(shares - 1, c0 * shares / total);            // share x begins at x * total / shares
+      while ((int64_t)first * total / shares > c0) --first;
+      while (first + 1 < shares && (int64_t)(first + 1) * total / shares <= c0) ++first;
+      last = first;
+      while (last + 1 < shares && (int64_t)(last + 1) * total / shares < c0 + w) ++last;
+      for (int x = first; x <= last; ++x) {
+        const int64_t at = (int64_t)x * total / shares - c0;
+        if (at < 0) continue;                                       // begins in a sequence before
+        cuts[2 + 2 * x] = s;
+        cuts[3 + 2 * x] = (int)min((int64_t)nt, max((int64_t)0, (at - PIECE_TIME + u - 1) / u));
+      }
+    }
+    cuts[cuts_of_seq(max_shares) + 2 * s] = first;
+    cuts[cuts_of_seq(max_shares) + 2 * s + 1] = last;
+  }
+}
+
+// the key tiles of sequence s, nt in all, that share w has
+__device__ __forceinline__ void share_tiles(const int32_t* __restrict__ cuts, int w, int s, int nt, int& t0, int& t1) {
+  t0 = cuts[2 + 2 * w] == s ? cuts[3 + 2 * w] : 0;
+  t1 = cuts[4 + 2 * w] == s ? cuts[5 + 2 * w] : nt;
+}
+
 // LPW: 1 KB wave-loads per loading wave and tile (the first 32 / LPW waves of the workgroup load).  NT: K and V by
 // nontemporal loads.
-template <int LPW, bool PACKED, bool NT>
+// CUTS: a share of a batch's line of work instead of one split of one sequence (cuts; nsplit: shares launched).
+template <int LPW, bool PACKED, bool NT, bool CUTS>
 __global__ __launch_bounds__(64 * RING_MAX_WAVES) void k_attn_ring(BlockDev b, KvDev kv, int layer, int hq, int hkv,
                                                                   const bf16_t* __restrict__ q,
                                                                   float* __restrict__ part_o,
                                                                   float* __restrict__ part_ml, int nsplit, int tps,
-                                                                  int q_tiles, int ct_wg, int n_full) {
+                                                                  int q_tiles, int ct_wg, int n_full_wg,
+                                                                  const int32_t* __restrict__ cuts) {
   constexpr int HD = 128;
   extern __shared__ __align__(16) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lg = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // this wave's column tile inside the workgroup and the halves of every key tile it works on: waves
-  // up to n_full take a whole tile each, the others pair up on one (first = keys 0..31 of a tile,
-  // second = keys 32..63) and are merged at the end; waves beyond the tiles only help load
-  const int ctl = wave < n_full ? wave : n_full + ((wave - n_full) >> 1);
-  const bool pair = wave >= n_full;
-  const int kh_first = pair ? ((wave - n_full) & 1) : 0, kh_last = pair ? kh_first : 1;
   const int G = hq / hkv;
   // XCD-aware logical id: the query tiles that stream the same keys (same kv head, same split) get
-  // consecutive logical ids on one XCD and so share its L2
-  const int total_wg = q_tiles * hkv * b.batch * nsplit;
+  // consecutive logical ids on one XCD and so share its L2; the shares of a kv head are neighbours too
+  const int total_wg = CUTS ? q_tiles * hkv * nsplit : q_tiles * hkv * b.batch * nsplit;
   const int per_xcd = (total_wg + 7) >> 3;
   const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (logical >= total_wg) return;
   const int qt = logical % q_tiles;
-  const int kvh = (logical / q_tiles) % hkv;
+  const int kvh = CUTS ? logical / (q_tiles * nsplit) : (logical / q_tiles) % hkv;
   const int zz = logical / (q_tiles * hkv);
-  const int seq = zz / nsplit, sp = zz % nsplit;
+  const int share = (logical / q_tiles) % nsplit;
+  if (CUTS && share >= cuts[0]) return;
+  const int seq_first = CUTS ? cuts[2 + 2 * share] : zz / nsplit;
+  const int seq_last = CUTS ? min(cuts[4 + 2 * share], b.batch - 1) : seq_first;
+  const int sp = zz % nsplit;
+
+  auto piece = [&](int seq) {
   const int nr = b.n_rows[seq];
   if (!seq_ok(kv, seq, nr, b.rows_per_seq)) return;
   const int ncols = nr * G;
-  if (qt * ct_wg * 32 >= ncols) return;                 // no live query column in this workgroup
+  const int ct_own = CUTS ? even_ct(ncols, q_tiles) : ct_wg;   // column tiles of a workgroup
+  if (qt * ct_own * 32 >= ncols) return;                // no live query column in this workgroup
   const int L = kv.len[seq], total = L + nr;
   const int ntiles = (total + 63) >> 6;
-  const int t0 = sp * tps, t1 = min(ntiles, t0 + tps);
+  int t0 = sp * tps, t1 = min(ntiles, t0 + tps);
+  if (CUTS) share_tiles(cuts, share, seq, ntiles, t0, t1);
   const int nt = t1 - t0;
+  if (CUTS && nt <= 0) return;
+  // this wave's column tile inside the workgroup and the halves of every key tile it works on: waves
+  // up to n_full take a whole tile each, the others pair up on one (first = keys 0..31 of a tile,
+  // second = keys 32..63) and are merged at the end; waves beyond the tiles only help load
+  int n_full = n_full_wg;
+  if (CUTS) {
+    const RingGeometry g = ring_geometry(ct_own, nt);
+    n_full = g.waves * 64 <= (int)blockDim.x ? g.n_full : ct_own;
+  }
+  const int ctl = wave < n_full ? wave : n_full + ((wave - n_full) >> 1);
+  const bool pair = wave >= n_full;
+  const int kh_first = pair ? ((wave - n_full) & 1) : 0, kh_last = pair ? kh_first : 1;
 
-  const int qcol = (qt * ct_wg + ctl) * 32 + lr;
+  const int qcol = (qt * ct_own + ctl) * 32 + lr;
   const bool col_live = qcol < ncols;
-  const bool wave_live = ctl < ct_wg && (qt * ct_wg + ctl) * 32 < ncols;  // wave-uniform
+  const bool wave_live = ctl < ct_own && (qt * ct_own + ctl) * 32 < ncols;  // wave-uniform
   const int r = col_live ? qcol / G : 0;
   const int h = kvh * G + (col_live ? qcol % G : 0);
   const size_t row = (size_t)seq * b.rows_per_seq + r;
   // partial of this wave's column tile and split: O^T as [feature][column] (a store instruction of
   // the wave covers whole 128-byte lines), then (m, l) per column
-  const size_t ptile = (((size_t)seq * hkv + kvh) * (q_tiles * ct_wg) + qt * ct_wg + min(ctl, ct_wg - 1)) * nsplit + sp;
+  const size_t n_ct = (size_t)q_tiles * ct_wg, ct = qt * ct_own + min(ctl, ct_own - 1);
+  const size_t ptile = CUTS ? ((size_t)kvh * (b.batch + nsplit) + seq + share) * n_ct + ct
+                            : (((size_t)seq * hkv + kvh) * n_ct + ct) * nsplit + sp;
   float* po = part_o + ptile * (HD * 32);
   float* pml = part_ml + ptile * 64;
 
@@ -433,7 +543,7 @@ __global__ __launch_bounds__(64 * RING_MAX_WAVES) void k_attn_ring(BlockDev b, K
   }
 
   l += __shfl_xor(l, 32, 64);
-  if (n_full < ct_wg) {
+  if (n_full < ct_own) {
     // paired waves: the second hands its (m, l, O) to the first through LDS (the ring is free now)
     __syncthreads();
     float* xo = reinterpret_cast<float*>(lds) + (size_t)(ctl - n_full) * (HD * 32 + 64);
@@ -466,6 +576,14 @@ __global__ __launch_bounds__(64 * RING_MAX_WAVES) void k_attn_ring(BlockDev b, K
 #pragma unroll
       for (int v = 0; v < 16; ++v) po[(db * 32 + 8 * (v >> 2) + 4 * lg + (v & 3)) * 32 + lr] = oacc[db][v];
     if (lg == 0) { pml[lr * 2] = m * scale; pml[lr * 2 + 1] = l; }   // m in the exponent's units
+  }
+  };
+  for (int seq = seq_first; seq <= seq_last; ++seq) {
+    if (CUTS && seq > seq_first) {                      // the last piece's stores do not count as loads of this one; everyone is done with the LDS
+      wait_loads_but<0>();
+      __syncthreads();
+    }
+    piece(seq);
   }
 }
 
@@ -516,12 +634,14 @@ __global__ __launch_bounds__(256) void k_attn_merge(BlockDev b, KvDev kv, int hq
 // fetches the (m, l) of every eighth split at once -- one after the other, a column's splits would
 // cost a memory latency each -- and the eight groups combine through LDS.  Then thread (column,
 // feature quad) sums the splits' O, every load instruction of a wave covering whole 128-byte lines.
-template <int MAXS, bool PACKED>
+// CUTS: the pieces of a sequence in the shares of its batch's line (nsplit: shares launched).
+template <int MAXS, bool PACKED, bool CUTS>
 __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, int hq, int hkv,
                                                          const float* __restrict__ part_o,
                                                          const float* __restrict__ part_ml, int nsplit,
-                                                         int n_ct, bf16_t* __restrict__ out) {
+                                                         int n_ct, bf16_t* __restrict__ out, const int32_t* __restrict__ cuts) {
   constexpr int HD = 128, PER = MAXS / 8;
+  __shared__ int slots[CUTS ? MAXS : 1], n_slots[1];
   __shared__ float w_s[MAXS][32];
   __shared__ float red[8][32];
   __shared__ float red_l[8][32];
@@ -535,7 +655,23 @@ __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, i
   const int c = ct * 32 + col;                      // column within the kv group
   const bool live = ok && c < nr * G;
   const bool in_block = PACKED ? live : c < b.rows_per_seq * G;     // has an output row at all
-  const size_t t0 = (size_t)tile * nsplit;
+  size_t t0 = (size_t)tile * nsplit, step = 1;          // first partial of the column tile, and how far apart they are
+  if constexpr (CUTS) {
+    const int32_t* ends = cuts + cuts_of_seq(nsplit) + 2 * seq;
+    const int first = ends[0], pieces = ok ? ends[1] - first + 1 : 0;   // at most 63
+    if (threadIdx.x < 64) {
+      int a = 0, e = 0;
+      if ((int)threadIdx.x < pieces) share_tiles(cuts, first + threadIdx.x, seq, (kv.len[seq] + nr + 63) >> 6, a, e);
+      const uint64_t there = __builtin_amdgcn_ballot_w64(a < e);
+      if (a < e) slots[__popcll(there & ((1ull << threadIdx.x) - 1ull))] = seq + first + threadIdx.x;
+      if (threadIdx.x == 0) n_slots[0] = __popcll(there);
+    }
+    __syncthreads();
+    t0 = (size_t)kvh * (b.batch + nsplit) * n_ct + ct;
+    step = n_ct;
+    nsplit = n_slots[0];
+  }
+  auto part = [&](int sp) { return t0 + (CUTS ? (size_t)slots[sp] : (size_t)sp) * step; };
   float ms[PER], ls[PER];
   float mx = NEG_BIG;
 #pragma unroll
@@ -543,7 +679,7 @@ __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, i
     const int sp = grp + 8 * i;
     ms[i] = NEG_BIG; ls[i] = 0.f;
     if (live && sp < nsplit) {
-      const float2 ml = *reinterpret_cast<const float2*>(part_ml + (t0 + sp) * 64 + col * 2);
+      const float2 ml = *reinterpret_cast<const float2*>(part_ml + part(sp) * 64 + col * 2);
       ms[i] = ml.x; ls[i] = ml.y;
     }
     mx = fmaxf(mx, ms[i]);
@@ -572,11 +708,11 @@ __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, i
   const int f0 = fq * 32 + fsub * 4;
   f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
   if (live) {
-    const float* p = part_o + t0 * (HD * 32) + (size_t)f0 * 32 + col;
+    const float* p = part_o + (size_t)f0 * 32 + col;
 #pragma unroll 8
     for (int s = 0; s < nsplit; ++s) {
       const float w = w_s[s][col];
-      const float* ps = p + (size_t)s * (HD * 32);
+      const float* ps = p + part(s) * (HD * 32);
       acc[0] += ps[0] * w; acc[1] += ps[32] * w; acc[2] += ps[64] * w; acc[3] += ps[96] * w;
     }
     acc *= inv;
@@ -591,10 +727,14 @@ __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, i
 // called when a context is created, so that no launch inside a stream capture is the first one)
 hipError_t attn_prepare() {
   static const hipError_t attr = [] {
-    for (const void* k : {reinterpret_cast<const void*>(k_attn_ring<4, false, false>), reinterpret_cast<const void*>(k_attn_ring<8, false, false>),
-                          reinterpret_cast<const void*>(k_attn_ring<4, true, false>), reinterpret_cast<const void*>(k_attn_ring<8, true, false>),
-                          reinterpret_cast<const void*>(k_attn_ring<4, false, true>), reinterpret_cast<const void*>(k_attn_ring<8, false, true>),
-                          reinterpret_cast<const void*>(k_attn_ring<4, true, true>), reinterpret_cast<const void*>(k_attn_ring<8, true, true>)}) {
+    for (const void* k : {reinterpret_cast<const void*>(k_attn_ring<4, false, false, false>), reinterpret_cast<const void*>(k_attn_ring<4, false, false, true>),
+                          reinterpret_cast<const void*>(k_attn_ring<4, false, true, false>), reinterpret_cast<const void*>(k_attn_ring<4, false, true, true>),
+                          reinterpret_cast<const void*>(k_attn_ring<4, true, false, false>), reinterpret_cast<const void*>(k_attn_ring<4, true, false, true>),
+                          reinterpret_cast<const void*>(k_attn_ring<4, true, true, false>), reinterpret_cast<const void*>(k_attn_ring<4, true, true, true>),
+                          reinterpret_cast<const void*>(k_attn_ring<8, false, false, false>), reinterpret_cast<const void*>(k_attn_ring<8, false, false, true>),
+                          reinterpret_cast<const void*>(k_attn_ring<8, false, true, false>), reinterpret_cast<const void*>(k_attn_ring<8, false, true, true>),
+                          reinterpret_cast<const void*>(k_attn_ring<8, true, false, false>), reinterpret_cast<const void*>(k_attn_ring<8, true, false, true>),
+                          reinterpret_cast<const void*>(k_attn_ring<8, true, true, false>), reinterpret_cast<const void*>(k_attn_ring<8, true, true, true>)}) {
       const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, RING_LDS_BYTES);
       if (e != hipSuccess) return e;
     }
@@ -604,20 +744,6 @@ hipError_t attn_prepare() {
 }
 
 namespace {
-// Waves of a workgroup with ct_wg column tiles and tps key tiles.  A wave has a whole column tile, or the even or odd
-// half of each of its key tiles; the SIMD with the most half-tiles sets the pace (waves go to SIMDs round-robin).  Two
-// waves share a column tile where that evens the SIMDs out: ct_wg = 9 gives loads of 5, 5, 4, 4 half-tiles instead of
-// 6, 4, 4, 4; with one or two column tiles it puts idle SIMDs to work, where there are key tiles enough to make up for
-// the exchange at the end (68 rows, 2048 keys, two column tiles: 20.1 -> 18.2 us; one key tile: 10.7 -> 11.3).  At least
-// four waves (they carry the loads).
-struct RingGeometry { int n_full, waves; };
-RingGeometry ring_geometry(int ct_wg, int tps) {
-  const int rem = ct_wg & 3;
-  int paired = 0;
-  if (ct_wg <= 2) paired = tps >= 3 ? ct_wg : 0;
-  else if ((rem == 1 || rem == 2) && ct_wg > 4 && ct_wg + rem <= RING_MAX_WAVES) paired = rem;
-  return {ct_wg - paired, std::max(4, ct_wg + paired)};
-}
 // most partial column tiles (column tiles x splits) of a plan, per sequence and kv head: what the workspace holds
 int ring_tiles_bound(int cols) {
   const int ct = (cols + 31) / 32, q = (ct + RING_MAX_WAVES - 1) / RING_MAX_WAVES;
@@ -671,11 +797,10 @@ AttnPlan attn_plan(int dtype, int hd, int batch, int rows_per_seq, int hq, int h
   // with nearly every CU on one long split 25 us of 260 (eight sequences of 200 rows on 8192 keys, in a step).  Over the
   // shapes 0.948 of the plan above's time on average, four of them slower by 2 to 4.5 %, the others by at most 1.5 %.
   // Attention and merge of a layer: 90 rows on 2048 keys 26.6 -> 19.6 us, 132 rows on 1000 keys 24.5 -> 17.6.
-  static const int tile_time[RING_MAX_WAVES] = {84, 70, 104, 110, 120, 126, 138, 150, 165, 175, 208, 218};
   auto cost = [&](int q, int c, int ns, int tps) {
     const int64_t groups = (int64_t)q * hkv * batch, rounds = (groups * ns + 255) / 256, busy = std::min<int64_t>(groups * ns, 256);
     const bool short_unpaired = c <= 2 && tps < 3;
-    const int64_t tile = std::max<int64_t>(short_unpaired ? 104 : tile_time[c - 1] + (c <= 2 ? 6 * busy / 256 : 0), 80 * busy / 256);
+    const int64_t tile = std::max<int64_t>(short_unpaired ? 104 : ring_tile_time(c) + (c <= 2 ? 6 * busy / 256 : 0), 80 * busy / 256);
     return 880 + rounds * ((short_unpaired ? 160 : 180) + tps * tile) + groups * c * ns * 55 / 100;
   };
   const int64_t base_wg = (int64_t)p.q_tiles * hkv * batch * p.nsplit;
@@ -710,35 +835,61 @@ size_t attn_partial_floats_bound(int dtype, int batch, int rows_per_seq, int hq,
   return (size_t)batch * rows_per_seq * hq * 64 * (hd + 2);
 }
 
+// Shares of a batch's line of work per kv head: as many as there are CUs for them; 0: a grid of equal splits.  The line costs 4 to
+// 8 us a launch (the cuts are looked up, a workgroup's second piece starts cold, more partials), so only where the longest
+// sequence's split takes 45 us or more.  Attention and merge of a layer, sequences of equal length and of an eighth to all of
+// it: 16 of 132 rows, 8192 keys 350 -> 346 us and 242 -> 172, on 2048 keys 107 -> 112 and 90 -> 81; 8 of 132 rows, 8192 keys 171 -> 172
+// and 129 -> 78.  Below the line: 6 of 200 rows, 2048 keys 72 -> 73 and 66 -> 63 (106 to 200 rows of one length 66 -> 74); eight layers,
+// 16 sequences of one row on 128 keys 816 -> 866.
+int attn_shares(int dtype, int hd, int batch, int rows_per_seq, int hq, int hkv, const AttnPlan& p) {
+  if (dtype != ESP_BF16 || hd != 128 || batch < 2 || p.tiles_per_split * ring_tile_time(p.ct_wg) < 4500) return 0;
+  // (batch + shares) x column tiles are what a share of the reserved partials holds
+  const int room = batch * (ring_tiles_bound(rows_per_seq * (hq / hkv)) / (p.q_tiles * p.ct_wg) - 1);
+  const int n = std::min(std::min(256 / (hkv * p.q_tiles), MAX_SHARES), room);
+  return n < 2 ? 0 : n;
+}
+size_t attn_cuts_ints(int batch) { return cuts_of_seq(MAX_SHARES) + 2 * (size_t)batch; }
+
+hipError_t launch_attn_cuts(hipStream_t st, const BlockDev& b, const KvDev& kv, int hq, int hkv, const AttnPlan& p, int shares, int32_t* cuts) {
+  hipLaunchKernelGGL(k_attn_cuts, dim3(1), dim3(256), 0, st, b, kv, hq / hkv, p.q_tiles, shares, cuts);
+  return hipGetLastError();
+}
+
 size_t attn_partial_floats(int dtype, int batch, int rows_per_seq, int hq, int hkv, int hd, const AttnPlan& p) {
-  if (dtype == ESP_BF16 && hd == 128) return (size_t)batch * hkv * p.q_tiles * p.ct_wg * p.nsplit * (32 * (hd + 2));
+  if (dtype == ESP_BF16 && hd == 128) {
+    const size_t whole = (size_t)p.q_tiles * p.ct_wg * hkv * (32 * (hd + 2)), shares = attn_shares(dtype, hd, batch, rows_per_seq, hq, hkv, p);
+    return whole * std::max((size_t)batch * p.nsplit, shares ? batch + shares : 0);
+  }
   return (size_t)batch * rows_per_seq * hq * p.nsplit * (hd + 2);
 }
 
 hipError_t launch_attn(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, int layer, int hq, int hkv,
-                       int hd, const void* q, float* partials, const AttnPlan& p) {
+                       int hd, const void* q, float* partials, const AttnPlan& p, const int32_t* cuts) {
   const int M = b.batch * b.rows_per_seq;
   const bool packed = b.packed != nullptr;
   float* part_o = partials;
   float* part_ml = partials + (size_t)M * hq * p.nsplit * hd;
   if (dtype == ESP_BF16 && hd == 128) {
-    const RingGeometry g = ring_geometry(p.ct_wg, p.tiles_per_split);
-    part_ml = partials + (size_t)b.batch * hkv * p.q_tiles * p.ct_wg * p.nsplit * (32 * hd);
-    const int total_wg = p.q_tiles * hkv * b.batch * p.nsplit;
+    const int shares = cuts ? attn_shares(dtype, hd, b.batch, b.rows_per_seq, hq, hkv, p) : 0, nsplit = shares ? shares : p.nsplit;
+    const RingGeometry g = ring_geometry(p.ct_wg, shares ? 64 : p.tiles_per_split);
+    part_ml = partials + (size_t)hkv * p.q_tiles * p.ct_wg * (shares ? b.batch + shares : b.batch * p.nsplit) * (32 * hd);
+    const int total_wg = p.q_tiles * hkv * (shares ? shares : b.batch * p.nsplit);
     const hipError_t attr = attn_prepare();
     if (attr != hipSuccess) return attr;
     const dim3 grid(((total_wg + 7) / 8) * 8), block(64 * g.waves);
     // Nontemporal where a key tile is read by one workgroup only.  Eight layers of the 8B shape, this alone: one row on 32768 keys
     // 994 -> 952 us, 68 rows 1357 -> 1341, 16 sequences of one row on 8192 keys 1717 -> 1626; up to 2048 keys within 1 %.  Where
     // several workgroups read a tile, 50 and 80 rows got 1 % slower with it and the others stayed the same.
-    const auto pick = [&](auto nt) {
-      constexpr bool NT = decltype(nt)::value;
-      return g.waves >= 8 ? (packed ? k_attn_ring<4, true, NT> : k_attn_ring<4, false, NT>)
-                          : (packed ? k_attn_ring<8, true, NT> : k_attn_ring<8, false, NT>);
+    const auto pick = [&](auto nt, auto line) {
+      constexpr bool NT = decltype(nt)::value, CUTS = decltype(line)::value;
+      return g.waves >= 8 ? (packed ? k_attn_ring<4, true, NT, CUTS> : k_attn_ring<4, false, NT, CUTS>)
+                          : (packed ? k_attn_ring<8, true, NT, CUTS> : k_attn_ring<8, false, NT, CUTS>);
     };
-    const auto kern = p.q_tiles == 1 ? pick(std::true_type{}) : pick(std::false_type{});
-    hipLaunchKernelGGL(kern, grid, block, RING_LDS_BYTES, st, b, kv, layer, hq, hkv, (const bf16_t*)q, part_o, part_ml, p.nsplit,
-                       p.tiles_per_split, p.q_tiles, p.ct_wg, g.n_full);
+    const std::true_type yes;
+    const std::false_type no;
+    const auto kern = shares ? (p.q_tiles == 1 ? pick(yes, yes) : pick(no, yes)) : (p.q_tiles == 1 ? pick(yes, no) : pick(no, no));
+    hipLaunchKernelGGL(kern, grid, block, RING_LDS_BYTES, st, b, kv, layer, hq, hkv, (const bf16_t*)q, part_o, part_ml, nsplit,
+                       p.tiles_per_split, p.q_tiles, p.ct_wg, g.n_full, cuts);
   } else {
     const dim3 grid(M, hq, p.nsplit);
     const bool vec = (((uintptr_t)kv.k | (uintptr_t)kv.v) & 15) == 0;
@@ -757,16 +908,18 @@ hipError_t launch_attn(hipStream_t st, int dtype, const BlockDev& b, const KvDev
 }
 
 hipError_t launch_attn_merge(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, int hq, int hkv, int hd,
-                             const float* partials, const AttnPlan& p, void* out) {
+                             const float* partials, const AttnPlan& p, void* out, const int32_t* cuts) {
   const bool packed = b.packed != nullptr;
   if (dtype == ESP_BF16 && hd == 128) {
     const int n_ct = p.q_tiles * p.ct_wg;
     const float* part_o = partials;
-    const float* part_ml = partials + (size_t)b.batch * hkv * n_ct * p.nsplit * (32 * hd);
+    const int shares = cuts ? attn_shares(dtype, hd, b.batch, b.rows_per_seq, hq, hkv, p) : 0;
+    const float* part_ml = partials + (size_t)hkv * n_ct * (shares ? b.batch + shares : b.batch * p.nsplit) * (32 * hd);
     const dim3 grid(b.batch * hkv * n_ct * 4);
     if (p.nsplit > 64) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((packed ? k_attn_merge_ring<64, true> : k_attn_merge_ring<64, false>), grid, dim3(256), 0, st, b, kv, hq, hkv,
-                       part_o, part_ml, p.nsplit, n_ct, (bf16_t*)out);
+    const auto kern = shares ? (packed ? k_attn_merge_ring<64, true, true> : k_attn_merge_ring<64, false, true>)
+                             : (packed ? k_attn_merge_ring<64, true, false> : k_attn_merge_ring<64, false, false>);
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, b, kv, hq, hkv, part_o, part_ml, shares ? shares : p.nsplit, n_ct, (bf16_t*)out, cuts);
     return hipGetLastError();
   }
   const int M = b.batch * b.rows_per_seq;

@@ -442,13 +442,12 @@ int large_tile_index(int mt, int ct) {
 // Tile and split-K parts of a large launch: the cheapest by LARGE_TILES, plus what the partials cost on their way out and in (1 us
 // for 4 MB).  A part has eight chunks of K at least, and all parts together one round of the CUs.  Of a batch, over numbers of rows
 // from two thirds of M up.
-GemmPlan large_plan(int M, int N, int K, int most_splits, bool batch, unsigned tiles = ~0u) {
+GemmPlan large_plan(int M, int N, int K, int most_splits, bool batch) {
   const int rows = (M + 31) / 32 * 32, blocks = N / 32, chunks = K / KC, at[3] = {rows, rows * 5 / 6, rows * 2 / 3};
   const int max_s = std::max(1, std::min(std::min(most_splits, chunks / 8), 8));
   GemmPlan best{};
   int64_t least = -1;
   for (int t = 0; t < N_LARGE_TILES; ++t) {
-    if (!(tiles >> t & 1u)) continue;
     const LargeTileCost& c = LARGE_TILES[t];
     const int m_tiles = (M + 32 * c.rt - 1) / (32 * c.rt), n_tiles = (blocks + c.ct - 1) / c.ct;
     for (int s = 1; s <= max_s; ++s) {
@@ -599,27 +598,61 @@ GateUpRule gate_up_rule(int M, int ff, int K, const void* act, bool ragged) {
   GateUpRule r;
   r.mt = even_row_tiles(M); r.chunks = K / KC; r.blocks = (2 * ff) >> 5;
   if (M <= 128) return r;
-  // tiles with a side of 256, and 192 x 320
-  constexpr unsigned SIDE256 = 1u << 7 | 1u << 9 | 1u << 10, W192x320 = 1u << 8;
-  static_assert(LARGE_TILES[7].ct == 8 && LARGE_TILES[9].rt == 8 && LARGE_TILES[10].rt == 8 && LARGE_TILES[8].ct == 10, "");
-  const unsigned of[GU_TILES] = {~0u, SIDE256, W192x320};
-  for (int t = 0; t < GU_TILES; ++t) {
-    const GemmPlan p = large_plan(M, 2 * ff, K, 1, ragged, of[t]);
-    r.tile[t] = large_tile_index(p.mt, p.ct);
-    r.cost[t] = LARGE_TILES[r.tile[t]];
+  if ((uintptr_t)act % 16 == 0 && ff % 8 == 0) {         // (the wide classes' results are stored 16 bytes at a time)
+    r.launched = 1u << r.by_rounds(M);
+    if (ragged)                                          // (every tile ends at a multiple of 32 rows)
+      for (int rows = (2 * M / 3) & ~31; rows < M; rows += 32) r.launched |= 1u << r.by_rounds(std::max(rows, 1));
   }
-  if ((uintptr_t)act % 16 || ff % 8) return r;           // (the classes' results are stored 16 bytes at a time)
-  r.launched = 1u << r.by_rounds(M);
-  if (ragged)                                            // (every tile ends at a multiple of 32 rows)
-    for (int rows = (2 * M / 3) & ~31; rows < M; rows += 32) r.launched |= 1u << r.by_rounds(std::max(rows, 1));
+  // tiles of the classes: any; a side of 256; 192 x 320
+  static_assert(LARGE_TILES[7].ct == 8 && LARGE_TILES[9].rt == 8 && LARGE_TILES[10].rt == 8 && LARGE_TILES[8].ct == 10, "");
+  const unsigned of[GU_TILES] = {(1u << N_LARGE_TILES) - 1u, 1u << 7 | 1u << 9 | 1u << 10, 1u << 8};
+  // for M rows, or of a batch for any number from 0.6 M up, each of which takes the cheapest of the tiles launched; all M rows
+  // may take 3 % longer than with the best for them
+  constexpr int MOST = 5;
+  const int n = ragged ? MOST : 1;
+  int64_t cost[N_LARGE_TILES][MOST];
+  for (int t = 0; t < N_LARGE_TILES; ++t)
+    for (int i = 0; i < n; ++i) cost[t][i] = large_cost(LARGE_TILES[t], std::max(M * (10 - i) / 10, 1), r.blocks, r.chunks, 1);
+  int64_t least = -1, best_full = -1;
+  for (int c = 0; c < GU_TILES; ++c)
+    for (int t = 0; t < N_LARGE_TILES; ++t)
+      if ((r.launched >> c & 1u) && (of[c] >> t & 1u) && (best_full < 0 || cost[t][0] < best_full)) best_full = cost[t][0];
+  int pick[GU_TILES];
+  auto choose = [&](auto&& self, int c) -> void {
+    if (c < GU_TILES) {
+      for (int t = 0; t < N_LARGE_TILES; ++t)
+        if (r.launched >> c & 1u ? of[c] >> t & 1u : t == 8) {       // (a class that is not launched: whichever)
+          pick[c] = t;
+          self(self, c + 1);
+        }
+      return;
+    }
+    int64_t sum = 0;
+    for (int i = 0; i < n; ++i) {
+      int64_t lowest = -1;
+      for (int k = 0; k < GU_TILES; ++k)
+        if (r.launched >> k & 1u)
+          if (lowest < 0 || cost[pick[k]][i] < lowest) lowest = cost[pick[k]][i];
+      if (i == 0 && lowest * 100 > best_full * 103) return;
+      sum += lowest;
+    }
+    if (least < 0 || sum < least) {
+      least = sum;
+      for (int k = 0; k < GU_TILES; ++k) { r.tile[k] = pick[k]; r.cost[k] = LARGE_TILES[pick[k]]; }
+    }
+  };
+  choose(choose, 0);
   return r;
 }
 unsigned gate_up_tiles(int M, int ff, int K, const void* act, bool ragged) { return gate_up_rule(M, ff, K, act, ragged).launched; }
 
 // Fused gate/up projection + SwiGLU (bf16, packed weights whose rows alternate in blocks of 32
 // between gate and up): act[M][ff] = silu(A Wg^T) * (A Wu^T), one pass over K per workgroup.
-hipError_t launch_gemm_swiglu(hipStream_t st, const void* A, const void* W, void* act, int M, int ff, int K,
-                              const int32_t* live) {
+hipError_t launch_gemm_swiglu(hipStream_t st, const void* A, const void* W, void* act, int M, int ff, int K, const int32_t* live) {
+  return launch_gate_up(st, A, W, act, M, ff, K, live, gate_up_rule(M, ff, K, act, live != nullptr));
+}
+hipError_t launch_gate_up(hipStream_t st, const void* A, const void* W, void* act, int M, int ff, int K, const int32_t* live,
+                          const GateUpRule& r) {
   if (M <= 0) return hipSuccess;
   if (M <= 128) {
     float* out = reinterpret_cast<float*>(act);
@@ -630,7 +663,6 @@ hipError_t launch_gemm_swiglu(hipStream_t st, const void* A, const void* W, void
       default: return launch_bf16<4, 1, true, 2>(st, A, nullptr, W, out, M, 2 * ff, K, 1);
     }
   }
-  const GateUpRule r = gate_up_rule(M, ff, K, act, live != nullptr);
   const unsigned tiles = r.launched;
   LargeGemm g{A, nullptr, W, act, M, 2 * ff, K, 1, 0, nullptr, 0u, live};
   if ((tiles & (tiles - 1)) == 0) {

@@ -191,6 +191,9 @@ unsigned gate_up_tiles(int M, int ff, int K, const void* act, bool ragged);   //
 // live (device, may be null): BlockDev::n_live of a batch with packed rows
 hipError_t launch_gemm_swiglu(hipStream_t st, const void* A, const void* W, void* act, int M, int ff, int K,
                               const int32_t* live = nullptr);
+// the same with gate_up_rule(M, ff, K, act, live != nullptr) at hand (a layer after the other)
+hipError_t launch_gate_up(hipStream_t st, const void* A, const void* W, void* act, int M, int ff, int K, const int32_t* live,
+                          const GateUpRule& r);
 // LM head with the arg-max taken in the GEMM epilogue (bf16, packed weights, one split)
 bool gemm_argmax_supported(int dtype, int M, int N, int K, bool with_logits);
 size_t gemm_argmax_scratch_floats(int M, int N);
@@ -282,10 +285,16 @@ hipError_t attn_prepare();   // one-time kernel attributes (dynamic LDS limit)
 size_t attn_partial_floats(int dtype, int batch, int rows_per_seq, int hq, int hkv, int hd, const AttnPlan& p);
 // what any plan for up to that many sequences and rows needs
 size_t attn_partial_floats_bound(int dtype, int batch, int rows_per_seq, int hq, int hkv, int hd);
+// A batch's sequences as one line of work per kv head, cut into equal shares (esp_attn.hip): how many (0: not this batch), and the
+// table of the cuts, which launch_attn_cuts fills from the lengths and rows that only the device knows, for all layers at once
+int attn_shares(int dtype, int hd, int batch, int rows_per_seq, int hq, int hkv, const AttnPlan& p);
+size_t attn_cuts_ints(int batch);
+hipError_t launch_attn_cuts(hipStream_t st, const BlockDev& b, const KvDev& kv, int hq, int hkv, const AttnPlan& p, int shares, int32_t* cuts);
+// cuts: null for a grid of equal splits
 hipError_t launch_attn(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, int layer, int hq,
-                       int hkv, int hd, const void* q, float* partials, const AttnPlan& p);
+                       int hkv, int hd, const void* q, float* partials, const AttnPlan& p, const int32_t* cuts);
 hipError_t launch_attn_merge(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, int hq, int hkv, int hd,
-                             const float* partials, const AttnPlan& p, void* out);
+                             const float* partials, const AttnPlan& p, void* out, const int32_t* cuts);
 
 // ---- softmax + top-k (esp_topk.hip) -----------------------------------------------------------
 size_t softmax_topk_scratch_floats(int rows, int vocab, int kp);
@@ -352,6 +361,7 @@ struct esp_ctx {
   int32_t* idx_a;    // [Mmax] gather rows
   int32_t* idx_b;    // [Mmax]
   int32_t* packed;   // packed rows of a ragged batch (BlockDev)
+  int32_t* cuts;     // shares of a batch's attention
   int32_t* status;   // device status word
   size_t gemm_out_floats, attn_part_floats, logits_rows;
   // optional launch-site timing with HIP events (esp_profile_enable / esp_profile_read)

@@ -994,6 +994,67 @@ def test_packed_rows_with_two_gate_up_tiles(B, counts):
         assert np.all(both[b, live:] == 0)
 
 
+class AttnPlan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("nsplit", "tiles_per_split", "q_tiles", "ct_wg")]
+
+
+@pytest.mark.parametrize("rows,lens,invalid", [
+    ([36] * 16, [8192] * 16, []),                                          # equal: cuts at the same places in every sequence
+    ([36, 1, 20, 9, 36, 30, 2, 36] * 2, [8192, 63, 1, 4000, 64, 0, 129, 8000] + [0, 0, 2000, 300, 8191, 65, 0, 12], []),
+    ([132, 7, 100, 60, 33, 132, 80, 12], [5000, 8100, 0, 64, 700, 8192, 3, 2500], [1, 6]),   # two column groups; sequences that are not valid
+    ([40] * 16, [8192] + [0] * 15, []),                                    # nearly all shares in one sequence
+    ([40] * 16, [8192] * 16, list(range(16)))])                            # nobody there
+def test_attention_shares_of_a_batch(B, rows, lens, invalid):
+    """A batch's sequences as one line of work cut into equal shares: every sequence gets what it gets alone (there in equal
+    splits), to the bf16 rounding of the result and of the probabilities, which depends on where the keys are split; rows that are not there
+    are zero."""
+    c = ctypes
+    batch, most = len(rows), max(rows)
+    shape = small_shape(d_model=256, n_q_heads=32, n_kv_heads=8, head_dim=128, d_ff=64, vocab=64, n_layers=1, dtype="bf16")
+    plan = internal("attn_plan", *[c.c_int] * 7, restype=AttnPlan)(B.ESP_BF16, 128, batch, most, 32, 8, max(lens))
+    shares = internal("attn_shares", *[c.c_int] * 6, c.POINTER(AttnPlan))(B.ESP_BF16, 128, batch, most, 32, 8, plan)
+    print(f"attention shares rows={rows} lens={lens} plan={[getattr(plan, n) for n, _ in plan._fields_]} shares={shares}", flush=True)
+    assert shares > 1
+    w = synth.make_weights(shape, seed=3)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    kvs = [[torch.randn(n + r, 8, 128, device="cuda", generator=g).bfloat16() for _ in (0, 1)] for n, r in zip(lens, rows)]
+    qs = [torch.randn(r, 32, 128, device="cuda", generator=g).bfloat16() for r in rows]
+
+    def run(which, pad):
+        eng = B.Engine(shape, w, len(which), pad, max(lens) + pad)
+        blk = B.BlockBuffers(len(which), pad, 0, 0)
+        trees = [synth.make_random_tree(rows[b], 6, shape.vocab, seed=b) for b in which]
+        blk.upload_trees([t.tolist() for t, _ in trees], [p.tolist() for _, p in trees])
+        eng.block_from_tree(blk)
+        kv = B.KvCache(shape, [lens[b] + pad for b in which])
+        for i, b in enumerate(which):
+            eng.kv_store(kv, 0, i, 0, *kvs[b])
+        kv.set_len([lens[b] for b in which])
+        for i, b in enumerate(which):
+            if b in invalid:
+                kv.len[i] = kv.len_bound + 1
+        q = torch.zeros(len(which) * pad, 32, 128, dtype=torch.bfloat16, device="cuda")
+        for i, b in enumerate(which):
+            q[i * pad:i * pad + rows[b]] = qs[b]
+        out = torch.full_like(q, 7.0)
+        eng.attn_tree(blk, kv, 0, q, out)
+        first = out.clone()
+        eng.attn_tree(blk, kv, 0, q, out)
+        assert torch.equal(first, out)                       # a second pass over the same buffers
+        eng.close()
+        return out.view(len(which), pad, 32, 128).float()
+
+    got = run(list(range(batch)), most)
+    for b in range(batch):
+        live = 0 if b in invalid else rows[b]
+        assert bool((got[b, live:] == 0).all()), b
+        if live:
+            want = run([b], rows[b])[0]
+            err = (got[b, :live] - want).norm() / want.norm()
+            assert float(err) < 5e-3, (b, float(err))        # two roundings to bf16 (2^-9 of a value at most) and those of the probabilities
+
+
 # ---------------------------------------------------------------------------------------- attention
 def run_attention_case(B, shape, eng, n_nodes, k, layout, cache_lens, seed):
     batch = len(cache_lens)
