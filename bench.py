@@ -479,7 +479,7 @@ def stage_rooflines(B, synth, torch, shape, lm_head_packed):
     am_scratch = torch.empty(B.load_library().esp_gemm_argmax_scratch_bytes(M, N), dtype=torch.uint8, device="cuda")
     ms = time_gpu(torch, lambda: B.gemm_argmax(A, lm_head_packed, am, am_scratch), 5, warm=2)
     fl = 2.0 * M * N * K
-    out["lm_head_rows1344"] = {"kernel": "k_gemm_large (arg-max epilogue) + k_argmax_tiles (LM head, 1344 rows)",
+    out["lm_head_rows1344"] = {"kernel": "k_gemm_tile (arg-max epilogue) + k_argmax_tiles (LM head, 1344 rows)",
                                "bound": "mfma", "achieved": fl / ms / 1e9,
                                "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                                "frac": fl / ms / 1e9 / MFMA_BF16_PEAK_TFLOPS,

@@ -10,8 +10,8 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libesp_hip.so")
-SOURCES = ["esp_api.hip", "esp_elementwise.hip", "esp_gemm.hip", "esp_gemm_large_out.hip", "esp_gemm_large_argmax.hip",
-           "esp_gemm_large_swiglu.hip", "esp_attn.hip", "esp_topk.hip", "esp_tree.hip"]
+SOURCES = ["esp_api.hip", "esp_elementwise.hip", "esp_gemm.hip", "esp_gemm_tile_out.hip", "esp_gemm_tile_argmax.hip",
+           "esp_gemm_tile_swiglu.hip", "esp_gemm_tile_both.hip", "esp_attn.hip", "esp_topk.hip", "esp_tree.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + os.path.join(ROOT, "include"),
          "-I" + CSRC, "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]

@@ -418,7 +418,7 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
       // 2*vocab*d_model bytes of the matrix.
       ESP_PROF(ESP_SITE_LM_HEAD);
       ESP_HIP(launch_gemm_argmax(s, hidden_out, nullptr, c->lm_head, M, m.vocab, d, c->gemm_out, node_argmax,
-                                 c->idx_b, 0, c->logits, c->idx_a, Mn, c->sample_on ? c->idx_c : nullptr,
+                                 c->idx_b, c->logits, c->idx_a, Mn, c->sample_on ? c->idx_c : nullptr,
                                  c->sample_seed));
       c->lm_cache_hidden = hidden_out;
       c->lm_cache_rows = M;
@@ -427,7 +427,7 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
       // arg-max in the GEMM epilogue: the [rows, vocab] logits are never written
       ESP_PROF(ESP_SITE_LM_HEAD);
       ESP_HIP(launch_gemm_argmax(s, hidden_out, c->idx_a, c->lm_head, Mn, m.vocab, d, c->logits, node_argmax,
-                                 c->idx_b, 0, nullptr, nullptr, Mn, draw_list, c->sample_seed, packed ? m_live + 1 : nullptr));
+                                 c->idx_b, nullptr, nullptr, Mn, draw_list, c->sample_seed, packed ? m_live + 1 : nullptr));
     } else {
       { ESP_PROF(ESP_SITE_LM_HEAD);
         ESP_HIP(launch_gemm(s, dt, hidden_out, c->idx_a, c->lm_head, c->logits, Mn, m.vocab, d, p_lm, pk)); }
@@ -643,8 +643,8 @@ esp_status esp_kv_load(esp_ctx* c, const esp_kv* kv, int32_t layer, int32_t seq_
 
 size_t esp_gemm_scratch_bytes(int32_t M, int32_t N, int32_t K) {
   if (M < 1 || N < 1 || K < 1) return 0;
-  GemmPlan p = gemm_plan(ESP_BF16, M, N, K);
-  return gemm_out_elems(p, M, N) * 4 + 256;
+  const GemmPlan p = gemm_plan(ESP_BF16, M, N, K);
+  return (size_t)std::max(p.splits, round_parts(M, N, K)) * M * N * 4 + 256;
 }
 
 esp_status esp_pack_weight(void* stream, const void* src, void* dst, int32_t N, int32_t K) {
@@ -689,7 +689,7 @@ esp_status esp_gemm_argmax(void* stream, const void* A, const void* W, int32_t M
   if (N % 32 || K % 64) return ESP_ESHAPE;
   if (!gemm_argmax_supported(ESP_BF16, M, N, K, false)) return ESP_ESHAPE;
   if (!scratch || scratch_bytes < gemm_argmax_scratch_floats(M, N) * 4) return ESP_ECAPACITY;
-  ESP_HIP(launch_gemm_argmax((hipStream_t)stream, A, nullptr, W, M, N, K, (float*)scratch, argmax, nullptr, 0, nullptr,
+  ESP_HIP(launch_gemm_argmax((hipStream_t)stream, A, nullptr, W, M, N, K, (float*)scratch, argmax, nullptr, nullptr,
                              nullptr, M, nullptr, 0u));
   return ESP_OK;
 }

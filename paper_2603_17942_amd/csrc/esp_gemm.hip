@@ -1,21 +1,14 @@
 // Dense projections of the decoder: out[s][M][N] (fp32 partial sums over split s) = A[M,K] * W[N,K]^T.
 //
 // bf16 path (the 8B-class workloads): M is the number of block rows (tens to hundreds) while W is
-// hundreds of MB per layer, so the kernel is a weight streamer.
-//  * Weights live in HBM in a streaming layout (k_pack_weight): the 32-row x 64-k tile of a wave and
-//    K-chunk is stored as [step][lane][8 values] = 4 KB contiguous in MFMA B-operand order, so every
-//    wave-wide load covers 1 KB of consecutive addresses and the data goes HBM -> VGPR -> MFMA with no
-//    LDS hop.  Tiles are ordered chunk-major ([chunk][row block]): at any moment the waves of the
-//    whole grid, which advance through the chunks together, read one contiguous window of HBM.
+// hundreds of MB per layer.
+//  * Weights live in HBM in a streaming layout (k_pack_weight): the 32-row x 64-k tile of a row block and
+//    K-chunk is stored as [step][lane][8 values] = 4 KB contiguous in MFMA operand order, so every
+//    wave-wide load covers 1 KB of consecutive addresses.  Tiles are ordered chunk-major ([chunk][row block]): at any
+//    moment the waves of the whole grid, which advance through the chunks together, read one contiguous window of HBM.
 //    Inside a chunk the k index is permuted identically for both operands (lane group g, step s
 //    holds k = 32 g + 8 s + 0..7), which leaves the dot product unchanged.
-//  * More than 128 rows: k_gemm_large (esp_gemm_large.h).  Up to there, operands in register rings:
-//  * A register ring keeps D chunks of weights in flight per wave.  The activations of a chunk (L2
-//    resident, shared by the four waves through LDS) ride in a ring of the same depth and are issued
-//    together with the weights of the same chunk: loads retire in order, so waiting for the
-//    activations of chunk c+1 leaves the D-2 younger chunks of the weight stream in flight.
-//  * v_mfma_f32_32x32x16_bf16, fp32 accumulation; LDS fragment reads are double-buffered one MFMA
-//    step ahead.
+//  * Packed weights: k_gemm_tile (esp_gemm_tile.h).  Row-major weights (esp_gemm alone): k_gemm_bf16 below.
 //  * Split-K (grid z): partial sums are reduced by the consumer in split order, so a result does
 //    not depend on scheduling.  The split count is a function of (N, K) up to 128 rows; above, it
 //    also depends on the number of row tiles (gemm_plan), so a row's low-order bits can differ
@@ -31,15 +24,15 @@ namespace {
 
 constexpr int A_ROW_BYTES = 144;  // 128 B of bf16 + 16 B pad: conflict-free ds_read_b128 over 8 rows
 
-// EPI: epilogue -- 0 fp32 tile out, 1 per-row arg-max over the workgroup's columns (pairs to out),
-// 2 SwiGLU of interleaved gate/up column blocks to bf16, 3 fp32 tile to out and arg-max pairs to out2
-// Register rings of depth D (even); TILED: packed weights (one column block per wave), otherwise row-major ones.
-template <int MT, int NB, int D, bool TILED, int EPI>
+// Row-major weights.  A register ring keeps D (even) chunks of weights in flight per wave; the activations of a chunk (L2
+// resident, shared by the four waves through LDS) ride in a ring of the same depth and are issued together with the weights of
+// the same chunk: loads retire in order, so waiting for the activations of chunk c+1 leaves the D-2 younger chunks of the
+// weight stream in flight.  v_mfma_f32_32x32x16_bf16; LDS fragment reads are double-buffered one MFMA step ahead.
+template <int MT, int NB, int D>
 __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t* __restrict__ A,
                                                const int32_t* __restrict__ a_rows, const bf16_t* __restrict__ W,
                                                float* __restrict__ out, int M, int N, int K, int splits,
-                                               int m_tiles, int n_tiles, int a_ld, float* __restrict__ out2,
-                                               const int32_t* __restrict__ draw_pos, uint32_t seed) {
+                                               int m_tiles, int n_tiles, int a_ld) {
   // XCD-aware logical id: consecutive hardware ids go to different XCDs, so give each XCD a
   // contiguous range of tiles (tiles sharing weight rows then share an L2).
   const int total = m_tiles * n_tiles * splits;
@@ -71,22 +64,8 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
   // weight pointers (clamped: out-of-range column blocks are computed but never stored)
   const u32x4_t* wp[NB];
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    if (TILED) {
-      int blk = min((n0 + nb * 32) >> 5, (N >> 5) - 1);
-      wp[nb] = reinterpret_cast<const u32x4_t*>(W) + (size_t)blk * 256 + lane;
-    } else {
-      int n = min(n0 + nb * 32 + lr, N - 1);
-      wp[nb] = reinterpret_cast<const u32x4_t*>(W + (size_t)n * K + 32 * lg);
-    }
-  }
-  const size_t W_CHUNK = TILED ? (size_t)(N >> 5) * 256 : KC * 2 / 16;   // u32x4_t between chunks of a lane's stream
-  constexpr int W_STEP = TILED ? 64 : 1;               // u32x4_t between the steps of a chunk
-  // The weights of a small-row launch pass once (up to 128 rows are one row tile): nontemporal
-  // loads keep them from pushing the activations, the partial sums and one another out of the caches.  Eight layers of the
-  // 8B shape on 2048 keys, this alone: one row 843 -> 779 us, 30 rows 886 -> 834, 68 rows 1055 -> 1014, 128 rows 1260 -> 1230 (two
-  // runs of one side differ by 0.3 %).  Row-major weights are read in pieces of a line: not those.
-  auto load_w = [](const u32x4_t* p) { return TILED ? __builtin_nontemporal_load(p) : *p; };
+  for (int nb = 0; nb < NB; ++nb) wp[nb] = reinterpret_cast<const u32x4_t*>(W + (size_t)min(n0 + nb * 32 + lr, N - 1) * K + 32 * lg);
+  constexpr size_t W_CHUNK = KC * 2 / 16;               // u32x4_t between chunks of a lane's stream
 
   // activation staging: thread handles MT pieces of 16 B; piece p -> row p/8, 16-byte column p%8
   const bf16_t* ap[MT];
@@ -129,7 +108,7 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) wreg[u][nb][s] = load_w(wp[nb] + (size_t)cc * W_CHUNK + s * W_STEP);
+      for (int s = 0; s < 4; ++s) wreg[u][nb][s] = wp[nb][(size_t)cc * W_CHUNK + s];
   }
 #pragma unroll
   for (int i = 0; i < MT; ++i)
@@ -162,7 +141,7 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
             // weight registers of step s-1 were consumed by the previous step
             const int cc = min(c + D, c_last);
             if (s == 0) areg[u][i] = *reinterpret_cast<const u32x4_t*>(ap[i] + (size_t)cc * a_cs);
-            else if (i < NB) wreg[u][i][s - 1] = load_w(wp[i] + (size_t)cc * W_CHUNK + (s - 1) * W_STEP);
+            else if (i < NB) wreg[u][i][s - 1] = wp[i][(size_t)cc * W_CHUNK + s - 1];
           }
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -183,7 +162,7 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
       if constexpr (REFILL) {
         const int cc = min(c + D, c_last);
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) wreg[u][nb][3] = load_w(wp[nb] + (size_t)cc * W_CHUNK + 3 * W_STEP);
+        for (int nb = 0; nb < NB; ++nb) wreg[u][nb][3] = wp[nb][(size_t)cc * W_CHUNK + 3];
       }
       __syncthreads();
     }
@@ -193,131 +172,39 @@ __device__ __forceinline__ void gemm_bf16_body(unsigned char* lds, const bf16_t*
   __syncthreads();                                      // the epilogues reuse the LDS
 
   // epilogue: lane holds column n, rows 8*(v/4) + 4*lg + v%4 of each 32x32 tile
-  if (EPI == 0 || EPI == 3) {
-    // Split-K partials of 65 to 128 rows go past the caches on their way out: eight layers of the 8B shape on 2048 keys, this
-    // alone, 65 rows 1025 -> 1008 us, 101 rows 1178 -> 1158, 128 rows 1253 -> 1230.  At one row, where they are 0.1 MB, it is 3 %
-    // slower; with large tiles it is neither.
-    constexpr bool NT_OUT = EPI == 0 && NB == 1 && MT >= 3;
-    float* o = out + (size_t)z * M * N;
+  float* o = out + (size_t)z * M * N;
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const int n = n0 + nb * 32 + lr;
-      if (n0 + nb * 32 < N) {
+  for (int nb = 0; nb < NB; ++nb) {
+    const int n = n0 + nb * 32 + lr;
+    if (n0 + nb * 32 < N) {
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            int m = m0 + i * 32 + 8 * (v >> 2) + 4 * lg + (v & 3);
-            if (m < M) {
-              if (NT_OUT) __builtin_nontemporal_store(acc[i][nb][v], o + (size_t)m * N + n);
-              else o[(size_t)m * N + n] = acc[i][nb][v];
-            }
-          }
-        }
-      }
-    }
-  }
-  if (EPI == 1 || EPI == 3) {
-    // Arg-max epilogue (LM head at the tree rows; needs splits == 1): per row the maximum over this workgroup's columns, lowest
-    // column on ties, by butterfly shuffles; [n_tiles][M] pairs (value, column as int bits).
-    float* red = reinterpret_cast<float*>(lds);            // [4 waves][MT*32 rows][2]
-#pragma unroll
-    for (int i = 0; i < MT; ++i) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        float best = -INFINITY;
-        int bi = 0x7fffffff;
-        // sample matching: the row draws its next token, arg-max of logit + Gumbel noise
-        const uint32_t pos =
-            draw_pos ? (uint32_t)draw_pos[min(m0 + i * 32 + 8 * (v >> 2) + 4 * lg + (v & 3), M - 1)] : 0u;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          const int n = n0 + nb * 32 + lr;
-          float x = acc[i][nb][v];
-          if (draw_pos) x += gumbel_noise(seed, pos, (uint32_t)n);
-          if (n0 + nb * 32 < N && (x > best || (x == best && n < bi))) { best = x; bi = n; }
-        }
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) {                  // over the 32 columns of a lane half
-          float ov = __shfl_xor(best, o, 64);
-          int oi = __shfl_xor(bi, o, 64);
-          if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-        }
-        if (lr == 0) {
-          const int rl = i * 32 + 8 * (v >> 2) + 4 * lg + (v & 3);
-          red[(wave * MT * 32 + rl) * 2 + 0] = best;
-          red[(wave * MT * 32 + rl) * 2 + 1] = __int_as_float(bi);
-        }
-      }
-    }
-    __syncthreads();
-    for (int rl = tid; rl < MT * 32; rl += 256) {
-      float best = red[rl * 2];
-      int bi = __float_as_int(red[rl * 2 + 1]);
-#pragma unroll
-      for (int w = 1; w < 4; ++w) {
-        float ov = red[(w * MT * 32 + rl) * 2];
-        int oi = __float_as_int(red[(w * MT * 32 + rl) * 2 + 1]);
-        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-      }
-      const int m = m0 + rl;
-      float* pairs = EPI == 3 ? out2 : out;
-      if (m < M) {
-        pairs[((size_t)ni * M + m) * 2 + 0] = best;
-        pairs[((size_t)ni * M + m) * 2 + 1] = __int_as_float(bi);
-      }
-    }
-  }
-  if (EPI == 2) {
-    // SwiGLU epilogue (fused gate/up projection; needs splits == 1): the weight rows alternate
-    // in blocks of 32 between gate and up, so output column block 2j is gate block j and 2j+1 is
-    // up block j.  `out` is the bf16 activation matrix [M][N/2]: act = silu(gate) * up.
-    bf16_t* act = reinterpret_cast<bf16_t*>(out);
-    const int ff = N >> 1;
-    static_assert(NB == 1 || EPI != 2, "packed weights have one block per wave");
-    // the odd wave of a pair holds the up block: hand it over through LDS
-    float* ex = reinterpret_cast<float*>(lds);              // [2 pairs][MT*32 rows][32]
-    if (wave & 1) {
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          ex[((wave >> 1) * MT * 32 + i * 32 + 8 * (v >> 2) + 4 * lg + (v & 3)) * 32 + lr] = acc[i][0][v];
-    }
-    __syncthreads();
-    if (!(wave & 1) && n0 < N) {
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
+      for (int i = 0; i < MT; ++i) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const int rl = i * 32 + 8 * (v >> 2) + 4 * lg + (v & 3);
-          const int m = m0 + rl;
-          const float g = acc[i][0][v], u = ex[((wave >> 1) * MT * 32 + rl) * 32 + lr];
-          if (m < M) act[(size_t)m * ff + (n0 >> 1) + lr] = (bf16_t)silu_mul(g, u);
+          int m = m0 + i * 32 + 8 * (v >> 2) + 4 * lg + (v & 3);
+          if (m < M) o[(size_t)m * N + n] = acc[i][nb][v];
         }
+      }
     }
   }
 }
 
-// Two entry points over the same body.  The small-tile one (<= 4 row tiles, one column block per
-// wave) leaves occupancy to the compiler.  The large-tile one tells it that one wave per SIMD is
-// all it will ever get, so registers go to prefetching.
-template <int MT, int NB, int D, bool TILED, int EPI>
+// Two entry points over the same body.  The small-tile one leaves occupancy to the compiler.  The large-tile one tells it that
+// one wave per SIMD is all it will ever get, so registers go to prefetching.
+template <int MT, int NB>
 __global__ __launch_bounds__(256) void k_gemm_bf16(const bf16_t* __restrict__ A, const int32_t* __restrict__ a_rows,
                                                    const bf16_t* __restrict__ W, float* __restrict__ out, int M,
-                                                   int N, int K, int splits, int m_tiles, int n_tiles, int a_ld,
-                                                   float* __restrict__ out2, const int32_t* __restrict__ draw_pos,
-                                                   uint32_t seed) {
+                                                   int N, int K, int splits, int m_tiles, int n_tiles, int a_ld) {
   extern __shared__ __align__(16) unsigned char lds[];   // 2 buffers of MT*32 rows * A_ROW_BYTES
-  gemm_bf16_body<MT, NB, D, TILED, EPI>(lds, A, a_rows, W, out, M, N, K, splits, m_tiles, n_tiles, a_ld, out2, draw_pos, seed);
+  gemm_bf16_body<MT, NB, 4>(lds, A, a_rows, W, out, M, N, K, splits, m_tiles, n_tiles, a_ld);
 }
 
-template <int MT, int NB, int D>   // row-major weights
+template <int MT, int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gemm_bf16_big(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ a_rows, const bf16_t* __restrict__ W,
     float* __restrict__ out, int M, int N, int K, int splits, int m_tiles, int n_tiles, int a_ld) {
   extern __shared__ __align__(16) unsigned char lds[];
-  gemm_bf16_body<MT, NB, D, false, 0>(lds, A, a_rows, W, out, M, N, K, splits, m_tiles, n_tiles, a_ld, nullptr, nullptr, 0u);
+  gemm_bf16_body<MT, NB, 2>(lds, A, a_rows, W, out, M, N, K, splits, m_tiles, n_tiles, a_ld);
 }
 
 // ---- fp32: one 32 x 32 tile per workgroup, its eight waves split K (v_mfma_f32_32x32x2_f32) --------
@@ -410,20 +297,13 @@ __global__ void k_pack_weight(const bf16_t* __restrict__ src, bf16_t* __restrict
   reinterpret_cast<uint4*>(dst)[piece] = *reinterpret_cast<const uint4*>(src + (size_t)n * K + k);
 }
 
-template <int MT, int NB, bool TILED, int EPI = 0>
+template <int MT, int NB>
 hipError_t launch_bf16(hipStream_t st, const void* A, const int32_t* a_rows, const void* W, float* out, int M, int N, int K, int splits,
-                       int a_ld = 0, float* out2 = nullptr, const int32_t* draw_pos = nullptr, uint32_t seed = 0) {
+                       int a_ld) {
   const int m_tiles = (M + 32 * MT - 1) / (32 * MT), n_tiles = (N + 128 * NB - 1) / (128 * NB);
-  const dim3 grid((m_tiles * n_tiles * splits + 7) / 8 * 8);
-  const size_t lds = 2 * (size_t)MT * 32 * A_ROW_BYTES;
-  if constexpr (MT * NB >= 8) {
-    static_assert(!TILED, "packed weights: k_gemm_large");
-    launch_kernel(k_gemm_bf16_big<MT, NB, 2>, grid, dim3(256), lds, st, (const bf16_t*)A, a_rows, (const bf16_t*)W, out, M, N, K, splits,
-                  m_tiles, n_tiles, a_ld);
-  } else {
-    launch_kernel(k_gemm_bf16<MT, NB, 4, TILED, EPI>, grid, dim3(256), lds, st, (const bf16_t*)A, a_rows, (const bf16_t*)W, out, M, N, K,
-                  splits, m_tiles, n_tiles, a_ld, out2, draw_pos, seed);
-  }
+  const auto kern = MT * NB >= 8 ? k_gemm_bf16_big<MT, NB> : k_gemm_bf16<MT, NB>;
+  launch_kernel(kern, dim3((m_tiles * n_tiles * splits + 7) / 8 * 8), dim3(256), 2 * (size_t)MT * 32 * A_ROW_BYTES, st, (const bf16_t*)A,
+                a_rows, (const bf16_t*)W, out, M, N, K, splits, m_tiles, n_tiles, a_ld);
   return hipGetLastError();
 }
 
@@ -433,32 +313,63 @@ int even_row_tiles(int M) {
   return (t + n - 1) / n;
 }
 
-int large_tile_index(int mt, int ct) {
-  for (int t = 0; t < N_LARGE_TILES; ++t)
-    if (LARGE_TILES[t].rt == mt && LARGE_TILES[t].ct == ct) return t;
+// of GEMM_TILES: the tile of a plan
+int tile_index(const GemmPlan& p) {
+  for (int t = p.nb == 1 ? 0 : N_ROW_TILES; t < N_GEMM_TILES; ++t)
+    if (GEMM_TILES[t].rt == p.mt && GEMM_TILES[t].ct == p.ct) return t;
   return -1;
 }
 
-// Tile and split-K parts of a large launch: the cheapest by LARGE_TILES, plus what the partials cost on their way out and in (1 us
-// for 4 MB).  A part has eight chunks of K at least, and all parts together one round of the CUs.  Of a batch, over numbers of rows
-// from two thirds of M up.
-GemmPlan large_plan(int M, int N, int K, int most_splits, bool batch) {
-  const int rows = (M + 31) / 32 * 32, blocks = N / 32, chunks = K / KC, at[3] = {rows, rows * 5 / 6, rows * 2 / 3};
+// Tile and split-K parts of a launch of more than 128 rows: the cheapest by GEMM_TILES, plus what the partials cost on their way
+// out and in (1 us for 4 MB).  A part has eight chunks of K at least, and all parts together one round of the CUs.  Of a
+// batch, over numbers of rows from two thirds of M up.
+GemmPlan tile_plan(int M, int N, int K, int most_splits, bool batch) {
+  const int rows = (M + 31) / 32 * 32, blocks = (N + 31) / 32, chunks = std::max(K / KC, 1), at[3] = {rows, rows * 5 / 6, rows * 2 / 3};
   const int max_s = std::max(1, std::min(std::min(most_splits, chunks / 8), 8));
   GemmPlan best{};
   int64_t least = -1;
-  for (int t = 0; t < N_LARGE_TILES; ++t) {
-    const LargeTileCost& c = LARGE_TILES[t];
+  for (int t = N_ROW_TILES; t < N_GEMM_TILES; ++t) {
+    const GemmTileCost& c = GEMM_TILES[t];
     const int m_tiles = (M + 32 * c.rt - 1) / (32 * c.rt), n_tiles = (blocks + c.ct - 1) / c.ct;
     for (int s = 1; s <= max_s; ++s) {
       if (s > 1 && (int64_t)m_tiles * n_tiles * s > 256) break;
       const int cps = (chunks + s - 1) / s;
       if ((chunks + cps - 1) / cps != s) continue;       // the same parts as with fewer
       int64_t cost = 0;
-      for (int i = 0; i < (batch ? 3 : 1); ++i) cost += large_cost(c, at[i], blocks, chunks, s) + (int64_t)s * at[i] * N / 1000;
+      for (int i = 0; i < (batch ? 3 : 1); ++i) cost += tile_cost(c, at[i], blocks, chunks, s) + (int64_t)s * at[i] * N / 1000;
       if (least < 0 || cost < least) {
         least = cost;
         best.splits = s; best.mt = c.rt; best.nb = 2; best.m_tiles = m_tiles; best.n_tiles = n_tiles; best.ct = c.ct;
+      }
+    }
+  }
+  return best;
+}
+
+// Up to 128 rows: one row tile.  The parts are a function of (N, K), those of 128 rows: a row's sums then do not depend on how
+// many rows there are beside it (for QKV, O and down of the 8B shapes 2, 4 and 4 parts of 64 columns, 0.90, 0.87 and 0.92 of the time
+// of twice as many of 128 columns over 1 to 128 rows, with the consumers' share).  The columns are what is cheapest for the
+// parts.  fewest_ct: 4 where pairs for every 128 columns have been reserved.
+GemmPlan row_plan(int M, int N, int K, int most_splits, int fewest_ct) {
+  const int blocks = (N + 31) / 32, chunks = std::max(K / KC, 1), rt = (M + 31) / 32;
+  const int max_s = std::max(1, std::min(std::min(most_splits, chunks / 8), 8));
+  GemmPlan best{};
+  for (int pass = 0; pass < 2; ++pass) {                 // the parts with four row tiles, then the columns with rt
+    const int pass_rt = pass ? rt : 4, s0 = pass ? best.splits : 1, s1 = pass ? best.splits : max_s;
+    int64_t least = -1;
+    for (int t = 0; t < N_ROW_TILES; ++t) {
+      const GemmTileCost& c = GEMM_TILES[t];
+      if (c.rt != pass_rt || c.ct < fewest_ct) continue;
+      const int n_tiles = (blocks + c.ct - 1) / c.ct;
+      for (int s = s0; s <= s1; ++s) {
+        if (!pass && s > 1 && n_tiles * s > 256) break;
+        const int cps = (chunks + s - 1) / s;
+        if ((chunks + cps - 1) / cps != s) continue;
+        const int64_t cost = tile_cost(c, 32 * pass_rt, blocks, chunks, s) + (int64_t)s * (32 * pass_rt * N / 1000 + 200);
+        if (least < 0 || cost < least) {
+          least = cost;
+          best.splits = s; best.mt = rt; best.nb = 1; best.m_tiles = 1; best.n_tiles = n_tiles; best.ct = c.ct;
+        }
       }
     }
   }
@@ -470,9 +381,10 @@ GemmPlan large_plan(int M, int N, int K, int most_splits, bool batch) {
 thread_local LaunchEvents g_launch_events;
 
 hipError_t gemm_prepare() {
-  hipError_t e = gemm_large_out_prepare();
-  if (e == hipSuccess) e = gemm_large_argmax_prepare();
-  if (e == hipSuccess) e = gemm_large_swiglu_prepare();
+  hipError_t e = gemm_tile_out_prepare();
+  if (e == hipSuccess) e = gemm_tile_argmax_prepare();
+  if (e == hipSuccess) e = gemm_tile_swiglu_prepare();
+  if (e == hipSuccess) e = gemm_tile_both_prepare();
   return e;
 }
 
@@ -482,30 +394,20 @@ GemmPlan gemm_plan(int dtype, int M, int N, int K) {
     p.splits = 1; p.mt = 1; p.nb = 1; p.m_tiles = (M + 31) / 32; p.n_tiles = (N + 31) / 32; p.ct = 1;
     return p;
   }
-  const int tiles32 = (M + 31) / 32;
-  if (tiles32 > 4) return large_plan(M, N, K, 8, false);
-  // up to 128 rows: one row tile per workgroup, 128 columns.
-  // split-K from (N, K) only: as many parts as keep the launch within 256 workgroups, one per CU
-  // (288 workgroups on the QKV shape leave 32 CUs with two: 24 us against 21 us at 68 rows), each of eight chunks at least
-  p.mt = tiles32; p.nb = 1; p.m_tiles = 1; p.ct = 4;
-  p.n_tiles = (N + 127) / 128;
-  p.splits = std::max(1, std::min(std::min(256 / p.n_tiles, std::max(1, K / (KC * 8))), 8));
-  return p;
+  return M > 128 ? tile_plan(M, N, K, 8, false) : row_plan(M, N, K, 8, 2);
 }
 
-GemmPlan batch_gemm_plan(int M, int N, int K) { return large_plan(M, N, K, 8, true); }
+GemmPlan batch_gemm_plan(int M, int N, int K) { return tile_plan(M, N, K, 8, true); }
 
-bool gemm_whole_rows(int dtype, int M, int N, int K) {
-  if (dtype == ESP_F32 || K / (KC * 8) < 2) return true;
+int round_parts(int M, int N, int K) {
   const int m_tiles = M <= 128 ? 1 : ((M + 31) / 32 + 4) / 5, n_tiles = M <= 128 ? (N + 127) / 128 : (N + 255) / 256;
-  return 256 / (m_tiles * n_tiles) < 2;                  // two parts would not fit one round
+  return std::max(1, std::min(std::min(256 / (m_tiles * n_tiles), K / (KC * 8)), 8));
 }
+bool gemm_whole_rows(int dtype, int M, int N, int K) { return dtype == ESP_F32 || round_parts(M, N, K) == 1; }
 
 GemmPlan whole_row_plan(int dtype, int M, int N, int K) {
-  if (dtype == ESP_BF16 && M > 128) return large_plan(M, N, K, 1, false);
-  GemmPlan p = gemm_plan(dtype, M, N, K);
-  p.splits = 1;
-  return p;
+  if (dtype == ESP_BF16) return M > 128 ? tile_plan(M, N, K, 1, false) : row_plan(M, N, K, 1, 4);
+  return gemm_plan(dtype, M, N, K);
 }
 
 size_t gemm_out_elems_bound(int dtype, int M, int N, int K) {
@@ -564,30 +466,15 @@ bool gemm_argmax_supported(int dtype, int M, int N, int K, bool with_logits) {
 size_t gemm_argmax_scratch_floats(int M, int N) { return (size_t)((N + 127) / 128) * M * 2; }
 
 hipError_t launch_gemm_argmax(hipStream_t st, const void* A, const int32_t* a_rows, const void* W, int M, int N,
-                              int K, float* scratch, int32_t* out, const int32_t* out_index, int a_ld,
+                              int K, float* scratch, int32_t* out, const int32_t* out_index,
                               float* logits_out, const int32_t* arg_rows, int n_arg, const int32_t* draw_pos,
                               uint32_t seed, const int32_t* m_live) {
   const GemmPlan p = whole_row_plan(ESP_BF16, M, N, K);
-  hipError_t e = hipErrorInvalidValue;
   // without logits_out: pairs only (the logits are never written); with it: the fp32 logits of all M
   // rows as well
-#define ESP_AMAX_CASE(MT_)                                                                                       \
-  case MT_:                                                                                                      \
-    e = logits_out ? launch_bf16<MT_, 1, true, 3>(st, A, a_rows, W, logits_out, M, N, K, 1, a_ld, scratch, draw_pos, seed) \
-                   : launch_bf16<MT_, 1, true, 1>(st, A, a_rows, W, scratch, M, N, K, 1, a_ld, nullptr, draw_pos, seed);   \
-    break;
-  if (p.nb == 2) {   // many rows: large tiles, pairs only
-    if (logits_out || a_ld) return hipErrorInvalidValue;
-    e = launch_gemm_large_argmax(st, {A, a_rows, W, scratch, M, N, K, 1, large_tile_index(p.mt, p.ct), draw_pos, seed, m_live});
-  } else {
-    switch (p.mt) {
-      ESP_AMAX_CASE(1)
-      ESP_AMAX_CASE(2)
-      ESP_AMAX_CASE(3)
-      ESP_AMAX_CASE(4)
-    }
-  }
-#undef ESP_AMAX_CASE
+  if (logits_out && p.nb != 1) return hipErrorInvalidValue;
+  const TileGemm g{A, a_rows, W, logits_out, M, N, K, 1, tile_index(p), draw_pos, seed, m_live, scratch};
+  const hipError_t e = logits_out ? launch_gemm_tile_both(st, g) : launch_gemm_tile_argmax(st, g);
   if (e != hipSuccess) return e;
   // out[out_index[i]] = arg-max of row arg_rows[i] (or of row i), i < n_arg
   hipLaunchKernelGGL(k_argmax_tiles, dim3(n_arg), dim3(256), 0, st, scratch, p.n_tiles, M, arg_rows, out, out_index);
@@ -597,31 +484,34 @@ hipError_t launch_gemm_argmax(hipStream_t st, const void* A, const int32_t* a_ro
 GateUpRule gate_up_rule(int M, int ff, int K, const void* act, bool ragged) {
   GateUpRule r;
   r.mt = even_row_tiles(M); r.chunks = K / KC; r.blocks = (2 * ff) >> 5;
-  if (M <= 128) return r;
+  if (M <= 128) {
+    r.tile[GU_PLAN] = tile_index(row_plan(M, 2 * ff, K, 1, 2));
+    return r;
+  }
   if ((uintptr_t)act % 16 == 0 && ff % 8 == 0) {         // (the wide classes' results are stored 16 bytes at a time)
     r.launched = 1u << r.by_rounds(M);
     if (ragged)                                          // (every tile ends at a multiple of 32 rows)
       for (int rows = (2 * M / 3) & ~31; rows < M; rows += 32) r.launched |= 1u << r.by_rounds(std::max(rows, 1));
   }
   // tiles of the classes: any; a side of 256; 192 x 320
-  static_assert(LARGE_TILES[7].ct == 8 && LARGE_TILES[9].rt == 8 && LARGE_TILES[10].rt == 8 && LARGE_TILES[8].ct == 10, "");
-  const unsigned of[GU_TILES] = {(1u << N_LARGE_TILES) - 1u, 1u << 7 | 1u << 9 | 1u << 10, 1u << 8};
+  static_assert(GEMM_TILES[19].ct == 8 && GEMM_TILES[21].rt == 8 && GEMM_TILES[22].rt == 8 && GEMM_TILES[20].ct == 10, "");
+  const unsigned of[GU_TILES] = {(1u << N_GEMM_TILES) - (1u << N_ROW_TILES), 1u << 19 | 1u << 21 | 1u << 22, 1u << 20};
   // for M rows, or of a batch for any number from 0.6 M up, each of which takes the cheapest of the tiles launched; all M rows
   // may take 3 % longer than with the best for them
   constexpr int MOST = 5;
   const int n = ragged ? MOST : 1;
-  int64_t cost[N_LARGE_TILES][MOST];
-  for (int t = 0; t < N_LARGE_TILES; ++t)
-    for (int i = 0; i < n; ++i) cost[t][i] = large_cost(LARGE_TILES[t], std::max(M * (10 - i) / 10, 1), r.blocks, r.chunks, 1);
+  int64_t cost[N_GEMM_TILES][MOST];
+  for (int t = 0; t < N_GEMM_TILES; ++t)
+    for (int i = 0; i < n; ++i) cost[t][i] = tile_cost(GEMM_TILES[t], std::max(M * (10 - i) / 10, 1), r.blocks, r.chunks, 1);
   int64_t least = -1, best_full = -1;
   for (int c = 0; c < GU_TILES; ++c)
-    for (int t = 0; t < N_LARGE_TILES; ++t)
+    for (int t = 0; t < N_GEMM_TILES; ++t)
       if ((r.launched >> c & 1u) && (of[c] >> t & 1u) && (best_full < 0 || cost[t][0] < best_full)) best_full = cost[t][0];
   int pick[GU_TILES];
   auto choose = [&](auto&& self, int c) -> void {
     if (c < GU_TILES) {
-      for (int t = 0; t < N_LARGE_TILES; ++t)
-        if (r.launched >> c & 1u ? of[c] >> t & 1u : t == 8) {       // (a class that is not launched: whichever)
+      for (int t = 0; t < N_GEMM_TILES; ++t)
+        if (r.launched >> c & 1u ? of[c] >> t & 1u : t == 20) {       // (a class that is not launched: whichever)
           pick[c] = t;
           self(self, c + 1);
         }
@@ -638,7 +528,7 @@ GateUpRule gate_up_rule(int M, int ff, int K, const void* act, bool ragged) {
     }
     if (least < 0 || sum < least) {
       least = sum;
-      for (int k = 0; k < GU_TILES; ++k) { r.tile[k] = pick[k]; r.cost[k] = LARGE_TILES[pick[k]]; }
+      for (int k = 0; k < GU_TILES; ++k) { r.tile[k] = pick[k]; r.cost[k] = GEMM_TILES[pick[k]]; }
     }
   };
   choose(choose, 0);
@@ -654,20 +544,11 @@ hipError_t launch_gemm_swiglu(hipStream_t st, const void* A, const void* W, void
 hipError_t launch_gate_up(hipStream_t st, const void* A, const void* W, void* act, int M, int ff, int K, const int32_t* live,
                           const GateUpRule& r) {
   if (M <= 0) return hipSuccess;
-  if (M <= 128) {
-    float* out = reinterpret_cast<float*>(act);
-    switch ((M + 31) / 32) {
-      case 1: return launch_bf16<1, 1, true, 2>(st, A, nullptr, W, out, M, 2 * ff, K, 1);
-      case 2: return launch_bf16<2, 1, true, 2>(st, A, nullptr, W, out, M, 2 * ff, K, 1);
-      case 3: return launch_bf16<3, 1, true, 2>(st, A, nullptr, W, out, M, 2 * ff, K, 1);
-      default: return launch_bf16<4, 1, true, 2>(st, A, nullptr, W, out, M, 2 * ff, K, 1);
-    }
-  }
   const unsigned tiles = r.launched;
-  LargeGemm g{A, nullptr, W, act, M, 2 * ff, K, 1, 0, nullptr, 0u, live};
+  TileGemm g{A, nullptr, W, act, M, 2 * ff, K, 1, 0, nullptr, 0u, live, nullptr};
   if ((tiles & (tiles - 1)) == 0) {
     g.tile = r.tile[__builtin_ctz(tiles)];
-    return launch_gemm_large_swiglu(st, g);
+    return launch_gemm_tile_swiglu(st, g);
   }
   const LaunchEvents span = g_launch_events;             // a profiling span covers all of them
   for (int t = 0; t < GU_TILES; ++t) {
@@ -675,7 +556,7 @@ hipError_t launch_gate_up(hipStream_t st, const void* A, const void* W, void* ac
     g_launch_events = LaunchEvents{(tiles & ((1u << t) - 1)) == 0 ? span.start : nullptr, (tiles >> (t + 1)) == 0 ? span.stop : nullptr};
     g.tile = r.tile[t];
     g.m_live = live + 2 + t;
-    const hipError_t e = launch_gemm_large_swiglu(st, g);
+    const hipError_t e = launch_gemm_tile_swiglu(st, g);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -697,25 +578,20 @@ hipError_t launch_gemm(hipStream_t st, int dtype, const void* A, const int32_t* 
                        (const float*)A, a_rows, (const float*)W, out, M, N, K);
     return hipGetLastError();
   }
-  if (p.nb == 2 && w_packed) {
+  if (w_packed) {
     if (a_ld) return hipErrorInvalidValue;
-    return launch_gemm_large_out(st, {A, a_rows, W, out, M, N, K, p.splits, large_tile_index(p.mt, p.ct), nullptr, 0u, m_live});
+    return launch_gemm_tile_out(st, {A, a_rows, W, out, M, N, K, p.splits, tile_index(p), nullptr, 0u, m_live, nullptr});
   }
-#define ESP_GEMM_CASE(MT_)                                                                                  \
-  case MT_:                                                                                                 \
-    return w_packed ? launch_bf16<MT_, 1, true>(st, A, a_rows, W, out, M, N, K, p.splits, a_ld)             \
-                    : launch_bf16<MT_, 1, false>(st, A, a_rows, W, out, M, N, K, p.splits, a_ld);
   if (p.nb == 1) switch (p.mt) {
-    ESP_GEMM_CASE(1)
-    ESP_GEMM_CASE(2)
-    ESP_GEMM_CASE(3)
-    ESP_GEMM_CASE(4)
+    case 1: return launch_bf16<1, 1>(st, A, a_rows, W, out, M, N, K, p.splits, a_ld);
+    case 2: return launch_bf16<2, 1>(st, A, a_rows, W, out, M, N, K, p.splits, a_ld);
+    case 3: return launch_bf16<3, 1>(st, A, a_rows, W, out, M, N, K, p.splits, a_ld);
+    case 4: return launch_bf16<4, 1>(st, A, a_rows, W, out, M, N, K, p.splits, a_ld);
   }
-#undef ESP_GEMM_CASE
-  if (p.nb == 2) switch (even_row_tiles(M)) {            // row-major weights
-    case 3: return launch_bf16<3, 2, false>(st, A, a_rows, W, out, M, N, K, p.splits, a_ld);
-    case 4: return launch_bf16<4, 2, false>(st, A, a_rows, W, out, M, N, K, p.splits, a_ld);
-    case 5: return launch_bf16<5, 2, false>(st, A, a_rows, W, out, M, N, K, p.splits, a_ld);
+  if (p.nb == 2) switch (even_row_tiles(M)) {
+    case 3: return launch_bf16<3, 2>(st, A, a_rows, W, out, M, N, K, p.splits, a_ld);
+    case 4: return launch_bf16<4, 2>(st, A, a_rows, W, out, M, N, K, p.splits, a_ld);
+    case 5: return launch_bf16<5, 2>(st, A, a_rows, W, out, M, N, K, p.splits, a_ld);
   }
   return hipErrorInvalidValue;
 }

@@ -1,18 +1,21 @@
-// Large-tile GEMM of the bf16 models (more than 128 rows): out[s][M][N] = A[M,K] * W[N,K]^T on packed weights, with three
-// epilogues.
+// GEMM of the bf16 models on packed weights: out[s][M][N] = A[M,K] * W[N,K]^T, with four epilogues.
 //
-// What bounds it is the chip's power: with the matrix cores busy the clock falls to 1.6 to 1.9 of 2.4 GHz, so the kernel that
-// spends the least energy per flop is the fastest.  Sustained on all CUs with operands from LDS, random data: 1.69 PFLOP/s with
+// Above 128 rows what bounds it is the chip's power: with the matrix cores busy the clock falls to 1.6 to 1.9 of 2.4 GHz, so the
+// kernel that spends the least energy per flop is the fastest.  Sustained on all CUs with operands from LDS, random data: 1.69 PFLOP/s with
 // v_mfma_f32_32x32x16_bf16 (1.79 without the LDS reads), 1.88 (2.07) with v_mfma_f32_16x16x32_bf16, which reads and writes an
 // accumulator half as often.  Hence 16x16x32; four waves in 2 x 2, one per SIMD with all 512 registers, which read fewer
 // fragment bytes per flop than four side by side; both operands global -> LDS without a register hop; consecutive MFMAs that
 // share an operand.  Accumulators in the 256 AGPRs, fragments of this k-step and the next in VGPRs.
+// Up to 128 rows it is a weight stream: 64 to 100 KB of weights in flight a CU, in a ring that takes most of the LDS.
 // The operands change places (D^T = W A^T): a lane then holds four consecutive columns of one row.
-// Sums run over K in the order of the small-row kernel and with the same rounding: results are equal bit for bit for equal splits.
-// MI355X, against the kernels with 32x32x16 before it (5 x 2 and 4 x 2 row and column tiles of 32 a wave, loads by four waves of
-// their own; 256 x 256 and 192 x 320 for gate/up), weights rotating: 320 x 28672 x 4096 82 -> 70 us, 512 x 28672 x 4096 107 -> 94,
-// 1317 x 28672 x 4096 273 -> 256, 512 x 6144 x 4096 33.7 -> 28.8, 320 x 4096 x 4096 24.8 -> 18.8 in half the splits,
-// 1317 x 4096 x 14336 176 -> 128, 1632 x 6144 x 4096 118 -> 71.
+// Sums run over K in the order of the kernel for row-major weights and with the same rounding: results are equal bit for bit for
+// equal splits, whatever the tile.
+// MI355X, weights rotating, against the kernels with 32x32x16 before it.  Above 128 rows (5 x 2 and 4 x 2 row and column tiles of 32
+// a wave, loads by four waves of their own; 256 x 256 and 192 x 320 for gate/up): 320 x 28672 x 4096 82 -> 70 us, 512 x 28672 x 4096
+// 107 -> 94, 1317 x 28672 x 4096 273 -> 256, 512 x 6144 x 4096 33.7 -> 28.8, 320 x 4096 x 4096 24.8 -> 18.8 in half the splits,
+// 1317 x 4096 x 14336 176 -> 128, 1632 x 6144 x 4096 118 -> 71.  Up to 128 rows (weights in register rings, 128 columns a workgroup,
+// twice the splits): 68 x 28672 x 4096 41.2 -> 37.8, 101 x 28672 x 4096 47.3 -> 42.4, 68 x 4096 x 4096 10.1 -> 9.3, 101 x 6144 x 4096
+// 17.0 -> 15.2, one row x 6144 x 4096 10.5 -> 9.6; 68 x 128256 x 4096 with logits and arg-max 224 -> 175.
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -25,7 +28,7 @@ namespace {
 // in LDS: whole chunks of both operands, STAGES of them (W_HALVES 0: what three times fits, one barrier a chunk), or STAGES + 1
 // chunks of activations and W_HALVES half chunks of weights (one barrier a half chunk; up to 160 KB that way).
 template <int RT_, int CT_, int STAGES_, int W_HALVES_>
-struct LargeTile {
+struct GemmTile {
   static constexpr int RT = RT_, CT = CT_;
   static constexpr bool WHOLE = W_HALVES_ == 0;
   static constexpr int S = STAGES_;
@@ -131,16 +134,16 @@ __device__ __forceinline__ void for_each_const(std::integer_sequence<int, t...>,
   (f(std::integral_constant<int, t>{}), ...);
 }
 
-// EPI: 0 fp32 tile out; 1 per-row arg-max over the workgroup's columns (pairs (value, column) to out, [n_tiles][M]); 2 SwiGLU of
-// column blocks that alternate between gate and up, bf16 [M][N / 2] to out.  1 and 2 need splits == 1.
+// EPI: 0 fp32 tile out; 1 per-row arg-max over the workgroup's columns (pairs (value, column) to `pairs`, [n_tiles][M]); 2 SwiGLU of
+// column blocks that alternate between gate and up, bf16 [M][N / 2] to out; 3 both 0 and 1.  1 to 3 need splits == 1.
 // NT_W: weights by nontemporal loads.  m_live (may be null): how many of the M rows are there (packed rows of a ragged batch); the
 // grid was sized for M, the tiles that are there take its first workgroups, strides stay those of M, and every row of the last
 // tile that is not there is loaded from the first of them, in which the forward pass keeps zeros (launch_embed).
 template <class T, int EPI, bool NT_W>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gemm_large(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_gemm_tile(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ a_rows, const bf16_t* __restrict__ W, float* __restrict__ out,
     int M, int N, int K, int splits, int m_tiles, int n_tiles, const int32_t* __restrict__ draw_pos, uint32_t seed,
-    const int32_t* __restrict__ m_live) {
+    const int32_t* __restrict__ m_live, float* __restrict__ pairs) {
   extern __shared__ __align__(16) unsigned char lds[];
   constexpr int RT = T::RT, CT = T::CT, DA = T::DA, DW = T::DW;
   const int M_ld = M;
@@ -216,7 +219,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       else load_a(q - T::W_ITEMS, c, astage);
     };
     // Lane (r, q) of a fragment holds row r, 16-byte piece 4 (q & 1) + 2 ks + q / 2 of the chunk (k-step ks of two): the pieces
-    // in the order in which the small-row kernel's 16-wide steps take them, so that a result does not depend on the kernel.
+    // in the order in which the 16-wide steps of the kernel for row-major weights take them.
     int a_rd[2];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) a_rd[ks] = (wm * 16 + lr) * 128 + (((4 * (lq & 1) + 2 * ks + (lq >> 1)) ^ swz(lr)) << 4);
@@ -325,7 +328,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       for (int j = 0; j < CT; ++j) asm volatile("" : "+a"(acc[i][j]));
   }
   // a lane holds rows i * 32 + wm * 16 + lr and columns j * 32 + wn * 16 + 4 lq .. + 3
-  if constexpr (EPI == 0) {
+  if constexpr (EPI == 0 || EPI == 3) {
     float* o = out + (size_t)z * M_ld * N;
     const bool vec = ((uintptr_t)out & 15) == 0;
 #pragma unroll
@@ -346,7 +349,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       }
     }
   }
-  if constexpr (EPI == 1) {
+  if constexpr (EPI == 1 || EPI == 3) {
     float* red = reinterpret_cast<float*>(lds);          // [2 wave columns][ROWS][2]
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
@@ -382,8 +385,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
       if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
       const int m = mt0 + rl;
       if (m < M) {
-        out[((size_t)ni * M_ld + m) * 2] = best;
-        out[((size_t)ni * M_ld + m) * 2 + 1] = __int_as_float(bi);
+        pairs[((size_t)ni * M_ld + m) * 2] = best;
+        pairs[((size_t)ni * M_ld + m) * 2 + 1] = __int_as_float(bi);
       }
     }
   }
@@ -416,54 +419,64 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
 }
 
-// The tiles there are, with the index of launch_gemm_large's `tile` (LARGE_TILES).
-#define ESP_LARGE_TILES(X) X(0, 3, 8, 3, 0) X(1, 4, 4, 5, 0) X(2, 4, 6, 4, 0) X(3, 4, 8, 3, 0) X(4, 5, 6, 3, 0) X(5, 5, 8, 3, 0) \
-  X(6, 6, 6, 3, 0) X(7, 6, 8, 2, 5) X(8, 6, 10, 2, 4) X(9, 8, 6, 2, 5) X(10, 8, 8, 2, 4)
+// The tiles there are, with their index in GEMM_TILES: those for up to 128 rows (weights always by nontemporal loads) and the others.
+#define ESP_ROW_TILES(X) X(0, 1, 2, 8, 0) X(1, 1, 4, 6, 0) X(2, 1, 6, 5, 0) X(3, 2, 2, 8, 0) X(4, 2, 4, 4, 0) X(5, 2, 6, 5, 0) X(6, 3, 2, 8, 0) \
+  X(7, 3, 4, 4, 0) X(8, 3, 6, 4, 0) X(9, 4, 2, 6, 0) X(10, 4, 4, 5, 0) X(11, 4, 6, 4, 0)
+#define ESP_WIDE_TILES(X) X(12, 3, 8, 3, 0) X(13, 4, 4, 5, 0) X(14, 4, 6, 4, 0) X(15, 4, 8, 3, 0) X(16, 5, 6, 3, 0) X(17, 5, 8, 3, 0) \
+  X(18, 6, 6, 3, 0) X(19, 6, 8, 2, 5) X(20, 6, 10, 2, 4) X(21, 8, 6, 2, 5) X(22, 8, 8, 2, 4)
 
 // dynamic LDS above the default needs an attribute, set once per kernel
 template <class T, int EPI, bool NT>
-hipError_t large_allow_lds() {
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_large<T, EPI, NT>),
+hipError_t tile_allow_lds() {
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tile<T, EPI, NT>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::LDS);
   return attr;
 }
 
 template <int EPI>
-hipError_t large_prepare() {
+hipError_t tile_prepare() {
   hipError_t e = hipSuccess;
-#define ESP_X(I_, RT_, CT_, S_, H_)                                                   \
-  static_assert(LARGE_TILES[I_].rt == RT_ && LARGE_TILES[I_].ct == CT_, "one table"); \
-  if (e == hipSuccess) e = large_allow_lds<LargeTile<RT_, CT_, S_, H_>, EPI, false>(); \
-  if (e == hipSuccess) e = large_allow_lds<LargeTile<RT_, CT_, S_, H_>, EPI, true>();
-  ESP_LARGE_TILES(ESP_X)
+#define ESP_X(I_, RT_, CT_, S_, H_)                                                 \
+  static_assert(GEMM_TILES[I_].rt == RT_ && GEMM_TILES[I_].ct == CT_, "one table"); \
+  if (e == hipSuccess) e = tile_allow_lds<GemmTile<RT_, CT_, S_, H_>, EPI, true>();
+  ESP_ROW_TILES(ESP_X)
+  if constexpr (EPI != 3) { ESP_WIDE_TILES(ESP_X) }
+#undef ESP_X
+#define ESP_X(I_, RT_, CT_, S_, H_) \
+  if (e == hipSuccess) e = tile_allow_lds<GemmTile<RT_, CT_, S_, H_>, EPI, false>();
+  if constexpr (EPI != 3) { ESP_WIDE_TILES(ESP_X) }
 #undef ESP_X
   return e;
 }
 
 template <class T, int EPI, bool NT>
-hipError_t large_launch(hipStream_t st, const LargeGemm& g) {
-  const hipError_t attr = large_allow_lds<T, EPI, NT>();
+hipError_t tile_launch(hipStream_t st, const TileGemm& g) {
+  const hipError_t attr = tile_allow_lds<T, EPI, NT>();
   if (attr != hipSuccess) return attr;
   const int m_tiles = (g.M + T::ROWS - 1) / T::ROWS, n_tiles = ((g.N >> 5) + T::CT - 1) / T::CT;
   const int64_t total = (int64_t)m_tiles * n_tiles * g.splits;
   if (total > INT32_MAX - 8) return hipErrorInvalidValue;
-  launch_kernel(k_gemm_large<T, EPI, NT>, dim3((unsigned)((total + 7) / 8 * 8)), dim3(256), T::LDS, st, (const bf16_t*)g.A, g.a_rows,
-                (const bf16_t*)g.W, (float*)g.out, g.M, g.N, g.K, g.splits, m_tiles, n_tiles, g.draw_pos, g.seed, g.m_live);
+  launch_kernel(k_gemm_tile<T, EPI, NT>, dim3((unsigned)((total + 7) / 8 * 8)), dim3(256), T::LDS, st, (const bf16_t*)g.A, g.a_rows,
+                (const bf16_t*)g.W, (float*)g.out, g.M, g.N, g.K, g.splits, m_tiles, n_tiles, g.draw_pos, g.seed, g.m_live, g.pairs);
   return hipGetLastError();
 }
 
 // Weights by nontemporal loads where at most four row tiles of 160 share them: a step of 320 rows 7511 -> 7387 us, 576 rows of the
 // Qwen3 shape 12227 -> 12105, prefill of 2049 tokens in chunks of 512 37.17 -> 36.64 ms; with 14 row tiles (16 ragged sequences)
-// 33.83 -> 34.00 ms, so not there.  (Measured with the kernels before this one.)
+// 33.83 -> 34.00 ms, so not there.  Up to 128 rows, eight layers of the 8B shape on 2048 keys: one row 843 -> 779 us, 30 rows 886 -> 834,
+// 68 rows 1055 -> 1014, 128 rows 1260 -> 1230.  (Measured with the kernels before this one.)
 template <int EPI>
-hipError_t large_dispatch(hipStream_t st, const LargeGemm& g) {
-  const bool nt = g.M <= 640;
-  switch (g.tile) {
+hipError_t tile_dispatch(hipStream_t st, const TileGemm& g) {
+  [[maybe_unused]] const bool nt = g.M <= 640;
 #define ESP_X(I_, RT_, CT_, S_, H_) \
-  case I_: return nt ? large_launch<LargeTile<RT_, CT_, S_, H_>, EPI, true>(st, g) : large_launch<LargeTile<RT_, CT_, S_, H_>, EPI, false>(st, g);
-    ESP_LARGE_TILES(ESP_X)
+  case I_: return tile_launch<GemmTile<RT_, CT_, S_, H_>, EPI, true>(st, g);
+  switch (g.tile) { ESP_ROW_TILES(ESP_X) }
 #undef ESP_X
-  }
+#define ESP_X(I_, RT_, CT_, S_, H_) \
+  case I_: return nt ? tile_launch<GemmTile<RT_, CT_, S_, H_>, EPI, true>(st, g) : tile_launch<GemmTile<RT_, CT_, S_, H_>, EPI, false>(st, g);
+  if constexpr (EPI != 3)
+    switch (g.tile) { ESP_WIDE_TILES(ESP_X) }
+#undef ESP_X
   return hipErrorInvalidValue;
 }
 

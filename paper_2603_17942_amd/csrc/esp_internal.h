@@ -101,21 +101,24 @@ __host__ __device__ __forceinline__ size_t v_off(int64_t slot, int d, int hd) {
 struct GemmPlan {
   int splits;        // split-K factor
   int mt;            // 32-row tiles per workgroup
-  int nb;            // bf16: 1 the small-row kernel (up to 128 rows), 2 the large tiles
+  int nb;            // bf16: 1 up to 128 rows, 2 above
   int m_tiles;       // workgroup tiles along M
   int n_tiles;       // workgroup tiles along N
   int ct;            // 32-column blocks per workgroup
 };
-// Large tiles (esp_gemm_large.h): row tiles and column blocks of 32 and what one costs, in ns: start and end of a round over the
-// 256 CUs, a chunk of 64 of K, and how much longer a chunk takes with all CUs at it (power and L2; with half of them, half of it).
-// Fitted to 3900 measured launches: M 136 to 2112, N and K of QKV, O, gate/up and down of two model shapes, 1 to 8 splits.  Of
-// the tiles and splits that were measured for a shape the model's choice is 0.8 % slower than the best on average, 10 % at most.
-struct LargeTileCost { int rt, ct, start, chunk, busy; };
-constexpr int N_LARGE_TILES = 11;
-constexpr LargeTileCost LARGE_TILES[N_LARGE_TILES] = {
+// Tiles of the bf16 kernel (esp_gemm_tile.h): row tiles and column blocks of 32 and what one costs, in ns: start and end of a round
+// over the 256 CUs, a chunk of 64 of K, and how much longer a chunk takes with all CUs at it (power, L2 and HBM; with half of them,
+// half of it).  Fitted to measured launches on N and K of QKV, O, gate/up and down of two model shapes, 1 to 8 splits: the first
+// N_ROW_TILES, for up to 128 rows, to 1300 of 1 to 128 rows, the others to 3900 of 136 to 2112 rows.  Of the tiles and splits that were
+// measured for a shape the model's choice is 0.8 % slower than the best on average, 10 % at most (17 % in one).
+struct GemmTileCost { int rt, ct, start, chunk, busy; };
+constexpr int N_GEMM_TILES = 23, N_ROW_TILES = 12;
+constexpr GemmTileCost GEMM_TILES[N_GEMM_TILES] = {
+    {1, 2, 1560, 130, 142}, {1, 4, 1770, 247, 260}, {1, 6, 2010, 381, 321}, {2, 2, 1440, 210, 88}, {2, 4, 1480, 344, 182}, {2, 6, 1640, 493, 239},
+    {3, 2, 1580, 271, 68}, {3, 4, 1160, 439, 134}, {3, 6, 1560, 596, 149}, {4, 2, 1150, 326, 68}, {4, 4, 1510, 493, 158}, {4, 6, 1810, 657, 106},
     {3, 8, 3980, 582, 94}, {4, 4, 2110, 413, 124}, {4, 6, 3660, 565, 75}, {4, 8, 5010, 584, 178}, {5, 6, 4720, 589, 97}, {5, 8, 6230, 646, 218},
     {6, 6, 5400, 585, 192}, {6, 8, 6860, 710, 311}, {6, 10, 7800, 982, 206}, {8, 6, 6660, 784, 220}, {8, 8, 8130, 885, 368}};
-__host__ __device__ inline int64_t large_cost(const LargeTileCost& t, int rows, int blocks, int chunks, int splits) {
+__host__ __device__ inline int64_t tile_cost(const GemmTileCost& t, int rows, int blocks, int chunks, int splits) {
   const int64_t n = (int64_t)((rows + 32 * t.rt - 1) / (32 * t.rt)) * ((blocks + t.ct - 1) / t.ct) * splits;
   if (n == 0) return 0;
   const int64_t before = (n - 1) / 256, last = n - 256 * before, c = (chunks + splits - 1) / splits;
@@ -125,6 +128,8 @@ GemmPlan gemm_plan(int dtype, int M, int N, int K);
 // of a batch with packed rows, of whose M rows only the device knows how many are there: for two thirds of them to all
 GemmPlan batch_gemm_plan(int M, int N, int K);
 // is a projection's output unsplit by its size (the LM head's epilogues see whole rows and are refused otherwise), and its plan
+// (by tiles of 128 columns up to 128 rows and of 160 x 256 above: not split if two parts would not fit one round of the CUs)
+int round_parts(int M, int N, int K);
 bool gemm_whole_rows(int dtype, int M, int N, int K);
 GemmPlan whole_row_plan(int dtype, int M, int N, int K);
 inline size_t gemm_out_elems(const GemmPlan& p, int M, int N) { return (size_t)p.splits * M * N; }
@@ -137,22 +142,25 @@ size_t gemm_out_elems_bound(int dtype, int M, int N, int K);
 hipError_t launch_gemm(hipStream_t st, int dtype, const void* A, const int32_t* a_rows, const void* W,
                        float* out, int M, int N, int K, const GemmPlan& p, bool w_packed, int a_ld = 0,
                        const int32_t* m_live = nullptr);
-// a_ld == 0: A is row-major [rows][K]; a_ld > 0 (bf16, up to 128 rows or unpacked weights): A is chunk-major [K/64][a_ld][64]
+// a_ld == 0: A is row-major [rows][K]; a_ld > 0 (bf16, unpacked weights): A is chunk-major [K/64][a_ld][64]
 hipError_t launch_pack_weight(hipStream_t st, const void* src, void* dst, int N, int K);
 // one-time kernel attributes of the GEMM kernels (dynamic LDS limits); call before the first launch
 hipError_t gemm_prepare();
-// the large-tile kernel, a launcher per epilogue
-struct LargeGemm {
+// the kernel for packed weights, a launcher per epilogue
+struct TileGemm {
   const void* A; const int32_t* a_rows; const void* W; void* out;
-  int M, N, K, splits, tile;               // tile: index into LARGE_TILES
+  int M, N, K, splits, tile;               // tile: index into GEMM_TILES
   const int32_t* draw_pos; uint32_t seed; const int32_t* m_live;
+  float* pairs;                            // launch_gemm_tile_both: the arg-max pairs
 };
-hipError_t launch_gemm_large_out(hipStream_t st, const LargeGemm& g);
-hipError_t launch_gemm_large_argmax(hipStream_t st, const LargeGemm& g);
-hipError_t launch_gemm_large_swiglu(hipStream_t st, const LargeGemm& g);
-hipError_t gemm_large_out_prepare();
-hipError_t gemm_large_argmax_prepare();
-hipError_t gemm_large_swiglu_prepare();
+hipError_t launch_gemm_tile_out(hipStream_t st, const TileGemm& g);
+hipError_t launch_gemm_tile_argmax(hipStream_t st, const TileGemm& g);
+hipError_t launch_gemm_tile_swiglu(hipStream_t st, const TileGemm& g);
+hipError_t launch_gemm_tile_both(hipStream_t st, const TileGemm& g);   // fp32 tile out and arg-max; tiles for up to 128 rows only
+hipError_t gemm_tile_out_prepare();
+hipError_t gemm_tile_argmax_prepare();
+hipError_t gemm_tile_swiglu_prepare();
+hipError_t gemm_tile_both_prepare();
 // Tile of the gate/up projection above 128 rows, in three classes: the plan's, one with a side of 256 (256 x 256, 192 x 256 or
 // 256 x 192, by cost), and 192 x 320.  The host takes the wide classes where they save rounds over the 256 CUs against row tiles of
 // up to 160: `rounds` in units of 10 ns, chunks x the time of one + start and epilogue.  K = 4096: 512 x 28672 128 us with
@@ -163,8 +171,8 @@ enum GateUpTile { GU_PLAN = 0, GU_SIDE256 = 1, GU_192x320 = 2, GU_TILES = 3 };
 struct GateUpRule {
   int mt = 1, chunks = 0, blocks = 0;      // row tiles of 32 where as few tiles as possible have up to five; chunks of 64 of K; column blocks of 32
   unsigned launched = 1u << GU_PLAN;       // bit t: class t is launched
-  int tile[GU_TILES] = {};                 // of LARGE_TILES
-  LargeTileCost cost[GU_TILES] = {};
+  int tile[GU_TILES] = {};                 // of GEMM_TILES; up to 128 rows the first
+  GemmTileCost cost[GU_TILES] = {};
   GateUpTile by_rounds(int rows) const {
     int64_t whole[GU_TILES];
     const int per[GU_TILES] = {32 * mt, 256, 192}, cols[GU_TILES] = {8, 8, 10};
@@ -180,7 +188,7 @@ struct GateUpRule {
     int64_t least = 0;
     for (int t = 0; t < GU_TILES; ++t)
       if (launched >> t & 1u) {
-        const int64_t c = large_cost(cost[t], rows, blocks, chunks, 1);
+        const int64_t c = tile_cost(cost[t], rows, blocks, chunks, 1);
         if (best < 0 || c < least) { best = t; least = c; }
       }
     return (GateUpTile)best;
@@ -200,7 +208,7 @@ size_t gemm_argmax_scratch_floats(int M, int N);
 // logits_out == NULL: arg-max of each of the M rows (out[out_index[m]]), logits never written.
 // logits_out != NULL: also writes the fp32 logits [M][N]; arg-max only for the n_arg rows arg_rows[i].
 hipError_t launch_gemm_argmax(hipStream_t st, const void* A, const int32_t* a_rows, const void* W, int M, int N,
-                              int K, float* scratch, int32_t* out, const int32_t* out_index, int a_ld,
+                              int K, float* scratch, int32_t* out, const int32_t* out_index,
                               float* logits_out, const int32_t* arg_rows, int n_arg,
                               const int32_t* draw_pos = nullptr, uint32_t seed = 0,   // draw_pos: per GEMM row
                               const int32_t* m_live = nullptr);

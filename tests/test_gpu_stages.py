@@ -175,31 +175,35 @@ def test_gemm_swiglu(B, M, ff, K, live, tile):
     assert bool((act[rows:] == -7).all())
 
 
-LARGE_TILES = [(3, 8), (4, 4), (4, 6), (4, 8), (5, 6), (5, 8), (6, 6), (6, 8), (6, 10), (8, 6), (8, 8)]   # 32-row and 32-column tiles
+ROW_TILES = 12                                            # the first are for up to 128 rows; 32-row and 32-column tiles
+GEMM_TILES = [(rt, ct) for rt in (1, 2, 3, 4) for ct in (2, 4, 6)] + [
+    (3, 8), (4, 4), (4, 6), (4, 8), (5, 6), (5, 8), (6, 6), (6, 8), (6, 10), (8, 6), (8, 8)]
 
 
-class LargePlan(ctypes.Structure):
+class TilePlan(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int) for n in ("splits", "mt", "nb", "m_tiles", "n_tiles", "ct")]
 
 
-class LargeGemm(ctypes.Structure):
+class TileGemm(ctypes.Structure):
     _fields_ = ([(n, ctypes.c_void_p) for n in ("A", "a_rows", "W", "out")] + [(n, ctypes.c_int) for n in ("M", "N", "K", "splits", "tile")] +
-                [("draw_pos", ctypes.c_void_p), ("seed", ctypes.c_uint32), ("m_live", ctypes.c_void_p)])
+                [("draw_pos", ctypes.c_void_p), ("seed", ctypes.c_uint32), ("m_live", ctypes.c_void_p), ("pairs", ctypes.c_void_p)])
 
 
-@pytest.mark.parametrize("tile", range(len(LARGE_TILES)))
+@pytest.mark.parametrize("tile", range(len(GEMM_TILES)))
 @pytest.mark.parametrize("M,N,K,splits,live", [
     (129, 544, 64, 1, None), (257, 352, 128, 1, None), (160, 1056, 192, 1, None), (300, 96, 256, 1, None), (192, 256, 320, 1, None),
     (513, 416, 704, 3, None), (256, 640, 512, 8, None), (320, 320, 1088, 2, None), (385, 192, 1536, 1, None),
-    (200, 320, 1088, 2, 77), (700, 288, 448, 1, 513), (300, 256, 384, 1, 1), (300, 256, 384, 1, 0)])
-def test_gemm_large_tiles(B, tile, M, N, K, splits, live):
-    """Every large tile at remainders of rows and columns, from one chunk of K (fewer than the loads reach ahead) to many, in
+    (200, 320, 1088, 2, 77), (700, 288, 448, 1, 513), (300, 256, 384, 1, 1), (300, 256, 384, 1, 0), (1, 96, 64, 1, None), (33, 320, 1600, 1, None),
+    (128, 544, 448, 7, None)])
+def test_gemm_tiles(B, tile, M, N, K, splits, live):
+    """Every tile at remainders of rows and columns, from one chunk of K (fewer than the loads reach ahead) to many, in
     parts, and with rows of a batch that are not there: bit for bit what the kernel for row-major weights gives, which adds in
-    the same order; with one part also its arg-max and SwiGLU epilogues against the same logits (ties: the lowest column)."""
+    the same order; with one part also its arg-max and SwiGLU epilogues against the same logits (ties: the lowest column).
+    The tiles for up to 128 rows also as several row tiles."""
     c = ctypes
-    rt, ct = LARGE_TILES[tile]
-    print(f"large tile {rt}x{ct} M={M} N={N} K={K} splits={splits} live={live}", flush=True)
-    gemm = internal("launch_gemm", c.c_void_p, c.c_int, c.c_void_p, c.c_void_p, c.c_void_p, c.c_void_p, *[c.c_int] * 3, c.POINTER(LargePlan),
+    rt, ct = GEMM_TILES[tile]
+    print(f"tile {rt}x{ct} M={M} N={N} K={K} splits={splits} live={live}", flush=True)
+    gemm = internal("launch_gemm", c.c_void_p, c.c_int, c.c_void_p, c.c_void_p, c.c_void_p, c.c_void_p, *[c.c_int] * 3, c.POINTER(TilePlan),
                     c.c_bool, c.c_int, c.c_void_p)
     a = synth.normal_like((M, K), 1.0, 16, 0, "cuda", torch.bfloat16)
     w = synth.normal_like((N, K), K ** -0.5, 16, 1, "cuda", torch.bfloat16)
@@ -207,32 +211,36 @@ def test_gemm_large_tiles(B, tile, M, N, K, splits, live):
     wp = B.pack_weight(w)
     n = None if live is None else torch.tensor([live], dtype=torch.int32, device="cuda")
     st = torch.cuda.current_stream().cuda_stream
-    plan = LargePlan(splits, rt, 2, (M + 32 * rt - 1) // (32 * rt), (N // 32 + ct - 1) // ct, ct)
+    plan = TilePlan(splits, rt, 1 if tile < ROW_TILES else 2, (M + 32 * rt - 1) // (32 * rt), (N // 32 + ct - 1) // ct, ct)
     got, want = (torch.full((splits, M, N), -7.0, device="cuda") for _ in range(2))
     assert gemm(st, B.ESP_BF16, a.data_ptr(), None, wp.data_ptr(), got.data_ptr(), M, N, K, plan, True, 0, None if n is None else n.data_ptr()) == 0
-    assert gemm(st, B.ESP_BF16, a.data_ptr(), None, w.data_ptr(), want.data_ptr(), M, N, K, plan, False, 0, None) == 0
+    ref_plan = TilePlan(splits, 1, 1, (M + 31) // 32, (N + 127) // 128, 4)   # row-major weights: one row tile a workgroup
+    assert gemm(st, B.ESP_BF16, a.data_ptr(), None, w.data_ptr(), want.data_ptr(), M, N, K, ref_plan, False, 0, None) == 0
     rows = M if live is None else live
     assert torch.equal(got[:, :rows], want[:, :rows]) and bool((got[:, rows:] == -7).all())
     ref = a.double() @ w.double().T
     assert float((want.double().sum(0) - ref).abs().max()) <= 2e-5 * float(ref.abs().max())   # fp32 sums of up to 1536 exact products
     if splits > 1 or not rows:
         return
-    out = torch.full((plan.n_tiles, M, 2), -7.0, device="cuda")
-    g = LargeGemm(a.data_ptr(), None, wp.data_ptr(), out.data_ptr(), M, N, K, 1, tile, None, 0, None if n is None else n.data_ptr())
-    assert internal("launch_gemm_large_argmax", c.c_void_p, c.POINTER(LargeGemm))(st, g) == 0
-    for t in range(plan.n_tiles):
-        cols = want[0, :rows, t * 32 * ct:(t + 1) * 32 * ct]
-        best = cols.amax(1)
-        assert torch.equal(out[t, :rows, 0], best)
-        first = (cols == best[:, None]).int().argmax(1) + t * 32 * ct
-        assert torch.equal(out[t, :rows, 1].contiguous().view(torch.int32).long(), first)
-    assert bool((out[:, rows:] == -7).all())
+    n_live = None if n is None else n.data_ptr()
+    for both in (False, True) if tile < ROW_TILES else (False,):
+        pairs, logits = torch.full((plan.n_tiles, M, 2), -7.0, device="cuda"), torch.full((M, N), -7.0, device="cuda")
+        g = TileGemm(a.data_ptr(), None, wp.data_ptr(), logits.data_ptr(), M, N, K, 1, tile, None, 0, n_live, pairs.data_ptr())
+        assert internal("launch_gemm_tile_both" if both else "launch_gemm_tile_argmax", c.c_void_p, c.POINTER(TileGemm))(st, g) == 0
+        for t in range(plan.n_tiles):
+            cols = want[0, :rows, t * 32 * ct:(t + 1) * 32 * ct]
+            best = cols.amax(1)
+            assert torch.equal(pairs[t, :rows, 0], best)
+            first = (cols == best[:, None]).int().argmax(1) + t * 32 * ct
+            assert torch.equal(pairs[t, :rows, 1].contiguous().view(torch.int32).long(), first)
+        assert bool((pairs[:, rows:] == -7).all())
+        assert torch.equal(logits[:rows], want[0, :rows]) if both else bool((logits == -7).all())
     if N % 64 == 0:
         act = torch.full((M + 1, N // 2), -7.0, dtype=torch.bfloat16, device="cuda")
         for offset in (0, 1):                                # results on and off the 16-byte alignment of the wide stores
             flat = act.view(-1)[offset:offset + M * (N // 2)]
             g.out = flat.data_ptr()
-            assert internal("launch_gemm_large_swiglu", c.c_void_p, c.POINTER(LargeGemm))(st, g) == 0
+            assert internal("launch_gemm_tile_swiglu", c.c_void_p, c.POINTER(TileGemm))(st, g) == 0
             blocks = want[0, :rows].double().view(rows, N // 64, 2, 32)
             gate, up = blocks[:, :, 0].reshape(rows, -1), blocks[:, :, 1].reshape(rows, -1)
             r = gate / (1 + torch.exp(-gate)) * up
