@@ -348,8 +348,10 @@ GemmPlan tile_plan(int M, int N, int K, int most_splits, bool batch) {
 
 // Up to 128 rows: one row tile.  The parts are a function of (N, K), those of 128 rows: a row's sums then do not depend on how
 // many rows there are beside it (for QKV, O and down of the 8B shapes 2, 4 and 4 parts of 64 columns, 0.90, 0.87 and 0.92 of the time
-// of twice as many of 128 columns over 1 to 128 rows, with the consumers' share).  The columns are what is cheapest for the
-// parts.  fewest_ct: 4 where pairs for every 128 columns have been reserved.
+// of twice as many of 128 columns over 1 to 128 rows, with the consumers' share).  A part costs 0.6 us beside its bytes: with 0.2, five
+// and eight parts for QKV and down, which alone take as long, a step of 101 rows takes 5410 us instead of 5325 and one of 30
+// rows 3482 instead of 3462.  The columns are what is cheapest for the parts.  fewest_ct: 4 where pairs for every 128 columns
+// have been reserved.
 GemmPlan row_plan(int M, int N, int K, int most_splits, int fewest_ct) {
   const int blocks = (N + 31) / 32, chunks = std::max(K / KC, 1), rt = (M + 31) / 32;
   const int max_s = std::max(1, std::min(std::min(most_splits, chunks / 8), 8));
@@ -365,7 +367,7 @@ GemmPlan row_plan(int M, int N, int K, int most_splits, int fewest_ct) {
         if (!pass && s > 1 && n_tiles * s > 256) break;
         const int cps = (chunks + s - 1) / s;
         if ((chunks + cps - 1) / cps != s) continue;
-        const int64_t cost = tile_cost(c, 32 * pass_rt, blocks, chunks, s) + (int64_t)s * (32 * pass_rt * N / 1000 + 200);
+        const int64_t cost = tile_cost(c, 32 * pass_rt, blocks, chunks, s) + (int64_t)s * (32 * pass_rt * N / 1000 + 600);
         if (least < 0 || cost < least) {
           least = cost;
           best.splits = s; best.mt = rt; best.nb = 1; best.m_tiles = 1; best.n_tiles = n_tiles; best.ct = c.ct;
