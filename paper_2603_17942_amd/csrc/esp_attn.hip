@@ -672,6 +672,18 @@ __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, i
     nsplit = n_slots[0];
   }
   auto part = [&](int sp) { return t0 + (CUTS ? (size_t)slots[sp] : (size_t)sp) * step; };
+  // O of the first splits is on its way before their weights are known: one memory latency instead of two, 68 rows on 2048 keys
+  // 5.3 -> 4.7 us (sixteen of them no better)
+  constexpr int EARLY = 8;
+  const int f0 = fq * 32 + grp * 4;
+  const float* p = part_o + (size_t)f0 * 32 + col;
+  float early[EARLY][4];
+#pragma unroll
+  for (int s = 0; s < EARLY; ++s)
+    if (s < nsplit) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) early[s][e] = p[part(s) * (HD * 32) + 32 * e];
+    }
   float ms[PER], ls[PER];
   float mx = NEG_BIG;
 #pragma unroll
@@ -704,13 +716,17 @@ __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, i
 #pragma unroll
   for (int g = 0; g < 8; ++g) lt += red_l[g][col];
   const float inv = lt > 0.f ? 1.f / lt : 0.f;
-  const int fsub = grp;
-  const int f0 = fq * 32 + fsub * 4;
   f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
   if (live) {
-    const float* p = part_o + (size_t)f0 * 32 + col;
+#pragma unroll
+    for (int s = 0; s < EARLY; ++s)
+      if (s < nsplit) {
+        const float w = w_s[s][col];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += early[s][e] * w;
+      }
 #pragma unroll 8
-    for (int s = 0; s < nsplit; ++s) {
+    for (int s = EARLY; s < nsplit; ++s) {
       const float w = w_s[s][col];
       const float* ps = p + part(s) * (HD * 32);
       acc[0] += ps[0] * w; acc[1] += ps[32] * w; acc[2] += ps[64] * w; acc[3] += ps[96] * w;

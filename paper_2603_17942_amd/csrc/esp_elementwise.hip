@@ -274,6 +274,10 @@ __global__ __launch_bounds__(256) void k_qkv_post(BlockDev b, KvDev kv, int laye
   if (hidx >= n_heads) return;
   const size_t c0 = ((size_t)row * n_heads + hidx) * HD + f0;
   f32x4_t x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
+  // the rotary table's entries (a row of it for every row of the activations) with the partials, not after the sequence's lengths:
+  // 68 rows of 32 + 16 heads 5.1 -> 4.8 us
+  const float* rt = rope_tab + ((size_t)row * HALF + f0) * 2;      // cos, sin of four pairs
+  const f32x4_t t0 = *reinterpret_cast<const f32x4_t*>(rt), t1 = *reinterpret_cast<const f32x4_t*>(rt + 4);
   x0 = add_splits<S>(x0, part + c0, split_stride);
   x1 = add_splits<S>(x1, part + c0 + HALF, split_stride);
   const int brow = PACKED ? b.live_rows()[row] : row;
@@ -311,8 +315,6 @@ __global__ __launch_bounds__(256) void k_qkv_post(BlockDev b, KvDev kv, int laye
         x1[e] *= inv * to_f32(g[HALF + e]);
       }
     }
-    const float* rt = rope_tab + ((size_t)row * HALF + f0) * 2;      // cos, sin of four pairs
-    const f32x4_t t0 = *reinterpret_cast<const f32x4_t*>(rt), t1 = *reinterpret_cast<const f32x4_t*>(rt + 4);
     const f32x4_t c = {t0[0], t0[2], t1[0], t1[2]}, s = {t0[1], t0[3], t1[1], t1[3]};
     const f32x4_t y0 = x0 * c - x1 * s, y1 = x1 * c + x0 * s;
     if (hidx < hq) {
