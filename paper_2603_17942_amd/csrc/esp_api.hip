@@ -365,7 +365,7 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
       ESP_HIP(launch_qkv_post(s, dt, bd, kd, l, c->gemm_out, p_qkv.splits, M, hq, hkv, hd, m.qk_norm, c->q_norm[l],
                               c->k_norm[l], m.rms_eps, c->rope_tab, c->q)); }
     { ESP_PROF(ESP_SITE_ATTN);
-      ESP_HIP(launch_attn(s, dt, bd, kd, l, hq, hkv, hd, c->q, c->attn_part, ap, cuts)); }
+      ESP_HIP(launch_attn(s, dt, bd, kd, l, hq, hkv, hd, c->q, c->attn_part, ap, cuts, c->attn_out)); }
     { ESP_PROF(ESP_SITE_ATTN_MERGE);
       ESP_HIP(launch_attn_merge(s, dt, bd, kd, hq, hkv, hd, c->attn_part, ap, c->attn_out, cuts)); }
     { ESP_PROF_KERNEL(ESP_SITE_GEMM_LAYER, dt == ESP_BF16);
@@ -712,7 +712,7 @@ esp_status esp_attn_tree(esp_ctx* c, const esp_block* blk, const esp_kv* kv, int
   { ESP_PROF(ESP_SITE_ATTN);
     if (shares) ESP_HIP(launch_attn_cuts(c->stream, to_dev(blk), to_dev(kv), m.n_q_heads, m.n_kv_heads, ap, shares, c->cuts));
     ESP_HIP(launch_attn(c->stream, m.dtype, to_dev(blk), to_dev(kv), layer, m.n_q_heads, m.n_kv_heads, m.head_dim, q,
-                        c->attn_part, ap, cuts)); }
+                        c->attn_part, ap, cuts, out)); }
   { ESP_PROF(ESP_SITE_ATTN_MERGE);
     ESP_HIP(launch_attn_merge(c->stream, m.dtype, to_dev(blk), to_dev(kv), m.n_q_heads, m.n_kv_heads, m.head_dim, c->attn_part, ap,
                               out, cuts)); }

@@ -1136,6 +1136,21 @@ def test_attn_tree_generic_forms(B, monkeypatch, dtype, head_dim, offset):
         assert err < TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype,head_dim", [("f32", 64), ("f32", 128), ("bf16", 64)])
+def test_attn_tree_generic_splits(B, dtype, head_dim):
+    """One split to more than a workgroup merges by itself (8 at a head of 64, 4 at 128), sequences that leave splits without a
+    key tile, and rows that are not there."""
+    shape = small_shape(d_model=256, n_q_heads=4, n_kv_heads=2, head_dim=head_dim, d_ff=128, vocab=512, n_layers=1, dtype=dtype)
+    w = synth.make_weights(shape, seed=5)
+    for n_nodes, lens in [(5, [0]), (5, [64, 1]), (5, [130]), (7, [250, 3]), (5, [300]), (6, [1000, 64, 600]), (1, [1400]), (6, [2600, 40])]:
+        rows = n_nodes * 3
+        eng = B.Engine(shape, w, max_batch=len(lens), max_rows_per_seq=rows, max_kv_len=max(lens) + rows + 64)
+        print(f"attn generic {dtype} hd={head_dim} n={n_nodes} L={lens}", flush=True)
+        err = run_attention_case(B, shape, eng, n_nodes, 2, 0, lens, seed=62)
+        eng.close()
+        assert err < TOL[dtype]
+
+
 @pytest.fixture(scope="module")
 def bf16_engine(B):
     shape = small_shape(d_model=256, n_q_heads=8, n_kv_heads=2, head_dim=128, d_ff=384, vocab=1024, n_layers=2,
