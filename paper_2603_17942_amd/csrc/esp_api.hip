@@ -328,7 +328,7 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
   auto plan = [&](int N, int K) { return packed ? batch_gemm_plan(M, N, K) : gemm_plan(dt, M, N, K); };
   const GemmPlan p_qkv = plan(nqkv, d), p_o = plan(d, hq * hd), p_dn = plan(d, ff);
   if (gemm_out_elems(p_qkv, M, nqkv) > c->gemm_out_floats || gemm_out_elems(p_o, M, d) > c->gemm_out_floats ||
-      (!pk && (size_t)M * 2 * ff > c->gemm_out_floats) || gemm_out_elems(p_dn, M, d) > c->gemm_out_floats)
+      gemm_out_elems(p_dn, M, d) > c->gemm_out_floats)
     return ESP_ECAPACITY;
   const AttnPlan ap = attn_plan(dt, hd, blk->batch, blk->rows_per_seq, hq, hkv, kv->len_bound);
   if (attn_partial_floats(dt, blk->batch, blk->rows_per_seq, hq, hkv, hd, ap) > c->attn_part_floats)
@@ -376,10 +376,8 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
       ESP_PROF_KERNEL(ESP_SITE_GEMM_LAYER, true);
       ESP_HIP(launch_gate_up(s, c->xn, c->wgu[l], c->act, M, ff, d, m_live, gate_up));
     } else {
-      { ESP_PROF(ESP_SITE_GEMM_LAYER);
-        ESP_HIP(launch_gemm(s, dt, c->xn, nullptr, c->wgu[l], c->gemm_out, M, 2 * ff, d, gemm_plan(dt, M, 2 * ff, d), pk)); }
-      { ESP_PROF(ESP_SITE_GLUE);
-        ESP_HIP(launch_swiglu(s, dt, c->gemm_out, 1, M, ff, c->act)); }
+      ESP_PROF(ESP_SITE_GEMM_LAYER);
+      ESP_HIP(launch_gemm_swiglu_f32(s, (const float*)c->xn, (const float*)c->wgu[l], (float*)c->act, M, ff, d));
     }
     { ESP_PROF_KERNEL(ESP_SITE_GEMM_LAYER, dt == ESP_BF16);
       ESP_HIP(launch_gemm(s, dt, c->act, nullptr, c->wdown[l], c->gemm_out, M, d, ff, p_dn, pk, 0, m_live)); }

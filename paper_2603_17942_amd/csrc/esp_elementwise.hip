@@ -1,4 +1,4 @@
-// Glue kernels of the ESP decode step: block assembly, norms, rotary + KV append, SwiGLU,
+// Glue kernels of the ESP decode step: block assembly, norms, rotary + KV append,
 // argmax, KV copies, mask-vector init / update.  All HBM-light; one pass over [rows, width].
 #include <algorithm>
 
@@ -365,35 +365,6 @@ hipError_t launch_qkv_post(hipStream_t st, int dtype, const BlockDev& b, const K
     else { ESP_SPLITS(splits, ESP_QKV_POST(bf16_t, 128, S, false)); }
   }
 #undef ESP_QKV_POST
-  return hipGetLastError();
-}
-
-// ---- SwiGLU over the fused gate/up GEMM output ---------------------------------------------------
-// one thread per 4 consecutive features (d_ff multiple of 4)
-template <typename T>
-__global__ __launch_bounds__(256) void k_swiglu(const float* __restrict__ part, int splits, size_t split_stride,
-                                                int dff, T* __restrict__ act, size_t total4) {
-  size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total4) return;
-  const int per_row = dff >> 2;
-  size_t row = i / per_row;
-  int j = (int)(i % per_row) * 4;
-  f32x4_t g = {0.f, 0.f, 0.f, 0.f}, u = {0.f, 0.f, 0.f, 0.f};
-  for (int s = 0; s < splits; ++s) {
-    const float* p = part + (size_t)s * split_stride + row * 2 * dff;
-    g += *reinterpret_cast<const f32x4_t*>(p + j);
-    u += *reinterpret_cast<const f32x4_t*>(p + dff + j);
-  }
-  f32x4_t o;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) o[e] = g[e] / (1.0f + expf(-g[e])) * u[e];
-  Pack4<T>::store(act + row * dff + j, o);
-}
-
-hipError_t launch_swiglu(hipStream_t st, int dtype, const float* part, int splits, int M, int dff, void* act) {
-  size_t total4 = (size_t)M * (dff >> 2);
-  ESP_DISPATCH(dtype, hipLaunchKernelGGL(k_swiglu<T>, dim3((unsigned)((total4 + 255) / 256)), dim3(256), 0, st,
-                                         part, splits, (size_t)M * 2 * dff, dff, (T*)act, total4));
   return hipGetLastError();
 }
 

@@ -232,17 +232,22 @@ __device__ __forceinline__ f32x4_t f32_piece(const float* __restrict__ row, int 
   return v;
 }
 
-template <bool VEC>
+// SWIGLU: the 32 weight rows of a tile are 16 gate features and the 16 up features of the same number (N rows behind), and
+// silu(gate) * up goes out, [M][N]: a launch less and twice the workgroups of a tile of each, bit for bit what the product and a
+// kernel for the activation after it gave.  60 x (2 x 688) x 256: 6.0 + 2.8 -> 6.2 us; 8.9 with a gate tile and an up tile in a
+// workgroup, of eight waves or of sixteen.
+template <bool VEC, bool SWIGLU>
 __global__ __launch_bounds__(64 * F32_WAVES) void k_gemm_f32(const float* __restrict__ A, const int32_t* __restrict__ a_rows,
                                                              const float* __restrict__ W, float* __restrict__ out, int M,
                                                              int N, int K) {
   __shared__ float part[F32_WAVES][16][64];
-  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 32;
+  constexpr int COLS = SWIGLU ? 16 : 32;
+  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * COLS;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lr = lane & 31, lg = lane >> 5;
   int m = min(m0 + lr, M - 1);                      // clamped rows and columns are computed, never stored
   if (a_rows) m = max(a_rows[m], 0);
   const float* ar = A + (size_t)m * K;
-  const float* wr = W + (size_t)min(n0 + lr, N - 1) * K;
+  const float* wr = W + (size_t)(min(n0 + lr % COLS, N - 1) + lr / COLS * N) * K;
   const int chunks = (K + 7) >> 3;
   const int mine = (chunks - wave + F32_WAVES - 1) / F32_WAVES;   // chunks wave, wave + 8, ...
   f32x16_t acc;
@@ -271,12 +276,18 @@ __global__ __launch_bounds__(64 * F32_WAVES) void k_gemm_f32(const float* __rest
 #pragma unroll
   for (int v = 0; v < 16; ++v) part[wave][v][lane] = acc[v];
   __syncthreads();
-  for (int e = tid; e < 1024; e += 64 * F32_WAVES) {
-    const int v = e >> 6, l = e & 63;
+  for (int e = tid; e < 32 * COLS; e += 64 * F32_WAVES) {
+    const int v = e / (2 * COLS), c = e % COLS, h = e / COLS % 2, l = 32 * h + c;
     float sum = part[0][v][l];
 #pragma unroll
     for (int q = 1; q < F32_WAVES; ++q) sum += part[q][v][l];
-    const int mo = m0 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3), no = n0 + (l & 31);
+    if (SWIGLU) {
+      float up = part[0][v][l + COLS];
+#pragma unroll
+      for (int q = 1; q < F32_WAVES; ++q) up += part[q][v][l + COLS];
+      sum = sum / (1.0f + expf(-sum)) * up;
+    }
+    const int mo = m0 + 8 * (v >> 2) + 4 * h + (v & 3), no = n0 + c;
     if (mo < M && no < N) out[(size_t)mo * N + no] = sum;
   }
 }
@@ -564,6 +575,13 @@ hipError_t launch_gate_up(hipStream_t st, const void* A, const void* W, void* ac
   return hipSuccess;
 }
 
+hipError_t launch_gemm_swiglu_f32(hipStream_t st, const float* A, const float* W, float* act, int M, int ff, int K) {
+  const bool vec = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0;
+  hipLaunchKernelGGL((vec ? k_gemm_f32<true, true> : k_gemm_f32<false, true>), dim3((ff + 15) / 16, (M + 31) / 32), dim3(64 * F32_WAVES), 0, st,
+                     A, (const int32_t*)nullptr, W, act, M, ff, K);
+  return hipGetLastError();
+}
+
 hipError_t launch_pack_weight(hipStream_t st, const void* src, void* dst, int N, int K) {
   size_t pieces = (size_t)N * K / 8;
   hipLaunchKernelGGL(k_pack_weight, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st, (const bf16_t*)src,
@@ -576,7 +594,7 @@ hipError_t launch_gemm(hipStream_t st, int dtype, const void* A, const int32_t* 
   if (M <= 0) return hipSuccess;
   if (dtype == ESP_F32) {
     const bool vec = K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0;
-    hipLaunchKernelGGL(vec ? k_gemm_f32<true> : k_gemm_f32<false>, dim3(p.n_tiles, p.m_tiles), dim3(64 * F32_WAVES), 0, st,
+    hipLaunchKernelGGL((vec ? k_gemm_f32<true, false> : k_gemm_f32<false, false>), dim3(p.n_tiles, p.m_tiles), dim3(64 * F32_WAVES), 0, st,
                        (const float*)A, a_rows, (const float*)W, out, M, N, K);
     return hipGetLastError();
   }

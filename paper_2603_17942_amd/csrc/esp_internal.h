@@ -143,6 +143,8 @@ hipError_t launch_gemm(hipStream_t st, int dtype, const void* A, const int32_t* 
                        float* out, int M, int N, int K, const GemmPlan& p, bool w_packed, int a_ld = 0,
                        const int32_t* m_live = nullptr);
 // a_ld == 0: A is row-major [rows][K]; a_ld > 0 (bf16, unpacked weights): A is chunk-major [K/64][a_ld][64]
+// fp32: act[M][ff] = silu(A Wg^T) * (A Wu^T), W = gate rows then up rows
+hipError_t launch_gemm_swiglu_f32(hipStream_t st, const float* A, const float* W, float* act, int M, int ff, int K);
 hipError_t launch_pack_weight(hipStream_t st, const void* src, void* dst, int N, int K);
 // one-time kernel attributes of the GEMM kernels (dynamic LDS limits); call before the first launch
 hipError_t gemm_prepare();
@@ -261,7 +263,6 @@ hipError_t launch_residual_norm(hipStream_t st, int dtype, float* h, const float
 hipError_t launch_qkv_post(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, int layer,
                            const float* part, int splits, int M, int hq, int hkv, int hd, int qk_norm,
                            const void* qg, const void* kg, float eps, const float* rope_tab, void* q_out);
-hipError_t launch_swiglu(hipStream_t st, int dtype, const float* part, int splits, int M, int dff, void* act);
 // draw_pos (nullable): sample instead of arg-max -- entry m draws position draw_pos[m] with `seed`
 hipError_t launch_argmax(hipStream_t st, const float* logits, size_t row_stride, const int32_t* row_map,
                          int n_rows_out, int vocab, int32_t* out, const int32_t* out_index,

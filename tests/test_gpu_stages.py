@@ -261,6 +261,26 @@ def test_gemm_f32(B, M, N, K):
 
 
 # ---------------------------------------------------------------------------------------- Top-K
+@pytest.mark.parametrize("offset", (0, 1))
+@pytest.mark.parametrize("M,ff,K", [(1, 1, 1), (31, 15, 7), (32, 16, 64), (33, 17, 77), (60, 688, 256), (13, 130, 1028)])
+def test_gemm_swiglu_f32(B, M, ff, K, offset):
+    """Gate and up features side by side in a tile: the logits are those of the plain product bit for bit, so only the
+    activation's own roundings are left (exp 2, sum 1/2, quotient 2.5, product 1/2 units of 2^-23).  Operands on and off a 16-byte
+    boundary, remainders of rows, features and K, nothing written behind the last feature."""
+    print(f"gemm swiglu f32 M={M} ff={ff} K={K} offset={offset}", flush=True)
+    a, w = (torch.zeros(n * K + offset, device="cuda")[offset:].view(n, K) for n in (M, 2 * ff))
+    a.copy_(synth.normal_like((M, K), 1.0, 13, 0, "cuda", torch.float32))
+    w.copy_(synth.normal_like((2 * ff, K), K ** -0.5, 13, 1, "cuda", torch.float32))
+    act = torch.full((M * ff + 1,), -7.0, device="cuda")
+    c = ctypes
+    run = internal("launch_gemm_swiglu_f32", c.c_void_p, c.c_void_p, c.c_void_p, c.c_void_p, c.c_int, c.c_int, c.c_int)
+    assert run(torch.cuda.current_stream().cuda_stream, a.data_ptr(), w.data_ptr(), act.data_ptr(), M, ff, K) == 0
+    gate, up = B.gemm(a, w).double().split(ff, dim=1)
+    want = gate / (1 + torch.exp(-gate)) * up
+    got = act[:-1].view(M, ff).double()
+    assert bool(((got - want).abs() <= 5.5 * 2.0 ** -23 * want.abs() + 1e-37).all()) and float(act[-1]) == -7
+
+
 def check_topk(ids, ps, logits, kp, tol):
     """Oracle comparison with the near-tie rule: position j must match where the oracle's gap
     between ranks j and j+1 exceeds the band; probabilities within tolerance everywhere."""
