@@ -22,12 +22,14 @@ namespace {
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float NEG_BIG = -1.0e30f;
 
+// UNIFORM: seq is the same for the wave, in a scalar
+template <bool UNIFORM = false>
 __device__ __forceinline__ bool seq_ok(const KvDev& kv, int seq, int n_rows, int rows_per_seq) {
+  const int base = kv.base[seq], cap = kv.seq_cap[seq];
   int L = kv.len[seq];
-  int base = kv.base[seq];
-  int cap = kv.seq_cap[seq];
-  return L >= 0 && L <= kv.len_bound && n_rows >= 0 && n_rows <= rows_per_seq && L + n_rows <= cap &&
-         base >= 0 && (base & 63) == 0 && (int64_t)base + cap <= kv.capacity;
+  if (UNIFORM) L = with_args(L, base, cap, n_rows, kv.len_bound);   // the loads together, and no short circuit
+  return (L >= 0) & (L <= kv.len_bound) & (n_rows >= 0) & (n_rows <= rows_per_seq) & (L + n_rows <= cap) & (base >= 0) &
+         ((base & 63) == 0) & ((int64_t)base + cap <= kv.capacity);
 }
 
 // --------------------------------------------------------------------------------------------------
@@ -76,7 +78,7 @@ __global__ __launch_bounds__(64 * (MERGE ? MERGE : 1)) void k_attn_generic(Block
   float* ps = ps_w[wave];
   const int seq = row / b.rows_per_seq, r = row % b.rows_per_seq;
   const int nr = b.n_rows[seq];
-  if (!seq_ok(kv, seq, nr, b.rows_per_seq) || r >= nr) {
+  if (!seq_ok<true>(kv, seq, nr, b.rows_per_seq) || r >= nr) {
     if (MERGE && !PACKED)
       for (int d = threadIdx.x; d < HD; d += blockDim.x) out[((size_t)row * hq + h) * HD + d] = from_f32<T>(0.f);
     return;
@@ -437,6 +439,9 @@ __global__ __launch_bounds__(64 * RING_MAX_WAVES) void k_attn_ring(BlockDev b, K
                                                                   const int32_t* __restrict__ cuts) {
   constexpr int HD = 128;
   extern __shared__ __align__(16) unsigned char lds[];
+  hkv = with_args(hkv, b.n_rows, b.rows_per_seq, b.batch, b.anc, kv.len, kv.base, kv.seq_cap, kv.capacity);
+  hkv = with_args(hkv, kv.len_bound, kv.k, kv.v, layer, hq, q, part_o, part_ml);
+  hkv = with_args(hkv, nsplit, tps, q_tiles, ct_wg, n_full_wg, b.anc_words, cuts, part_ml);
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lg = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = hq / hkv;
@@ -457,7 +462,7 @@ __global__ __launch_bounds__(64 * RING_MAX_WAVES) void k_attn_ring(BlockDev b, K
 
   auto piece = [&](int seq) {
   const int nr = b.n_rows[seq];
-  if (!seq_ok(kv, seq, nr, b.rows_per_seq)) return;
+  if (!seq_ok<!CUTS>(kv, seq, nr, b.rows_per_seq)) return;
   const int ncols = nr * G;
   const int ct_own = CUTS ? even_ct(ncols, q_tiles) : ct_wg;   // column tiles of a workgroup
   if (qt * ct_own * 32 >= ncols) return;                // no live query column in this workgroup
@@ -684,12 +689,14 @@ __global__ __launch_bounds__(256) void k_attn_merge_ring(BlockDev b, KvDev kv, i
   __shared__ float w_s[MAXS][32];
   __shared__ float red[8][32];
   __shared__ float red_l[8][32];
+  n_ct = with_args(n_ct, b.n_rows, b.rows_per_seq, kv.len, kv.base, kv.seq_cap, kv.capacity, kv.len_bound, b.batch);
+  n_ct = with_args(n_ct, hq, hkv, part_o, part_ml, nsplit, out, cuts, hq);
   const int G = hq / hkv;
   const int fq = blockIdx.x & 3;
   const int tile = blockIdx.x >> 2;                 // (seq * hkv + kvh) * n_ct + ct
   const int ct = tile % n_ct, kvh = (tile / n_ct) % hkv, seq = tile / (n_ct * hkv);
   const int nr = b.n_rows[seq];
-  const bool ok = seq_ok(kv, seq, nr, b.rows_per_seq);
+  const bool ok = seq_ok<true>(kv, seq, nr, b.rows_per_seq);
   const int col = threadIdx.x & 31, grp = threadIdx.x >> 5;
   const int c = ct * 32 + col;                      // column within the kv group
   const bool live = ok && c < nr * G;

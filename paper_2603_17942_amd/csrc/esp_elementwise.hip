@@ -15,12 +15,13 @@
     }                                     \
   } while (0)
 
+// no short circuit: the loads are issued together
+__device__ __forceinline__ bool seq_valid(const KvDev& kv, int L, int base, int cap, int n_rows) {
+  return (L >= 0) & (L <= kv.len_bound) & (n_rows >= 0) & (L + n_rows <= cap) & (base >= 0) & ((base & 63) == 0) &
+         ((int64_t)(uint32_t)base + (uint32_t)cap <= kv.capacity);   // a negative one has failed already
+}
 __device__ __forceinline__ bool seq_ok(const KvDev& kv, int seq, int n_rows) {
-  int L = kv.len[seq];
-  int base = kv.base[seq];
-  int cap = kv.seq_cap[seq];
-  return L >= 0 && L <= kv.len_bound && n_rows >= 0 && L + n_rows <= cap && base >= 0 && (base & 63) == 0 &&
-         (int64_t)base + cap <= kv.capacity;
+  return seq_valid(kv, kv.len[seq], kv.base[seq], kv.seq_cap[seq], n_rows);
 }
 
 __device__ __forceinline__ float block_sum_256(float v, float* red) {
@@ -148,19 +149,22 @@ hipError_t launch_embed(hipStream_t st, int dtype, const BlockDev& b, const KvDe
 // 13 us at 320 (42 MB); with a running split count and the row read back: 12 to 13 us at 320.
 template <typename T> struct Pack4;
 template <> struct Pack4<float> {
+  using Raw = f32x4_t;
+  static __device__ __forceinline__ f32x4_t value(Raw v) { return v; }
   static __device__ __forceinline__ void store(float* p, f32x4_t v) { *reinterpret_cast<f32x4_t*>(p) = v; }
   static __device__ __forceinline__ f32x4_t load(const float* p) { return *reinterpret_cast<const f32x4_t*>(p); }
 };
 template <> struct Pack4<bf16_t> {
+  using Raw = bf16x4_t;
+  static __device__ __forceinline__ f32x4_t value(Raw i) {
+    f32x4_t o = {(float)i[0], (float)i[1], (float)i[2], (float)i[3]};
+    return o;
+  }
   static __device__ __forceinline__ void store(bf16_t* p, f32x4_t v) {
     bf16x4_t o = {(bf16_t)v[0], (bf16_t)v[1], (bf16_t)v[2], (bf16_t)v[3]};
     *reinterpret_cast<bf16x4_t*>(p) = o;
   }
-  static __device__ __forceinline__ f32x4_t load(const bf16_t* p) {
-    bf16x4_t i = *reinterpret_cast<const bf16x4_t*>(p);
-    f32x4_t o = {(float)i[0], (float)i[1], (float)i[2], (float)i[3]};
-    return o;
-  }
+  static __device__ __forceinline__ f32x4_t load(const bf16_t* p) { return value(*reinterpret_cast<const bf16x4_t*>(p)); }
 };
 
 // v + the S partials at p, p + stride, ..., added in split order
@@ -180,6 +184,7 @@ __global__ __launch_bounds__(1024) void k_residual_norm(float* __restrict__ h, c
                                                         size_t split_stride, int d, const T* __restrict__ gain,
                                                         float eps, T* __restrict__ xn, const int32_t* __restrict__ live) {
   __shared__ float red[16];
+  d = with_args(d, h, part, split_stride, gain, eps, xn, live, __builtin_amdgcn_workgroup_size_x());
   const size_t row_out = blockIdx.x;
   const int d4 = d >> 2, tid = threadIdx.x, step = blockDim.x;
   size_t row = row_out;
@@ -194,8 +199,9 @@ __global__ __launch_bounds__(1024) void k_residual_norm(float* __restrict__ h, c
     row = (size_t)at;
   }
   float* hr = h + row * d;
-  f32x4_t keep = {0.f, 0.f, 0.f, 0.f}, g0 = keep;    // this thread's first column and its gain
-  if (tid < d4) g0 = Pack4<T>::load(gain + 4 * tid);
+  f32x4_t keep = {0.f, 0.f, 0.f, 0.f};               // this thread's first column
+  typename Pack4<T>::Raw g0 = {};                    // and its gain, as it was loaded: converting it here would wait for it
+  if (tid < d4) g0 = *reinterpret_cast<const typename Pack4<T>::Raw*>(gain + 4 * tid);
   float ss = 0.f;
   for (int i = tid; i < d4; i += step) {
     const f32x4_t v = add_splits<S>(*reinterpret_cast<const f32x4_t*>(hr + 4 * i), part + row * d + 4 * i, split_stride);
@@ -211,7 +217,7 @@ __global__ __launch_bounds__(1024) void k_residual_norm(float* __restrict__ h, c
   const float inv = 1.0f / sqrtf(tot / (float)d + eps);
   for (int i = tid; i < d4; i += step) {
     const f32x4_t v = i == tid ? keep : *reinterpret_cast<const f32x4_t*>(hr + 4 * i);   // written by this thread above
-    const f32x4_t g = i == tid ? g0 : Pack4<T>::load(gain + 4 * i);
+    const f32x4_t g = i == tid ? Pack4<T>::value(g0) : Pack4<T>::load(gain + 4 * i);
     Pack4<T>::store(xn + row_out * d + 4 * i, v * inv * g);
   }
 }
@@ -266,34 +272,36 @@ __global__ __launch_bounds__(256) void k_qkv_post(BlockDev b, KvDev kv, int laye
                                                   const T* __restrict__ qg, const T* __restrict__ kg, float eps,
                                                   const float* __restrict__ rope_tab, T* __restrict__ q_out) {
   constexpr int LPH = HD / 8, HALF = HD / 2;
+  hq = with_args(hq, part, split_stride, rope_tab, q_out, kv.len, kv.base, kv.seq_cap, kv.capacity);
+  hq = with_args(hq, b.n_rows, b.rows_per_seq, kv.len_bound, kv.k, kv.v, layer, hkv, qk_norm);
   const int row = blockIdx.y;                       // of the activations
   if (PACKED && row >= *b.n_live()) return;
   const int hidx = (blockIdx.x * 256 + threadIdx.x) / LPH;
   const int f0 = (threadIdx.x % LPH) * 4;
   const int n_heads = hq + 2 * hkv;
   if (hidx >= n_heads) return;
-  const size_t c0 = ((size_t)row * n_heads + hidx) * HD + f0;
-  f32x4_t x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
-  // the rotary table's entries (a row of it for every row of the activations) with the partials, not after the sequence's lengths:
-  // 68 rows of 32 + 16 heads 5.1 -> 4.8 us
-  const float* rt = rope_tab + ((size_t)row * HALF + f0) * 2;      // cos, sin of four pairs
-  const f32x4_t t0 = *reinterpret_cast<const f32x4_t*>(rt), t1 = *reinterpret_cast<const f32x4_t*>(rt + 4);
-  x0 = add_splits<S>(x0, part + c0, split_stride);
-  x1 = add_splits<S>(x1, part + c0 + HALF, split_stride);
+  // The sequence's scalars, the partials and the rotary table's entries (a row of it for every row of the activations), all asked for
+  // before the first of them is waited for: 68 rows of 32 + 16 heads 5.1 -> 4.8 us.
   const int brow = PACKED ? b.live_rows()[row] : row;
-  const int seq = brow / b.rows_per_seq, r = brow % b.rows_per_seq;
-  const int nr = b.n_rows[seq];
-  const bool live = seq_ok(kv, seq, nr) && nr <= b.rows_per_seq && r < nr;
-  const int64_t slot = (int64_t)kv.base[seq] + kv.len[seq] + r;
-  if (!live) {   // a row that is not there: its query is zero, whatever its partials hold
-    if (hidx < hq) {
-      T* qo = q_out + ((size_t)row * hq + hidx) * HD + f0;
-      const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
-      Pack4<T>::store(qo, zero);
-      Pack4<T>::store(qo + HALF, zero);
-    }
-    return;
+  const int seq = (int)((unsigned)brow / (unsigned)b.rows_per_seq), r = brow - seq * b.rows_per_seq;
+  const int nr = b.n_rows[seq], base = kv.base[seq], len = kv.len[seq], cap = kv.seq_cap[seq];
+  __builtin_amdgcn_sched_barrier(0);
+  const size_t c0 = ((size_t)row * n_heads + hidx) * HD + f0;
+  const float* rt = rope_tab + ((size_t)row * HALF + f0) * 2;      // cos, sin of four pairs
+  f32x4_t t0 = *reinterpret_cast<const f32x4_t*>(rt), t1 = *reinterpret_cast<const f32x4_t*>(rt + 4);
+  f32x4_t p0[S], p1[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    p0[s] = *reinterpret_cast<const f32x4_t*>(part + c0 + (size_t)s * split_stride);
+    p1[s] = *reinterpret_cast<const f32x4_t*>(part + c0 + (size_t)s * split_stride + HALF);
   }
+  __builtin_amdgcn_sched_barrier(0);
+  const bool live = seq_valid(kv, len, base, cap, nr) && nr <= b.rows_per_seq && r < nr;
+  const int64_t slot = (int64_t)(uint32_t)base + (uint32_t)len + r;   // of a live row: none is negative
+  f32x4_t x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;            // added in split order
+#pragma unroll
+  for (int s = 0; s < S; ++s) { x0 += p0[s]; x1 += p1[s]; }
+  asm volatile("" : "+v"(t0), "+v"(t1));                 // here, not in the branch that uses them
   if (hidx < hq + hkv) {
     if (qk_norm) {
       // The squares are added as a balanced tree over the rotary pairs, the farthest pairs first (distance
@@ -317,11 +325,12 @@ __global__ __launch_bounds__(256) void k_qkv_post(BlockDev b, KvDev kv, int laye
     }
     const f32x4_t c = {t0[0], t0[2], t1[0], t1[2]}, s = {t0[1], t0[3], t1[1], t1[3]};
     const f32x4_t y0 = x0 * c - x1 * s, y1 = x1 * c + x0 * s;
-    if (hidx < hq) {
+    if (hidx < hq) {   // a row that is not there: its query is zero, whatever its partials hold
       T* qo = q_out + ((size_t)row * hq + hidx) * HD + f0;
-      Pack4<T>::store(qo, y0);
-      Pack4<T>::store(qo + HALF, y1);
-    } else {       // four features are consecutive in a K fragment
+      const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+      Pack4<T>::store(qo, live ? y0 : zero);
+      Pack4<T>::store(qo + HALF, live ? y1 : zero);
+    } else if (live) {       // four features are consecutive in a K fragment
       T* kp = (T*)kv.k + kv_plane(layer, hidx - hq, hkv, kv.capacity, HD);
       if constexpr (HD == 128 && sizeof(T) == 2) {   // the attention kernel of this form reads 16-byte pieces anyway
         Pack4<T>::store(kp + k_off(slot, f0, HD), y0);
@@ -334,7 +343,7 @@ __global__ __launch_bounds__(256) void k_qkv_post(BlockDev b, KvDev kv, int laye
         }
       }
     }
-  } else {
+  } else if (live) {
     T* vp = (T*)kv.v + kv_plane(layer, hidx - hq - hkv, hkv, kv.capacity, HD);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {

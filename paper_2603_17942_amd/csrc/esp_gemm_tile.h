@@ -146,6 +146,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int32_t* __restrict__ m_live, float* __restrict__ pairs) {
   extern __shared__ __align__(16) unsigned char lds[];
   constexpr int RT = T::RT, CT = T::CT, DA = T::DA, DW = T::DW;
+  n_tiles = with_args(n_tiles, A, a_rows, W, M, N, K, splits, m_tiles);
   const int M_ld = M;
   if (m_live) {                                          // only the first *m_live rows are there
     M = min(*m_live, M);
@@ -158,12 +159,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   if ((int)(blockIdx.x >> 3) >= per_xcd) return;
   const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (logical >= total) return;
-  const int mi = logical % m_tiles, ni = (logical / m_tiles) % n_tiles, z = logical / (m_tiles * n_tiles);
+  const unsigned ti = (unsigned)logical / (unsigned)m_tiles;
+  const int mi = logical - (int)ti * m_tiles, z = (int)(ti / (unsigned)n_tiles), ni = (int)ti - z * n_tiles;
   const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
   const int mt0 = mi * T::ROWS;
   const int blk0 = ni * CT, nblk = N >> 5;
-  const int chunks = K / KC, cps = (chunks + splits - 1) / splits, c_begin = z * cps;
+  const int chunks = K / KC, cps = (int)((unsigned)(chunks + splits - 1) / (unsigned)splits), c_begin = z * cps;
   const int nc = min(chunks, c_begin + cps) - c_begin;
 
   f32x4_t acc[RT][CT];
