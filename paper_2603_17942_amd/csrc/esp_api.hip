@@ -354,10 +354,10 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
     ESP_HIP(launch_live_rows(s, bd, kd, nodes_bound(blk), gate_up));
     m_live = bd.n_live();
   }
+  const NodeLists lists{node_argmax ? nodes_bound(blk) : 0, c->idx_a, c->idx_b, c->idx_d, node_argmax && c->sample_on ? c->idx_c : nullptr};
   ESP_HIP(launch_embed(s, dt, bd, kd, c->embed, mask_embed, c->h, d, m.vocab, c->rope_tab, hd, m.rope_theta,
-                       c->status, c->mask_per_seq ? (size_t)blk->k_masks * d : 0, end));
-  if (shares) ESP_HIP(launch_attn_cuts(s, bd, kd, hq, hkv, ap, shares, c->cuts));
-  ESP_HIP(launch_residual_norm(s, dt, c->h, nullptr, 0, M, d, c->norm_attn[0], m.rms_eps, c->xn, m_live)); }
+                       c->status, c->mask_per_seq ? (size_t)blk->k_masks * d : 0, end, lists, c->norm_attn[0], m.rms_eps, c->xn));
+  if (shares) ESP_HIP(launch_attn_cuts(s, bd, kd, hq, hkv, ap, shares, c->cuts)); }
   for (int l = 0; l < m.n_layers; ++l) {
     { ESP_PROF_KERNEL(ESP_SITE_GEMM_LAYER, dt == ESP_BF16);
       ESP_HIP(launch_gemm(s, dt, c->xn, nullptr, c->wqkv[l], c->gemm_out, M, nqkv, d, p_qkv, pk, 0, m_live)); }
@@ -395,7 +395,6 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
     if (node_argmax) {
       const int nb = nodes_bound(blk);
       ESP_PROF(ESP_SITE_GLUE);
-      ESP_HIP(launch_node_rows(s, bd, nb, c->idx_a, c->idx_b, kd.len, c->idx_d));
       ESP_HIP(launch_argmax(s, logits_dbg, (size_t)m.vocab, c->idx_a, blk->batch * nb, m.vocab, node_argmax,
                             c->idx_b, c->sample_on ? c->idx_d : nullptr, c->sample_seed));
     }
@@ -405,9 +404,6 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
     if ((size_t)Mn > c->logits_rows) return ESP_ECAPACITY;
     const GemmPlan p_lm = whole_row_plan(dt, Mn, m.vocab, d);
     const int32_t* draw_list = c->sample_on ? c->idx_d : nullptr;   // draw positions per node-list entry
-    { ESP_PROF(ESP_SITE_GLUE);
-      ESP_HIP(launch_node_rows(s, bd, nb, c->idx_a, c->idx_b, kd.len, c->idx_d));
-      if (c->sample_on) ESP_HIP(launch_row_positions(s, bd, kd.len, c->idx_c)); }
     if (blk->k_masks > 0 && gemm_argmax_supported(dt, M, m.vocab, d, true) && (size_t)M <= c->logits_rows &&
         gemm_argmax_scratch_floats(M, m.vocab) <= c->gemm_out_floats) {
       // few rows (<= 128): one pass over the LM head for all block rows.  The tree rows get their

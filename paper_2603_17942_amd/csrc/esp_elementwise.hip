@@ -24,6 +24,16 @@ __device__ __forceinline__ bool seq_ok(const KvDev& kv, int seq, int n_rows) {
   return seq_valid(kv, kv.len[seq], kv.base[seq], kv.seq_cap[seq], n_rows);
 }
 
+// 1 / rms of a row of width d, from the threads' sums of squares
+__device__ __forceinline__ float rms_scale(float ss, int d, float eps, float* red) {
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  float tot = 0.f;
+  for (int w = 0; w < (int)blockDim.x >> 6; ++w) tot += red[w];
+  return 1.0f / sqrtf(tot / (float)d + eps);
+}
+
 __device__ __forceinline__ float block_sum_256(float v, float* red) {
   v = wave_sum(v);
   int w = threadIdx.x >> 6;
@@ -78,75 +88,6 @@ hipError_t launch_live_rows(hipStream_t st, const BlockDev& b, const KvDev& kv, 
   return hipGetLastError();
 }
 
-// PACKED: the row behind the live ones in the projections' inputs is set to zero; no kernel of the layers writes it, and the row
-// tiles load it for every row that is not there.  (A copy of the last live row keeps the matrix cores as busy as a real one, zeros
-// do not, and the card is at its power limit in the large tiles: eight layers of the 8B shape on 2048 keys, 172 rows of 318 there
-// 1930 -> 1672 us, 273 of 448 2142 -> 1902.  A zero row for each instead cost the loads of it: 64 of 224 rows 1392 -> 1448.)
-template <typename T, bool PACKED>
-__global__ __launch_bounds__(256) void k_embed(BlockDev b, KvDev kv, const T* __restrict__ embed,
-                                               const T* __restrict__ mask_embed, float* __restrict__ h, int d,
-                                               int vocab, float* __restrict__ rope_tab, int hd, float theta,
-                                               int32_t* status, size_t mask_seq_stride, PackedEnd end) {
-  const int row = blockIdx.x;
-  if (PACKED) {
-    if (row == b.n_live()[0]) {
-      const u32x4_t zero = {0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        u32x4_t* dst = reinterpret_cast<u32x4_t*>(end.rows[t] + (size_t)row * end.width[t]);
-        for (int i = threadIdx.x; i < end.width[t] / 8; i += blockDim.x) dst[i] = zero;
-      }
-    }
-  }
-  const int seq = row / b.rows_per_seq, r = row % b.rows_per_seq;
-  const int nr = b.n_rows[seq];
-  const bool ok = seq_ok(kv, seq, nr) && nr <= b.rows_per_seq;
-  if (r == 0 && threadIdx.x == 0 && !ok) atomicOr(status, ESP_DEV_LEN_OVER_BOUND);
-  const bool live = ok && r < nr;
-  if (PACKED && !live) return;
-  const size_t at = PACKED ? (size_t)b.packed_row()[row] : (size_t)row;
-  const T* src = nullptr;
-  if (live) {
-    int j = b.mask_j[row];
-    if (j > 0) {
-      if (j <= b.k_masks) src = mask_embed + seq * mask_seq_stride + (size_t)(j - 1) * d;
-    } else {
-      int t = b.tok[row];
-      if (t < 0 || t >= vocab) {
-        if (threadIdx.x == 0) atomicOr(status, ESP_DEV_BAD_TOKEN);
-      } else {
-        src = embed + (size_t)t * d;
-      }
-    }
-  }
-  float* hr = h + at * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) hr[i] = src ? to_f32(src[i]) : 0.f;
-  const int half = hd >> 1;
-  for (int i = threadIdx.x; i < half; i += blockDim.x) {
-    // angle in double: positions reach 1e4..1e5 where an fp32 product loses the fraction
-    double pos = live ? (double)(kv.len[seq] + b.depth[row]) : 0.0;
-    double ang = pos * pow((double)theta, -2.0 * (double)i / (double)hd);
-    rope_tab[(at * half + i) * 2 + 0] = (float)cos(ang);
-    rope_tab[(at * half + i) * 2 + 1] = (float)sin(ang);
-  }
-}
-
-hipError_t launch_embed(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, const void* embed,
-                        const void* mask_embed, float* h, int d, int vocab, float* rope_tab, int hd,
-                        float theta, int32_t* status, size_t mask_seq_stride, const PackedEnd& end) {
-  int M = b.batch * b.rows_per_seq;
-  ESP_DISPATCH(dtype, hipLaunchKernelGGL((b.packed ? k_embed<T, true> : k_embed<T, false>), dim3(M), dim3(256), 0, st, b, kv, (const T*)embed,
-                                         (const T*)mask_embed, h, d, vocab, rope_tab, hd, theta, status,
-                                         mask_seq_stride, end));
-  return hipGetLastError();
-}
-
-// ---- residual add of split-K partials + RMSNorm ------------------------------------------------
-// One workgroup per row; a thread owns float4 columns (one each up to d = 4096).  The kernel is bound by the
-// fp32 partials it reads (S * d * 4 bytes per row), so the split count is a template parameter: all S loads of
-// a column are in flight before the first is waited for, and the row stays in registers between the two
-// passes.  d must be a multiple of 4.  d = 4096: 4.4 us at one row, 5.7 us at 68 rows (8 partials, 9 MB), 11 to
-// 13 us at 320 (42 MB); with a running split count and the row read back: 12 to 13 us at 320.
 template <typename T> struct Pack4;
 template <> struct Pack4<float> {
   using Raw = f32x4_t;
@@ -167,10 +108,126 @@ template <> struct Pack4<bf16_t> {
   static __device__ __forceinline__ f32x4_t load(const bf16_t* p) { return value(*reinterpret_cast<const bf16x4_t*>(p)); }
 };
 
+// Gather lists for the LM head over node rows: logical row m = seq*max_nodes + i; in a batch with packed rows the
+// tree rows that are there come first, one after the other, and the rest of the lists is marked unused.
+__device__ __forceinline__ void node_row(const BlockDev& b, const KvDev& kv, const NodeLists& n, int m) {
+  if (m >= b.batch * n.max_nodes) return;
+  const int seq = m / n.max_nodes, i = m % n.max_nodes;
+  const int nn = b.n_nodes[seq];
+  const bool live = i < nn && nn <= b.n_rows[seq] && b.n_rows[seq] <= b.rows_per_seq;
+  const int row = seq * b.rows_per_seq + (live ? i : 0);
+  if (b.packed) {
+    if (m >= b.n_live()[1]) { n.a_rows[m] = 0; n.out_rows[m] = -1; n.positions[m] = 0; }
+    if (!live) return;
+    m = b.seq_node0()[seq] + i;
+  }
+  n.a_rows[m] = row;
+  n.out_rows[m] = live ? row : -1;
+  n.positions[m] = kv.len[seq] + b.depth[row] + 1;
+}
+
+// One workgroup per block row: its embedding, its rotary table and the first layer's norm of it (threads and order of the sum as in
+// k_residual_norm); the workgroups behind the rows write the LM head's gather lists.  A launch each for the norm, the lists and the
+// positions of a draw cost 4.6 us a step.  The table's double-precision functions take the last waves about as long as the others wait for the embedding.
+// PACKED: the row behind the live ones in the projections' inputs is set to zero; no kernel of the layers writes it, and the row
+// tiles load it for every row that is not there.  (A copy of the last live row keeps the matrix cores as busy as a real one, zeros
+// do not, and the card is at its power limit in the large tiles: eight layers of the 8B shape on 2048 keys, 172 rows of 318 there
+// 1930 -> 1672 us, 273 of 448 2142 -> 1902.  A zero row for each instead cost the loads of it: 64 of 224 rows 1392 -> 1448.)
+template <typename T, bool PACKED>
+__global__ __launch_bounds__(1024) void k_embed(BlockDev b, KvDev kv, const T* __restrict__ embed, const T* __restrict__ mask_embed,
+                                                float* __restrict__ h, int d, int vocab, float* __restrict__ rope_tab, int hd,
+                                                float theta, int32_t* status, size_t mask_seq_stride, PackedEnd end, NodeLists lists,
+                                                const T* __restrict__ gain, float eps, T* __restrict__ xn) {
+  __shared__ float red[16];
+  const int row = blockIdx.x, tid = threadIdx.x, step = blockDim.x, behind = row - b.batch * b.rows_per_seq;
+  if (behind >= 0) {
+    node_row(b, kv, lists, behind * step + tid);
+    return;
+  }
+  if (PACKED) {
+    if (row == b.n_live()[0]) {
+      const u32x4_t zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        u32x4_t* dst = reinterpret_cast<u32x4_t*>(end.rows[t] + (size_t)row * end.width[t]);
+        for (int i = tid; i < end.width[t] / 8; i += step) dst[i] = zero;
+      }
+    }
+  }
+  const int seq = row / b.rows_per_seq, r = row % b.rows_per_seq;
+  const int nr = b.n_rows[seq], len = kv.len[seq], j = b.mask_j[row], t = b.tok[row], depth = b.depth[row];
+  const bool ok = seq_valid(kv, len, kv.base[seq], kv.seq_cap[seq], nr) && nr <= b.rows_per_seq;
+  if (r == 0 && tid == 0 && !ok) atomicOr(status, ESP_DEV_LEN_OVER_BOUND);
+  const bool live = ok && r < nr;
+  if (lists.row_positions && tid == 0) lists.row_positions[row] = len + depth + 1;
+  if (PACKED && !live) return;
+  const size_t at = PACKED ? (size_t)b.packed_row()[row] : (size_t)row;
+  const T* src = nullptr;
+  if (live) {
+    if (j > 0) {
+      if (j <= b.k_masks) src = mask_embed + seq * mask_seq_stride + (size_t)(j - 1) * d;
+    } else if (t < 0 || t >= vocab) {
+      if (tid == 0) atomicOr(status, ESP_DEV_BAD_TOKEN);
+    } else {
+      src = embed + (size_t)t * d;
+    }
+  }
+  const int d4 = d >> 2;
+  auto column = [&](int i) {                             // scalar loads: the caller's rows need no more than their type's alignment
+    f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+    if (src)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = to_f32(src[4 * i + e]);
+    return v;
+  };
+  f32x4_t keep = {0.f, 0.f, 0.f, 0.f};                   // this thread's first column
+  if (tid < d4) keep = column(tid);
+  const int half = hd >> 1;
+  for (int i = step - 1 - tid; i < half; i += step) {
+    // angle in double: positions reach 1e4..1e5 where an fp32 product loses the fraction
+    double pos = live ? (double)(len + depth) : 0.0;
+    double ang = pos * pow((double)theta, -2.0 * (double)i / (double)hd);
+    rope_tab[(at * half + i) * 2 + 0] = (float)cos(ang);
+    rope_tab[(at * half + i) * 2 + 1] = (float)sin(ang);
+  }
+  float* hr = h + at * d;
+  float ss = 0.f;
+  for (int i = tid; i < d4; i += step) {
+    const f32x4_t v = i == tid ? keep : column(i);
+    *reinterpret_cast<f32x4_t*>(hr + 4 * i) = v;
+    ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+  }
+  const float inv = rms_scale(ss, d, eps, red);
+  for (int i = tid; i < d4; i += step) {
+    const f32x4_t v = i == tid ? keep : *reinterpret_cast<const f32x4_t*>(hr + 4 * i);   // written by this thread above
+    Pack4<T>::store(xn + at * d + 4 * i, v * inv * Pack4<T>::load(gain + 4 * i));
+  }
+}
+
+// threads of a workgroup for a row's norm
+static int norm_threads(int d) { return std::min(1024, ((d >> 2) + 63) & ~63); }
+
+hipError_t launch_embed(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, const void* embed,
+                        const void* mask_embed, float* h, int d, int vocab, float* rope_tab, int hd,
+                        float theta, int32_t* status, size_t mask_seq_stride, const PackedEnd& end, const NodeLists& lists,
+                        const void* gain, float eps, void* xn) {
+  const int threads = norm_threads(d), M = b.batch * b.rows_per_seq, behind = (b.batch * lists.max_nodes + threads - 1) / threads;
+  ESP_DISPATCH(dtype, hipLaunchKernelGGL((b.packed ? k_embed<T, true> : k_embed<T, false>), dim3(M + behind), dim3(threads), 0, st, b, kv,
+                                         (const T*)embed, (const T*)mask_embed, h, d, vocab, rope_tab, hd, theta, status,
+                                         mask_seq_stride, end, lists, (const T*)gain, eps, (T*)xn));
+  return hipGetLastError();
+}
+
+// ---- residual add of split-K partials + RMSNorm ------------------------------------------------
+// One workgroup per row; a thread owns float4 columns (one each up to d = 4096).  The kernel is bound by the
+// fp32 partials it reads (S * d * 4 bytes per row), so the split count is a template parameter: all S loads of
+// a column are in flight before the first is waited for, and the row stays in registers between the two
+// passes.  d must be a multiple of 4.  d = 4096: 4.4 us at one row, 5.7 us at 68 rows (8 partials, 9 MB), 11 to
+// 13 us at 320 (42 MB); with a running split count and the row read back: 12 to 13 us at 320.
 // v + the S partials at p, p + stride, ..., added in split order
 template <int S>
 __device__ __forceinline__ f32x4_t add_splits(f32x4_t v, const float* __restrict__ p, size_t stride) {
-  f32x4_t x[S > 0 ? S : 1];
+  f32x4_t x[S];
 #pragma unroll
   for (int s = 0; s < S; ++s) x[s] = *reinterpret_cast<const f32x4_t*>(p + (size_t)s * stride);
 #pragma unroll
@@ -205,16 +262,11 @@ __global__ __launch_bounds__(1024) void k_residual_norm(float* __restrict__ h, c
   float ss = 0.f;
   for (int i = tid; i < d4; i += step) {
     const f32x4_t v = add_splits<S>(*reinterpret_cast<const f32x4_t*>(hr + 4 * i), part + row * d + 4 * i, split_stride);
-    if (S > 0) *reinterpret_cast<f32x4_t*>(hr + 4 * i) = v;
+    *reinterpret_cast<f32x4_t*>(hr + 4 * i) = v;
     if (i == tid) keep = v;
     ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
   }
-  ss = wave_sum(ss);
-  if ((tid & 63) == 0) red[tid >> 6] = ss;
-  __syncthreads();
-  float tot = 0.f;
-  for (int w = 0; w < step >> 6; ++w) tot += red[w];
-  const float inv = 1.0f / sqrtf(tot / (float)d + eps);
+  const float inv = rms_scale(ss, d, eps, red);
   for (int i = tid; i < d4; i += step) {
     const f32x4_t v = i == tid ? keep : *reinterpret_cast<const f32x4_t*>(hr + 4 * i);   // written by this thread above
     const f32x4_t g = i == tid ? Pack4<T>::value(g0) : Pack4<T>::load(gain + 4 * i);
@@ -239,19 +291,14 @@ __global__ __launch_bounds__(1024) void k_residual_norm(float* __restrict__ h, c
 hipError_t launch_residual_norm(hipStream_t st, int dtype, float* h, const float* part, int splits, int M,
                                 int d, const void* gain, float eps, void* xn_out, const int32_t* n_live,
                                 const int32_t* packed_row) {
-  const dim3 grid(M), block(std::min(1024, ((d >> 2) + 63) & ~63));
+  const dim3 grid(M), block(norm_threads(d));
   const size_t stride = (size_t)M * d;
 #define ESP_NORM(T_, S_, P_, LIVE_)                                                                                      \
   hipLaunchKernelGGL((k_residual_norm<T_, S_, P_>), grid, block, 0, st, h, part, stride, d, (const T_*)gain, eps, (T_*)xn_out, \
                      (const int32_t*)(LIVE_))
   if (dtype == ESP_F32) {          // the fp32 GEMM splits K inside a workgroup; fp32 batches are not packed
-    if (splits > 1 || n_live || packed_row) return hipErrorInvalidValue;
-    if (splits == 0) ESP_NORM(float, 0, 0, nullptr);
-    else ESP_NORM(float, 1, 0, nullptr);
-  } else if (splits == 0) {
-    if (packed_row) ESP_NORM(bf16_t, 0, 2, packed_row);
-    else if (n_live) ESP_NORM(bf16_t, 0, 1, n_live);
-    else ESP_NORM(bf16_t, 0, 0, nullptr);
+    if (splits != 1 || n_live || packed_row) return hipErrorInvalidValue;
+    ESP_NORM(float, 1, 0, nullptr);
   } else if (packed_row) {
     ESP_SPLITS(splits, ESP_NORM(bf16_t, S, 2, packed_row));
   } else if (n_live) {
@@ -427,46 +474,6 @@ hipError_t launch_argmax(hipStream_t st, const float* logits, size_t row_stride,
   if (n_rows_out <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_argmax, dim3(n_rows_out), dim3(256), 0, st, logits, row_stride, row_map, vocab, out,
                      out_index, draw_pos, seed);
-  return hipGetLastError();
-}
-
-// gather lists for the LM head over node rows: logical row m = seq*max_nodes + i; in a batch with packed rows the
-// tree rows that are there come first, one after the other, and the rest of the lists is marked unused
-__global__ void k_node_rows(BlockDev b, int max_nodes, int32_t* a_rows, int32_t* out_rows,
-                            const int32_t* __restrict__ kv_len, int32_t* pos_list) {
-  int m = blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= b.batch * max_nodes) return;
-  int seq = m / max_nodes, i = m % max_nodes;
-  int nn = b.n_nodes[seq];
-  bool live = i < nn && nn <= b.n_rows[seq] && b.n_rows[seq] <= b.rows_per_seq;
-  const int row = seq * b.rows_per_seq + (live ? i : 0);
-  if (b.packed) {
-    if (m >= b.n_live()[1]) { a_rows[m] = 0; out_rows[m] = -1; if (pos_list) pos_list[m] = 0; }
-    if (!live) return;
-    m = b.seq_node0()[seq] + i;
-  }
-  a_rows[m] = row;
-  out_rows[m] = live ? row : -1;
-  if (pos_list) pos_list[m] = kv_len[seq] + b.depth[row] + 1;
-}
-
-hipError_t launch_node_rows(hipStream_t st, const BlockDev& b, int max_nodes, int32_t* a_rows,
-                            int32_t* out_rows, const int32_t* kv_len, int32_t* pos_list) {
-  int n = b.batch * max_nodes;
-  hipLaunchKernelGGL(k_node_rows, dim3((n + 255) / 256), dim3(256), 0, st, b, max_nodes, a_rows, out_rows, kv_len,
-                     pos_list);
-  return hipGetLastError();
-}
-
-__global__ void k_row_positions(BlockDev b, const int32_t* __restrict__ kv_len, int32_t* pos_rows) {
-  int row = blockIdx.x * blockDim.x + threadIdx.x;
-  if (row >= b.batch * b.rows_per_seq) return;
-  pos_rows[row] = kv_len[row / b.rows_per_seq] + b.depth[row] + 1;
-}
-
-hipError_t launch_row_positions(hipStream_t st, const BlockDev& b, const int32_t* kv_len, int32_t* pos_rows) {
-  int n = b.batch * b.rows_per_seq;
-  hipLaunchKernelGGL(k_row_positions, dim3((n + 255) / 256), dim3(256), 0, st, b, kv_len, pos_rows);
   return hipGetLastError();
 }
 

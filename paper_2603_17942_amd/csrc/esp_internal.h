@@ -268,9 +268,17 @@ struct PackedEnd {
   bf16_t* rows[3] = {};
   int width[3] = {};
 };
+// gather lists for the LM head over the tree rows (max_nodes 0: not wanted): block row of node-list entry m, row of its result (-1:
+// none), position of the token that follows it (len + depth + 1); row_positions (nullable): the same for every block row
+struct NodeLists {
+  int max_nodes = 0;
+  int32_t *a_rows = nullptr, *out_rows = nullptr, *positions = nullptr, *row_positions = nullptr;
+};
+// h and the rotary table of every row, xn = its norm with `gain`, and the lists
 hipError_t launch_embed(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, const void* embed,
                         const void* mask_embed, float* h, int d, int vocab, float* rope_tab, int hd,
-                        float theta, int32_t* status, size_t mask_seq_stride, const PackedEnd& end);
+                        float theta, int32_t* status, size_t mask_seq_stride, const PackedEnd& end, const NodeLists& lists,
+                        const void* gain, float eps, void* xn);
 // n_live (nullable): rows there are.  packed_row (nullable): row m of xn_out comes from row packed_row[m], or is zero
 hipError_t launch_residual_norm(hipStream_t st, int dtype, float* h, const float* part, int splits, int M,
                                 int d, const void* gain, float eps, void* xn_out, const int32_t* n_live = nullptr,
@@ -282,11 +290,6 @@ hipError_t launch_qkv_post(hipStream_t st, int dtype, const BlockDev& b, const K
 hipError_t launch_argmax(hipStream_t st, const float* logits, size_t row_stride, const int32_t* row_map,
                          int n_rows_out, int vocab, int32_t* out, const int32_t* out_index,
                          const int32_t* draw_pos = nullptr, uint32_t seed = 0);
-// pos_list (nullable): position of the token that follows node-list entry m (len + depth + 1)
-hipError_t launch_node_rows(hipStream_t st, const BlockDev& b, int max_nodes, int32_t* a_rows, int32_t* out_rows,
-                            const int32_t* kv_len = nullptr, int32_t* pos_list = nullptr);
-// pos_rows[row] = len[seq] + depth[row] + 1 for every block row
-hipError_t launch_row_positions(hipStream_t st, const BlockDev& b, const int32_t* kv_len, int32_t* pos_rows);
 hipError_t launch_kv_copy(hipStream_t st, int dtype, const KvDev& kv, int layer, int n_kv, int hd,
                           int seq_base, int first_slot, int n_slots, void* k_rows, void* v_rows, int to_cache);
 hipError_t launch_mask_mean(hipStream_t st, int dtype, const void* embed, const int32_t* tokens, int n, int k,
