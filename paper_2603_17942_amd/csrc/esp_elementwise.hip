@@ -47,7 +47,7 @@ __device__ __forceinline__ float block_sum_256(float v, float* red) {
 // ---- block assembly (Sec. 3.1, Sec. 3.3): h0 rows and the per-row rotary table ---------------
 // Packed rows of a batch (BlockDev): one workgroup per sequence adds up the row counts of the sequences before it
 // and writes its own rows' places.  A sequence that is not valid (or a count that does not fit) has no rows; its tree
-// rows follow the block alone, as in k_node_rows.
+// rows follow the block alone, as in node_row.
 __global__ __launch_bounds__(256) void k_live_rows(BlockDev b, KvDev kv, int max_nodes, GateUpRule gate_up) {
   __shared__ float red[4];
   const int seq = blockIdx.x;
@@ -128,7 +128,8 @@ __device__ __forceinline__ void node_row(const BlockDev& b, const KvDev& kv, con
 
 // One workgroup per block row: its embedding, its rotary table and the first layer's norm of it (threads and order of the sum as in
 // k_residual_norm); the workgroups behind the rows write the LM head's gather lists.  A launch each for the norm, the lists and the
-// positions of a draw cost 4.6 us a step.  The table's double-precision functions take the last waves about as long as the others wait for the embedding.
+// positions of a draw cost 4.6 us a step; embedding and norm of 68 rows of 4096 12.3 + 4.7 -> 6.3 us, of 2112 27.9 + 12.6 -> 40.6.
+// The table's double-precision functions take the last waves about as long as the others wait for the embedding.
 // PACKED: the row behind the live ones in the projections' inputs is set to zero; no kernel of the layers writes it, and the row
 // tiles load it for every row that is not there.  (A copy of the last live row keeps the matrix cores as busy as a real one, zeros
 // do not, and the card is at its power limit in the large tiles: eight layers of the 8B shape on 2048 keys, 172 rows of 318 there

@@ -235,9 +235,9 @@ struct BlockDev {   // device-side view of esp_block + esp_kv scalars, passed by
 };
 // x, once the arguments named with it are there too: a kernel's first use of x then finds all their loads issued together.  The
 // compiler loads an argument in the block that uses it, behind whatever branch comes first, and a small kernel waits for one
-// line of its arguments after the other.  With this in the kernels of a layer a step of one row on 2048 keys took 3196 -> 3148 us, of
-// 68 rows 4084 -> 4013 (attention 11.5 -> 11.1 us a layer, each GEMM 0.1 to 0.6).  Not volatile: a statement with side effects would turn the uniform loads after it into
-// vector ones.
+// line of its arguments after the other.  With this in the kernels of a layer a step of one row on 2048 keys took 3196 -> 3148
+// us, of 68 rows 4084 -> 4013 (attention 11.5 -> 11.1 us a layer, each GEMM 0.1 to 0.6).  Not volatile: a statement with side
+// effects would turn the uniform loads after it into vector ones.
 template <typename X, typename A, typename B, typename C, typename D>
 __device__ __forceinline__ X with_args(X x, A a, B b, C c, D d) {
   asm("" : "+s"(x) : "s"(a), "s"(b), "s"(c), "s"(d));

@@ -926,6 +926,68 @@ def test_qkv_epilogue_forms(B, dtype, head_dim, d_model, hq, hkv, qk_norm):
     eng.close()
 
 
+class BlockDev(ctypes.Structure):
+    _fields_ = ([(n, ctypes.c_int) for n in ("batch", "rows_per_seq", "k_masks", "layout", "anc_words")] +
+                [(n, ctypes.c_void_p) for n in ("n_rows", "n_nodes", "tok", "parent", "depth", "mask_j", "attach", "anc", "packed")])
+
+
+class KvDev(ctypes.Structure):
+    _fields_ = ([(n, ctypes.c_void_p) for n in ("k", "v", "len", "base", "seq_cap")] + [("capacity", ctypes.c_int64), ("len_bound", ctypes.c_int)])
+
+
+class PackedEnd(ctypes.Structure):
+    _fields_ = [("rows", ctypes.c_void_p * 3), ("width", ctypes.c_int * 3)]
+
+
+class NodeLists(ctypes.Structure):
+    _fields_ = [("max_nodes", ctypes.c_int)] + [(n, ctypes.c_void_p) for n in ("a_rows", "out_rows", "positions", "row_positions")]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,hd,rows,nodes", [(64, 128, 75, 70), (320, 64, 9, 3), (4096, 128, 5, 1), (8192 + 12, 128, 4, 4)])
+def test_embed_norm_and_lists(B, dtype, d, hd, rows, nodes):
+    """A row's embedding, rotary table and norm, and the LM head's lists behind them: fewer columns than the table has entries, more
+    than a thread has, lists of several workgroups, rows and a whole sequence that are not there."""
+    print(f"embed {dtype} d={d} hd={hd} rows={rows} nodes={nodes}", flush=True)
+    c, dt, vocab, k, theta, eps = ctypes, torch.float32 if dtype == "f32" else torch.bfloat16, 50, 4, 5e5, 1e-5
+    g = torch.Generator().manual_seed(17)
+    ints = lambda *shape, hi: torch.randint(0, hi, shape, generator=g, dtype=torch.int32).cuda()
+    emb, masks = (synth.normal_like((n, d), 1.0, 19, i, "cuda", dt) for i, n in enumerate((vocab, k)))
+    gain = synth.normal_like((d,), 1.0, 19, 2, "cuda", dt)
+    dev = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    n_rows, n_nodes = dev([rows, rows - 1, 1, rows]), dev([nodes, max(nodes - 2, 1), 1, nodes])
+    lens, base, cap = dev([1000, 3, 70000, -1]), dev([0, 2048, 4096, 128000]), dev([2000, 1024, 100000, 1000])   # the last one is invalid
+    tok, depth = ints(4, rows, hi=vocab), ints(4, rows, hi=7)
+    mask_j = torch.where(torch.arange(rows, device="cuda")[None] < n_nodes[:, None], 0, 1 + ints(4, rows, hi=k))
+    M = 4 * rows
+    h, rope, xn = torch.full((M, d), -7.0, device="cuda"), torch.zeros(M, hd // 2, 2, device="cuda"), torch.full((M, d), -7.0, dtype=dt, device="cuda")
+    lists = torch.full((3, 4 * nodes), -7, dtype=torch.int32, device="cuda")
+    where, status = torch.zeros(M, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    p = lambda t: t.data_ptr()
+    blk = BlockDev(4, rows, k, 0, 2, p(n_rows), p(n_nodes), p(tok), None, p(depth), p(mask_j), None, None, None)
+    kv = KvDev(None, None, p(lens), p(base), p(cap), 1 << 20, 80000)
+    run = internal("launch_embed", c.c_void_p, c.c_int, c.POINTER(BlockDev), c.POINTER(KvDev), c.c_void_p, c.c_void_p, c.c_void_p, c.c_int, c.c_int,
+                   c.c_void_p, c.c_int, c.c_float, c.c_void_p, c.c_size_t, c.POINTER(PackedEnd), c.POINTER(NodeLists), c.c_void_p, c.c_float, c.c_void_p)
+    assert run(torch.cuda.current_stream().cuda_stream, B.ESP_F32 if dtype == "f32" else B.ESP_BF16, blk, kv, p(emb), p(masks), p(h), d, vocab, p(rope), hd,
+               theta, p(status), 0, PackedEnd(), NodeLists(nodes, p(lists[0]), p(lists[1]), p(lists[2]), p(where)), p(gain), eps, p(xn)) == 0
+    live = (torch.arange(rows, device="cuda")[None] < n_rows[:, None]) & (torch.arange(4, device="cuda")[:, None] < 3)
+    want = torch.where((mask_j > 0)[..., None], masks[(mask_j - 1).clamp(min=0).long()], emb[tok.long()]).float() * live[..., None]
+    assert torch.equal(h, want.view(M, d)) and int(status) != 0
+    norm = want.double() / (want.double().square().mean(-1, keepdim=True) + eps).sqrt() * gain.double()
+    # fp32 sums of d squares in a tree of at most 3 + 6 + 16 levels, root and quotient, two products; then the rounding to bf16
+    tol = 2.0 ** -8 if dtype == "bf16" else 20 * 2.0 ** -23
+    assert bool(((xn.double() - norm.view(M, d)).abs() <= tol * norm.view(M, d).abs() + 1e-30).all())
+    pos = torch.where(live, lens[:, None] + depth, 0).double().view(M, 1)
+    angle = pos * theta ** (-2.0 * torch.arange(hd // 2, dtype=torch.float64, device="cuda") / hd)
+    assert float((rope.double() - torch.stack((angle.cos(), angle.sin()), -1)).abs().max()) <= 2.0 ** -24 + 1e-10   # rounding; 77000 radians to 2^-52
+    assert torch.equal(where.view(4, rows), lens[:, None] + depth + 1)
+    for m in range(4 * nodes):
+        s, i = divmod(m, nodes)
+        there = i < int(n_nodes[s])
+        row = s * rows + (i if there else 0)
+        assert lists[:, m].tolist() == [row, row if there else -1, int(lens[s]) + int(depth.view(-1)[row]) + 1]
+
+
 # ---------------------------------------------------------------------------- packed rows of a batch
 @pytest.mark.parametrize("head_dim,counts,sample,invalid", [
     (128, [14, 1, 5], False, []), (128, [1, 14, 3, 14, 9, 2], True, []), (64, [2, 14, 8, 1], True, []), (128, [1, 1, 1, 1], False, []),
