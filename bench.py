@@ -597,7 +597,7 @@ def main():
         return dict(rows=rows, n_nodes=r["n_nodes"], tokens_per_s=tokens_per_s, ms_per_step=r["ms_per_step"],
                     pct=r["step_ms_p10_p50_p90"],
                     tau=r["emitted"] / args.steps,
-                    roofline={"kernel": "k_gemm_bf16 (layer projections: QKV, O, gate/up, down)", "bound": "hbm",
+                    roofline={"kernel": "k_gemm_tile (layer projections: QKV, O, gate/up, down)", "bound": "hbm",
                               "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                               "frac": (achieved / HBM_PEAK_GBS) if achieved else None,
                               "traffic": measured_traffic(layout_name, rows),
