@@ -332,20 +332,20 @@ int tile_index(const GemmPlan& p) {
 }
 
 // Tile and split-K parts of a launch of more than 128 rows: the cheapest by GEMM_TILES, plus what the partials cost on their way
-// out and in (1 us for 4 MB).  A part has eight chunks of K at least, and all parts together one round of the CUs.  Of a
-// batch, over numbers of rows from two thirds of M up.
-GemmPlan tile_plan(int M, int N, int K, int most_splits, bool batch) {
+// out and in (1 us for 4 MB).  There are `fewest` parts at least (gemm_plan); more of them fit one round of the CUs and have eight
+// chunks of K or more.  Of a batch, over numbers of rows from two thirds of M up.
+GemmPlan tile_plan(int M, int N, int K, int fewest, int most, bool batch) {
   const int rows = (M + 31) / 32 * 32, blocks = (N + 31) / 32, chunks = std::max(K / KC, 1), at[3] = {rows, rows * 5 / 6, rows * 2 / 3};
-  const int max_s = std::max(1, std::min(std::min(most_splits, chunks / 8), 8));
+  const int max_s = std::max(fewest, std::min(most, chunks / 8));
   GemmPlan best{};
   int64_t least = -1;
   for (int t = N_ROW_TILES; t < N_GEMM_TILES; ++t) {
     const GemmTileCost& c = GEMM_TILES[t];
     const int m_tiles = (M + 32 * c.rt - 1) / (32 * c.rt), n_tiles = (blocks + c.ct - 1) / c.ct;
-    for (int s = 1; s <= max_s; ++s) {
-      if (s > 1 && (int64_t)m_tiles * n_tiles * s > 256) break;
+    for (int s = fewest; s <= max_s; ++s) {
+      if (s > fewest && (int64_t)m_tiles * n_tiles * s > 256) break;
       const int cps = (chunks + s - 1) / s;
-      if ((chunks + cps - 1) / cps != s) continue;       // the same parts as with fewer
+      if (s > fewest && (chunks + cps - 1) / cps != s) continue;   // the same parts as with fewer
       int64_t cost = 0;
       for (int i = 0; i < (batch ? 3 : 1); ++i) cost += tile_cost(c, at[i], blocks, chunks, s) + (int64_t)s * at[i] * N / 1000;
       if (least < 0 || cost < least) {
@@ -358,26 +358,24 @@ GemmPlan tile_plan(int M, int N, int K, int most_splits, bool batch) {
 }
 
 // Up to 128 rows: one row tile.  The parts are a function of (N, K), those of 128 rows: a row's sums then do not depend on how
-// many rows there are beside it (for QKV, O and down of the 8B shapes 2, 4 and 4 parts of 64 columns, 0.90, 0.87 and 0.92 of the time
-// of twice as many of 128 columns over 1 to 128 rows, with the consumers' share).  A part costs 0.6 us beside its bytes: with 0.2, five
-// and eight parts for QKV and down, which alone take as long, a step of 101 rows takes 5410 us instead of 5325 and one of 30
-// rows 3482 instead of 3462.  The columns are what is cheapest for the parts.  fewest_ct: 4 where pairs for every 128 columns
-// have been reserved.
-GemmPlan row_plan(int M, int N, int K, int most_splits, int fewest_ct) {
+// many rows there are beside it.  There are `fewest` at least (gemm_plan; 5, 8 and 8 for QKV, O and down of the 8B shapes), and a part
+// beyond that costs its consumer 0.6 us beside its bytes.  The columns are what is cheapest for the parts.  fewest_ct: 4 where pairs
+// for every 128 columns have been reserved.
+GemmPlan row_plan(int M, int N, int K, int fewest, int most, int fewest_ct) {
   const int blocks = (N + 31) / 32, chunks = std::max(K / KC, 1), rt = (M + 31) / 32;
-  const int max_s = std::max(1, std::min(std::min(most_splits, chunks / 8), 8));
+  const int max_s = std::max(fewest, std::min(most, chunks / 8));
   GemmPlan best{};
   for (int pass = 0; pass < 2; ++pass) {                 // the parts with four row tiles, then the columns with rt
-    const int pass_rt = pass ? rt : 4, s0 = pass ? best.splits : 1, s1 = pass ? best.splits : max_s;
+    const int pass_rt = pass ? rt : 4, s0 = pass ? best.splits : fewest, s1 = pass ? best.splits : max_s;
     int64_t least = -1;
     for (int t = 0; t < N_ROW_TILES; ++t) {
       const GemmTileCost& c = GEMM_TILES[t];
       if (c.rt != pass_rt || c.ct < fewest_ct) continue;
       const int n_tiles = (blocks + c.ct - 1) / c.ct;
       for (int s = s0; s <= s1; ++s) {
-        if (!pass && s > 1 && n_tiles * s > 256) break;
+        if (s > s0 && n_tiles * s > 256) break;
         const int cps = (chunks + s - 1) / s;
-        if ((chunks + cps - 1) / cps != s) continue;
+        if (s > s0 && (chunks + cps - 1) / cps != s) continue;
         const int64_t cost = tile_cost(c, 32 * pass_rt, blocks, chunks, s) + (int64_t)s * (32 * pass_rt * N / 1000 + 600);
         if (least < 0 || cost < least) {
           least = cost;
@@ -401,16 +399,20 @@ hipError_t gemm_prepare() {
   return e;
 }
 
+// No fewer parts than round_parts: a part is one running fp32 sum, whose error grows with the root of its terms.  Chosen by time
+// alone (2, 4 and 4 parts for QKV, O and down up to 128 rows, 4 and 5 for QKV and O at 320) the products' error against 64 bits was up to
+// 1.62 times as large (QKV up to 128 rows 2.72e-7, now 1.68e-7).  The time of a step that way and this way: one row 3139 and 3178 us,
+// 68 rows 3973 and 4063, 101 rows of the Qwen3 shape 5149 and 5335, 320 rows 6845 and 7068, 576 rows of the Qwen3 shape 10828 and 10723.
 GemmPlan gemm_plan(int dtype, int M, int N, int K) {
   GemmPlan p;
   if (dtype == ESP_F32) {
     p.splits = 1; p.mt = 1; p.nb = 1; p.m_tiles = (M + 31) / 32; p.n_tiles = (N + 31) / 32; p.ct = 1;
     return p;
   }
-  return M > 128 ? tile_plan(M, N, K, 8, false) : row_plan(M, N, K, 8, 2);
+  return M > 128 ? tile_plan(M, N, K, round_parts(M, N, K), 8, false) : row_plan(M, N, K, round_parts(M, N, K), 8, 2);
 }
 
-GemmPlan batch_gemm_plan(int M, int N, int K) { return tile_plan(M, N, K, 8, true); }
+GemmPlan batch_gemm_plan(int M, int N, int K) { return tile_plan(M, N, K, round_parts(M, N, K), 8, true); }
 
 int round_parts(int M, int N, int K) {
   const int m_tiles = M <= 128 ? 1 : ((M + 31) / 32 + 4) / 5, n_tiles = M <= 128 ? (N + 127) / 128 : (N + 255) / 256;
@@ -419,7 +421,7 @@ int round_parts(int M, int N, int K) {
 bool gemm_whole_rows(int dtype, int M, int N, int K) { return dtype == ESP_F32 || round_parts(M, N, K) == 1; }
 
 GemmPlan whole_row_plan(int dtype, int M, int N, int K) {
-  if (dtype == ESP_BF16) return M > 128 ? tile_plan(M, N, K, 1, false) : row_plan(M, N, K, 1, 4);
+  if (dtype == ESP_BF16) return M > 128 ? tile_plan(M, N, K, 1, 1, false) : row_plan(M, N, K, 1, 1, 4);
   return gemm_plan(dtype, M, N, K);
 }
 
@@ -498,7 +500,7 @@ GateUpRule gate_up_rule(int M, int ff, int K, const void* act, bool ragged) {
   GateUpRule r;
   r.mt = even_row_tiles(M); r.chunks = K / KC; r.blocks = (2 * ff) >> 5;
   if (M <= 128) {
-    r.tile[GU_PLAN] = tile_index(row_plan(M, 2 * ff, K, 1, 2));
+    r.tile[GU_PLAN] = tile_index(row_plan(M, 2 * ff, K, 1, 1, 2));
     return r;
   }
   if ((uintptr_t)act % 16 == 0 && ff % 8 == 0) {         // (the wide classes' results are stored 16 bytes at a time)

@@ -127,9 +127,10 @@ __host__ __device__ inline int64_t tile_cost(const GemmTileCost& t, int rows, in
 GemmPlan gemm_plan(int dtype, int M, int N, int K);
 // of a batch with packed rows, of whose M rows only the device knows how many are there: for two thirds of them to all
 GemmPlan batch_gemm_plan(int M, int N, int K);
-// is a projection's output unsplit by its size (the LM head's epilogues see whole rows and are refused otherwise), and its plan
-// (by tiles of 128 columns up to 128 rows and of 160 x 256 above: not split if two parts would not fit one round of the CUs)
+// split-K parts by size alone: what one round of the CUs holds of tiles of 128 columns up to 128 rows and of 160 x 256 above, each
+// part with eight chunks of K or more
 int round_parts(int M, int N, int K);
+// is a projection's output unsplit by that (the LM head's epilogues see whole rows and are refused otherwise), and its plan
 bool gemm_whole_rows(int dtype, int M, int N, int K);
 GemmPlan whole_row_plan(int dtype, int M, int N, int K);
 inline size_t gemm_out_elems(const GemmPlan& p, int M, int N) { return (size_t)p.splits * M * N; }

@@ -28,6 +28,26 @@ def test_gate_up_tiles(m, ff, full, batch):
     assert tiles(m, ff, 4096, 8, True) == 0b001             # results off the 16-byte alignment of the wide tiles' stores
 
 
+class GemmPlan(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("splits", "mt", "nb", "m_tiles", "n_tiles", "ct")]
+
+
+@pytest.mark.parametrize("n,k", [(6144, 4096), (4096, 4096), (4096, 14336), (4096, 12288), (28672, 4096), (1024, 8192), (544, 2048), (96, 640), (32, 64)])
+def test_gemm_parts(n, k):
+    """A product's split-K parts are no fewer than one round of the 256 CUs holds of tiles of 128 columns (up to 128 rows) or of 160
+    x 256 (above), each of 512 of K or more: a running fp32 sum's error grows with the root of its terms, so the parts bound it.
+    Up to 128 rows the parts do not depend on the rows."""
+    one, batch = (internal(f, *[C.c_int] * a, restype=GemmPlan) for f, a in (("gemm_plan", 4), ("batch_gemm_plan", 3)))
+    of_128 = one(binding.ESP_BF16, 128, n, k).splits
+    for m in (1, 17, 32, 33, 68, 101, 128, 129, 160, 161, 200, 320, 321, 400, 512, 576, 700, 1024, 1344, 2112):
+        tiles = -(-n // 128) if m <= 128 else -(-n // 256) * -(-(-(-m // 32)) // 5)
+        least = max(1, min(256 // tiles, k // 512, 8))
+        p = one(binding.ESP_BF16, m, n, k)
+        assert least <= p.splits <= 8 and (m > 128 or p.splits == of_128), (m, p.splits, least)
+        if m > 128:
+            assert batch(m, n, k).splits >= least, (m, least)
+
+
 class AttnPlan(C.Structure):
     _fields_ = [("nsplit", C.c_int), ("tiles_per_split", C.c_int), ("q_tiles", C.c_int), ("ct_wg", C.c_int)]
 
