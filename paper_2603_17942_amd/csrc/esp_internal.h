@@ -130,6 +130,7 @@ GemmPlan batch_gemm_plan(int M, int N, int K);
 // split-K parts by size alone: what one round of the CUs holds of tiles of 128 columns up to 128 rows and of 160 x 256 above, each
 // part with eight chunks of K or more
 int round_parts(int M, int N, int K);
+GemmPlan row_major_plan(int M, int N, int K);     // bf16 weights that are not packed
 // is a projection's output unsplit by that (the LM head's epilogues see whole rows and are refused otherwise), and its plan
 bool gemm_whole_rows(int dtype, int M, int N, int K);
 GemmPlan whole_row_plan(int dtype, int M, int N, int K);

@@ -48,6 +48,22 @@ def test_gemm_parts(n, k):
             assert batch(m, n, k).splits >= least, (m, least)
 
 
+@pytest.mark.parametrize("n,k", [(6144, 4096), (4096, 4096), (4096, 14336), (28672, 4096), (2048, 2048), (544, 2048), (160, 1664), (32, 64)])
+def test_row_major_gemm_plan(n, k):
+    """Row-major weights have a kernel with tiles of its own, 128 columns wide up to 128 rows and 160 x 256 above: as many parts as
+    one round of the 256 CUs has room for, and a tile the kernel is built for."""
+    plan, scratch = internal("row_major_plan", *[C.c_int] * 3, restype=GemmPlan), binding.load_library().esp_gemm_scratch_bytes
+    for m in (1, 32, 33, 68, 128, 129, 160, 161, 192, 320, 321, 512, 1024, 1344, 2112):
+        p = plan(m, n, k)
+        cols = 128 if m <= 128 else 256
+        tiles = -(-n // cols) * (1 if m <= 128 else -(-m // 160))
+        assert p.splits == max(1, min(256 // tiles, k // 512, 8)), (m, p.splits)
+        assert p.splits == 1 or p.m_tiles * p.n_tiles * p.splits <= 256
+        assert (p.nb, p.mt) in [(1, 1), (1, 2), (1, 3), (1, 4), (2, 3), (2, 4), (2, 5)] and (p.nb == 1) == (m <= 128)
+        assert p.m_tiles * p.mt * 32 >= m and p.n_tiles * cols >= n and p.ct * 32 == cols
+        assert scratch(m, n, k) >= p.splits * m * n * 4
+
+
 class AttnPlan(C.Structure):
     _fields_ = [("nsplit", C.c_int), ("tiles_per_split", C.c_int), ("q_tiles", C.c_int), ("ct_wg", C.c_int)]
 
