@@ -907,12 +907,16 @@ static bool generic_merges(int hd, const AttnPlan& p) { return p.nsplit <= (hd =
 // it: 16 of 132 rows, 8192 keys 350 -> 346 us and 242 -> 172, on 2048 keys 107 -> 112 and 90 -> 81; 8 of 132 rows, 8192 keys 171 -> 172
 // and 129 -> 78.  Below the line: 6 of 200 rows, 2048 keys 72 -> 73 and 66 -> 63 (106 to 200 rows of one length 66 -> 74); eight layers,
 // 16 sequences of one row on 128 keys 816 -> 866.
+// And only where the shares, 63 a kv head at most, have work for three quarters of the CUs, with two sequences to a share at most: one
+// or two kv heads had 63 or 126 workgroups (256 sequences of one row, 4000 keys, one kv head 87 -> 290 us; 64 on 8000 keys, two kv heads
+// 89 -> 142), and a grid of several rounds evens itself out (128 sequences of one row on 4096 keys, four layers 1990 -> 2060 us, 1535 ->
+// 1555 with lengths of an eighth to all; 64 of them 1202 -> 1165 and 945 -> 905).
 int attn_shares(int dtype, int hd, int batch, int rows_per_seq, int hq, int hkv, const AttnPlan& p) {
   if (dtype != ESP_BF16 || hd != 128 || batch < 2 || p.tiles_per_split * ring_tile_time(p.ct_wg) < 4500) return 0;
   // (batch + shares) x column tiles are what a share of the reserved partials holds
   const int room = batch * (ring_tiles_bound(rows_per_seq * (hq / hkv)) / (p.q_tiles * p.ct_wg) - 1);
   const int n = std::min(std::min(256 / (hkv * p.q_tiles), MAX_SHARES), room);
-  return n < 2 ? 0 : n;
+  return n < 2 || n * hkv * p.q_tiles < 192 || batch > 2 * n ? 0 : n;
 }
 size_t attn_cuts_ints(int batch) { return cuts_of_seq(MAX_SHARES) + 2 * (size_t)batch; }
 

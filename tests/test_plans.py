@@ -110,3 +110,14 @@ def test_ring_attention_plans_fit_their_workspace():
                     p = fn(dtype, hd, batch, rows, hq, hkv, keys)
                     assert 1 <= p.nsplit <= 64 and p.nsplit * p.tiles_per_split * 64 >= keys + rows
                     assert need(dtype, batch, rows, hq, hkv, hd, p) <= most, (dtype, batch, rows, keys)
+
+
+@pytest.mark.parametrize("hkv,batch,rows,keys,shares", [
+    # workgroups for three quarters of the CUs, and no more than two sequences to a share
+    (8, 16, 132, 8192, 16), (8, 16, 1, 16384, 32), (8, 64, 1, 4096, 32), (4, 64, 1, 8192, 63), (2, 16, 200, 32768, 42),
+    (1, 256, 1, 4000, 0), (1, 1024, 1, 4000, 0), (2, 64, 1, 8000, 0), (2, 64, 68, 8192, 0), (8, 128, 1, 4096, 0), (4, 128, 1, 8192, 0)])
+def test_attention_shares(hkv, batch, rows, keys, shares):
+    """Shares of a batch's attention, four query heads to a kv head, at shapes whose longest split takes 45 us and more."""
+    plan = internal("attn_plan", *[C.c_int] * 7, restype=AttnPlan)(binding.ESP_BF16, 128, batch, rows, 4 * hkv, hkv, keys)
+    n = internal("attn_shares", *[C.c_int] * 6, C.POINTER(AttnPlan))(binding.ESP_BF16, 128, batch, rows, 4 * hkv, hkv, plan)
+    assert n == shares
