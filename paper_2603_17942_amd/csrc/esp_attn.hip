@@ -366,59 +366,62 @@ constexpr int PIECE_TIME = 180;                          // start and end of a w
 // rises along the line: pieces never share one, and those of a sequence are consecutive.
 // Table of the cuts (ints): [0] shares; share w begins at tile [3 + 2 w] of sequence [2 + 2 w], w <= shares; then per sequence
 // the first and the last share that has any of it.
-constexpr int MAX_SHARES = 63;
+constexpr int MAX_SHARES = 63, MAX_SHARED_SEQS = 2 * MAX_SHARES;
 __host__ __device__ constexpr int cuts_of_seq(int max_shares) { return 2 + 2 * (max_shares + 1); }
 
 // columns of a sequence in a workgroup: its column tiles spread evenly over the groups
 __device__ __forceinline__ int even_ct(int ncols, int q_tiles) { return ((ncols + 31) / 32 + q_tiles - 1) / q_tiles; }
 
-__global__ __launch_bounds__(256) void k_attn_cuts(BlockDev b, KvDev kv, int G, int q_tiles, int max_shares, int32_t* __restrict__ cuts) {
-  __shared__ int64_t red[4];
-  const int tid = threadIdx.x;
-  // weight and key tiles of a sequence
-  auto weigh = [&](int s, int& nt, int& u) {
+// One workgroup, a thread per sequence.  What is before a sequence on the line is a sum over the lanes; a thread that added up the
+// sequences in front of its own, a chain of loads for each, took 8.4 us at 16 sequences and 29.9 at 126, this 4.6 and 3.7.
+__global__ __launch_bounds__(128) void k_attn_cuts(BlockDev b, KvDev kv, int G, int q_tiles, int max_shares, int32_t* __restrict__ cuts) {
+  static_assert(MAX_SHARED_SEQS <= 128, "a thread each");
+  __shared__ int64_t first_wave, all;
+  const int s = threadIdx.x;
+  int w = 0, nt = 0, u = 1;                              // weight and key tiles of the sequence, and the weight of one
+  if (s < b.batch) {
     const int nr = b.n_rows[s];
-    nt = 0; u = 1;
-    if (!seq_ok(kv, s, nr, b.rows_per_seq) || nr == 0) return 0;
-    nt = (kv.len[s] + nr + 63) >> 6;
-    u = ring_tile_time(even_ct(nr * G, q_tiles));
-    return PIECE_TIME + nt * u;
-  };
-  int nt, u;
-  int64_t sum = 0;
-  for (int s = tid; s < b.batch; s += 256) sum += weigh(s, nt, u);
-  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-  if ((tid & 63) == 0) red[tid >> 6] = sum;
+    if (seq_ok(kv, s, nr, b.rows_per_seq) && nr > 0) {
+      nt = (kv.len[s] + nr + 63) >> 6;
+      u = ring_tile_time(even_ct(nr * G, q_tiles));
+      w = PIECE_TIME + nt * u;
+    }
+  }
+  int64_t upto = w;                                      // of this sequence and those before it
+  for (int o = 1; o < 64; o <<= 1) {
+    const int64_t x = __shfl_up(upto, o, 64);
+    if ((s & 63) >= o) upto += x;
+  }
+  if (s == 63) first_wave = upto;
   __syncthreads();
-  const int64_t total = red[0] + red[1] + red[2] + red[3];
+  if (s >= 64) upto += first_wave;
+  if (s == 127) all = upto;
+  __syncthreads();
+  const int64_t total = all, c0 = upto - w;
   // a share of less than about two key tiles costs more in its partial than it gives
   const int64_t shares = max((int64_t)1, min((int64_t)max_shares, total / 400));
-  if (tid == 0) {
+  if (s == 0) {
     cuts[0] = (int)shares;
     cuts[2 + 2 * shares] = b.batch; cuts[3 + 2 * shares] = 0;
     if (total == 0) { cuts[2] = b.batch; cuts[3] = 0; }
   }
-  for (int s = tid; s < b.batch; s += 256) {
-    int64_t c0 = 0;
-    for (int i = 0; i < s; ++i) c0 += weigh(i, nt, u);
-    const int w = weigh(s, nt, u);
-    int first = 0, last = -1;
-    if (w > 0) {
-      first = (int)min(shares - 1, c0 * shares / total);            // share x begins at x * total / shares
-      while ((int64_t)first * total / shares > c0) --first;
-      while (first + 1 < shares && (int64_t)(first + 1) * total / shares <= c0) ++first;
-      last = first;
-      while (last + 1 < shares && (int64_t)(last + 1) * total / shares < c0 + w) ++last;
-      for (int x = first; x <= last; ++x) {
-        const int64_t at = (int64_t)x * total / shares - c0;
-        if (at < 0) continue;                                       // begins in a sequence before
-        cuts[2 + 2 * x] = s;
-        cuts[3 + 2 * x] = (int)min((int64_t)nt, max((int64_t)0, (at - PIECE_TIME + u - 1) / u));
-      }
+  if (s >= b.batch) return;
+  int first = 0, last = -1;
+  if (w > 0) {
+    first = (int)min(shares - 1, c0 * shares / total);              // share x begins at x * total / shares
+    while ((int64_t)first * total / shares > c0) --first;
+    while (first + 1 < shares && (int64_t)(first + 1) * total / shares <= c0) ++first;
+    last = first;
+    while (last + 1 < shares && (int64_t)(last + 1) * total / shares < c0 + w) ++last;
+    for (int x = first; x <= last; ++x) {
+      const int64_t at = (int64_t)x * total / shares - c0;
+      if (at < 0) continue;                                         // begins in a sequence before
+      cuts[2 + 2 * x] = s;
+      cuts[3 + 2 * x] = (int)min((int64_t)nt, max((int64_t)0, (at - PIECE_TIME + u - 1) / u));
     }
-    cuts[cuts_of_seq(max_shares) + 2 * s] = first;
-    cuts[cuts_of_seq(max_shares) + 2 * s + 1] = last;
   }
+  cuts[cuts_of_seq(max_shares) + 2 * s] = first;
+  cuts[cuts_of_seq(max_shares) + 2 * s + 1] = last;
 }
 
 // the key tiles of sequence s, nt in all, that share w has
@@ -901,12 +904,13 @@ size_t attn_partial_floats_bound(int dtype, int batch, int rows_per_seq, int hq,
 constexpr int GENERIC_WAVES_64 = 8, GENERIC_WAVES_128 = 4;
 static bool generic_merges(int hd, const AttnPlan& p) { return p.nsplit <= (hd == 64 ? GENERIC_WAVES_64 : GENERIC_WAVES_128); }
 
-// Shares of a batch's line of work per kv head: as many as there are CUs for them; 0: a grid of equal splits.  The line costs 4 to
-// 8 us a launch (the cuts are looked up, a workgroup's second piece starts cold, more partials), so only where the longest
-// sequence's split takes 45 us or more.  Attention and merge of a layer, sequences of equal length and of an eighth to all of
-// it: 16 of 132 rows, 8192 keys 350 -> 346 us and 242 -> 172, on 2048 keys 107 -> 112 and 90 -> 81; 8 of 132 rows, 8192 keys 171 -> 172
-// and 129 -> 78.  Below the line: 6 of 200 rows, 2048 keys 72 -> 73 and 66 -> 63 (106 to 200 rows of one length 66 -> 74); eight layers,
-// 16 sequences of one row on 128 keys 816 -> 866.
+// Shares of a batch's line of work per kv head: as many as there are CUs for them; 0: a grid of equal splits.  The line costs up to 3 us a
+// layer (the cuts are looked up, a workgroup's second piece starts cold, more partials) and one launch a forward pass, so only
+// where the longest sequence's split takes 45 us or more.  Steps of the 8B shape, a grid and shares, sequences of equal length and of an
+// eighth to all of it: four layers, 16 of 132 rows on 16384 keys 5.54 -> 5.53 and 4.99 -> 4.60 ms, 8 of 68 on 8192 1416 -> 1429 and 1351
+// -> 1331 us, 6 of 132 on 4096 1699 -> 1705 and 1632 -> 1591; 32 layers, 16 of 132 on 2048 28.4 -> 28.75 and 28.14 -> 28.17 ms, 3 of
+// 132 on 16384 11.45 -> 11.60.  Below the line: 6 of 200 rows, 2048 keys, attention of a layer 72 -> 73 and 66 -> 63 us (106 to 200
+// rows of one length 66 -> 74); eight layers, 16 sequences of one row on 128 keys 816 -> 866.
 // And only where the shares, 63 a kv head at most, have work for three quarters of the CUs, with two sequences to a share at most: one
 // or two kv heads had 63 or 126 workgroups (256 sequences of one row, 4000 keys, one kv head 87 -> 290 us; 64 on 8000 keys, two kv heads
 // 89 -> 142), and a grid of several rounds evens itself out (128 sequences of one row on 4096 keys, four layers 1990 -> 2060 us, 1535 ->
@@ -921,7 +925,8 @@ int attn_shares(int dtype, int hd, int batch, int rows_per_seq, int hq, int hkv,
 size_t attn_cuts_ints(int batch) { return cuts_of_seq(MAX_SHARES) + 2 * (size_t)batch; }
 
 hipError_t launch_attn_cuts(hipStream_t st, const BlockDev& b, const KvDev& kv, int hq, int hkv, const AttnPlan& p, int shares, int32_t* cuts) {
-  hipLaunchKernelGGL(k_attn_cuts, dim3(1), dim3(256), 0, st, b, kv, hq / hkv, p.q_tiles, shares, cuts);
+  if (b.batch > MAX_SHARED_SEQS) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_attn_cuts, dim3(1), dim3(128), 0, st, b, kv, hq / hkv, p.q_tiles, shares, cuts);
   return hipGetLastError();
 }
 

@@ -1145,6 +1145,80 @@ def test_attention_shares_of_a_batch(B, rows, lens, invalid):
             assert float(err) < 5e-3, (b, float(err))        # two roundings to bf16 (2^-9 of a value at most) and those of the probabilities
 
 
+class BlockDev(ctypes.Structure):
+    _fields_ = ([(n, ctypes.c_int) for n in ("batch", "rows_per_seq", "k_masks", "layout", "anc_words")] +
+                [(n, ctypes.c_void_p) for n in ("n_rows", "n_nodes", "tok", "parent", "depth", "mask_j", "attach", "anc", "packed")])
+
+
+class KvDev(ctypes.Structure):
+    _fields_ = ([(n, ctypes.c_void_p) for n in ("k", "v", "len", "base", "seq_cap")] + [("capacity", ctypes.c_int64), ("len_bound", ctypes.c_int)])
+
+
+def attention_cuts(B, lens, rows, q_tiles, shares, seq_cap=8320, rows_per_seq=132):
+    """(call that fills the table of the cuts for 4 query heads to a kv head, table)"""
+    c, batch = ctypes, len(lens)
+    dev = [torch.tensor(v, dtype=torch.int32, device="cuda") for v in (rows, lens, [i * seq_cap for i in range(batch)], [seq_cap] * batch)]
+    table = torch.full((2 + 2 * (shares + 1) + 2 * batch,), -7, dtype=torch.int32, device="cuda")
+    blk = BlockDev(batch, rows_per_seq, 0, 0, 3, dev[0].data_ptr())
+    kv = KvDev(None, None, dev[1].data_ptr(), dev[2].data_ptr(), dev[3].data_ptr(), batch * seq_cap, 8192)
+    fn = internal("launch_attn_cuts", c.c_void_p, c.POINTER(BlockDev), c.POINTER(KvDev), c.c_int, c.c_int, c.POINTER(AttnPlan), c.c_int, c.c_void_p)
+    plan = AttnPlan(1, 130, q_tiles, 12)
+
+    def run(keep=dev):
+        assert fn(torch.cuda.current_stream().cuda_stream, blk, kv, 32, 8, plan, shares, table.data_ptr()) == 0
+    return run, table
+
+
+@pytest.mark.parametrize("batch,q_tiles,shares", [(2, 1, 32), (16, 2, 16), (63, 1, 32), (64, 1, 63), (65, 1, 63), (126, 2, 63), (126, 1, 63)])
+def test_attention_cuts(B, batch, q_tiles, shares):
+    """The table of a batch's cuts against whole numbers: share x begins where x / shares of the weight of all key tiles lies before
+    it, inside one sequence; sequences without rows, without keys and not valid among them."""
+    most = 96 if q_tiles == 1 else 132                       # twelve column tiles of 8 rows for a workgroup
+    rows = [(17 * i) % (most + 1) if i % 5 else most for i in range(batch)]
+    lens = [(i * 977) % 8000 if i % 7 else 0 for i in range(batch)]
+    lens[-1] = 9000                                          # over the host's bound
+    print(f"attention cuts batch={batch} q_tiles={q_tiles} shares={shares}", flush=True)
+    time_of = [84, 70, 104, 110, 120, 126, 138, 150, 165, 175, 208, 218]
+    unit = [time_of[-(-(-(-r * 4 // 32)) // q_tiles) - 1] for r in rows]
+    tiles = [(n + r + 63) // 64 if r and n <= 8192 else 0 for r, n in zip(rows, lens)]
+    weight = [180 + t * u if t else 0 for t, u in zip(tiles, unit)]
+    total = sum(weight)
+    n = max(1, min(shares, total // 400))
+    start = [sum(weight[:i]) for i in range(batch)]
+    begin = [x * total // n for x in range(n)]
+    want = [n, -7]
+    for at in begin:
+        s = max(i for i in range(batch) if weight[i] and start[i] <= at)
+        want += [s, min(tiles[s], max(0, -(-(at - start[s] - 180) // unit[s])))]
+    want += [batch, 0] + [-7] * (2 * (shares - n))
+    for i in range(batch):
+        of = [x for x in range(n) if begin[x] < start[i] + weight[i] and (begin[x + 1] if x + 1 < n else total) > start[i]]
+        want += [of[0], of[-1]] if weight[i] else [0, -1]
+    run, table = attention_cuts(B, lens, rows, q_tiles, shares)
+    run()
+    assert table.tolist() == want
+
+
+def test_attention_cuts_do_not_wait_for_one_sequence_after_the_other(B):
+    """The cuts of 126 sequences take as long as those of 2 (a chain of loads a sequence made it 4.3 times)."""
+    best = []
+    for batch in (2, 126):
+        run, _ = attention_cuts(B, [64 * i for i in range(batch)], [8] * batch, 1, 63)
+        for _ in range(20):
+            run()
+        times = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(100):
+                run()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        best.append(min(times))
+    assert best[1] < 2 * best[0], best
+
+
 # ---------------------------------------------------------------------------------------- attention
 def run_attention_case(B, shape, eng, n_nodes, k, layout, cache_lens, seed):
     batch = len(cache_lens)
