@@ -202,7 +202,8 @@ esp_status esp_set_sampling(esp_ctx *ctx, int32_t enabled, uint32_t seed);
  *               node rows (lowest id on ties); entries of mask rows are left untouched
  *   logits_dbg  NULL, or device [batch*rows_per_seq, vocab] fp32 receiving the LM-head logits of
  *               every row (parity tests)
- * Errors: EINVAL, ECAPACITY (batch/rows beyond ctx, len_bound + rows_per_seq > max_kv_len). */
+ * Errors: EINVAL, ECAPACITY (batch/rows beyond ctx, len_bound + rows_per_seq > max_kv_len; bf16 with node_argmax and without
+ * logits_dbg, as esp_mask_topk: hidden states of 4 GiB and more). */
 esp_status esp_tree_forward(esp_ctx *ctx, const esp_block *blk, const void *mask_embed,
                             const esp_kv *kv, void *hidden_out, int32_t *node_argmax,
                             float *logits_dbg);

@@ -339,6 +339,7 @@ esp_status esp_tree_forward(esp_ctx* c, const esp_block* blk, const void* mask_e
     const int Mlm = logits_dbg ? M : blk->batch * nodes_bound(blk);
     if (!logits_dbg && (size_t)Mlm > c->logits_rows) return ESP_ECAPACITY;
     if (!gemm_whole_rows(dt, Mlm, m.vocab, d)) return ESP_ESHAPE;
+    if (dt == ESP_BF16 && !logits_dbg && !gemm_rows_fit(M, d)) return ESP_ECAPACITY;   // the tree rows are a list
   }
 
   const int shares = attn_shares(dt, hd, blk->batch, blk->rows_per_seq, hq, hkv, ap);
@@ -458,6 +459,7 @@ esp_status esp_mask_topk(esp_ctx* c, const esp_block* blk, const int32_t* star_r
   if (Kp < 1 || Kp > ESP_MAX_TOPK || Kp > c->m.vocab || blk->k_masks < 1) return ESP_EINVAL;
   const esp_model_desc& m = c->m;
   const int rows = blk->batch * blk->k_masks;
+  if (m.dtype == ESP_BF16 && !gemm_rows_fit((int64_t)blk->batch * blk->rows_per_seq, m.d_model)) return ESP_ECAPACITY;
   hipStream_t s = c->stream;
   BlockDev bd = to_dev(blk);
   { ESP_PROF(ESP_SITE_TREE);

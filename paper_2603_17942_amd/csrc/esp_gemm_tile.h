@@ -17,6 +17,7 @@
 // twice the splits): 68 x 28672 x 4096 41.2 -> 37.8, 101 x 28672 x 4096 47.3 -> 42.4, 68 x 4096 x 4096 10.1 -> 9.3, 101 x 6144 x 4096
 // 17.0 -> 15.2, one row x 6144 x 4096 10.5 -> 9.6; 68 x 128256 x 4096 with logits and arg-max 224 -> 175.
 #pragma once
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -180,15 +181,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // row r of 128 bytes keeps its eight 16-byte pieces XOR-swizzled, so that the fragment reads below are free of bank conflicts
     auto swz = [](int r) { return (r >> 1) & 3; };
     const uint32_t lds0 = (uint32_t)(uintptr_t)lds, ldsw = lds0 + T::A_STAGES * T::A_STAGE;
+    const int a_row0 = a_rows ? 0 : mt0;                 // lane offsets have 32 bits: from the tile's first row, or over all rows of a list
     uint32_t aoff[RT];                                   // this lane's piece of row tile j: row 8 wave + lane / 8 of 32
 #pragma unroll
     for (int j = 0; j < RT; ++j) {
       const int rt = 8 * wave + (lane >> 3);
       int m = min(mt0 + j * 32 + rt, m_last);
       if (a_rows) m = max(a_rows[m], 0);
-      aoff[j] = (uint32_t)(((size_t)m * K + 8 * ((lane & 7) ^ swz(rt))) * 2);
+      aoff[j] = (uint32_t)(((size_t)(m - a_row0) * K + 8 * ((lane & 7) ^ swz(rt))) * 2);
     }
-    const unsigned char* a_base = reinterpret_cast<const unsigned char*>(A) + (size_t)c_begin * (KC * 2);
+    const unsigned char* a_base = reinterpret_cast<const unsigned char*>(A) + ((size_t)a_row0 * K + (size_t)c_begin * KC) * 2;
     const size_t W_CHUNK = (size_t)nblk * 4096;
     const uint32_t lane16 = (uint32_t)lane * 16;
     auto load_a = [&](int j, int c, uint32_t stage) { lds_load16<false>(a_base + (size_t)c * (KC * 2), aoff[j], lds0 + stage + (wave + 4 * j) * 1024); };
@@ -457,7 +459,7 @@ hipError_t tile_launch(hipStream_t st, const TileGemm& g) {
   if (attr != hipSuccess) return attr;
   const int m_tiles = (g.M + T::ROWS - 1) / T::ROWS, n_tiles = ((g.N >> 5) + T::CT - 1) / T::CT;
   const int64_t total = (int64_t)m_tiles * n_tiles * g.splits;
-  if (total > INT32_MAX - 8) return hipErrorInvalidValue;
+  if (total > INT32_MAX - 8 || !gemm_rows_fit(std::min(g.M, T::ROWS), g.K)) return hipErrorInvalidValue;
   launch_kernel(k_gemm_tile<T, EPI, NT>, dim3((unsigned)((total + 7) / 8 * 8)), dim3(256), T::LDS, st, (const bf16_t*)g.A, g.a_rows,
                 (const bf16_t*)g.W, (float*)g.out, g.M, g.N, g.K, g.splits, m_tiles, n_tiles, g.draw_pos, g.seed, g.m_live, g.pairs);
   return hipGetLastError();

@@ -157,6 +157,8 @@ struct TileGemm {
   const int32_t* draw_pos; uint32_t seed; const int32_t* m_live;
   float* pairs;                            // launch_gemm_tile_both: the arg-max pairs
 };
+// rows of K that a 32-bit offset in bytes reaches: those of a tile have to, and all that a list (a_rows) may name
+inline bool gemm_rows_fit(int64_t rows, int64_t K) { return rows * K * 2 <= (int64_t)UINT32_MAX; }
 hipError_t launch_gemm_tile_out(hipStream_t st, const TileGemm& g);
 hipError_t launch_gemm_tile_argmax(hipStream_t st, const TileGemm& g);
 hipError_t launch_gemm_tile_swiglu(hipStream_t st, const TileGemm& g);

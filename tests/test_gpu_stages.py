@@ -80,6 +80,50 @@ def test_gemm_bf16_cache_policy_edges(B, M):
     assert rel_err_rows(got, to_np(a) @ to_np(w).T) < 1e-5      # fp32 sums of 512 exact products
 
 
+def test_gemm_bf16_rows_beyond_4_gib(B):
+    """Activations of more bytes than a 32-bit offset reaches (524288 rows of 4096): rows on both sides of that line, and the last."""
+    M, N, K = 524288 + 333, 64, 4096
+    print(f"gemm bf16 M={M} N={N} K={K}", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    a = torch.empty(M, K, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    w = torch.empty(N, K, dtype=torch.bfloat16, device="cuda").normal_(0, 0.05, generator=g)
+    wp = B.pack_weight(w)
+    got, first = B.gemm(a, wp, packed=True), B.gemm_argmax(a, wp)
+    for rows in (slice(0, 300), slice(524288 - 300, 524288 + 300), slice(M - 300, M)):
+        want = a[rows].double() @ w.double().T
+        assert rel_err_rows(got[rows].cpu().numpy(), want.cpu().numpy()) < 1e-5      # fp32 sums of 4096 exact products
+        assert torch.equal(first[rows].long(), got[rows].argmax(1))
+
+
+def test_lists_of_rows_beyond_4_gib_are_refused(B):
+    """The LM head reads its rows by a list, whose offsets have 32 bits: hidden states of more bytes are refused before anything is
+    launched (a forward pass without the arg-max has no list)."""
+    shape = small_shape(d_model=65536, n_q_heads=1, n_kv_heads=1, head_dim=64, d_ff=64, vocab=64, n_layers=1, dtype="bf16")
+    batch, rows = 33, 1000                                   # 33000 rows of 128 KB
+    mat = lambda r, c: torch.zeros(r, c, dtype=torch.bfloat16, device="cuda")   # noqa: E731
+    d = shape.d_model
+    w = {"embed": mat(64, d), "lm_head": mat(64, d), "final_norm": mat(1, d)[0], "layers": [dict(
+        wq=mat(64, d), wk=mat(64, d), wv=mat(64, d), wo=mat(d, 64), w_gate=mat(64, d), w_up=mat(64, d), w_down=mat(d, 64),
+        norm_attn=mat(1, d)[0], norm_mlp=mat(1, d)[0], q_norm=mat(1, 64)[0], k_norm=mat(1, 64)[0])]}
+    eng = B.Engine(shape, w, batch, rows, 1088)
+    blk = B.BlockBuffers(batch, rows, 1, 1)
+    blk.upload_trees([[0]] * batch, [[-1]] * batch)
+    eng.block_from_tree(blk)
+    kv = B.KvCache(shape, [1088] * batch)
+    hidden = torch.full((batch * rows, d), 3.0, dtype=torch.bfloat16, device="cuda")
+    i32 = dict(dtype=torch.int32, device="cuda")
+    zeros = torch.zeros(batch * rows, **i32)
+    with pytest.raises(B.EspError) as e:
+        eng.tree_forward(blk, mat(1, d), kv, hidden, zeros)
+    assert e.value.code == 3
+    with pytest.raises(B.EspError) as e:
+        eng.mask_topk(blk, zeros, zeros, hidden, 4, torch.zeros(batch, 4, **i32), torch.zeros(batch, 4, device="cuda"), zeros)
+    assert e.value.code == 3
+    assert bool((hidden[-1] == 3).all()) and not bool(kv.k.any())
+    eng.close()
+
+
 class GemmPlan(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int) for n in ("splits", "mt", "nb", "m_tiles", "n_tiles", "wm")]
 
