@@ -203,7 +203,10 @@ esp_status esp_create(const esp_model_desc* m, const esp_weights* w, int32_t max
       !w->norm_attn || !w->norm_mlp)
     return ESP_EINVAL;
   if (m->qk_norm && (!w->q_norm || !w->k_norm)) return ESP_EINVAL;
-  if (gemm_prepare() != hipSuccess || attn_prepare() != hipSuccess || tree_prepare() != hipSuccess) return ESP_EDEVICE;
+  // (the kernels with more than 64 KB of LDS; an fp32 model launches none of the products' and attention's, whose 100 attributes
+  // take 6 to 7 ms of a process)
+  if (m->dtype == ESP_BF16 && (gemm_prepare() != hipSuccess || attn_prepare() != hipSuccess)) return ESP_EDEVICE;
+  if (tree_prepare() != hipSuccess) return ESP_EDEVICE;
   if (((uintptr_t)workspace) % 256) return ESP_EINVAL;
   for (int l = 0; l < m->n_layers; ++l) {
     if (!w->wqkv[l] || !w->wo[l] || !w->w_gate_up[l] || !w->w_down[l] || !w->norm_attn[l] || !w->norm_mlp[l])

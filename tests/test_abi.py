@@ -4,6 +4,8 @@ here needs a GPU)."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -123,3 +125,38 @@ def test_static_topk_rejects_on_the_host(lib):
     assert f(None, one, 4, 3, 4, one, one) == 1                       # Kp > vocab
     assert f(None, one, 132, 128256, 32, one, one) == 3               # ESP_ECAPACITY
     assert f(None, one, 100000, 128256, 1, one, one) == 3
+
+
+COUNTING_HIP = """
+static int n;
+int attributes(void) { return n; }
+int hipFuncSetAttribute(const void* f, int a, int v) { (void)f; (void)a; (void)v; ++n; return 0; }
+int hipMemsetAsync(void* p, int v, unsigned long c, void* s) { (void)p; (void)v; (void)c; (void)s; return 0; }
+"""
+CREATE = """
+import ctypes as C, sys
+hip = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)        # stands in front of the runtime
+lib = C.CDLL(sys.argv[2])
+desc = [1, 256, 4, 2, 64, 256, 512]
+one = C.c_void_p(256)
+table = (C.c_void_p * 1)(one)
+w = (C.c_void_p * 11)(*[256] * 3, *[C.addressof(table)] * 8)
+lib.esp_workspace_bytes.restype = C.c_size_t
+for dtype in (0, 1):
+    class Desc(C.Structure):
+        _fields_ = [("i", C.c_int32 * 7), ("theta", C.c_float), ("eps", C.c_float), ("qk_norm", C.c_int32), ("dtype", C.c_int32)]
+    d = Desc((C.c_int32 * 7)(*desc), 1e4, 1e-5, 0, dtype)
+    need, ctx = lib.esp_workspace_bytes(C.byref(d), 1, 64, C.c_int64(512)), C.c_void_p()
+    assert lib.esp_create(C.byref(d), w, 1, 64, C.c_int64(512), one, C.c_size_t(need), None, C.byref(ctx)) == 0
+    print(hip.attributes())
+"""
+
+
+def test_fp32_contexts_prepare_no_bf16_kernels(lib, tmp_path):
+    """esp_create sets the attributes of kernels that its model launches: of the tree's two alone for fp32, the bf16 products' and
+    attention's come with the first bf16 context (a process of its own, in front of the runtime; nothing is launched)."""
+    src, so = tmp_path / "hip.c", tmp_path / "hip.so"
+    src.write_text(COUNTING_HIP)
+    subprocess.run(["gcc", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
+    out = subprocess.run([sys.executable, "-c", CREATE, str(so), B.LIB_PATH], check=True, capture_output=True, text=True, timeout=60).stdout.split()
+    assert out[0] == "2" and int(out[1]) > 100
