@@ -46,9 +46,11 @@ WsLayout ws_layout(const esp_model_desc* m, int max_batch, int max_rows, int64_t
   w.act = take(M * (size_t)ff * e);
   // a call may use fewer rows / a shorter bound and hence another split count: size for the worst
   const int rows = (int)M;
-  size_t go = std::max(M * 2 * ff, gemm_out_elems_bound(m->dtype, rows, nqkv, d));
+  size_t go = gemm_out_elems_bound(m->dtype, rows, nqkv, d);
   go = std::max(go, gemm_out_elems_bound(m->dtype, rows, d, hq * hd));
   go = std::max(go, gemm_out_elems_bound(m->dtype, rows, d, ff));
+  // and the arg-max pairs of the LM head that writes logits as well
+  if (m->dtype == ESP_BF16) go = std::max(go, gemm_argmax_scratch_floats(std::min(rows, 128), m->vocab));
   w.gemm_out_floats = go;
   w.gemm_out = take(go * 4);
   size_t apf = attn_partial_floats_bound(m->dtype, max_batch, max_rows, hq, hkv, hd);

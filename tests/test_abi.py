@@ -127,6 +127,15 @@ def test_static_topk_rejects_on_the_host(lib):
     assert f(None, one, 100000, 128256, 1, one, one) == 3
 
 
+@pytest.mark.parametrize("name", ["llama3_8b", "tiny"])
+def test_workspace_holds_no_gate_up_product(lib, name):
+    """The activation is applied where the gate/up product is made: twice the features cost the workspace the activations and no
+    fp32 product of them."""
+    s, rows, batch = synth.SHAPES[name], 528, 4
+    small, large = (lib.esp_workspace_bytes(C.byref(B.model_desc(s.replace(d_ff=ff))), batch, rows, 4096) for ff in (s.d_ff, 2 * s.d_ff))
+    assert large - small <= batch * rows * s.d_ff * (2 if s.dtype == "bf16" else 4) + 256
+
+
 COUNTING_HIP = """
 static int n;
 int attributes(void) { return n; }
