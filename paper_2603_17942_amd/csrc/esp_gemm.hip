@@ -534,6 +534,11 @@ GateUpRule gate_up_rule(int M, int ff, int K, const void* act, bool ragged) {
   for (int c = 0; c < GU_TILES; ++c)
     for (int t = 0; t < N_GEMM_TILES; ++t)
       if ((r.launched >> c & 1u) && (of[c] >> t & 1u) && (best_full < 0 || cost[t][0] < best_full)) best_full = cost[t][0];
+  if (!ragged) {
+    int64_t best = cost[N_ROW_TILES][0];
+    for (int t = N_ROW_TILES; t < N_GEMM_TILES; ++t) best = std::min(best, cost[t][0]);
+    if (best_full * 100 > best * 106) { r.launched = 1u << GU_PLAN; best_full = best; }
+  }
   int pick[GU_TILES];
   auto choose = [&](auto&& self, int c) -> void {
     if (c < GU_TILES) {

@@ -167,10 +167,12 @@ hipError_t gemm_tile_out_prepare();
 hipError_t gemm_tile_argmax_prepare();
 hipError_t gemm_tile_swiglu_prepare();
 hipError_t gemm_tile_both_prepare();
-// Tile of the gate/up projection above 128 rows, in three classes: the plan's, one with a side of 256 (256 x 256, 192 x 256 or
-// 256 x 192, by cost), and 192 x 320.  The host takes the wide classes where they save rounds over the 256 CUs against row tiles of
-// up to 160: `rounds` in units of 10 ns, chunks x the time of one + start and epilogue.  K = 4096: 512 x 28672 128 us with
-// 160 x 256 in two rounds, 95 with 256 x 256; 576 x 24576 108 and 93 with 192 x 320; 384 x 28672 101 and 79 with 192 x 256.
+// Tile of the gate/up projection above 128 rows, in three classes: any, by cost; one with a side of 256 (256 x 256, 192 x 256 or
+// 256 x 192, by cost); and 192 x 320.  Which classes there are to choose from is said by their rounds over the 256 CUs against row
+// tiles of up to 160: `rounds` in units of 10 ns, chunks x the time of one + start and epilogue (fitted to kernels before these; on its
+// own it took 192 x 256 for 321 to 384 rows x 24576, where tile_cost and the clock have 192 x 192: 70 to 73 us against 65 to 66).
+// For one sequence it gives way where tile_cost has another tile 6 % cheaper; up to its 1024 rows, d_ff 8192 to 18944, it is
+// within 4 % otherwise.  512 x 28672 takes 95 us with 256 x 256, 576 x 24576 93 with 192 x 320, 384 x 28672 79 with 192 x 256.
 // Of a batch of M block rows only the device knows how many are there: the host launches every class that a number from two
 // thirds of M up asks for, the device (k_live_rows) hands the rows to the cheapest of these, and the others end at once (1.6 us).
 enum GateUpTile { GU_PLAN = 0, GU_SIDE256 = 1, GU_192x320 = 2, GU_TILES = 3 };
