@@ -465,13 +465,13 @@ hipError_t tile_launch(hipStream_t st, const TileGemm& g) {
   return hipGetLastError();
 }
 
-// Weights by nontemporal loads where at most four row tiles of 160 share them: a step of 320 rows 7511 -> 7387 us, 576 rows of the
-// Qwen3 shape 12227 -> 12105, prefill of 2049 tokens in chunks of 512 37.17 -> 36.64 ms; with 14 row tiles (16 ragged sequences)
-// 33.83 -> 34.00 ms, so not there.  Up to 128 rows, eight layers of the 8B shape on 2048 keys: one row 843 -> 779 us, 30 rows 886 -> 834,
-// 68 rows 1055 -> 1014, 128 rows 1260 -> 1230.  (Measured with the kernels before this one.)
+// Weights by nontemporal loads up to 2400 rows.  Eight layers on 2048 keys of the 8B shape, without and with: one row 822 -> 766 us, 30 rows
+// 874 -> 829, 68 rows 966 -> 949, 128 rows 1158 -> 1154, 160 rows 1365 -> 1349, 320 rows 1759 -> 1712, 512 rows 2208 -> 2175, batches of 672
+// rows 3008 -> 2945, 768 rows 3115 -> 3084, 960 (720 there) 3399 -> 3366, 1344 rows 5039 -> 4983, 2112 rows 7182 -> 7132; four of 1024 keys, 2560
+// rows 8.00 -> 8.00 ms, 3200 10.20 -> 10.24, 5120 15.96 -> 16.05 (3584 there 12.40 -> 12.55).
 template <int EPI>
 hipError_t tile_dispatch(hipStream_t st, const TileGemm& g) {
-  [[maybe_unused]] const bool nt = g.M <= 640;
+  [[maybe_unused]] const bool nt = g.M <= 2400;
 #define ESP_X(I_, RT_, CT_, S_, H_) \
   case I_: return tile_launch<GemmTile<RT_, CT_, S_, H_>, EPI, true>(st, g);
   switch (g.tile) { ESP_ROW_TILES(ESP_X) }

@@ -67,9 +67,8 @@ def test_gemm_bf16_ring_depth(B, M, chunks):
 
 @pytest.mark.parametrize("M", [64, 65, 96, 128, 640, 641])
 def test_gemm_bf16_cache_policy_edges(B, M):
-    """Both sides of the two lines at which accesses become nontemporal: stores of the partials from three row tiles of 32 on
-    (65 rows), weights up to four row tiles of 160 (640 rows).  Row-major weights are loaded the ordinary way and add in the
-    same order."""
+    """Packed weights are loaded nontemporally, row-major ones the ordinary way, and both add in the same order (the row count up to
+    which that is so: test_gemm_tiles_cache_policy_edge)."""
     N, K = 544, 512
     print(f"gemm bf16 cache policy M={M} N={N} K={K}", flush=True)
     a = synth.normal_like((M, K), 1.0, 14, 0, "cuda", torch.bfloat16)
@@ -292,6 +291,30 @@ def test_gemm_tiles(B, tile, M, N, K, splits, live):
             res = flat.view(M, N // 2)[:rows].double()
             assert bool(((res - r).abs() <= r.abs() * (2.0 ** -8 + 1e-6) + 1e-30).all())
             assert bool((flat.view(M, N // 2)[rows:] == -7).all()) if offset == 0 else True
+
+
+@pytest.mark.parametrize("tile", range(ROW_TILES, len(GEMM_TILES)))
+@pytest.mark.parametrize("M", [2400, 2401])
+def test_gemm_tiles_cache_policy_edge(B, tile, M):
+    """Both sides of the row count up to which weights are loaded nontemporally, every tile above 128 rows: one product on all tiles, bit for bit
+    what the kernel for row-major weights gives, and its arg-max and SwiGLU epilogues."""
+    c, (rt, ct), N, K = ctypes, GEMM_TILES[tile], 256, 192
+    print(f"tile {rt}x{ct} M={M}", flush=True)
+    a = synth.normal_like((M, K), 1.0, 18, 0, "cuda", torch.bfloat16)
+    w = synth.normal_like((N, K), K ** -0.5, 18, 1, "cuda", torch.bfloat16)
+    wp, want, st = B.pack_weight(w), B.gemm(a, w), torch.cuda.current_stream().cuda_stream
+    got, pairs, n_tiles = torch.full((M, N), -7.0, device="cuda"), torch.full((8, M, 2), -7.0, device="cuda"), (N // 32 + ct - 1) // ct
+    act = torch.full((M, N // 2), -7.0, dtype=torch.bfloat16, device="cuda")
+    for name, out in (("out", got), ("argmax", got), ("swiglu", act)):
+        g = TileGemm(a.data_ptr(), None, wp.data_ptr(), out.data_ptr(), M, N, K, 1, tile, None, 0, None, pairs.data_ptr())
+        assert internal(f"launch_gemm_tile_{name}", c.c_void_p, c.POINTER(TileGemm))(st, g) == 0
+    assert torch.equal(got, want)
+    best = torch.stack([want[:, 32 * ct * t:32 * ct * (t + 1)].amax(1) for t in range(n_tiles)])
+    assert torch.equal(pairs[:n_tiles, :, 0], best)
+    blocks = want.double().view(M, N // 64, 2, 32)
+    gate, up = blocks[:, :, 0].reshape(M, -1), blocks[:, :, 1].reshape(M, -1)
+    r = gate / (1 + torch.exp(-gate)) * up
+    assert bool(((act.double() - r).abs() <= r.abs() * (2.0 ** -8 + 1e-6) + 1e-30).all())   # exp and reciprocal to 1 ulp, then bf16
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (13, 4096, 256), (52, 688, 256), (52, 256, 688), (70, 130, 77)])
