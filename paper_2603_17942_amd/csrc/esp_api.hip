@@ -644,7 +644,7 @@ esp_status esp_kv_load(esp_ctx* c, const esp_kv* kv, int32_t layer, int32_t seq_
 
 size_t esp_gemm_scratch_bytes(int32_t M, int32_t N, int32_t K) {
   if (M < 1 || N < 1 || K < 1) return 0;
-  const size_t parts = std::max(gemm_plan(ESP_BF16, M, N, K).splits, row_major_plan(M, N, K).splits);
+  const size_t parts = std::max(product_plan(M, N, K).splits, row_major_plan(M, N, K).splits);
   return parts * M * N * 4 + 256;
 }
 
@@ -661,7 +661,7 @@ esp_status esp_gemm(void* stream, int32_t dtype, const void* A, const void* W, i
   if (dtype != ESP_F32 && dtype != ESP_BF16) return ESP_EDTYPE;
   if (dtype == ESP_BF16 && (N % 32 || K % 64)) return ESP_ESHAPE;
   if (w_packed && dtype != ESP_BF16) return ESP_EDTYPE;
-  GemmPlan p = dtype == ESP_BF16 && !w_packed ? row_major_plan(M, N, K) : gemm_plan(dtype, M, N, K);
+  GemmPlan p = dtype == ESP_F32 ? gemm_plan(dtype, M, N, K) : w_packed ? product_plan(M, N, K) : row_major_plan(M, N, K);
   // a product that fills the CUs without split-K takes no scratch if there is none
   if (p.splits > 1 && (!partials || partial_bytes < gemm_out_elems(p, M, N) * 4) && gemm_whole_rows(dtype, M, N, K))
     p = whole_row_plan(dtype, M, N, K);

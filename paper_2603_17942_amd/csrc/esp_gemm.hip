@@ -437,6 +437,19 @@ GemmPlan whole_row_plan(int dtype, int M, int N, int K) {
   return gemm_plan(dtype, M, N, K);
 }
 
+// Of a product on its own, whose parts nobody adds up but a launch more: not split where a round of the CUs had no room for it; above
+// 128 rows unless that saves the launch (5 us) and its traffic (4 TB/s) too.  Whole and in two parts with their sum: 101 x 24576 x
+// 4096 42 and 47.5 us, 128 x 18944 x 2048 24.8 and 31, 180 x 28672 x 4096 59 and 72, 1344 x 4096 x 4096 50 and 56.5.
+GemmPlan product_plan(int M, int N, int K) {
+  const GemmPlan p = gemm_plan(ESP_BF16, M, N, K);
+  if (p.splits == 1 || !gemm_whole_rows(ESP_BF16, M, N, K)) return p;
+  if (M <= 128) return row_plan(M, N, K, 1, 1, 2);
+  const GemmPlan whole = whole_row_plan(ESP_BF16, M, N, K);
+  const int blocks = (N + 31) / 32, chunks = std::max(K / KC, 1);
+  const int64_t add = 5000 + (int64_t)(p.splits + 1) * M * N / 1000;
+  return tile_cost(GEMM_TILES[tile_index(whole)], M, blocks, chunks, 1) <= tile_cost(GEMM_TILES[tile_index(p)], M, blocks, chunks, p.splits) + add ? whole : p;
+}
+
 size_t gemm_out_elems_bound(int dtype, int M, int N, int K) {
   size_t most = gemm_out_elems(gemm_plan(dtype, M, N, K), M, N);
   if (dtype != ESP_BF16) return most;

@@ -131,6 +131,7 @@ GemmPlan batch_gemm_plan(int M, int N, int K);
 // part with eight chunks of K or more
 int round_parts(int M, int N, int K);
 GemmPlan row_major_plan(int M, int N, int K);     // bf16 weights that are not packed
+GemmPlan product_plan(int M, int N, int K);       // bf16, packed, for a product that is added up by a launch of its own
 // is a projection's output unsplit by that (the LM head's epilogues see whole rows and are refused otherwise), and its plan
 bool gemm_whole_rows(int dtype, int M, int N, int K);
 GemmPlan whole_row_plan(int dtype, int M, int N, int K);

@@ -67,6 +67,15 @@ def test_gemm_parts(n, k):
             assert batch(m, n, k).splits >= least, (m, least)
 
 
+@pytest.mark.parametrize("m,n,k,splits", [(192, 28672, 4096, 1), (180, 24576, 4096, 1), (1, 24576, 4096, 1), (128, 18944, 2048, 1), (1344, 4096, 4096, 1), (1344, 4096, 14336, 2), (320, 4096, 4096, 8),
+                                          (68, 6144, 4096, 5), (2112, 4096, 4096, 1), (512, 28672, 4096, 1), (64, 96, 64, 1)])
+def test_product_plan(m, n, k, splits):
+    """A product on its own needs a launch more for its parts: whole where it used to be, unless the parts save more than that."""
+    p = internal("product_plan", *[C.c_int] * 3, restype=GemmPlan)(m, n, k)
+    assert p.splits == splits
+    assert binding.load_library().esp_gemm_scratch_bytes(m, n, k) >= splits * m * n * 4
+
+
 @pytest.mark.parametrize("n,k", [(6144, 4096), (4096, 4096), (4096, 14336), (28672, 4096), (2048, 2048), (544, 2048), (160, 1664), (32, 64)])
 def test_row_major_gemm_plan(n, k):
     """Row-major weights have a kernel with tiles of its own, 128 columns wide up to 128 rows and 160 x 256 above: as many parts as
