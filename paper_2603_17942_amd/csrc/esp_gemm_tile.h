@@ -355,31 +355,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
   if constexpr (EPI == 1 || EPI == 3) {
     float* red = reinterpret_cast<float*>(lds);          // [2 wave columns][ROWS][2]
+    auto scan = [&](auto sampled) {
 #pragma unroll
-    for (int i = 0; i < RT; ++i) {
-      const int rl = i * 32 + wm * 16 + lr;
-      const uint32_t pos = draw_pos ? (uint32_t)draw_pos[min(mt0 + rl, M - 1)] : 0u;
-      float best = -INFINITY;
-      int bi = 0x7fffffff;
+      for (int i = 0; i < RT; ++i) {
+        const int rl = i * 32 + wm * 16 + lr;
+        const uint32_t pos = sampled ? (uint32_t)draw_pos[min(mt0 + rl, M - 1)] : 0u;
+        float best = -INFINITY;
+        int bi = 0x7fffffff;
 #pragma unroll
-      for (int j = 0; j < CT; ++j)
-        if (blk0 + j < nblk) {
+        for (int j = 0; j < CT; ++j)
+          if (blk0 + j < nblk) {
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {                  // columns ascend: ties keep the lower one
-            const int n = (blk0 + j) * 32 + wn * 16 + 4 * lq + v;
-            float x = acc[i][j][v];
-            if (draw_pos) x += gumbel_noise(seed, pos, (uint32_t)n);
-            if (x > best) { best = x; bi = n; }
+            for (int v = 0; v < 4; ++v) {                // columns ascend: ties keep the lower one
+              const int n = (blk0 + j) * 32 + wn * 16 + 4 * lq + v;
+              float x = acc[i][j][v];
+              if (sampled) x += gumbel_noise(seed, pos, (uint32_t)n);
+              if (x > best) { best = x; bi = n; }
+            }
           }
-        }
 #pragma unroll
-      for (int o = 32; o >= 16; o >>= 1) {
-        const float ov = __shfl_xor(best, o, 64);
-        const int oi = __shfl_xor(bi, o, 64);
-        if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
+        for (int o = 32; o >= 16; o >>= 1) {
+          const float ov = __shfl_xor(best, o, 64);
+          const int oi = __shfl_xor(bi, o, 64);
+          if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
+        }
+        if (lq == 0) { red[(wn * T::ROWS + rl) * 2] = best; red[(wn * T::ROWS + rl) * 2 + 1] = __int_as_float(bi); }
       }
-      if (lq == 0) { red[(wn * T::ROWS + rl) * 2] = best; red[(wn * T::ROWS + rl) * 2 + 1] = __int_as_float(bi); }
-    }
+    };
+    // (a loop each: with the noise of 256 values a lane as a branch in one, 256 jumps over code that does not fit the instruction cache)
+    if (draw_pos) scan(std::true_type{});
+    else scan(std::false_type{});
     __syncthreads();
     for (int rl = tid; rl < T::ROWS; rl += 256) {
       float best = red[rl * 2];

@@ -317,6 +317,30 @@ def test_gemm_tiles_cache_policy_edge(B, tile, M):
     assert bool(((act.double() - r).abs() <= r.abs() * (2.0 ** -8 + 1e-6) + 1e-30).all())   # exp and reciprocal to 1 ulp, then bf16
 
 
+def test_arg_max_epilogue_is_no_slower_than_writing_the_logits(B):
+    """2048 workgroups of 256 x 256 with two chunks of K: the arg-max leaves 8 bytes a row and workgroup where the logits are 537 MB (the
+    epilogue took longer with the noise of a draw as a branch inside its loop)."""
+    c, M, N, K, tile = ctypes, 2048, 65536, 128, len(GEMM_TILES) - 1
+    a = synth.normal_like((M, K), 1.0, 19, 0, "cuda", torch.bfloat16)
+    wp = B.pack_weight(synth.normal_like((N, K), K ** -0.5, 19, 1, "cuda", torch.bfloat16))
+    out, pairs = torch.empty(M, N, device="cuda"), torch.empty(N // 256, M, 2, device="cuda")
+    best = {}
+    for name in ("out", "argmax"):
+        g = TileGemm(a.data_ptr(), None, wp.data_ptr(), out.data_ptr(), M, N, K, 1, tile, None, 0, None, pairs.data_ptr())
+        fn = internal(f"launch_gemm_tile_{name}", c.c_void_p, c.POINTER(TileGemm))
+        times = []
+        for _ in range(12):
+            e = [torch.cuda.Event(enable_timing=True) for _ in (0, 1)]
+            e[0].record()
+            assert fn(torch.cuda.current_stream().cuda_stream, g) == 0
+            e[1].record()
+            e[1].synchronize()
+            times.append(e[0].elapsed_time(e[1]))
+        best[name] = min(times)
+    print(f"out {best['out']:.3f} ms, arg-max {best['argmax']:.3f} ms", flush=True)
+    assert best["argmax"] < 0.8 * best["out"], best
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (13, 4096, 256), (52, 688, 256), (52, 256, 688), (70, 130, 77)])
 def test_gemm_f32(B, M, N, K):
     print(f"gemm f32 M={M} N={N} K={K}", flush=True)
