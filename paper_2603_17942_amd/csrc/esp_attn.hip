@@ -22,6 +22,12 @@ namespace {
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float NEG_BIG = -1.0e30f;
 
+// one condition after the other (k_attn_generic says where)
+__device__ __forceinline__ bool seq_ok_in_turn(const KvDev& kv, int seq, int n_rows, int rows_per_seq) {
+  const int L = kv.len[seq], base = kv.base[seq], cap = kv.seq_cap[seq];
+  return L >= 0 && L <= kv.len_bound && n_rows >= 0 && n_rows <= rows_per_seq && L + n_rows <= cap && base >= 0 && (base & 63) == 0 &&
+         (int64_t)base + cap <= kv.capacity;
+}
 // UNIFORM: seq is the same for the wave, in a scalar
 template <bool UNIFORM = false>
 __device__ __forceinline__ bool seq_ok(const KvDev& kv, int seq, int n_rows, int rows_per_seq) {
@@ -63,8 +69,9 @@ __device__ __forceinline__ void wave_sync() {
 // three tiles; now 5.6 in three splits).  Sums run over features and keys in ascending order.
 // MERGE: the splits of a (row, head) are waves of one workgroup, up to MERGE of them, which merge through LDS in split order (as
 // k_attn_merge does from memory) and write the result: a launch less, 60 rows on 128 keys 5.6 + 4.3 -> 6.1 us.
+// Three waves a SIMD of HD 64 (two took 170 registers where three have 168: 400 rows on 16 keys 20.8 -> 22.7 us).
 template <typename T, int HD, bool PACKED, bool VEC, int MERGE>
-__global__ __launch_bounds__(64 * (MERGE ? MERGE : 1)) void k_attn_generic(BlockDev b, KvDev kv, int layer, int hq, int hkv,
+__global__ __launch_bounds__(64 * (MERGE ? MERGE : 1), HD == 64 ? 3 : 1) void k_attn_generic(BlockDev b, KvDev kv, int layer, int hq, int hkv,
                                                                           const T* __restrict__ q, float* __restrict__ part_o,
                                                                           float* __restrict__ part_ml, int nsplit, int tps,
                                                                           T* __restrict__ out) {
@@ -72,13 +79,18 @@ __global__ __launch_bounds__(64 * (MERGE ? MERGE : 1)) void k_attn_generic(Block
   __shared__ float qs_w[WAVES][HD];
   __shared__ float ps_w[WAVES][64];
   __shared__ float m_w[WAVES], l_w[WAVES];
-  const int row = blockIdx.x, h = blockIdx.y, lane = threadIdx.x & 63;
+  auto sync = [] { if constexpr (MERGE > 0) wave_sync(); else __syncthreads(); };
+  const int row = blockIdx.x, h = blockIdx.y, lane = MERGE ? threadIdx.x & 63 : threadIdx.x;
   const int wave = MERGE ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0, sp = MERGE ? wave : (int)blockIdx.z;
   float* qs = qs_w[wave];
   float* ps = ps_w[wave];
   const int seq = row / b.rows_per_seq, r = row % b.rows_per_seq;
   const int nr = b.n_rows[seq];
-  if (!seq_ok<true>(kv, seq, nr, b.rows_per_seq) || r >= nr) {
+  // What the compiler makes of the key loop depends on how it comes by these scalars: fp32 with HD 64 takes 0.92 to 0.98 of the time with
+  // one condition after the other, bf16 1.05 to 1.1 and HD 128 1.03 to 1.07 (20 rows on 16000 keys, four sequences 164 -> 151 us, 339 -> 368,
+  // 315 -> 330).
+  const bool ok = sizeof(T) == 4 && HD == 64 ? seq_ok_in_turn(kv, seq, nr, b.rows_per_seq) : seq_ok<(MERGE > 0)>(kv, seq, nr, b.rows_per_seq);
+  if (!ok || r >= nr) {
     if (MERGE && !PACKED)
       for (int d = threadIdx.x; d < HD; d += blockDim.x) out[((size_t)row * hq + h) * HD + d] = from_f32<T>(0.f);
     return;
@@ -92,7 +104,7 @@ __global__ __launch_bounds__(64 * (MERGE ? MERGE : 1)) void k_attn_generic(Block
   const int64_t base = kv.base[seq];
   const float scale = LOG2E / sqrtf((float)HD);
   for (int d = lane; d < HD; d += 64) qs[d] = to_f32(q[(act_row<PACKED>(b, seq, r) * hq + h) * HD + d]) * scale;
-  wave_sync();
+  sync();
   const uint64_t* anc = b.anc + (size_t)row * b.anc_words;
   float m = NEG_BIG, l = 0.f;
   float o[HD / 64];
@@ -129,7 +141,7 @@ __global__ __launch_bounds__(64 * (MERGE ? MERGE : 1)) void k_attn_generic(Block
     l = l * alpha + wave_sum(p);
     m = m_new;
     ps[lane] = p;
-    wave_sync();
+    sync();
     const int nk = min(64, total - t * 64);     // entries past the sequence are not touched: cache memory may hold anything
 #pragma unroll
     for (int i = 0; i < HD / 64; ++i) {
@@ -141,7 +153,7 @@ __global__ __launch_bounds__(64 * (MERGE ? MERGE : 1)) void k_attn_generic(Block
       }
       o[i] = a;
     }
-    wave_sync();
+    sync();
   }
   if constexpr (MERGE > 0) {
     if (lane == 0) { m_w[wave] = m; l_w[wave] = l; }
@@ -902,7 +914,13 @@ size_t attn_partial_floats_bound(int dtype, int batch, int rows_per_seq, int hq,
 
 // The generic kernel merges its splits itself where they are waves that a workgroup can hold with the registers they take.
 constexpr int GENERIC_WAVES_64 = 8, GENERIC_WAVES_128 = 4;
-static bool generic_merges(int hd, const AttnPlan& p) { return p.nsplit <= (hd == 64 ? GENERIC_WAVES_64 : GENERIC_WAVES_128); }
+// And only where all workgroups have a place at once: their waves share a CU four at a time or more, a workgroup waits for room for all of
+// its own and none leaves before the last (200 rows of four heads on 4000 keys, five splits: 73 us in two launches, 121 in one; four
+// sequences of 60 rows on 1000 keys, HD 128, three splits: 76 and 92).  A single split merges nothing and always does.
+bool attn_generic_merges(int hd, const AttnPlan& p, int64_t groups) {
+  const int room = hd == 64 ? 12 : 4;                    // waves of a CU
+  return p.nsplit <= (hd == 64 ? GENERIC_WAVES_64 : GENERIC_WAVES_128) && (p.nsplit == 1 || groups <= 256 * (p.nsplit > 4 ? 1 : room / p.nsplit));
+}
 
 // Shares of a batch's line of work per kv head: as many as there are CUs for them; 0: a grid of equal splits.  The line costs up to 3 us a
 // layer (the cuts are looked up, a workgroup's second piece starts cold, more partials) and one launch a forward pass, so only
@@ -966,7 +984,7 @@ hipError_t launch_attn(hipStream_t st, int dtype, const BlockDev& b, const KvDev
     hipLaunchKernelGGL(kern, grid, block, RING_LDS_BYTES, st, b, kv, layer, hq, hkv, (const bf16_t*)q, part_o, part_ml, nsplit,
                        p.tiles_per_split, p.q_tiles, p.ct_wg, g.n_full, cuts);
   } else {
-    const bool vec = (((uintptr_t)kv.k | (uintptr_t)kv.v) & 15) == 0, merge = generic_merges(hd, p);
+    const bool vec = (((uintptr_t)kv.k | (uintptr_t)kv.v) & 15) == 0, merge = attn_generic_merges(hd, p, (int64_t)M * hq);
     const dim3 grid(M, hq, merge ? 1 : p.nsplit), block(merge ? 64 * p.nsplit : 64);
 #define ESP_GENERIC(T_, HD_, P_)                                                                                             \
   do {                                                                                                                       \
@@ -1002,8 +1020,8 @@ hipError_t launch_attn_merge(hipStream_t st, int dtype, const BlockDev& b, const
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, b, kv, hq, hkv, part_o, part_ml, shares ? shares : p.nsplit, n_ct, (bf16_t*)out, cuts);
     return hipGetLastError();
   }
-  if (generic_merges(hd, p)) return hipSuccess;          // done by the attention launch
   const int M = b.batch * b.rows_per_seq;
+  if (attn_generic_merges(hd, p, (int64_t)M * hq)) return hipSuccess;   // done by the attention launch
   const float* part_o = partials;
   const float* part_ml = partials + (size_t)M * hq * p.nsplit * hd;
   const int n_items = M * hq, per_wg = 256 / (hd / 4);

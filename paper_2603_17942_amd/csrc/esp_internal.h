@@ -324,6 +324,8 @@ size_t attn_partial_floats_bound(int dtype, int batch, int rows_per_seq, int hq,
 int attn_shares(int dtype, int hd, int batch, int rows_per_seq, int hq, int hkv, const AttnPlan& p);
 size_t attn_cuts_ints(int batch);
 hipError_t launch_attn_cuts(hipStream_t st, const BlockDev& b, const KvDev& kv, int hq, int hkv, const AttnPlan& p, int shares, int32_t* cuts);
+// does the generic kernel merge its splits itself, groups: (row, head) pairs
+bool attn_generic_merges(int hd, const AttnPlan& p, int64_t groups);
 // cuts: null for a grid of equal splits.  launch_attn writes `partials`, or `out` itself where launch_attn_merge then does nothing.
 hipError_t launch_attn(hipStream_t st, int dtype, const BlockDev& b, const KvDev& kv, int layer, int hq,
                        int hkv, int hd, const void* q, float* partials, const AttnPlan& p, const int32_t* cuts, void* out);

@@ -149,3 +149,14 @@ def test_attention_shares(hkv, batch, rows, keys, shares):
     plan = internal("attn_plan", *[C.c_int] * 7, restype=AttnPlan)(binding.ESP_BF16, 128, batch, rows, 4 * hkv, hkv, keys)
     n = internal("attn_shares", *[C.c_int] * 6, C.POINTER(AttnPlan))(binding.ESP_BF16, 128, batch, rows, 4 * hkv, hkv, plan)
     assert n == shares
+
+
+@pytest.mark.parametrize("hd,batch,rows,heads,keys,splits,merges", [
+    (64, 1, 60, 4, 128, 3, True), (64, 4, 20, 4, 128, 3, True), (64, 1, 20, 4, 1000, 8, True), (64, 1, 124, 4, 128, 4, True), (64, 4, 60, 4, 512, 3, True),
+    (64, 1, 200, 4, 1000, 5, False), (64, 1, 400, 4, 128, 2, False), (64, 4, 20, 4, 512, 5, False), (64, 4, 124, 4, 16000, 2, False), (64, 1, 20, 4, 16000, 32, False),
+    (64, 4, 400, 4, 4000, 1, True), (128, 1, 60, 4, 128, 3, True), (128, 4, 60, 4, 512, 3, False), (128, 1, 200, 4, 128, 3, False)])
+def test_generic_attention_merges_where_all_workgroups_fit(hd, batch, rows, heads, keys, splits, merges):
+    """Splits that are waves of one workgroup only where every (row, head) has its place on a CU at once, or there is one."""
+    plan = internal("attn_plan", *[C.c_int] * 7, restype=AttnPlan)(binding.ESP_F32, hd, batch, rows, heads, 2, keys)
+    assert plan.nsplit == splits
+    assert internal("attn_generic_merges", C.c_int, C.POINTER(AttnPlan), C.c_int64, restype=C.c_bool)(hd, plan, batch * rows * heads) is merges
