@@ -6,16 +6,19 @@
 // accumulator half as often.  Hence 16x16x32; four waves in 2 x 2, one per SIMD with all 512 registers, which read fewer
 // fragment bytes per flop than four side by side; both operands global -> LDS without a register hop; consecutive MFMAs that
 // share an operand.  Accumulators in the 256 AGPRs, fragments of this k-step and the next in VGPRs.
-// Up to 128 rows it is a weight stream: 64 to 100 KB of weights in flight a CU, in a ring that takes most of the LDS.
+// Up to 128 rows it is a weight stream: (stages - 1) x column blocks x 4 KB of weights in flight a CU, 40 to 96 KB, in a ring that takes
+// most of the LDS.
 // The operands change places (D^T = W A^T): a lane then holds four consecutive columns of one row.
 // Sums run over K in the order of the kernel for row-major weights and with the same rounding: results are equal bit for bit for
 // equal splits, whatever the tile.
-// MI355X, weights rotating, against the kernels with 32x32x16 before it.  Above 128 rows (5 x 2 and 4 x 2 row and column tiles of 32
-// a wave, loads by four waves of their own; 256 x 256 and 192 x 320 for gate/up): 320 x 28672 x 4096 82 -> 70 us, 512 x 28672 x 4096
-// 107 -> 94, 1317 x 28672 x 4096 273 -> 256, 512 x 6144 x 4096 33.7 -> 28.8, 320 x 4096 x 4096 24.8 -> 18.8 in half the splits,
-// 1317 x 4096 x 14336 176 -> 128, 1632 x 6144 x 4096 118 -> 71.  Up to 128 rows (weights in register rings, 128 columns a workgroup,
-// twice the splits): 68 x 28672 x 4096 41.2 -> 37.8, 101 x 28672 x 4096 47.3 -> 42.4, 68 x 4096 x 4096 10.1 -> 9.3, 101 x 6144 x 4096
-// 17.0 -> 15.2, one row x 6144 x 4096 10.5 -> 9.6; 68 x 128256 x 4096 with logits and arg-max 224 -> 175.
+// MI355X, weights rotating, against the kernels with 32x32x16 before it, as many parts up to 128 rows and no fewer above.  Above 128 rows
+// (5 x 2 and 4 x 2 row and column tiles of 32 a wave, loads by four waves of their own; 256 x 256 and 192 x 320 for gate/up):
+// 320 x 28672 x 4096 82 -> 70 us, 512 x 28672 x 4096 107 -> 94, 1317 x 28672 x 4096 273 -> 256, 320 x 6144 x 4096 27.4 -> 24.3, 512 x 6144
+// x 4096 34.0 -> 30.3, 320 x 4096 x 4096 23.3 -> 20.2, 320 x 4096 x 14336 41.3 -> 40.6, 1317 x 4096 x 14336 174 -> 126, 1632 x 6144 x
+// 4096 121 -> 75; 1344 x 128256 x 4096 with arg-max 1190 -> 1010.  Up to 128 rows (weights in register rings): 68 x 28672 x 4096 43.9 ->
+// 41.4, 101 x 28672 x 4096 50.5 -> 47.0, 68 x 6144 x 4096 14.0 -> 12.1, 68 x 4096 x 4096 11.3 -> 9.7, 68 x 4096 x 14336 25.3 -> 21.6,
+// 101 x 6144 x 4096 16.3 -> 14.4, one row x 6144 x 4096 10.2 -> 9.5; 68 x 128256 x 4096 with arg-max 204 -> 166; not 101 x 4096 x 4096,
+// 12.2 -> 13.5, and x 14336, 26.6 -> 28.1.
 #pragma once
 #include <algorithm>
 #include <type_traits>
